@@ -75,6 +75,31 @@ def test_special_groups():
     assert np.array_equal(back[:64], w[:64]) and np.array_equal(back[128:256], w[128:256])  # exact cases
 
 
+@pytest.mark.parametrize("kind", ["halfway", "coarse", "wide", "subnormal", "subnormal_scale"])
+def test_quantize_rounding_edges(kind):
+    """Quotients at and next to half integers, and scales whose reciprocal is not finite: bit for bit."""
+    rng = np.random.default_rng(7)
+    g, n = 8192 // 64 + 3, 64
+    if kind == "halfway":        # min 0, max 15 * 2^k, values at multiples of half a step
+        w = rng.integers(0, 31, (g, n)) * 0.5
+        w[:, 0], w[:, 1] = 0.0, 15.0
+        w = w * 2.0 ** rng.integers(-20, 20, (g, 1))
+    elif kind == "coarse":       # few mantissa bits: many exact ties
+        w = rng.integers(-12, 13, (g, n)) * 2.0 ** rng.integers(-6, 6, (g, 1))
+    elif kind == "wide":         # one large weight among tiny ones, and the largest finite range
+        w = rng.standard_normal((g, n)) * 2.0 ** rng.integers(-60, 60, (g, n))
+        w[0, :2] = [1.6e38, -1.6e38]
+    elif kind == "subnormal":
+        w = rng.integers(-128, 128, (g, n)) * 2.0 ** -133
+    else:                        # scale itself subnormal: range / 15 below 2^-126
+        w = rng.integers(-128, 128, (g, n)) * 2.0 ** -130
+    w = I.f32_to_bf16_bits(w.astype(np.float32).reshape(-1))
+    codes, qp = _gpu_quantize(w)
+    ref_codes, ref_qp = Q.quantize(w)
+    assert np.array_equal(qp, ref_qp)
+    assert np.array_equal(codes, ref_codes)
+
+
 def test_empty_tensor_is_a_no_op():
     out = _gpu_dequantize(np.zeros(0, np.uint8), np.zeros((0, 2), np.uint16), 0)
     assert np.all(I.bf16_bits_to_f32(out) == -1.0)
