@@ -42,7 +42,8 @@ int32_t moe_debug_gemm_units(const int32_t* expert_offsets, int32_t n_local, int
 int32_t moe_debug_ffn_plan(int32_t cap_rows, const moe_shard_t* shard, int32_t* plan);
 
 /*
- * Row-block height of the tiled kernels moe_expert_ffn would use for (cap_rows, shard): 256 (row
+ * Row-block height of the tiled kernels moe_expert_ffn would use for (cap_rows, shard) where it does not use tall row
+ * blocks (moe_debug_tall below): 256 (row
  * blocks of 256 rows plus 128- and 64-row remainder tiles, moe_debug_gemm_units), or 160 (every
  * expert's rows in blocks of 160, moe_debug_even_units), which the library picks for calls with a
  * few hundred rows per expert: there a remainder tile behind one 256-row tile would stream the
@@ -82,11 +83,35 @@ int32_t moe_debug_down_slices(const int32_t* expert_offsets, int32_t cap_rows, c
 #define MOE_DEBUG_DEVICE_INTS 9
 
 /*
- * The same work lists as the two calls above, evaluated on the DEVICE by the wave-parallel code the
+ * Whether the tiled kernels of moe_expert_ffn may give an expert's last rows to its 256-row blocks for
+ * (cap_rows, shard), 16, 32 or 48 rows to a block (a remainder tile of their own would stream the
+ * expert's weights once more; "Generative Inference": prefill is bound by compute as long as weights are read
+ * once): 1 or 0, or a negative MOE_ERR_* code.  Calls for which this is 1 run the work lists of
+ * moe_debug_tall_units, the others those of moe_debug_gemm_units, moe_debug_even_units and moe_debug_down_slices.
+ */
+int32_t moe_debug_tall(int32_t cap_rows, const moe_shard_t* shard);
+
+/*
+ * The work lists of such calls: for max_slices == 0 the plain list (gate/up projection, bf16 down
+ * projection), for max_slices >= 1 the list of a down projection of nk k-tiles that may be cut along K into up to
+ * that many slices.  Launches that do not fill the chip have no tall blocks in them.
+ * units  [max_units][MOE_DEBUG_DEVICE_INTS] int32 HOST, records as moe_debug_device_units writes them (heights
+ *        256 to 304, 128, 64)
+ * Returns the grid size, or a negative MOE_ERR_* code.
+ */
+int32_t moe_debug_tall_units(const int32_t* expert_offsets, int32_t n_local, int32_t cap_rows,
+                             int32_t n_col_blocks, int32_t nk, int32_t max_slices, int32_t* units,
+                             int32_t max_units);
+
+#define MOE_DEBUG_TALL 64 /* added to max_slices of moe_debug_device_units: the list with tall blocks */
+
+/*
+ * The same work lists as the calls above, evaluated on the DEVICE by the wave-parallel code the
  * GEMM kernels use (one wavefront per workgroup id), for tests that compare it with the host code.
  * expert_offsets [n_local+1] int32 DEVICE; n_col_blocks, nk (k-tiles of 64): as the kernel is launched
  * max_slices     0: the plain list of moe_debug_gemm_units; >= 1: the sliced list of
- *                moe_debug_down_slices with that maximum; -1: the list of moe_debug_even_units
+ *                moe_debug_down_slices with that maximum; -1: the list of moe_debug_even_units;
+ *                MOE_DEBUG_TALL + 0 or + that maximum: the lists of moe_debug_tall_units
  * units          [max_units][MOE_DEBUG_DEVICE_INTS] int32 DEVICE, written asynchronously on `stream`:
  *                {tile height (0 = no work), local expert, row0, row_end, column block, slice,
  *                 first k-tile, k-tiles, scratch row of row0 (-1: writes y_perm)}

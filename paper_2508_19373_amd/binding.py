@@ -31,12 +31,13 @@ MOE_PERMUTE_STATIC_MAX_COUNTS = 262144
 EXPORTS = ("moe_route_topk", "moe_permute", "moe_permute_static", "moe_expert_ffn", "moe_expert_ffn_gather", "moe_combine", "moe_workspace_bytes",
            "moe_ffn_workspace_bytes", "moe_status_string")
 DEBUG_EXPORTS = ("moe_debug_gemm_units", "moe_debug_ffn_plan", "moe_debug_down_slices", "moe_debug_device_units",
-                 "moe_debug_tile_rows", "moe_debug_even_units")
+                 "moe_debug_tile_rows", "moe_debug_even_units", "moe_debug_tall", "moe_debug_tall_units")
 INT4_EXPORTS = ("moe_int4_dequantize", "moe_int4_quantize")
 INT4_GROUP = 64
 DEBUG_UNIT_INTS = 5
 DEBUG_SLICE_INTS = 8
 DEBUG_DEVICE_INTS = 9
+DEBUG_TALL = 64
 
 
 class MoeShard(ctypes.Structure):
@@ -94,6 +95,10 @@ def lib() -> ctypes.CDLL:
         L.moe_debug_even_units.restype = i32
         L.moe_debug_tile_rows.argtypes = [i32, shp]
         L.moe_debug_tile_rows.restype = i32
+        L.moe_debug_tall.argtypes = [i32, shp]
+        L.moe_debug_tall.restype = i32
+        L.moe_debug_tall_units.argtypes = [vp, i32, i32, i32, i32, i32, vp, i32]
+        L.moe_debug_tall_units.restype = i32
         _lib = L
     return _lib
 
@@ -226,6 +231,33 @@ def moe_debug_tile_rows(cap_rows, shard: MoeShard) -> int:
     return int(n)
 
 
+def moe_debug_tall(cap_rows, shard: MoeShard) -> bool:
+    """Host-only: whether the tiled kernels may give an expert's last rows to its 256-row blocks."""
+    n = lib().moe_debug_tall(cap_rows, ctypes.byref(shard))
+    if n < 0:
+        raise MoeError("moe_debug_tall", n)
+    return bool(n)
+
+
+def _max_device_units(cap_rows, n_local, n_col_blocks):
+    return 8 * ((cap_rows // 256 + n_local) * n_col_blocks // 8 + 1 + 2 * (n_local * n_col_blocks // 8 + 1) + 64)
+
+
+def moe_debug_tall_units(expert_offsets, cap_rows, n_col_blocks, nk, max_slices):
+    """Host-only: the work list with tall row blocks for one routing, int32 [grid, DEBUG_DEVICE_INTS] (see
+    include/moe_shard_debug.h).  `expert_offsets` is a host sequence."""
+    import numpy as np
+    offs = np.ascontiguousarray(expert_offsets, dtype=np.int32)
+    n_local = offs.size - 1
+    max_units = _max_device_units(cap_rows, n_local, n_col_blocks)
+    out = np.zeros((max_units, DEBUG_DEVICE_INTS), dtype=np.int32)
+    n = lib().moe_debug_tall_units(offs.ctypes.data, n_local, cap_rows, n_col_blocks, nk, max_slices, out.ctypes.data,
+                                   max_units)
+    if n < 0:
+        raise MoeError("moe_debug_tall_units", n)
+    return out[:n]
+
+
 def moe_debug_down_slices(expert_offsets, cap_rows, shard: MoeShard, with_units=False):
     """Host-only: how the tiled fp32 down projection is cut along K for this routing (see
     include/moe_shard_debug.h): (slices of the 256-row tiles, slices of the remainder tiles, rows
@@ -254,7 +286,7 @@ def moe_debug_device_units(expert_offsets, cap_rows, n_col_blocks, nk, max_slice
     device int32 tensor."""
     import torch
     n_local = expert_offsets.numel() - 1
-    max_units = 8 * ((cap_rows // 256 + n_local) * n_col_blocks // 8 + 1 + 2 * (n_local * n_col_blocks // 8 + 1) + 64)
+    max_units = _max_device_units(cap_rows, n_local, n_col_blocks)
     out = torch.full((max_units, DEBUG_DEVICE_INTS), -7, dtype=torch.int32, device=expert_offsets.device)
     n = lib().moe_debug_device_units(_ptr(expert_offsets), n_local, cap_rows, n_col_blocks, nk, max_slices,
                                      _ptr(out), max_units, _stream(stream))

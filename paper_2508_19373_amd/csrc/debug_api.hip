@@ -78,6 +78,64 @@ extern "C" int32_t moe_debug_even_units(const int32_t* expert_offsets, int32_t n
   return grid;
 }
 
+extern "C" int32_t moe_debug_tall(int32_t cap_rows, const moe_shard_t* shard) {
+  if (cap_rows < 0 || shard == nullptr) return MOE_ERR_INVALID_ARG;
+  if (shard->n_experts < 1 || shard->n_local_experts < 1 || shard->n_local_experts > shard->n_experts)
+    return MOE_ERR_INVALID_ARG;
+  return moe::tall_blocks_allowed(moe::expected_rows(cap_rows, shard), shard->n_local_experts) ? 1 : 0;
+}
+
+extern "C" int32_t moe_debug_tall_units(const int32_t* expert_offsets, int32_t n_local, int32_t cap_rows,
+                                        int32_t n_col_blocks, int32_t nk, int32_t max_slices, int32_t* units,
+                                        int32_t max_units) {
+  using namespace moe::gg;
+  if (expert_offsets == nullptr || units == nullptr || n_local < 1 || cap_rows < 0 || n_col_blocks < 1 || nk < 1 ||
+      max_slices < 0 || max_slices > kMaxKSlices)
+    return MOE_ERR_INVALID_ARG;
+  for (int e = 0; e < n_local; ++e)
+    if (expert_offsets[e] > expert_offsets[e + 1]) return MOE_ERR_INVALID_ARG;
+  if (expert_offsets[0] < 0 || expert_offsets[n_local] > cap_rows) return MOE_ERR_INVALID_ARG;
+  const bool sliced = max_slices > 0;
+  const int grid = sliced ? sliced_grid(cap_rows, n_local, n_col_blocks) : max_grid(cap_rows, n_local, n_col_blocks);
+  if (grid > max_units) return MOE_ERR_WORKSPACE;
+  const ClassCounts cc =
+      count_tiles(expert_offsets, n_local, n_col_blocks, sliced ? sliced_pad_from(nk) : kPadLowTiles, true);
+  const SliceChoice sc = sliced ? choose_slices(cc, n_col_blocks, nk, max_slices) : SliceChoice{0, 1};
+  for (int b = 0; b < grid; ++b) {
+    int32_t* rec = units + (size_t)b * MOE_DEBUG_DEVICE_INTS;
+    for (int i = 0; i < MOE_DEBUG_DEVICE_INTS; ++i) rec[i] = 0;
+    int cls, idx, z = 0;
+    if (sliced) {
+      const SlicedUnit u = find_sliced_unit(cc, sc, n_col_blocks, b);
+      cls = u.cls, idx = u.idx, z = u.z;
+    } else {
+      const Unit u = find_unit(cc, b);
+      cls = u.cls, idx = u.idx;
+    }
+    if (cls < 0) continue;
+    const TileCoord tc =
+        sliced && (cls == 3 || cls == 0)
+            ? locate_full_tile(expert_offsets, n_local, n_col_blocks, sc.keep_rb, cls == 0, idx, cc.pad_low, cc.tall)
+            : locate_tile(expert_offsets, n_local, n_col_blocks, cls, idx, cc.pad_low, cc.tall);
+    const int s = !sliced || cls == 3 ? 1 : sc.slices;
+    const int kt0 = z * nk / s;
+    rec[0] = (cls == 3 || cls == 0) ? 256 + 16 * tc.nx : (cls == 1 ? 128 : 64);
+    rec[1] = tc.expert;
+    rec[2] = tc.row0;
+    rec[3] = tc.row_end;
+    rec[4] = tc.nb;
+    rec[5] = z;
+    rec[6] = kt0;
+    rec[7] = (z + 1) * nk / s - kt0;
+    rec[8] = -1;
+    if (z > 0) {
+      const SlicedRows sr = sliced_rows(expert_offsets, n_local, tc.expert, sc.keep_rb, cc.pad_low, cc.tall);
+      rec[8] = (z - 1) * sr.total + sr.base + tc.row0 - sr.first;
+    }
+  }
+  return grid;
+}
+
 extern "C" int32_t moe_debug_down_slices(const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard,
                                          int32_t* slices, int32_t* units, int32_t max_units) {
   if (expert_offsets == nullptr || cap_rows < 0 || shard == nullptr || slices == nullptr) return MOE_ERR_INVALID_ARG;
@@ -126,7 +184,7 @@ extern "C" int32_t moe_debug_down_slices(const int32_t* expert_offsets, int32_t 
 namespace {
 // One wavefront per workgroup id of the GEMM grid: the record the GEMM kernels would act on.
 __global__ __launch_bounds__(64) void device_units_kernel(const int32_t* __restrict__ expert_offsets, int n_local,
-                                                         int n_col_blocks, int nk, int max_slices,
+                                                         int n_col_blocks, int nk, int max_slices, bool tall,
                                                          int32_t* __restrict__ units) {
   using namespace moe::gg;
   int32_t rec[MOE_DEBUG_DEVICE_INTS] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -144,8 +202,9 @@ __global__ __launch_bounds__(64) void device_units_kernel(const int32_t* __restr
   } else if (max_slices == 0) {
     int cls = 0;
     TileCoord tc;
-    if (find_tile(expert_offsets, n_local, n_col_blocks, blockIdx.x, cls, tc)) {
-      rec[0] = cls == 0 ? 256 : (cls == 1 ? 128 : 64);
+    if (tall ? find_tile<true>(expert_offsets, n_local, n_col_blocks, blockIdx.x, cls, tc)
+             : find_tile(expert_offsets, n_local, n_col_blocks, blockIdx.x, cls, tc)) {
+      rec[0] = cls == 0 ? 256 + 16 * tc.nx : (cls == 1 ? 128 : 64);
       rec[1] = tc.expert;
       rec[2] = tc.row0;
       rec[3] = tc.row_end;
@@ -154,9 +213,11 @@ __global__ __launch_bounds__(64) void device_units_kernel(const int32_t* __restr
       rec[8] = -1;
     }
   } else {
-    const WaveSlicedUnit u = find_sliced_unit_of(expert_offsets, n_local, n_col_blocks, nk, max_slices, blockIdx.x);
+    const WaveSlicedUnit u =
+        tall ? find_sliced_unit_of<true>(expert_offsets, n_local, n_col_blocks, nk, max_slices, blockIdx.x)
+             : find_sliced_unit_of(expert_offsets, n_local, n_col_blocks, nk, max_slices, blockIdx.x);
     if (u.valid) {
-      rec[0] = (u.cls == 3 || u.cls == 0) ? 256 : (u.cls == 1 ? 128 : 64);
+      rec[0] = (u.cls == 3 || u.cls == 0) ? 256 + 16 * u.tc.nx : (u.cls == 1 ? 128 : 64);
       rec[1] = u.tc.expert;
       rec[2] = u.tc.row0;
       rec[3] = u.tc.row_end;
@@ -176,6 +237,8 @@ extern "C" int32_t moe_debug_device_units(const int32_t* expert_offsets, int32_t
                                           int32_t n_col_blocks, int32_t nk, int32_t max_slices, int32_t* units,
                                           int32_t max_units, void* stream) {
   using namespace moe::gg;
+  const bool tall = max_slices >= MOE_DEBUG_TALL;
+  if (tall) max_slices -= MOE_DEBUG_TALL;
   if (expert_offsets == nullptr || units == nullptr || n_local < 1 || n_local > MOE_MAX_EXPERTS || cap_rows < 0 ||
       n_col_blocks < 1 || nk < 1 || max_slices < -1 || max_slices > 16)
     return MOE_ERR_INVALID_ARG;
@@ -184,6 +247,6 @@ extern "C" int32_t moe_debug_device_units(const int32_t* expert_offsets, int32_t
                                                     : max_grid(cap_rows, n_local, n_col_blocks));
   if (grid > max_units) return MOE_ERR_WORKSPACE;
   hipLaunchKernelGGL(device_units_kernel, dim3(grid), dim3(64), 0, static_cast<hipStream_t>(stream), expert_offsets,
-                     n_local, n_col_blocks, nk, max_slices, units);
+                     n_local, n_col_blocks, nk, max_slices, tall, units);
   return hipGetLastError() == hipSuccess ? grid : MOE_ERR_HIP;
 }

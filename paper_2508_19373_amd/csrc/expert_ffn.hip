@@ -22,9 +22,10 @@
 namespace moe {
 namespace {
 
-// Prefill-sized groups: LDS-DMA kernel, 256-column tiles of 256 / 128 / 64 rows.
+// Prefill-sized groups: LDS-DMA kernel, 256-column tiles of 256 / 128 / 64 rows.  `tall`: full row blocks may take
+// their expert's remainder.
 template <int BN>
-hipError_t launch_pair_dlds(const void* x_perm, RowMap rows, const int32_t* expert_offsets, int cap_rows, int est_rows, int n_local, int H,
+hipError_t launch_pair_dlds(bool tall, const void* x_perm, RowMap rows, const int32_t* expert_offsets, int cap_rows, int est_rows, int n_local, int H,
                             int I_s, const void* w_gate, const void* w_up, const void* w_down, void* h_ws,
                             void* y_perm, void* workspace, uint32_t flags, hipStream_t stream) {
   const bool y_bf16 = (flags & MOE_Y_PERM_BF16) != 0;
@@ -34,7 +35,9 @@ hipError_t launch_pair_dlds(const void* x_perm, RowMap rows, const int32_t* expe
   auto grid_for = [&](int ncb) { return dim3((unsigned)gg::max_grid(cap_rows, n_local, ncb)); };
   if (!(flags & MOE_FFN_SKIP_GATEUP)) {
     const int ncb = (I_s + BN / 2 - 1) / (BN / 2);
-    hipLaunchKernelGGL((gg::grouped_gemm_dlds_kernel<BN, true, uint16_t, false>), grid_for(ncb), block, 0, stream, xp,
+    const auto kernel = tall ? gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>
+                             : gg::grouped_gemm_dlds_kernel<BN, true, uint16_t, false>;
+    hipLaunchKernelGGL(kernel, grid_for(ncb), block, 0, stream, xp,
                        expert_offsets, n_local, cap_rows, static_cast<const uint16_t*>(w_gate),
                        static_cast<const uint16_t*>(w_up), I_s, H, hw, ncb, static_cast<uint16_t*>(nullptr), 0, rows);
     hipError_t err = hipGetLastError();
@@ -43,7 +46,9 @@ hipError_t launch_pair_dlds(const void* x_perm, RowMap rows, const int32_t* expe
   if (flags & MOE_FFN_SKIP_DOWN) return hipSuccess;
   const int ncb = (H + BN - 1) / BN;
   if (y_bf16) {
-    hipLaunchKernelGGL((gg::grouped_gemm_dlds_kernel<BN, false, uint16_t, false>), grid_for(ncb), block, 0, stream, hw,
+    const auto kernel = tall ? gg::grouped_gemm_tall_kernel<BN, false, uint16_t, false>
+                             : gg::grouped_gemm_dlds_kernel<BN, false, uint16_t, false>;
+    hipLaunchKernelGGL(kernel, grid_for(ncb), block, 0, stream, hw,
                        expert_offsets, n_local, cap_rows, static_cast<const uint16_t*>(w_down),
                        static_cast<const uint16_t*>(nullptr), H, I_s, static_cast<uint16_t*>(y_perm), ncb,
                        static_cast<uint16_t*>(nullptr), 0, RowMap{nullptr, 1});
@@ -54,19 +59,23 @@ hipError_t launch_pair_dlds(const void* x_perm, RowMap rows, const int32_t* expe
   float* ws = static_cast<float*>(workspace);
   const uint16_t* wd = static_cast<const uint16_t*>(w_down);
   if (sp.max_slices == 1) {
-    hipLaunchKernelGGL((gg::grouped_gemm_dlds_kernel<BN, false, float, false>), grid_for(ncb), block, 0, stream, hw,
+    const auto kernel = tall ? gg::grouped_gemm_tall_kernel<BN, false, float, false>
+                             : gg::grouped_gemm_dlds_kernel<BN, false, float, false>;
+    hipLaunchKernelGGL(kernel, grid_for(ncb), block, 0, stream, hw,
                        expert_offsets, n_local, cap_rows, wd, static_cast<const uint16_t*>(nullptr), H, I_s, yp, ncb,
                        static_cast<float*>(nullptr), 0, RowMap{nullptr, 1});
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((gg::grouped_gemm_dlds_kernel<BN, false, float, true>),
+  const auto kernel = tall ? gg::grouped_gemm_tall_kernel<BN, false, float, true>
+                           : gg::grouped_gemm_dlds_kernel<BN, false, float, true>;
+  hipLaunchKernelGGL(kernel,
                      dim3(gg::sliced_grid(cap_rows, n_local, ncb)), block, 0, stream, hw, expert_offsets, n_local,
                      cap_rows, wd, static_cast<const uint16_t*>(nullptr), H, I_s, ws, ncb, yp, sp.max_slices,
                      RowMap{nullptr, 1});
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   hipLaunchKernelGGL(gg::sum_sliced_kernel, dim3(192, (H + 1023) / 1024), dim3(256), 0, stream, ws, expert_offsets, n_local, ncb,
-                     I_s / gg::BK, sp.max_slices, H, yp);
+                     I_s / gg::BK, sp.max_slices, tall, H, yp);
   return hipGetLastError();
 }
 
@@ -265,7 +274,8 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
   return walk < tiled;
 }
 
-// Row-block height of the tiled kernels for a call: 160 (the one-height list) or 256.
+// Row-block height of the tiled kernels for a call without tall row blocks (tall_blocks_allowed comes first: of the
+// two bands below it leaves the lower one): 160 (the one-height list) or 256.
 // The 160-row tiling pays where it saves the second stream of an expert's weights (or a padded
 // 256-row tile) without adding a block: with the rows per expert just below a multiple of 160.
 // Measured, gate/up + down projection in us, 256-row tiling against 160-row tiling, by average rows
@@ -286,6 +296,17 @@ inline bool prefer_even(int est_rows, int n_local, int H, int I_s) {
 }
 
 }  // namespace
+
+// Whether a tiled call's full row blocks may take their expert's remainder (the kernel then does so in launches
+// that fill the chip).  From 150 rows per expert on: below, hardly an expert has a full block.  Measured, gate/up +
+// down projection in us on one box, without / with: Mixtral (8 experts) 1053 rows each 1653 + 833 / 1419 + 722, 1088:
+// 1667 + 836 / 1463 + 744, 1152: 1714 + 862 / 1569 + 845; its TP=4 slice 2068: 738 + 430 / 693 + 381; counts as a router
+// spreads 4096 tokens 1538 + 780 / 1461 + 735; no remainders at all (1024) 1353 + 675 / 1363 + 675.  Qwen1.5-MoE (60
+// experts, the 160-row tiling before) 256: 262 + 144 / 216 + 123, 286: 262 + 150 / 234 + 134, spread about 273: 258 +
+// 154 / 223 + 144.
+bool tall_blocks_allowed(int est_rows, int n_local) {
+  return (double)est_rows / n_local >= 150.0;
+}
 
 int tiled_block_rows(int cap_rows, int est_rows, int n_local, int H, int I_s) {
   (void)cap_rows;
@@ -326,13 +347,14 @@ hipError_t launch_expert_ffn(const void* x_perm, RowMap rows, const int32_t* exp
   if (cap_rows == 0) return hipSuccess;
   // each GEMM picks its kernel family on its own: h is row-major bf16 for both
   const int mt = decode_mt(cap_rows, est_rows, n_local);
-  const bool even = prefer_even(est_rows, n_local, H, I_s);
+  const bool tall = tall_blocks_allowed(est_rows, n_local);
+  const bool even = !tall && prefer_even(est_rows, n_local, H, I_s);
   auto run = [&](bool walk, uint32_t f) {
     if (!walk && even)
       return launch_pair_even(x_perm, rows, expert_offsets, cap_rows, n_local, H, I_s, w_gate, w_up, w_down, h_ws,
                               y_perm, f, stream);
     if (!walk)
-      return launch_pair_dlds<256>(x_perm, rows, expert_offsets, cap_rows, est_rows, n_local, H, I_s, w_gate, w_up, w_down,
+      return launch_pair_dlds<256>(tall, x_perm, rows, expert_offsets, cap_rows, est_rows, n_local, H, I_s, w_gate, w_up, w_down,
                                    h_ws, y_perm, workspace, f, stream);
     if (mt == 1)
       return launch_pair_decode<1>(x_perm, rows, expert_offsets, cap_rows, n_local, H, I_s, w_gate, w_up, w_down, h_ws,

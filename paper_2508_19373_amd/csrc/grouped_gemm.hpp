@@ -78,6 +78,38 @@ constexpr int dma_slack(int j, int NSA, int NSB, int A_INST, int B_INST) {
   return n;
 }
 
+// Buffer descriptor over the 4 GiB from p on (raw: offsets in bytes), and loads through it into LDS and into
+// registers.  (The host compilation does not know the descriptor type.)
+constexpr uint32_t kBufBytes = 0xFFFFFFFFu;
+#ifdef __HIP_DEVICE_COMPILE__
+typedef __amdgpu_buffer_rsrc_t buf_t;
+__device__ __forceinline__ buf_t make_buf(const void* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, kBufBytes, 0x00027000);
+}
+__device__ __forceinline__ void buf_to_lds(buf_t b, lds_void_t* dst, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(b, dst, 16, lane_off, off, 0, 0);
+}
+__device__ __forceinline__ bf16x8 buf_load(buf_t b, uint32_t lane_off, uint32_t off) {
+  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b, lane_off, off, 0));
+}
+#else
+struct buf_t {};
+__device__ inline buf_t make_buf(const void*) { return buf_t{}; }
+__device__ inline void buf_to_lds(buf_t, lds_void_t*, uint32_t, uint32_t) {}
+__device__ inline bf16x8 buf_load(buf_t, uint32_t, uint32_t) { return bf16x8{}; }
+#endif
+
+// acc += a . b with the accumulator in the vector half of the register file (the compiler keeps the accumulators of
+// a kernel's own MFMAs in the 256 accumulation registers, and a tall tile has up to 304).  The compiler does not see
+// that this is an MFMA and adds no wait states for it: 2 after a VALU write of an operand (gemm_tile keeps two
+// MFMAs in between), none before a dependent MFMA of the same kind, and the accumulator is next read by
+// another instruction hundreds of MFMAs later.
+__device__ __forceinline__ void mfma_vgpr(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+#endif
+}
+
 // One (BM x BN) output tile, computed by the whole workgroup of WM x WN wavefronts, on
 // v_mfma_f32_16x16x32_bf16 with the k-tile's operands resident in registers.
 //
@@ -89,7 +121,13 @@ constexpr int dma_slack(int j, int NSA, int NSB, int A_INST, int B_INST) {
 // right after its last use.  LDS is then a multi-stage landing buffer in front of the register
 // tile, still with one barrier per k-tile.
 // The traversal order and the refresh schedule are described at k_tile below.
-template <int BM, int BN, int WM, int WN, int NSA, int NSB, bool GATEUP, typename OutT>
+//
+// NX > 0 (tall tile): 16 * NX more rows behind the BM rows, so that an expert's last few rows ride along with
+// its full row blocks instead of streaming the expert's weights again in a remainder tile.  All of LDS is
+// taken, so their operands go from memory (L2: every column block reads the same rows) straight to registers,
+// one k-tile ahead; the two wave-rows share their MFMA work, each taking half of the wave-column's weight rows.
+// Those have to be the same registers in both: wave-row 1 numbers its weight row blocks from the middle.
+template <int BM, int BN, int WM, int WN, int NSA, int NSB, bool GATEUP, typename OutT, int NX = 0, bool BUF = false>
 __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, const uint16_t* __restrict__ A,
                                             int cap_rows, const uint16_t* __restrict__ B0,
                                             const uint16_t* __restrict__ B1, int n_out, int K, int kt0, int nk,
@@ -106,30 +144,44 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
   static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0, "loader mismatch");
   static_assert(!GATEUP || (TN % 2 == 0), "gate and up column blocks must pair up inside a wave");
   static_assert(TM >= 3, "needs a first, a middle and a last row block");
+  static_assert(NX == 0 || (WM == 2 && TN % 4 == 0), "the extra rows are shared by two wave-rows");
+  constexpr int XN = NX > 0 ? TN / WM : 0;  // weight row blocks a wave multiplies the extra rows with
   const int row0 = tc.row0, hi = tc.row_end, col0 = tc.nb * NCOLS;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
 
+  // DMA instruction j of a wave loads 8 rows of 128 bytes; the swizzled chunk a lane fetches is the same for all j
+  static_assert(NW % 2 == 0, "a wave's DMA instructions start at rows with the same swizzle");
+  const int dma_row = lane >> 3, dma_chunk = (lane & 7) ^ swz(wave * 8 + dma_row);
+  // BUF: both operands are addressed as buffers (32-bit lane offsets + scalar offsets).  That saves the registers
+  // a tall tile's extra rows need, and only between buffer instructions does the compiler count how many loads may be
+  // outstanding behind a register load (behind global_load_lds it waits for all of them)
+  static_assert(NX == 0 || BUF, "extra rows need buffer addressing");
+  const uint16_t* a_base = A + (rows.row_src ? 0 : (size_t)row0 * K) + (size_t)kt0 * BK;
+  const int a_row0 = rows.row_src ? 0 : row0;
+  uint32_t a_lane[A_INST];  // BUF: byte offsets from a_base
   const uint16_t* a_src[A_INST];
-  const uint16_t* b_src[B_INST];
 #pragma unroll
   for (int j = 0; j < A_INST; ++j) {
-    const int inst = j * NW + wave;
-    const int r = inst * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ swz(r);
+    const int r = row0 + (j * NW + wave) * 8 + dma_row;
     // rows past the tile's expert are computed and dropped: they read any valid row (with a row
     // map, the expert's last one: entries past the routed rows are not defined)
-    const int gr = rows.row_src ? rows(min(row0 + r, hi - 1)) : min(row0 + r, cap_rows - 1);
-    a_src[j] = A + (size_t)gr * K + (size_t)kt0 * BK + c * 8;
+    const int gr = rows.row_src ? rows(min(r, hi - 1)) : min(r, cap_rows - 1);
+    a_src[j] = A + (size_t)gr * K + (size_t)kt0 * BK + dma_chunk * 8;
+    a_lane[j] = (uint32_t)(gr - a_row0) * (uint32_t)K * 2u + (uint32_t)dma_chunk * 16u;
   }
+  // weights: the 8 rows of an instruction are consecutive rows of one matrix, so their address is a scalar base
+  // per instruction plus one 32-bit lane offset for all of them (14 vector registers fewer than lane pointers);
+  // n_out is a multiple of 64, so the last column block is clamped by whole instructions
+  const uint32_t b_lane = (uint32_t)dma_row * (uint32_t)K * 2u + (uint32_t)dma_chunk * 16u;
+  const uint16_t* b_src[B_INST];
+  uint32_t b_off[B_INST];  // BUF: byte offset from the tile's first weight row
   const size_t expert_stride = (size_t)n_out * K;
 #pragma unroll
   for (int j = 0; j < B_INST; ++j) {
-    const int inst = j * NW + wave;
-    const int r = inst * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ swz(r);
+    const int r = (j * NW + wave) * 8;
     const uint16_t* base = B0;
     int wrow;
     if (GATEUP) {  // 16-row blocks alternate gate, up, gate, up ... of the same output columns
@@ -139,9 +191,34 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
     } else {
       wrow = col0 + r;
     }
-    wrow = min(wrow, n_out - 1);
-    b_src[j] = base + (size_t)tc.expert * expert_stride + (size_t)wrow * K + (size_t)kt0 * BK + c * 8;
+    wrow = min(wrow, n_out - 8);
+    b_src[j] = base + (size_t)tc.expert * expert_stride + (size_t)wrow * K + (size_t)kt0 * BK;
+    b_off[j] = (uint32_t)(wrow - col0) * (uint32_t)K * 2u;
   }
+  // (in GATEUP mode all instructions of a wave load from the same matrix: 16-row blocks alternate, a wave's
+  // instructions are NW * 8 = 32 rows apart)
+  static_assert(!GATEUP || NW * 8 % 32 == 0, "one matrix per wave");
+  const uint16_t* b_base = (GATEUP && ((wave >> 1) & 1) ? B1 : B0) + (size_t)tc.expert * expert_stride +
+                           (size_t)col0 * K + (size_t)kt0 * BK;
+  const buf_t a_buf = make_buf(a_base), b_buf = make_buf(b_base);
+
+  const int lrow = lane & 15;
+  const int kq = lane >> 4;
+  uint32_t x_lane[NX > 0 ? NX : 1];
+#pragma unroll
+  for (int x = 0; x < NX; ++x) {
+    const int r = row0 + BM + x * 16 + lrow;
+    const int gr = rows.row_src ? rows(min(r, hi - 1)) : min(r, cap_rows - 1);
+    x_lane[x] = (uint32_t)(gr - a_row0) * (uint32_t)K * 2u + (uint32_t)kq * 16u;
+  }
+  bf16x8 xf[NX > 0 ? NX : 1][2];
+  auto load_x = [&](int kt) {
+#pragma unroll
+    for (int x = 0; x < NX; ++x)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+        xf[x][ks] = buf_load(a_buf, x_lane[x] + ks * 64, kt * (BK * 2));
+  };
 
   constexpr int N_DMA = A_INST + B_INST;
   // DMA instruction `idx` of a k-tile's group: the activation rows first, then the weight rows
@@ -149,19 +226,27 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
   auto issue_dma = [&](int kt_a, int stage_a, int kt_b, int stage_b, auto idx_tag) {
     constexpr int idx = decltype(idx_tag)::value;
     if constexpr (idx < A_INST) {
-      __builtin_amdgcn_global_load_lds((global_void_t*)(a_src[idx] + (size_t)kt_a * BK),
-                                       (lds_void_t*)(smem + stage_a * A_STAGE + (idx * NW + wave) * 8 * BK), 16, 0, 0);
+      lds_void_t* dst = (lds_void_t*)(smem + stage_a * A_STAGE + (idx * NW + wave) * 8 * BK);
+      if constexpr (BUF)
+        buf_to_lds(a_buf, dst, a_lane[idx], kt_a * (BK * 2));
+      else
+        __builtin_amdgcn_global_load_lds((global_void_t*)(a_src[idx] + (size_t)kt_a * BK), dst, 16, 0, 0);
     } else {
       constexpr int j = idx - A_INST;
-      __builtin_amdgcn_global_load_lds(
-          (global_void_t*)(b_src[j] + (size_t)kt_b * BK),
-          (lds_void_t*)(smem + NSA * A_STAGE + stage_b * B_STAGE + (j * NW + wave) * 8 * BK), 16, 0, 0);
+      lds_void_t* dst = (lds_void_t*)(smem + NSA * A_STAGE + stage_b * B_STAGE + (j * NW + wave) * 8 * BK);
+      if constexpr (BUF)
+        buf_to_lds(b_buf, dst, b_lane, b_off[j] + kt_b * (BK * 2));
+      else
+        __builtin_amdgcn_global_load_lds(
+            (global_void_t*)(reinterpret_cast<const char*>(b_src[j] + (size_t)kt_b * BK) + b_lane), dst, 16, 0, 0);
     }
   };
 
-  const int a_row = wm * (BM / WM) + (lane & 15);
-  const int b_row = wn * (BN / WN) + (lane & 15);
-  const int kq = lane >> 4;
+  const int a_row = wm * (BM / WM) + lrow;
+  const int b_row = wn * (BN / WN) + lrow;
+  // weight row block j of the wave's own numbering (see NX above)
+  const int b_half[2] = {b_row + (NX > 0 ? wm * (XN * 16) : 0), b_row - (NX > 0 ? wm * (XN * 16) : 0)};
+  auto j_phys = [&](int j) { return NX == 0 ? j : (j < XN ? j + wm * XN : j - wm * XN); };
   bf16x8 af[TM][2], bfr[TN][2];
   auto read_a = [&](int stage, auto i_tag, auto ks_tag) {
     constexpr int i = decltype(i_tag)::value, ks = decltype(ks_tag)::value;
@@ -170,7 +255,7 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
   auto read_b = [&](int stage, auto j_tag, auto ks_tag) {
     constexpr int j = decltype(j_tag)::value, ks = decltype(ks_tag)::value;
     bfr[j][ks] = *reinterpret_cast<const bf16x8*>(smem + NSA * A_STAGE + stage * B_STAGE +
-                                                  lds_off(b_row + j * 16, ks * 4 + kq));
+                                                  lds_off(b_half[NX > 0 && j >= XN] + j * 16, ks * 4 + kq));
   };
 
   f32x4 acc[TM][TN];
@@ -178,6 +263,11 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 xacc[NX > 0 ? NX : 1][XN > 0 ? XN : 1];
+#pragma unroll
+  for (int x = 0; x < NX; ++x)
+#pragma unroll
+    for (int j = 0; j < XN; ++j) xacc[x][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   using T_ = std::true_type;
   using F_ = std::false_type;
@@ -220,6 +310,16 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
       // lane ends up with 4 CONSECUTIVE output columns of one row (one 8- or 16-byte store)
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j][0], af[i][0], acc[i][j], 0, 0, 0);
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j][1], af[i][1], acc[i][j], 0, 0, 0);
+      if constexpr (NX > 0 && p < TN && p % 2 == 0) {  // extra rows: before their registers are loaded again below
+        __builtin_amdgcn_sched_barrier(0);  // two MFMAs of the compiler's own stand between its last VALU write and these
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+          constexpr int jx = p / 2 < XN ? p / 2 : 0;
+          mfma_vgpr(xacc[x][jx], bfr[jx][0], xf[x][0]);
+          mfma_vgpr(xacc[x][jx], bfr[jx][1], xf[x][1]);
+        }
+      }
+      if constexpr (NX > 0 && SYNC && p == TN) load_x(kt + 1);  // ahead of the DMA group: dma_slack need not count it
       if constexpr (p < LOWER_SPAN)
         static_for<(p * TM + LOWER_SPAN - 1) / LOWER_SPAN, ((p + 1) * TM + LOWER_SPAN - 1) / LOWER_SPAN>([&](auto r_tag) {
           constexpr int r = decltype(r_tag)::value;
@@ -257,6 +357,7 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
 
   // prologue: tile 0, then the groups that tiles -(NSB-1) .. -1 would have issued, in their order
   static_for<0, N_DMA>([&](auto d_tag) { issue_dma(0, 0, 0, 0, d_tag); });
+  load_x(0);
   wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   static_for<1 - NSB, 0>([&](auto t_tag) {
@@ -293,42 +394,43 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
 
   // ---- epilogue: accumulator register v of tile (i, j) is row i*16 + lane%16, column
   // j*16 + (lane/16)*4 + v of the wave's sub-tile
-  const int lrow = lane & 15, lcol = (lane >> 4) * 4;
-  const bool full = (row0 + BM <= hi) && (col0 + NCOLS <= n_out);  // n_out is a multiple of 4
+  const int lcol = kq * 4;
+  const bool full = (row0 + BM + 16 * NX <= hi) && (col0 + NCOLS <= n_out);  // n_out is a multiple of 4
   auto store_tile = [&](auto guard) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int row = row0 + wm * (BM / WM) + i * 16 + lrow;
+    auto store_row = [&](int row, const f32x4* r, int n_blocks) {
       if constexpr (GATEUP) {
 #pragma unroll
-        for (int j = 0; j < TN; j += 2) {
-          const int jb = wn * TN + j;  // even: gate block; jb + 1: up block of the same columns
+        for (int j = 0; j < n_blocks; j += 2) {
+          const int jb = wn * TN + j_phys(j);  // even: gate block; jb + 1: up block of the same columns
           const int col = col0 + (jb >> 1) * 16 + lcol;
           if (guard(row, col)) {
             uint2 o;
-            o.x = pack_bf16x2(silu_mul(acc[i][j][0], acc[i][j + 1][0]), silu_mul(acc[i][j][1], acc[i][j + 1][1]));
-            o.y = pack_bf16x2(silu_mul(acc[i][j][2], acc[i][j + 1][2]), silu_mul(acc[i][j][3], acc[i][j + 1][3]));
+            o.x = pack_bf16x2(silu_mul(r[j][0], r[j + 1][0]), silu_mul(r[j][1], r[j + 1][1]));
+            o.y = pack_bf16x2(silu_mul(r[j][2], r[j + 1][2]), silu_mul(r[j][3], r[j + 1][3]));
             *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(C) + (size_t)row * n_out + col) = o;
           }
         }
       } else {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int col = col0 + wn * (BN / WN) + j * 16 + lcol;
+        for (int j = 0; j < n_blocks; ++j) {
+          const int col = col0 + wn * (BN / WN) + j_phys(j) * 16 + lcol;
           if (guard(row, col)) {
             if constexpr (sizeof(OutT) == 4) {
-              *reinterpret_cast<float4*>(C + (size_t)row * n_out + col) =
-                  make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+              *reinterpret_cast<float4*>(C + (size_t)row * n_out + col) = make_float4(r[j][0], r[j][1], r[j][2], r[j][3]);
             } else {
               uint2 o;
-              o.x = pack_bf16x2(acc[i][j][0], acc[i][j][1]);
-              o.y = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
+              o.x = pack_bf16x2(r[j][0], r[j][1]);
+              o.y = pack_bf16x2(r[j][2], r[j][3]);
               *reinterpret_cast<uint2*>(C + (size_t)row * n_out + col) = o;
             }
           }
         }
       }
-    }
+    };
+#pragma unroll
+    for (int i = 0; i < TM; ++i) store_row(row0 + wm * (BM / WM) + i * 16 + lrow, acc[i], TN);
+#pragma unroll
+    for (int x = 0; x < NX; ++x) store_row(row0 + BM + x * 16 + lrow, xacc[x], XN);
   };
   if (full)
     store_tile([](int, int) { return true; });
@@ -373,6 +475,77 @@ __global__ __launch_bounds__(256) void grouped_gemm_dlds_kernel(
     gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
 }
 
+// The same GEMM with tall row blocks (RowBlocks in unit_list.hpp), bound: bf16 MFMA at the power limit, like the
+// 256-row tile (1088 rows per expert, four tiles of 272: gate/up 1397 TFLOP/s, four of 256 1411; with remainder tiles
+// 1226).  A kernel of its own: the additional variants would cost the one above registers.  Its 256-row tiles use
+// buffer addressing too (gate/up at 1024 rows per expert 1426 -> 1363 us).
+template <int BN, bool GATEUP, typename OutT, bool SLICED>
+__global__ __launch_bounds__(256) void grouped_gemm_tall_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
+    const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, OutT* __restrict__ C,
+    int n_col_blocks, OutT* __restrict__ y, int max_slices, const RowMap rows) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kLdsBytes / 2];
+  int nk = K / BK, kt0 = 0, cls;
+  OutT* out = C;
+  TileCoord tc;
+  if constexpr (SLICED) {
+    const WaveSlicedUnit u = find_sliced_unit_of<true>(expert_offsets, n_local, n_col_blocks, nk, max_slices, blockIdx.x);
+    if (!u.valid) return;
+    cls = u.cls;
+    // uniform by construction; the buffer descriptors made from them have to be seen to be
+    tc.expert = __builtin_amdgcn_readfirstlane(u.tc.expert);
+    tc.row0 = __builtin_amdgcn_readfirstlane(u.tc.row0);
+    tc.row_end = __builtin_amdgcn_readfirstlane(u.tc.row_end);
+    tc.nb = __builtin_amdgcn_readfirstlane(u.tc.nb);
+    tc.nx = __builtin_amdgcn_readfirstlane(u.tc.nx);
+    kt0 = __builtin_amdgcn_readfirstlane(u.kt0);
+    nk = __builtin_amdgcn_readfirstlane(u.nk);
+    out = u.z == 0 ? y : C + u.scratch_shift * n_out;
+  } else {
+    if (!find_tile<true>(expert_offsets, n_local, n_col_blocks, blockIdx.x, cls, tc)) return;
+  }
+  // full blocks address their input rows with 32-bit byte offsets: from their own first row, or from x when the
+  // rows are gathered; rows of x beyond 4 GiB (assignments are in order inside an expert, so its last row is the
+  // furthest) run as 64-row tiles one after the other, which address any row
+  if (cls == 0 && rows.row_src != nullptr) {
+    const int end = min(tc.row_end, tc.row0 + 256 + 16 * tc.nx);
+    if ((uint64_t)(rows(end - 1) + 1) * K * 2 > kBufBytes) {
+      tc.row_end = end;
+      cls = 2;
+    }
+  }
+  if constexpr (SLICED) {
+    if (cls == 3) {  // a whole tile: constant k range and output
+      if (tc.nx == 0)
+        gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 0, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, 0, K / BK, y);
+      else if (tc.nx == 1)
+        gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 1, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, 0, K / BK, y);
+      else if (tc.nx == 2)
+        gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 2, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, 0, K / BK, y);
+      else
+        gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 3, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, 0, K / BK, y);
+      return;
+    }
+  }
+  if (cls == 0 && tc.nx == 0)
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 0, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+  else if (cls == 0 && tc.nx == 1)
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 1, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+  else if (cls == 0 && tc.nx == 2)
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 2, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+  else if (cls == 0)
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 3, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+  else if (cls == 1)
+    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+  else
+    for (;;) {
+      gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+      tc.row0 += 64;
+      if (tc.row0 >= tc.row_end) break;  // a 64-row tile proper is its expert's last
+      __syncthreads();                   // before the next one refills the LDS stages
+    }
+}
+
 // The same GEMM on the work list of unit_list_even.hpp: every tile is 160 rows x 256 weight rows, four
 // wavefronts side by side, each with all 160 rows and 64 weight rows (10 x 4 accumulator blocks), three
 // LDS stages of each operand.  Chosen on the host for launches with a few hundred rows per expert.
@@ -392,9 +565,9 @@ __global__ __launch_bounds__(256) void grouped_gemm_even_kernel(
 // grid.x walks the rows, grid.y the column chunks.
 __global__ __launch_bounds__(256) void sum_sliced_kernel(const float* __restrict__ partial,
                                                         const int32_t* __restrict__ expert_offsets, int n_local,
-                                                        int n_col_blocks, int nk, int max_slices, int n_out,
-                                                        float* __restrict__ y) {
-  const SumPlan plan = sum_plan(expert_offsets, n_local, n_col_blocks, nk, max_slices);
+                                                        int n_col_blocks, int nk, int max_slices, bool allow_tall,
+                                                        int n_out, float* __restrict__ y) {
+  const SumPlan plan = sum_plan(expert_offsets, n_local, n_col_blocks, nk, max_slices, allow_tall);
   if (plan.slices == 1) return;
   const int total = plan.total;
   const size_t stride = (size_t)total * n_out / 4;

@@ -22,13 +22,34 @@ constexpr int kNumXcd = 8;
 // and the second stream is pure loss (Mixtral at 128 rows per expert: 892 -> 673 us per layer); in
 // a launch short of tiles it keeps 128 + 64, whose deeper pipelines stream faster per compute unit
 // (a single expert of 181 rows: GEMM1 72 against 81 us).
+//
+// Tall row blocks (`tall`): the remainder of an expert that has full blocks is dealt to them, 16 * nx rows more
+// for each of the first nt blocks, with the smallest nx <= kMaxExtra that holds it.  Then no remainder tile streams
+// the expert's weights again, at the cost of nx / 16 of a block's MFMA work for nt blocks (never much more than
+// the one padded block it replaces).  A remainder above kMaxTallRemainder rows is a padded block as before: that
+// keeps more tiles of the cheapest height for nearly the same work (TP=4 slice of Mixtral, 8 experts of 2048 rows
+// on average, spread as a router does: gate/up 802 us with every remainder dealt out, 691 with this limit, 716-742
+// without tall blocks).  Only in launches that fill the chip (ClassCounts::tall): with compute units
+// to spare a remainder tile of its own costs nothing.
+constexpr int kMaxExtra = 3;
+constexpr int kMaxTallRemainder = 144;
 struct RowBlocks {
   int n256, n128, n64;
+  int nx, nt;
   __host__ __device__ inline int total() const { return n256 + n128 + n64; }
+  // first row of full block b, or of what follows the full blocks (b = n256)
+  __host__ __device__ inline int start(int b) const { return b * 256 + (b < nt ? b : nt) * nx * 16; }
+  __host__ __device__ inline int extra(int b) const { return b < nt ? nx : 0; }
 };
-__host__ __device__ inline RowBlocks row_blocks(int rows, bool pad_low) {
-  RowBlocks rb;
+__host__ __device__ inline RowBlocks row_blocks(int rows, bool pad_low, bool tall = false) {
+  RowBlocks rb = {0, 0, 0, 0, 0};
   const int q = rows >> 8, r = rows & 255;
+  if (tall && r > 0 && r <= kMaxTallRemainder && r <= q * (kMaxExtra * 16)) {
+    rb.n256 = q;
+    rb.nx = r <= q * 16 ? 1 : (r <= q * 32 ? 2 : 3);
+    rb.nt = (r + rb.nx * 16 - 1) / (rb.nx * 16);
+    return rb;
+  }
   const int pad = (q > 0 || pad_low) ? 128 : 192;  // remainders above this become a 256-row block
   rb.n256 = q + (r > pad ? 1 : 0);
   rb.n128 = (r > 64 && r <= pad) ? 1 : 0;
@@ -36,16 +57,18 @@ __host__ __device__ inline RowBlocks row_blocks(int rows, bool pad_low) {
   return rb;
 }
 
+// nx: the tile has 16 * nx rows more than its height class
 struct TileCoord {
-  int expert, row0, row_end, nb;
+  int expert, row0, row_end, nb, nx;
 };
 
 // Tiles per height class (0: 256 rows, 1: 128, 2: 64), over all local experts and column blocks.
 // pad_low: the launch has at least 256 tiles before any padding of experts below 256 rows, that is,
 // it fills every compute unit (every function below takes the flag from here).
+// tall: full blocks take the remainders where they can (the call allows it and the launch fills the chip).
 struct ClassCounts {
   int n[3];
-  bool pad_low;
+  bool pad_low, tall;
 };
 constexpr int kPadLowTiles = 256;
 // The sliced down projection pads from 128 tiles on (sliced_pad_from): its tiles are cut along K until they fill the
@@ -59,13 +82,14 @@ constexpr int kPadLowTiles = 256;
 // 179 -> 172 us at 768).
 __host__ __device__ inline int sliced_pad_from(int nk) { return nk >= 48 ? 128 : kPadLowTiles; }
 __host__ __device__ inline ClassCounts count_tiles(const int32_t* __restrict__ expert_offsets, int n_local,
-                                                   int n_col_blocks, int pad_from = kPadLowTiles) {
-  ClassCounts c = {{0, 0, 0}, false};
+                                                   int n_col_blocks, int pad_from = kPadLowTiles, bool allow_tall = false) {
+  ClassCounts c = {{0, 0, 0}, false, false};
   int blocks = 0;
   for (int e = 0; e < n_local; ++e) blocks += row_blocks(expert_offsets[e + 1] - expert_offsets[e], false).total();
   c.pad_low = blocks * n_col_blocks >= pad_from;
+  c.tall = allow_tall && c.pad_low;
   for (int e = 0; e < n_local; ++e) {
-    const RowBlocks rb = row_blocks(expert_offsets[e + 1] - expert_offsets[e], c.pad_low);
+    const RowBlocks rb = row_blocks(expert_offsets[e + 1] - expert_offsets[e], c.pad_low, c.tall);
     c.n[0] += rb.n256 * n_col_blocks;
     c.n[1] += rb.n128 * n_col_blocks;
     c.n[2] += rb.n64 * n_col_blocks;
@@ -77,18 +101,20 @@ __host__ __device__ inline ClassCounts count_tiles(const int32_t* __restrict__ e
 // inside a column block the row blocks of that class (row block fastest, so neighbours share the
 // weight panel and a run of tiles covers all full row blocks of a few column blocks).
 __host__ __device__ inline TileCoord locate_tile(const int32_t* __restrict__ expert_offsets, int n_local,
-                                                 int n_col_blocks, int cls, int idx, bool pad_low) {
-  TileCoord t = {0, 0, 0, 0};
+                                                 int n_col_blocks, int cls, int idx, bool pad_low,
+                                                 bool tall = false) {
+  TileCoord t = {0, 0, 0, 0, 0};
   for (int e = 0; e < n_local; ++e) {
     const int lo = expert_offsets[e], hi = expert_offsets[e + 1];
-    const RowBlocks rb = row_blocks(hi - lo, pad_low);
+    const RowBlocks rb = row_blocks(hi - lo, pad_low, tall);
     const int mbs = cls == 0 ? rb.n256 : (cls == 1 ? rb.n128 : rb.n64);
     const int tiles = mbs * n_col_blocks;
     if (idx < tiles) {
       t.expert = e;
       t.nb = idx / mbs;
       t.row_end = hi;
-      t.row0 = lo + (cls == 0 ? (idx % mbs) * 256 : (cls == 1 ? rb.n256 * 256 : rb.n256 * 256 + rb.n128 * 128));
+      t.row0 = lo + (cls == 0 ? rb.start(idx % mbs) : (cls == 1 ? rb.n256 * 256 : rb.n256 * 256 + rb.n128 * 128));
+      t.nx = cls == 0 ? rb.extra(idx % mbs) : 0;
       return t;
     }
     idx -= tiles;
@@ -160,6 +186,8 @@ __host__ __device__ inline int fit_slices(int n_tiles, int nk, int max_slices, i
   if (hi > nk / 8) hi = nk / 8;
   int best = 1, best_cost = nk * 16;
   for (int s = 2; s <= hi; ++s) {
+    // what the scratch holds; with blocks of 256 rows the workgroup count above already keeps to it
+    if ((s - 1) * rows > 65536 / n_col_blocks) break;
     const int cost = (nk * 16 + s - 1) / s + 64 + rows * n_col_blocks * (s + 1) / 275;
     if (cost < best_cost) best = s, best_cost = cost;
   }
@@ -182,7 +210,9 @@ __host__ __device__ inline SliceChoice choose_slices(const ClassCounts& c, int n
     if (last > 0 && last <= 128) tail_rb = (last + n_col_blocks - 1) / n_col_blocks;
   }
   SliceChoice sc;
-  sc.slices = fit_slices(tail_rb * n_col_blocks + n_small, nk, max_slices, tail_rb * 256 + small_rows, n_col_blocks);
+  const int block_rows = c.tall ? 256 + kMaxExtra * 16 : 256;  // at most
+  sc.slices = fit_slices(tail_rb * n_col_blocks + n_small, nk, max_slices, tail_rb * block_rows + small_rows,
+                         n_col_blocks);
   if (sc.slices == 1 && n_small > 0 && tail_rb > 0) {
     sc.slices = fit_slices(n_small, nk, max_slices, small_rows, n_col_blocks);
     tail_rb = 0;
@@ -228,12 +258,13 @@ __host__ __device__ inline SlicedUnit find_sliced_unit(const ClassCounts& c, con
 // experts in order, column blocks, row blocks fastest, as locate_tile.
 __host__ __device__ inline TileCoord locate_full_tile(const int32_t* __restrict__ expert_offsets, int n_local,
                                                       int n_col_blocks, int keep_rb, bool tail, int idx,
-                                                      bool pad_low) {
-  TileCoord t = {0, 0, 0, 0};
+                                                      bool pad_low, bool tall = false) {
+  TileCoord t = {0, 0, 0, 0, 0};
   int before = 0;
   for (int e = 0; e < n_local; ++e) {
     const int lo = expert_offsets[e], hi = expert_offsets[e + 1];
-    const int n256 = row_blocks(hi - lo, pad_low).n256;
+    const RowBlocks rb = row_blocks(hi - lo, pad_low, tall);
+    const int n256 = rb.n256;
     const int kept = min(max(keep_rb - before, 0), n256);
     const int mbs = tail ? n256 - kept : kept;
     const int tiles = mbs * n_col_blocks;
@@ -241,7 +272,8 @@ __host__ __device__ inline TileCoord locate_full_tile(const int32_t* __restrict_
       t.expert = e;
       t.nb = idx / mbs;
       t.row_end = hi;
-      t.row0 = lo + (idx % mbs + (tail ? kept : 0)) * 256;
+      t.row0 = lo + rb.start(idx % mbs + (tail ? kept : 0));
+      t.nx = rb.extra(idx % mbs + (tail ? kept : 0));
       return t;
     }
     idx -= tiles;
@@ -253,18 +285,19 @@ __host__ __device__ inline TileCoord locate_full_tile(const int32_t* __restrict_
 // whole 256-row blocks.  For expert e: `first` is its first such row and `base` that row's compact
 // number; `total` counts them over the shard.  Slice z >= 1 keeps the partial sums of compact row i
 // at row (z - 1) * total + i of the scratch: (slices - 1) * total <= 65536 / n_col_blocks rows,
-// since slices * tiles <= 256 and a tile has at most 256 rows.
+// since slices * tiles <= 256 and a tile has at most 256 rows (taller ones: fit_slices sees to it).
 struct SlicedRows {
   int base, first, total;
 };
 __host__ __device__ inline SlicedRows sliced_rows(const int32_t* __restrict__ expert_offsets, int n_local, int e,
-                                                  int keep_rb, bool pad_low) {
+                                                  int keep_rb, bool pad_low, bool tall = false) {
   SlicedRows r = {0, 0, 0};
   int before = 0;
   for (int i = 0; i < n_local; ++i) {
     const int lo = expert_offsets[i], hi = expert_offsets[i + 1];
-    const int n256 = row_blocks(hi - lo, pad_low).n256;
-    const int first = min(hi, lo + min(max(keep_rb - before, 0), n256) * 256);
+    const RowBlocks rb = row_blocks(hi - lo, pad_low, tall);
+    const int n256 = rb.n256;
+    const int first = min(hi, lo + rb.start(min(max(keep_rb - before, 0), n256)));
     if (i == e) {
       r.base = r.total;
       r.first = first;

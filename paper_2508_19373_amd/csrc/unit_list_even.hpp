@@ -37,7 +37,7 @@ __host__ __device__ inline int even_tile_index(int n_tiles, int vb) {
 
 __host__ __device__ inline TileCoord even_locate(const int32_t* __restrict__ expert_offsets, int n_local,
                                                  int n_col_blocks, int idx) {
-  TileCoord t = {0, 0, 0, 0};
+  TileCoord t = {0, 0, 0, 0, 0};
   for (int e = 0; e < n_local; ++e) {
     const int lo = expert_offsets[e], hi = expert_offsets[e + 1];
     const int mbs = even_blocks(hi - lo), tiles = mbs * n_col_blocks;

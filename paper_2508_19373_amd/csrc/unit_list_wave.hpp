@@ -78,12 +78,13 @@ __device__ inline int wave_pick(const int (&a)[kLaneChunks], const WaveHit& h) {
 struct WaveRouting {
   int chunks;
   int lo[kLaneChunks], rows[kLaneChunks];
-  int n256[kLaneChunks], n128[kLaneChunks], n64[kLaneChunks];
+  int n256[kLaneChunks], n128[kLaneChunks], n64[kLaneChunks], nx[kLaneChunks], nt[kLaneChunks];
   int pre256[kLaneChunks];
   ClassCounts cc;  // as count_tiles
 };
 __device__ inline WaveRouting wave_routing(const int32_t* __restrict__ expert_offsets, int n_local,
-                                           int n_col_blocks, int pad_from = kPadLowTiles) {
+                                           int n_col_blocks, int pad_from = kPadLowTiles,
+                                           bool allow_tall = false) {
   WaveRouting w;
   const int lane = threadIdx.x & 63;
   w.chunks = (n_local + 63) >> 6;
@@ -97,10 +98,13 @@ __device__ inline WaveRouting wave_routing(const int32_t* __restrict__ expert_of
     blocks += row_blocks(w.rows[j], false).total();
   }
   w.cc.pad_low = __builtin_amdgcn_readlane(wave_incl_scan(blocks), 63) * n_col_blocks >= pad_from;
+  w.cc.tall = allow_tall && w.cc.pad_low;
   int t128 = 0, t64 = 0;
 #pragma unroll
   for (int j = 0; j < kLaneChunks; ++j) {
-    const RowBlocks rb = row_blocks(w.rows[j], w.cc.pad_low);
+    const RowBlocks rb = row_blocks(w.rows[j], w.cc.pad_low, w.cc.tall);
+    w.nx[j] = rb.nx;
+    w.nt[j] = rb.nt;
     w.n256[j] = rb.n256;
     w.n128[j] = rb.n128;
     w.n64[j] = rb.n64;
@@ -117,21 +121,29 @@ __device__ inline WaveRouting wave_routing(const int32_t* __restrict__ expert_of
 }
 
 // Tile `idx` of a list in which the lane's experts have `mbs` row blocks each, the first of them
-// `base` rows into the expert: experts in order, column blocks, row blocks fastest.
+// `base` rows into the expert: experts in order, column blocks, row blocks fastest.  TALL (full blocks that may be
+// tall): `base` is the number of the expert's first block in the list, and RowBlocks::start says where that is.
+template <bool TALL = false>
 __device__ inline TileCoord wave_locate(const WaveRouting& w, const int (&mbs)[kLaneChunks],
                                         const int (&base)[kLaneChunks], int n_col_blocks, int idx,
                                         int block_rows = 256) {
   int pre[kLaneChunks];
   wave_prefix(mbs, w.chunks, pre);
   const WaveHit h = wave_find(pre, mbs, w.chunks, idx / n_col_blocks);
-  TileCoord t = {0, 0, 0, 0};
+  TileCoord t = {0, 0, 0, 0, 0};
   if (!h.found) return t;
   const int m = wave_pick(mbs, h), lo = wave_pick(w.lo, h);
   const int local = idx - wave_pick(pre, h) * n_col_blocks;
   // (the values are uniform by construction; reading them from the first lane tells the compiler so)
   t.expert = __builtin_amdgcn_readfirstlane(h.lane + 64 * h.j);
   t.nb = __builtin_amdgcn_readfirstlane(local / m);
-  t.row0 = __builtin_amdgcn_readfirstlane(lo + wave_pick(base, h) + (local % m) * block_rows);
+  if constexpr (TALL) {
+    const int b = wave_pick(base, h) + local % m, nt = wave_pick(w.nt, h), nx = wave_pick(w.nx, h);
+    t.row0 = __builtin_amdgcn_readfirstlane(lo + b * 256 + min(b, nt) * nx * 16);
+    t.nx = __builtin_amdgcn_readfirstlane(b < nt ? nx : 0);
+  } else {
+    t.row0 = __builtin_amdgcn_readfirstlane(lo + wave_pick(base, h) + (local % m) * block_rows);
+  }
   t.row_end = __builtin_amdgcn_readfirstlane(lo + wave_pick(w.rows, h));
   return t;
 }
@@ -145,25 +157,26 @@ __device__ inline TileCoord wave_locate_small(const WaveRouting& w, int n_col_bl
 }
 
 // find_unit + locate_tile.  Returns false if the workgroup has no tile.
+template <bool TALL = false>
 __device__ inline bool wave_find_tile(const int32_t* __restrict__ expert_offsets, int n_local, int n_col_blocks,
                                       int bid, int& cls, TileCoord& tc) {
-  const WaveRouting w = wave_routing(expert_offsets, n_local, n_col_blocks);
+  const WaveRouting w = wave_routing(expert_offsets, n_local, n_col_blocks, kPadLowTiles, TALL);
   const Unit u = find_unit(w.cc, bid);
   if (u.cls < 0) return false;
   cls = u.cls;
   if (u.cls == 0) {
     const int base[kLaneChunks] = {0, 0, 0, 0};
-    tc = wave_locate(w, w.n256, base, n_col_blocks, u.idx);
+    tc = wave_locate<TALL>(w, w.n256, base, n_col_blocks, u.idx);
   } else {
     tc = wave_locate_small(w, n_col_blocks, u.cls, u.idx);
   }
   return true;
 }
 
-// Rows with partial sums (sliced_rows): per lane expert, the 256-row blocks that run whole and the
+// Rows with partial sums (sliced_rows): per lane expert, the full blocks that run whole, their rows and the
 // number of rows behind them.
 struct WaveSliced {
-  int kept[kLaneChunks], cnt[kLaneChunks], pre_cnt[kLaneChunks];
+  int kept[kLaneChunks], whole[kLaneChunks], cnt[kLaneChunks], pre_cnt[kLaneChunks];
   int total;
 };
 __device__ inline WaveSliced wave_sliced_rows(const WaveRouting& w, int keep_rb) {
@@ -171,7 +184,8 @@ __device__ inline WaveSliced wave_sliced_rows(const WaveRouting& w, int keep_rb)
 #pragma unroll
   for (int j = 0; j < kLaneChunks; ++j) {
     s.kept[j] = min(max(keep_rb - w.pre256[j], 0), w.n256[j]);
-    s.cnt[j] = w.rows[j] - min(w.rows[j], s.kept[j] * 256);
+    s.whole[j] = min(w.rows[j], s.kept[j] * 256 + min(s.kept[j], w.nt[j]) * w.nx[j] * 16);
+    s.cnt[j] = w.rows[j] - s.whole[j];
   }
   s.total = wave_prefix(s.cnt, w.chunks, s.pre_cnt);
   return s;
@@ -186,11 +200,12 @@ struct WaveSlicedUnit {
   TileCoord tc;
   long scratch_shift;
 };
+template <bool TALL = false>
 __device__ inline WaveSlicedUnit wave_find_sliced_unit(const int32_t* __restrict__ expert_offsets, int n_local,
                                                        int n_col_blocks, int nk_all, int max_slices, int bid) {
   WaveSlicedUnit r;
   r.valid = false;
-  const WaveRouting w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all));
+  const WaveRouting w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL);
   const SliceChoice sc = choose_slices(w.cc, n_col_blocks, nk_all, max_slices);
   const SlicedUnit u = find_sliced_unit(w.cc, sc, n_col_blocks, bid);
   if (u.cls < 0) return r;
@@ -208,9 +223,9 @@ __device__ inline WaveSlicedUnit wave_find_sliced_unit(const int32_t* __restrict
     for (int j = 0; j < kLaneChunks; ++j) {
       const int kept = min(max(sc.keep_rb - w.pre256[j], 0), w.n256[j]);
       mbs[j] = u.cls == 3 ? kept : w.n256[j] - kept;
-      base[j] = u.cls == 3 ? 0 : kept * 256;
+      base[j] = u.cls == 3 ? 0 : kept * (TALL ? 1 : 256);
     }
-    r.tc = wave_locate(w, mbs, base, n_col_blocks, u.idx);
+    r.tc = wave_locate<TALL>(w, mbs, base, n_col_blocks, u.idx);
   }
   if (u.cls != 3) {
     r.kt0 = u.z * nk_all / sc.slices;
@@ -220,7 +235,7 @@ __device__ inline WaveSlicedUnit wave_find_sliced_unit(const int32_t* __restrict
       const int e = __builtin_amdgcn_readfirstlane(r.tc.expert);
       const WaveHit h = {e >> 6, e & 63, true};
       const int lo = wave_pick(w.lo, h);
-      const int first = lo + min(wave_pick(w.rows, h), wave_pick(s.kept, h) * 256);
+      const int first = lo + wave_pick(s.whole, h);
       r.scratch_shift = (long)(u.z - 1) * s.total + wave_pick(s.pre_cnt, h) - first;
     }
   }
@@ -232,24 +247,26 @@ __device__ inline WaveSlicedUnit wave_find_sliced_unit(const int32_t* __restrict
 // the short launches of expert-parallel shards with one or two experts)
 constexpr int kPlainLoopExperts = 4;
 
+template <bool TALL = false>
 __device__ inline bool find_tile(const int32_t* __restrict__ expert_offsets, int n_local, int n_col_blocks, int bid,
                                  int& cls, TileCoord& tc) {
-  if (n_local > kPlainLoopExperts) return wave_find_tile(expert_offsets, n_local, n_col_blocks, bid, cls, tc);
-  const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks);
+  if (n_local > kPlainLoopExperts) return wave_find_tile<TALL>(expert_offsets, n_local, n_col_blocks, bid, cls, tc);
+  const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, kPadLowTiles, TALL);
   const Unit u = find_unit(cc, bid);
   if (u.cls < 0) return false;
   cls = u.cls;
-  tc = locate_tile(expert_offsets, n_local, n_col_blocks, u.cls, u.idx, cc.pad_low);
+  tc = locate_tile(expert_offsets, n_local, n_col_blocks, u.cls, u.idx, cc.pad_low, cc.tall);
   return true;
 }
 
+template <bool TALL = false>
 __device__ inline WaveSlicedUnit find_sliced_unit_of(const int32_t* __restrict__ expert_offsets, int n_local,
                                                      int n_col_blocks, int nk_all, int max_slices, int bid) {
   if (n_local > kPlainLoopExperts)
-    return wave_find_sliced_unit(expert_offsets, n_local, n_col_blocks, nk_all, max_slices, bid);
+    return wave_find_sliced_unit<TALL>(expert_offsets, n_local, n_col_blocks, nk_all, max_slices, bid);
   WaveSlicedUnit r;
   r.valid = false;
-  const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all));
+  const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL);
   const SliceChoice sc = choose_slices(cc, n_col_blocks, nk_all, max_slices);
   const SlicedUnit u = find_sliced_unit(cc, sc, n_col_blocks, bid);
   if (u.cls < 0) return r;
@@ -260,13 +277,14 @@ __device__ inline WaveSlicedUnit find_sliced_unit_of(const int32_t* __restrict__
   r.nk = nk_all;
   r.scratch_shift = 0;
   r.tc = (u.cls == 3 || u.cls == 0)
-             ? locate_full_tile(expert_offsets, n_local, n_col_blocks, sc.keep_rb, u.cls == 0, u.idx, cc.pad_low)
-             : locate_tile(expert_offsets, n_local, n_col_blocks, u.cls, u.idx, cc.pad_low);
+             ? locate_full_tile(expert_offsets, n_local, n_col_blocks, sc.keep_rb, u.cls == 0, u.idx, cc.pad_low,
+                                cc.tall)
+             : locate_tile(expert_offsets, n_local, n_col_blocks, u.cls, u.idx, cc.pad_low, cc.tall);
   if (u.cls != 3) {
     r.kt0 = u.z * nk_all / sc.slices;
     r.nk = (u.z + 1) * nk_all / sc.slices - r.kt0;
     if (u.z > 0) {
-      const SlicedRows sr = sliced_rows(expert_offsets, n_local, r.tc.expert, sc.keep_rb, cc.pad_low);
+      const SlicedRows sr = sliced_rows(expert_offsets, n_local, r.tc.expert, sc.keep_rb, cc.pad_low, cc.tall);
       r.scratch_shift = (long)(u.z - 1) * sr.total + sr.base - sr.first;
     }
   }
@@ -277,25 +295,26 @@ __device__ inline WaveSlicedUnit find_sliced_unit_of(const int32_t* __restrict__
 // number, and the row behind compact number i.
 struct SumPlan {
   int slices, total, keep_rb;
-  bool plain, pad_low;
+  bool plain, pad_low, tall;
   WaveRouting w;
   WaveSliced s;
 };
 __device__ inline SumPlan sum_plan(const int32_t* __restrict__ expert_offsets, int n_local, int n_col_blocks,
-                                   int nk_all, int max_slices) {
+                                   int nk_all, int max_slices, bool allow_tall) {
   SumPlan p;
   p.plain = n_local <= kPlainLoopExperts;
   p.total = 0;
-  p.pad_low = false;
+  p.pad_low = p.tall = false;
   if (p.plain) {
-    const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all));
+    const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), allow_tall);
     const SliceChoice sc = choose_slices(cc, n_col_blocks, nk_all, max_slices);
     p.slices = sc.slices;
     p.keep_rb = sc.keep_rb;
     p.pad_low = cc.pad_low;
-    if (sc.slices > 1) p.total = sliced_rows(expert_offsets, n_local, 0, sc.keep_rb, cc.pad_low).total;
+    p.tall = cc.tall;
+    if (sc.slices > 1) p.total = sliced_rows(expert_offsets, n_local, 0, sc.keep_rb, cc.pad_low, cc.tall).total;
   } else {
-    p.w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all));
+    p.w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), allow_tall);
     const SliceChoice sc = choose_slices(p.w.cc, n_col_blocks, nk_all, max_slices);
     p.slices = sc.slices;
     p.keep_rb = sc.keep_rb;
@@ -309,13 +328,14 @@ __device__ inline SumPlan sum_plan(const int32_t* __restrict__ expert_offsets, i
 __device__ inline int sum_plan_row(const SumPlan& p, const int32_t* __restrict__ expert_offsets, int n_local, int i) {
   if (!p.plain) {
     const WaveHit h = wave_find(p.s.pre_cnt, p.s.cnt, p.w.chunks, i);
-    return wave_pick(p.w.lo, h) + min(wave_pick(p.w.rows, h), wave_pick(p.s.kept, h) * 256) + i - wave_pick(p.s.pre_cnt, h);
+    return wave_pick(p.w.lo, h) + wave_pick(p.s.whole, h) + i - wave_pick(p.s.pre_cnt, h);
   }
   int base = 0, before = 0;
   for (int e = 0; e < n_local; ++e) {
     const int lo = expert_offsets[e], hi = expert_offsets[e + 1];
-    const int n256 = row_blocks(hi - lo, p.pad_low).n256;
-    const int first = min(hi, lo + min(max(p.keep_rb - before, 0), n256) * 256);
+    const RowBlocks rb = row_blocks(hi - lo, p.pad_low, p.tall);
+    const int n256 = rb.n256;
+    const int first = min(hi, lo + rb.start(min(max(p.keep_rb - before, 0), n256)));
     if (i < base + hi - first) return first + i - base;
     base += hi - first;
     before += n256;

@@ -27,6 +27,10 @@ def edge_rows(offs, cap_rows, ffn_shard):
         for h, e, row0, row_end, nb in units[units[:, 0] > 0]:
             if nb == 0 or nb == ncb - 1:
                 rows.update((int(row0), int(min(row0 + h, row_end)) - 1))
+        if B.moe_debug_tall(cap_rows, ffn_shard):
+            units = B.moe_debug_tall_units(offs, cap_rows, ncb, 64, 0)
+            for h, e, row0, row_end in units[(units[:, 0] > 0) & (units[:, 4] == 0), :4]:
+                rows.update((int(row0), int(min(row0 + 255, row_end - 1)), int(min(row0 + h, row_end)) - 1))
     n_sliced = 0
     if not even and B.moe_ffn_workspace_bytes(cap_rows, ffn_shard) > 0:
         _, units = B.moe_debug_down_slices(offs, cap_rows, ffn_shard, with_units=True)

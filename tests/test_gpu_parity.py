@@ -281,6 +281,83 @@ def test_expert_ffn_even_row_blocks(H, I_s, lo, hi, gather):
     assert np.all(np.isnan(h_only))   # y_perm untouched
 
 
+@pytest.mark.parametrize("H,I_s,n,lo,hi,gather", [
+    (512, 512, 64, 240, 340, False),     # one block per expert, 0 to 3 x 16 rows more, or a remainder tile
+    (512, 512, 64, 250, 1300, True),     # up to five blocks, the first ones tall; rows read through row_src
+    (1024, 1088, 40, 257, 560, False),   # ragged last column block; down projection may be cut along K (17 k-tiles)
+    (2048, 1024, 4, 2049, 2500, True),   # few experts: the plain loops find the tiles
+])
+def test_expert_ffn_tall_row_blocks(H, I_s, n, lo, hi, gather):
+    """Launches that fill the chip give an expert's last rows to its 256-row blocks."""
+    rng = np.random.default_rng(H + n)
+    counts = rng.integers(lo, hi + 1, n)
+    counts[:4] = (lo // 256 * 256 + 256) + np.array([0, 1, 16, 33])
+    offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    R = int(offs[-1])
+    cap = R + 5
+    shard = B.make_shard(n, n, 0, H, I_s, I_s)
+    assert B.moe_debug_tall(cap, shard) and B.moe_debug_ffn_plan(cap, shard)[:2] == (False, False)
+    heights = B.moe_debug_tall_units(offs, cap, (I_s + 127) // 128, H // 64, 0)[:, 0]
+    assert 272 in heights and (288 in heights or lo > 2000)
+    wg, wu, wd = I.make_expert_weights(5, I.MoEShape("f", H, n, 1, I_s, True))
+    if gather:
+        T = (cap + 1) // 2
+        x = I.make_x(3, T, H)
+        row_src = rng.permutation(T * 2)[:cap].astype(np.int32)
+        xp, kw = x[row_src // 2], dict(gather=(x, row_src, 2))
+    else:
+        xp, kw = I.make_x(3, cap, H), {}
+    y = _ffn_gpu(xp, offs, shard, wg, wu, wd, **kw)
+    ref = O.expert_ffn(xp[:R], offs, wg, wu, wd)
+    assert np.all(np.isnan(y[R:])), "rows past R must not be written"
+    assert _rel(y[:R], ref) < REL_L2 and np.abs(y[:R] - ref).max() < MAX_ABS
+    yb = _ffn_gpu(xp, offs, shard, wg, wu, wd, y_bf16=True, **kw)
+    assert np.all(np.isnan(yb[R:])) and _rel(yb[:R], ref) < REL_L2
+
+
+def test_expert_ffn_160_row_blocks():
+    """About 130 rows per expert: one or two blocks of 160 rows."""
+    n, H, I_s = 64, 512, 320
+    counts = np.random.default_rng(7).integers(60, 200, n)
+    counts[:4] = 160, 161, 0, 320
+    offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    R = int(offs[-1])
+    shard = B.make_shard(n, n, 0, H, I_s, I_s)
+    assert not B.moe_debug_tall(R, shard) and B.moe_debug_tile_rows(R, shard) == 160
+    assert B.moe_debug_ffn_plan(R, shard)[:2] == (False, False)
+    wg, wu, wd = I.make_expert_weights(2, I.MoEShape("f", H, n, 1, I_s, True))
+    xp = I.make_x(3, R, H)
+    y, ref = _ffn_gpu(xp, offs, shard, wg, wu, wd), O.expert_ffn(xp, offs, wg, wu, wd)
+    assert _rel(y, ref) < REL_L2 and np.abs(y - ref).max() < MAX_ABS
+
+
+def test_expert_ffn_tall_row_blocks_of_rows_beyond_4_gib():
+    """Gathered rows whose byte offset in x does not fit 32 bits (the tall tiles' lane offsets)."""
+    H, I_s, n = 512, 512, 64
+    rng = np.random.default_rng(1)
+    counts = rng.integers(250, 400, n)
+    offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    R = int(offs[-1])
+    T = (1 << 32) // (2 * H) + 3000          # x: 4 GiB and 3000 rows
+    row_src = np.sort(rng.choice(T - 6000, R, replace=False)).astype(np.int32)
+    row_src[-5000:] = np.arange(T - 5000, T)  # the last experts' tokens lie on both sides of the 4 GiB line
+    shard = B.make_shard(n, n, 0, H, I_s, I_s)
+    assert B.moe_debug_tall(R, shard)
+    w = [bf16_tensor(a) for a in I.make_expert_weights(5, I.MoEShape("f", H, n, 1, I_s, True))]
+    xp = bf16_tensor(I.make_x(3, R, H))
+    x = torch.empty((T, H), dtype=torch.bfloat16, device="cuda")
+    x[torch.from_numpy(row_src).long().cuda()] = xp
+    o, src = _dev(offs), _dev(row_src)
+    ws = torch.empty(max(B.moe_ffn_workspace_bytes(R, shard), 256), dtype=torch.uint8, device="cuda")
+    h = torch.empty((R, I_s), dtype=torch.bfloat16, device="cuda")
+    ys = [torch.full((R, H), float("nan"), device="cuda") for _ in range(2)]
+    B.moe_expert_ffn(xp, o, R, shard, *w, h, ys[0], ws, 0)
+    B.moe_expert_ffn_gather(x, src, 1, o, R, shard, *w, h, ys[1], ws, 0)
+    torch.cuda.synchronize()
+    # the same products in the same order of k, whichever tile holds the row
+    assert not torch.isnan(ys[0]).any() and torch.equal(ys[0], ys[1])
+
+
 def test_expert_ffn_streaming_kernel_with_experts_that_need_several_row_passes():
     """24 small experts, three of them with 17 to 33 rows: 26 (expert, pass) units over 256
     workgroups do not divide evenly, so the ranges of the streaming kernel cross from one unit into

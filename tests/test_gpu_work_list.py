@@ -85,3 +85,18 @@ def test_even_work_list_on_the_device_equals_the_host_one(n_local, ncb, max_rows
         host = B.moe_debug_even_units(offs, cap, ncb)
         assert dev.shape[0] == host.shape[0]
         assert np.array_equal(dev[:, :5], host), counts
+
+
+@pytest.mark.parametrize("n_local,ncb,nk,max_slices,max_rows", [(8, 112, 64, 0, 17000), (8, 16, 224, 16, 17000),
+                                                                (2, 16, 224, 16, 20000), (60, 11, 32, 0, 17000),
+                                                                (60, 8, 22, 2, 17000), (4, 16, 224, 16, 6000),
+                                                                (200, 2, 64, 8, 60000)])
+def test_tall_work_list_on_the_device_equals_the_host_one(n_local, ncb, nk, max_slices, max_rows):
+    rng = np.random.default_rng(n_local * 37 + ncb)
+    for counts in _routings(rng, n_local, max_rows):
+        offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+        cap = max(int(offs[-1]), 1) + int(rng.integers(0, 700))
+        dev = B.moe_debug_device_units(torch.from_numpy(offs).cuda(), cap, ncb, nk, B.DEBUG_TALL + max_slices)
+        torch.cuda.synchronize()
+        host = B.moe_debug_tall_units(offs, cap, ncb, nk, max_slices)
+        assert np.array_equal(dev.cpu().numpy(), host), counts

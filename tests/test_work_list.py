@@ -5,6 +5,7 @@ launcher uses must hold."""
 import ctypes
 
 import numpy as np
+import pytest
 
 from paper_2508_19373_amd import binding as B
 
@@ -178,3 +179,63 @@ def test_tile_rows_rule():
     assert B.moe_debug_tile_rows(4096 * 2, B.make_shard(8, 8, 0, 4096, 14336, 14336)) == 256   # 1024 rows per expert
     assert B.lib().moe_debug_tile_rows(-1, ctypes.byref(qwen)) == B.MOE_ERR_INVALID_ARG
     assert B.lib().moe_debug_tile_rows(-1, None) == B.MOE_ERR_INVALID_ARG
+
+
+def _routings_for_tall_blocks(rng, n_local):
+    kind = rng.integers(0, 4)
+    if kind == 0:
+        return rng.integers(0, 1500, n_local) * (rng.random(n_local) < 0.8)
+    if kind == 1:    # around the heights where a block more, or a remainder tile, becomes necessary
+        return rng.choice([1, 64, 129, 193, 255, 256, 257, 272, 273, 288, 304, 305, 320, 512, 513, 544, 608, 609, 767, 768,
+                           1024, 1053, 1216, 1217, 4096 + 255, 8192 + 17], n_local)
+    if kind == 2:    # as a balanced router spreads a batch
+        return rng.multinomial(n_local * int(rng.integers(150, 1200)), np.ones(n_local) / n_local)
+    return rng.integers(0, 260, n_local)
+
+
+@pytest.mark.parametrize("n_local,ncb,nk,max_slices", [(8, 112, 64, 0), (8, 16, 224, 16), (2, 16, 224, 16), (60, 11, 32, 0),
+                                                       (60, 8, 22, 2), (5, 3, 40, 5), (4, 14, 320, 16), (1, 1, 16, 2)])
+def test_tall_row_blocks_cover_every_row_and_k_tile_once(n_local, ncb, nk, max_slices):
+    rng = np.random.default_rng(n_local * 100 + ncb)
+    n_tall = 0
+    for _ in range(60):
+        rows = np.asarray(_routings_for_tall_blocks(rng, n_local), dtype=np.int64)
+        offs = _offsets(rows)
+        R = int(offs[-1])
+        cap = R + int(rng.integers(0, 300))
+        units = B.moe_debug_tall_units(offs, cap, ncb, nk, max_slices)
+        cover = np.zeros((max(R, 1), ncb), dtype=np.int64)      # k-tiles summed for each row and column block
+        scratch_rows = min(65536 // ncb, (max(max_slices, 1) - 1) * cap)
+        cells = {}
+        for h, e, row0, row_end, nb, z, kt0, n, srow in units[units[:, 0] > 0].tolist():
+            assert h in (304, 288, 272, 256, 128, 64)
+            assert 0 <= nb < ncb and offs[e] <= row0 < row_end == offs[e + 1]
+            assert 0 <= kt0 and n >= 1 and kt0 + n <= nk
+            end = min(row0 + h, row_end)
+            cover[row0:end, nb] += n
+            n_tall += h > 256
+            assert (srow == -1) == (z == 0)
+            if z > 0:
+                assert 0 <= srow and srow + end - row0 <= scratch_rows
+                for r in range(end - row0):
+                    assert cells.setdefault((srow + r, nb), (z, row0 + r)) == (z, row0 + r)
+                    # the partial sums of one row and slice: one place, whatever the column block
+                    assert cells.setdefault((srow + r, "row"), (z, row0 + r)) == (z, row0 + r)
+        assert (cover[:R] == nk).all(), rows
+    assert n_tall > 0 or ncb < 8
+
+
+def test_tall_row_blocks_are_the_fewest_that_hold_the_remainder():
+    for rows in list(range(1, 1300)) + [4096 + 200, 4096 + 255, 16 * 256 + 1, 20 * 256 + 255]:
+        units = B.moe_debug_tall_units(_offsets([rows]), rows, 256, 64, 0)
+        h = units[(units[:, 0] > 0) & (units[:, 4] == 0), 0]
+        q, r = divmod(rows, 256)
+        if q and 0 < r <= min(48 * q, 144):     # a larger one is a padded block as in the plain list
+            nx = -(-r // (16 * q))
+            assert sorted(h) == sorted([256 + 16 * nx] * -(-r // (16 * nx)) + [256] * (q - -(-r // (16 * nx))))
+        else:
+            plain = B.moe_debug_gemm_units(_offsets([rows]), rows, 256)
+            assert sorted(h) == sorted(plain[(plain[:, 0] > 0) & (plain[:, 4] == 0), 0])
+    # a launch that leaves compute units idle has none: a remainder tile of its own costs nothing there
+    units = B.moe_debug_tall_units(_offsets([1040, 1050]), 2090, 20, 64, 0)
+    assert set(units[:, 0].tolist()) == {0, 256, 64}
