@@ -150,6 +150,28 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
                                         static_cast<hipStream_t>(stream)));
 }
 
+int moe_forward(const moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard_t* ffn_shard, void* stream) {
+  if (a == nullptr || shard == nullptr || ffn_shard == nullptr) return MOE_ERR_INVALID_ARG;
+  const int32_t H = shard->hidden;
+  int st = moe_route_topk(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k, a->route_flags, a->topk_idx,
+                          a->topk_w, stream);
+  if (st != MOE_OK) return st;
+  st = moe_permute(a->x_bf16, a->topk_idx, a->T, a->k, shard, a->x_perm, a->expert_offsets, a->row_src, a->slot_row,
+                   a->workspace, a->workspace_bytes, stream);
+  if (st != MOE_OK) return st;
+  const int32_t cap_rows = a->T * a->k;  // moe_permute has checked the range
+  if (a->x_perm == nullptr)
+    st = moe_expert_ffn_gather(a->x_bf16, a->row_src, a->k, a->expert_offsets, cap_rows, ffn_shard, a->w_gate, a->w_up,
+                               a->w_down, a->h_workspace, a->y_perm, a->ffn_workspace, a->ffn_workspace_bytes,
+                               a->ffn_flags, stream);
+  else
+    st = moe_expert_ffn(a->x_perm, a->expert_offsets, cap_rows, ffn_shard, a->w_gate, a->w_up, a->w_down, a->h_workspace,
+                        a->y_perm, a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags, stream);
+  if (st != MOE_OK || a->y_out == nullptr) return st;
+  return moe_combine(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x, a->w_shared_gate,
+                     a->y_out, a->combine_flags, stream);
+}
+
 const char* moe_status_string(int status) {
   switch (status) {
     case MOE_OK: return "ok";

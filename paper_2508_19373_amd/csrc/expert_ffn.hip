@@ -25,17 +25,22 @@ namespace {
 // Prefill-sized groups: LDS-DMA kernel, 256-column tiles of 256 / 128 / 64 rows.  `tall`: full row blocks may take
 // their expert's remainder.
 template <int BN>
-hipError_t launch_pair_dlds(bool tall, const void* x_perm, RowMap rows, const int32_t* expert_offsets, int cap_rows, int est_rows, int n_local, int H,
+hipError_t launch_pair_dlds(bool allow_tall, const void* x_perm, RowMap rows, const int32_t* expert_offsets, int cap_rows, int est_rows, int n_local, int H,
                             int I_s, const void* w_gate, const void* w_up, const void* w_down, void* h_ws,
                             void* y_perm, void* workspace, uint32_t flags, hipStream_t stream) {
   const bool y_bf16 = (flags & MOE_Y_PERM_BF16) != 0;
   const dim3 block(256);
+  // the kernel with tall blocks only where the launch is expected to fill the chip: one that does not has none of
+  // them and would pay for the larger kernel (shared expert of 333 rows, 88 tiles: gate/up 53.1 -> 56.6 us)
+  auto tall_for = [&](int ncb, int from) {
+    return allow_tall && gg::expected_tiles(est_rows, n_local, ncb, n_local == 1 && est_rows == cap_rows) >= from;
+  };
   const uint16_t* xp = static_cast<const uint16_t*>(x_perm);
   uint16_t* hw = static_cast<uint16_t*>(h_ws);
   auto grid_for = [&](int ncb) { return dim3((unsigned)gg::max_grid(cap_rows, n_local, ncb)); };
   if (!(flags & MOE_FFN_SKIP_GATEUP)) {
     const int ncb = (I_s + BN / 2 - 1) / (BN / 2);
-    const auto kernel = tall ? gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>
+    const auto kernel = tall_for(ncb, gg::kPadLowTiles) ? gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>
                              : gg::grouped_gemm_dlds_kernel<BN, true, uint16_t, false>;
     hipLaunchKernelGGL(kernel, grid_for(ncb), block, 0, stream, xp,
                        expert_offsets, n_local, cap_rows, static_cast<const uint16_t*>(w_gate),
@@ -45,6 +50,7 @@ hipError_t launch_pair_dlds(bool tall, const void* x_perm, RowMap rows, const in
   }
   if (flags & MOE_FFN_SKIP_DOWN) return hipSuccess;
   const int ncb = (H + BN - 1) / BN;
+  const bool tall = tall_for(ncb, y_bf16 ? gg::kPadLowTiles : gg::sliced_pad_from(I_s / gg::BK));
   if (y_bf16) {
     const auto kernel = tall ? gg::grouped_gemm_tall_kernel<BN, false, uint16_t, false>
                              : gg::grouped_gemm_dlds_kernel<BN, false, uint16_t, false>;
@@ -74,8 +80,9 @@ hipError_t launch_pair_dlds(bool tall, const void* x_perm, RowMap rows, const in
                      RowMap{nullptr, 1});
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(gg::sum_sliced_kernel, dim3(192, (H + 1023) / 1024), dim3(256), 0, stream, ws, expert_offsets, n_local, ncb,
-                     I_s / gg::BK, sp.max_slices, tall, H, yp);
+  const auto sum = tall ? gg::sum_sliced_kernel<true> : gg::sum_sliced_kernel<false>;
+  hipLaunchKernelGGL(sum, dim3(192, (H + 1023) / 1024), dim3(256), 0, stream, ws, expert_offsets, n_local, ncb,
+                     I_s / gg::BK, sp.max_slices, H, yp);
   return hipGetLastError();
 }
 
@@ -303,9 +310,10 @@ inline bool prefer_even(int est_rows, int n_local, int H, int I_s) {
 // 1667 + 836 / 1463 + 744, 1152: 1714 + 862 / 1569 + 845; its TP=4 slice 2068: 738 + 430 / 693 + 381; counts as a router
 // spreads 4096 tokens 1538 + 780 / 1461 + 735; no remainders at all (1024) 1353 + 675 / 1363 + 675.  Qwen1.5-MoE (60
 // experts, the 160-row tiling before) 256: 262 + 144 / 216 + 123, 286: 262 + 150 / 234 + 134, spread about 273: 258 +
-// 154 / 223 + 144.
-bool tall_blocks_allowed(int est_rows, int n_local) {
-  return (double)est_rows / n_local >= 150.0;
+// 154 / 223 + 144.  Both K extents have to be 1024 at least: on a short walk the larger kernel costs more than it
+// saves (8 and 16 k-tiles, 8 experts of 932 rows each: layer 81 -> 87 us).
+bool tall_blocks_allowed(int est_rows, int n_local, int H, int I_s) {
+  return (double)est_rows / n_local >= 150.0 && H >= 1024 && I_s >= 1024;
 }
 
 int tiled_block_rows(int cap_rows, int est_rows, int n_local, int H, int I_s) {
@@ -347,7 +355,7 @@ hipError_t launch_expert_ffn(const void* x_perm, RowMap rows, const int32_t* exp
   if (cap_rows == 0) return hipSuccess;
   // each GEMM picks its kernel family on its own: h is row-major bf16 for both
   const int mt = decode_mt(cap_rows, est_rows, n_local);
-  const bool tall = tall_blocks_allowed(est_rows, n_local);
+  const bool tall = tall_blocks_allowed(est_rows, n_local, H, I_s);
   const bool even = !tall && prefer_even(est_rows, n_local, H, I_s);
   auto run = [&](bool walk, uint32_t f) {
     if (!walk && even)

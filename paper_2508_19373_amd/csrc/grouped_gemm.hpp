@@ -172,8 +172,8 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
     a_src[j] = A + (size_t)gr * K + (size_t)kt0 * BK + dma_chunk * 8;
     a_lane[j] = (uint32_t)(gr - a_row0) * (uint32_t)K * 2u + (uint32_t)dma_chunk * 16u;
   }
-  // weights: the 8 rows of an instruction are consecutive rows of one matrix, so their address is a scalar base
-  // per instruction plus one 32-bit lane offset for all of them (14 vector registers fewer than lane pointers);
+  // weights: the 8 rows of an instruction are consecutive rows of one matrix, so as buffers their address is a scalar
+  // offset per instruction plus one 32-bit lane offset for all of them (14 vector registers fewer than lane pointers);
   // n_out is a multiple of 64, so the last column block is clamped by whole instructions
   const uint32_t b_lane = (uint32_t)dma_row * (uint32_t)K * 2u + (uint32_t)dma_chunk * 16u;
   const uint16_t* b_src[B_INST];
@@ -191,9 +191,9 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
     } else {
       wrow = col0 + r;
     }
-    wrow = min(wrow, n_out - 8);
-    b_src[j] = base + (size_t)tc.expert * expert_stride + (size_t)wrow * K + (size_t)kt0 * BK;
-    b_off[j] = (uint32_t)(wrow - col0) * (uint32_t)K * 2u;
+    b_src[j] = base + (size_t)tc.expert * expert_stride + (size_t)min(wrow + dma_row, n_out - 1) * K +
+               (size_t)kt0 * BK + dma_chunk * 8;
+    b_off[j] = (uint32_t)(min(wrow, n_out - 8) - col0) * (uint32_t)K * 2u;
   }
   // (in GATEUP mode all instructions of a wave load from the same matrix: 16-row blocks alternate, a wave's
   // instructions are NW * 8 = 32 rows apart)
@@ -237,8 +237,7 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
       if constexpr (BUF)
         buf_to_lds(b_buf, dst, b_lane, b_off[j] + kt_b * (BK * 2));
       else
-        __builtin_amdgcn_global_load_lds(
-            (global_void_t*)(reinterpret_cast<const char*>(b_src[j] + (size_t)kt_b * BK) + b_lane), dst, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((global_void_t*)(b_src[j] + (size_t)kt_b * BK), dst, 16, 0, 0);
     }
   };
 
@@ -563,11 +562,12 @@ __global__ __launch_bounds__(256) void grouped_gemm_even_kernel(
 // y[r, :] += partial sums of slices 1, 2, ... in that order, for the rows the sliced kernel cut
 // along K (it repeats that kernel's decision).  A workgroup adds 1024 columns of one row at a time:
 // grid.x walks the rows, grid.y the column chunks.
+template <bool TALL>
 __global__ __launch_bounds__(256) void sum_sliced_kernel(const float* __restrict__ partial,
                                                         const int32_t* __restrict__ expert_offsets, int n_local,
-                                                        int n_col_blocks, int nk, int max_slices, bool allow_tall,
-                                                        int n_out, float* __restrict__ y) {
-  const SumPlan plan = sum_plan(expert_offsets, n_local, n_col_blocks, nk, max_slices, allow_tall);
+                                                        int n_col_blocks, int nk, int max_slices, int n_out,
+                                                        float* __restrict__ y) {
+  const SumPlan plan = sum_plan<TALL>(expert_offsets, n_local, n_col_blocks, nk, max_slices);
   if (plan.slices == 1) return;
   const int total = plan.total;
   const size_t stride = (size_t)total * n_out / 4;

@@ -29,7 +29,9 @@ constexpr int kNumXcd = 8;
 // the one padded block it replaces).  A remainder above kMaxTallRemainder rows is a padded block as before: that
 // keeps more tiles of the cheapest height for nearly the same work (TP=4 slice of Mixtral, 8 experts of 2048 rows
 // on average, spread as a router does: gate/up 802 us with every remainder dealt out, 691 with this limit, 716-742
-// without tall blocks).  Only in launches that fill the chip (ClassCounts::tall): with compute units
+// without tall blocks).  An expert with several blocks takes 16 rows more per block at most: an XCD runs a contiguous
+// eighth of the tiles, often one expert's, and waits for nobody else's (blocks of 288 rows there would make the launch an
+// eighth longer).  Only in launches that fill the chip (ClassCounts::tall): with compute units
 // to spare a remainder tile of its own costs nothing.
 constexpr int kMaxExtra = 3;
 constexpr int kMaxTallRemainder = 144;
@@ -44,7 +46,7 @@ struct RowBlocks {
 __host__ __device__ inline RowBlocks row_blocks(int rows, bool pad_low, bool tall = false) {
   RowBlocks rb = {0, 0, 0, 0, 0};
   const int q = rows >> 8, r = rows & 255;
-  if (tall && r > 0 && r <= kMaxTallRemainder && r <= q * (kMaxExtra * 16)) {
+  if (tall && r > 0 && r <= kMaxTallRemainder && r <= q * 16 * (q == 1 ? kMaxExtra : 1)) {
     rb.n256 = q;
     rb.nx = r <= q * 16 ? 1 : (r <= q * 32 ? 2 : 3);
     rb.nt = (r + rb.nx * 16 - 1) / (rb.nx * 16);
@@ -179,15 +181,17 @@ __host__ __device__ inline Unit find_unit(const ClassCounts& c, int bid) {
 // reading s - 1 partial sums of `rows` rows and updating y at about 4 TB/s.  (Measured: 120
 // remainder tiles of 22 k-tiles and 1500 rows are not worth cutting in two, 16 tiles of 88 k-tiles
 // and 512 rows are worth cutting in 11.)
-__host__ __device__ inline int fit_slices(int n_tiles, int nk, int max_slices, int rows, int n_col_blocks) {
+__host__ __device__ inline int fit_slices(int n_tiles, int nk, int max_slices, int rows, int n_col_blocks,
+                                                   bool tall) {
   if (n_tiles <= 0) return 1;
   int hi = 256 / n_tiles;
   if (hi > max_slices) hi = max_slices;
   if (hi > nk / 8) hi = nk / 8;
+  // what the scratch holds; with blocks of 256 rows the workgroup count already keeps to it
+  if (tall)
+    while (hi > 1 && (hi - 1) * rows * n_col_blocks > 65536) --hi;
   int best = 1, best_cost = nk * 16;
   for (int s = 2; s <= hi; ++s) {
-    // what the scratch holds; with blocks of 256 rows the workgroup count above already keeps to it
-    if ((s - 1) * rows > 65536 / n_col_blocks) break;
     const int cost = (nk * 16 + s - 1) / s + 64 + rows * n_col_blocks * (s + 1) / 275;
     if (cost < best_cost) best = s, best_cost = cost;
   }
@@ -212,9 +216,9 @@ __host__ __device__ inline SliceChoice choose_slices(const ClassCounts& c, int n
   SliceChoice sc;
   const int block_rows = c.tall ? 256 + kMaxExtra * 16 : 256;  // at most
   sc.slices = fit_slices(tail_rb * n_col_blocks + n_small, nk, max_slices, tail_rb * block_rows + small_rows,
-                         n_col_blocks);
+                         n_col_blocks, c.tall);
   if (sc.slices == 1 && n_small > 0 && tail_rb > 0) {
-    sc.slices = fit_slices(n_small, nk, max_slices, small_rows, n_col_blocks);
+    sc.slices = fit_slices(n_small, nk, max_slices, small_rows, n_col_blocks, c.tall);
     tail_rb = 0;
   }
   sc.keep_rb = sc.slices > 1 ? n_rb - tail_rb : n_rb;

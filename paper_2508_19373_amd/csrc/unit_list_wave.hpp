@@ -299,14 +299,15 @@ struct SumPlan {
   WaveRouting w;
   WaveSliced s;
 };
+template <bool TALL>
 __device__ inline SumPlan sum_plan(const int32_t* __restrict__ expert_offsets, int n_local, int n_col_blocks,
-                                   int nk_all, int max_slices, bool allow_tall) {
+                                   int nk_all, int max_slices) {
   SumPlan p;
   p.plain = n_local <= kPlainLoopExperts;
   p.total = 0;
   p.pad_low = p.tall = false;
   if (p.plain) {
-    const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), allow_tall);
+    const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL);
     const SliceChoice sc = choose_slices(cc, n_col_blocks, nk_all, max_slices);
     p.slices = sc.slices;
     p.keep_rb = sc.keep_rb;
@@ -314,7 +315,7 @@ __device__ inline SumPlan sum_plan(const int32_t* __restrict__ expert_offsets, i
     p.tall = cc.tall;
     if (sc.slices > 1) p.total = sliced_rows(expert_offsets, n_local, 0, sc.keep_rb, cc.pad_low, cc.tall).total;
   } else {
-    p.w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), allow_tall);
+    p.w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL);
     const SliceChoice sc = choose_slices(p.w.cc, n_col_blocks, nk_all, max_slices);
     p.slices = sc.slices;
     p.keep_rb = sc.keep_rb;

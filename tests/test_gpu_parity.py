@@ -282,8 +282,8 @@ def test_expert_ffn_even_row_blocks(H, I_s, lo, hi, gather):
 
 
 @pytest.mark.parametrize("H,I_s,n,lo,hi,gather", [
-    (512, 512, 64, 240, 340, False),     # one block per expert, 0 to 3 x 16 rows more, or a remainder tile
-    (512, 512, 64, 250, 1300, True),     # up to five blocks, the first ones tall; rows read through row_src
+    (1024, 1024, 64, 240, 340, False),   # one block per expert, 0 to 3 x 16 rows more, or a remainder tile
+    (1024, 1024, 24, 300, 1300, True),   # up to five blocks, the first ones tall; rows read through row_src
     (1024, 1088, 40, 257, 560, False),   # ragged last column block; down projection may be cut along K (17 k-tiles)
     (2048, 1024, 4, 2049, 2500, True),   # few experts: the plain loops find the tiles
 ])
@@ -298,7 +298,7 @@ def test_expert_ffn_tall_row_blocks(H, I_s, n, lo, hi, gather):
     shard = B.make_shard(n, n, 0, H, I_s, I_s)
     assert B.moe_debug_tall(cap, shard) and B.moe_debug_ffn_plan(cap, shard)[:2] == (False, False)
     heights = B.moe_debug_tall_units(offs, cap, (I_s + 127) // 128, H // 64, 0)[:, 0]
-    assert 272 in heights and (288 in heights or lo > 2000)
+    assert 272 in heights and (288 in heights or lo >= 300)
     wg, wu, wd = I.make_expert_weights(5, I.MoEShape("f", H, n, 1, I_s, True))
     if gather:
         T = (cap + 1) // 2
@@ -333,7 +333,7 @@ def test_expert_ffn_160_row_blocks():
 
 def test_expert_ffn_tall_row_blocks_of_rows_beyond_4_gib():
     """Gathered rows whose byte offset in x does not fit 32 bits (the tall tiles' lane offsets)."""
-    H, I_s, n = 512, 512, 64
+    H, I_s, n = 1024, 1024, 64
     rng = np.random.default_rng(1)
     counts = rng.integers(250, 400, n)
     offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)

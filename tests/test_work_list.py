@@ -230,7 +230,7 @@ def test_tall_row_blocks_are_the_fewest_that_hold_the_remainder():
         units = B.moe_debug_tall_units(_offsets([rows]), rows, 256, 64, 0)
         h = units[(units[:, 0] > 0) & (units[:, 4] == 0), 0]
         q, r = divmod(rows, 256)
-        if q and 0 < r <= min(48 * q, 144):     # a larger one is a padded block as in the plain list
+        if q and 0 < r <= (48 if q == 1 else min(16 * q, 144)):   # a larger one is a tile of its own, as in the plain list
             nx = -(-r // (16 * q))
             assert sorted(h) == sorted([256 + 16 * nx] * -(-r // (16 * nx)) + [256] * (q - -(-r // (16 * nx))))
         else:
