@@ -193,6 +193,43 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
                 const void* x_bf16, const float* w_shared_gate, void* y_out,
                 uint32_t flags, void* stream);
 
+/*
+ * A whole forward of one shard in one call: moe_route_topk, moe_permute, moe_expert_ffn (or, with x_perm == NULL,
+ * moe_expert_ffn_gather) and moe_combine with the arguments below, on one stream and in this order; with
+ * y_out == NULL it ends before the combine.  Same checks and results as the separate calls; it returns the
+ * first error, and what was enqueued before it runs.  For callers that a call per step costs too much: a
+ * small batch's kernels take less time than marshalling and checking the arguments of four calls.
+ * shard describes the routing and permutation, ffn_shard the matrices (they differ where a slice of the
+ * intermediate dimension was padded).
+ */
+typedef struct {
+  const void* x_bf16;
+  const float* w_router;
+  float* logits;
+  int32_t* topk_idx;
+  float* topk_w;
+  void* x_perm;
+  int32_t* expert_offsets;
+  int32_t* row_src;
+  int32_t* slot_row;
+  void* workspace;
+  size_t workspace_bytes;
+  const void* w_gate;
+  const void* w_up;
+  const void* w_down;
+  void* h_workspace;
+  void* y_perm;
+  void* ffn_workspace;
+  size_t ffn_workspace_bytes;
+  const void* y_shared;
+  const void* shared_gate_x;
+  const float* w_shared_gate;
+  void* y_out;
+  int32_t T, k;
+  uint32_t route_flags, ffn_flags, combine_flags;
+} moe_forward_args_t;
+int moe_forward(const moe_forward_args_t* args, const moe_shard_t* shard, const moe_shard_t* ffn_shard, void* stream);
+
 /* Bytes of scratch moe_permute needs for (T, k, shard); 0 on invalid arguments. */
 size_t moe_workspace_bytes(int32_t T, int32_t k, const moe_shard_t* shard);
 

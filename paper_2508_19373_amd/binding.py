@@ -28,7 +28,7 @@ MOE_MAX_EXPERTS = 256
 MOE_MAX_TOPK = 16
 MOE_PERMUTE_STATIC_MAX_COUNTS = 262144
 
-EXPORTS = ("moe_route_topk", "moe_permute", "moe_permute_static", "moe_expert_ffn", "moe_expert_ffn_gather", "moe_combine", "moe_workspace_bytes",
+EXPORTS = ("moe_route_topk", "moe_permute", "moe_permute_static", "moe_expert_ffn", "moe_expert_ffn_gather", "moe_combine", "moe_forward", "moe_workspace_bytes",
            "moe_ffn_workspace_bytes", "moe_status_string")
 DEBUG_EXPORTS = ("moe_debug_gemm_units", "moe_debug_ffn_plan", "moe_debug_down_slices", "moe_debug_device_units",
                  "moe_debug_tile_rows", "moe_debug_even_units", "moe_debug_tall", "moe_debug_tall_units")
@@ -44,6 +44,17 @@ class MoeShard(ctypes.Structure):
     _fields_ = [("n_experts", ctypes.c_int32), ("n_local_experts", ctypes.c_int32),
                 ("expert_offset", ctypes.c_int32), ("hidden", ctypes.c_int32),
                 ("inter_full", ctypes.c_int32), ("inter_slice", ctypes.c_int32)]
+
+
+class MoeForwardArgs(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_void_p) for n in ("x_bf16", "w_router", "logits", "topk_idx", "topk_w", "x_perm",
+                                                "expert_offsets", "row_src", "slot_row", "workspace")]
+                + [("workspace_bytes", ctypes.c_size_t)]
+                + [(n, ctypes.c_void_p) for n in ("w_gate", "w_up", "w_down", "h_workspace", "y_perm", "ffn_workspace")]
+                + [("ffn_workspace_bytes", ctypes.c_size_t)]
+                + [(n, ctypes.c_void_p) for n in ("y_shared", "shared_gate_x", "w_shared_gate", "y_out")]
+                + [("T", ctypes.c_int32), ("k", ctypes.c_int32), ("route_flags", ctypes.c_uint32),
+                   ("ffn_flags", ctypes.c_uint32), ("combine_flags", ctypes.c_uint32)])
 
 
 class MoeError(RuntimeError):
@@ -73,6 +84,8 @@ def lib() -> ctypes.CDLL:
         L.moe_expert_ffn_gather.restype = ctypes.c_int
         L.moe_combine.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp, vp, vp, u32, vp]
         L.moe_combine.restype = ctypes.c_int
+        L.moe_forward.argtypes = [ctypes.POINTER(MoeForwardArgs), shp, shp, vp]
+        L.moe_forward.restype = ctypes.c_int
         L.moe_workspace_bytes.argtypes = [i32, i32, shp]
         L.moe_workspace_bytes.restype = sz
         L.moe_ffn_workspace_bytes.argtypes = [i32, shp]
@@ -183,6 +196,11 @@ def moe_expert_ffn_gather(x, row_src, k, expert_offsets, cap_rows, shard: MoeSha
 def moe_combine(y_perm, slot_row, topk_w, T, k, H, y_shared, x, w_shared_gate, y_out, flags=0, stream=None):
     _check("moe_combine", lib().moe_combine(_ptr(y_perm), _ptr(slot_row), _ptr(topk_w), T, k, H, _ptr(y_shared),
                                             _ptr(x), _ptr(w_shared_gate), _ptr(y_out), flags, _stream(stream)))
+
+
+def moe_forward(args: MoeForwardArgs, shard: MoeShard, ffn_shard: MoeShard, stream=None):
+    _check("moe_forward", lib().moe_forward(ctypes.byref(args), ctypes.byref(shard), ctypes.byref(ffn_shard),
+                                            _stream(stream)))
 
 
 def moe_int4_dequantize(codes, qparams, n_elems, w_bf16, stream=None):

@@ -2,6 +2,8 @@
 and issues the C-ABI calls in order.  No arithmetic happens here."""
 from __future__ import annotations
 
+from typing import NamedTuple
+
 import numpy as np
 import torch
 
@@ -65,6 +67,13 @@ def routed_hint_beside_shared(ffn_shard, shared_shard, T) -> int:
     return B.MOE_FFN_TILED if gateup_tiles >= 512 else B.MOE_FFN_LEAVE_ROOM
 
 
+class _Plan(NamedTuple):
+    ffn_ws: int
+    ffn_ws_sh: int
+    hint: int
+    gather: bool
+
+
 class ExpertShardLayer:
     """route -> permute -> expert FFN (-> shared expert FFN) -> combine, on the current stream.
 
@@ -113,6 +122,7 @@ class ExpertShardLayer:
         # buffers a captured graph still points at are kept alive when a larger batch makes the
         # layer allocate anew, so replaying an older graph stays valid (it works on its own buffers)
         self._captured, self._retired = False, []
+        self._plans = {}
         if max_tokens:
             self._alloc(max_tokens)
 
@@ -171,6 +181,21 @@ class ExpertShardLayer:
             return self.gather_in_ffn
         return bool(B.moe_debug_ffn_plan(T * self.k, self.ffn_shard)[0])   # GEMM1 on the streaming kernel
 
+    def _plan(self, T) -> "_Plan":
+        """What a forward of T tokens needs to know about itself: a function of T, the shards and the switches,
+        kept per token count (at most 256 of them)."""
+        key = (T, self.gather_in_ffn, self.overlap_shared)
+        plan = self._plans.get(key)
+        if plan is None:
+            sh = self.shared is not None
+            hint = routed_hint_beside_shared(self.ffn_shard, self.shared_shard, T) if sh and self.overlap_shared else 0
+            plan = _Plan(B.moe_ffn_workspace_bytes(T * self.k, self.ffn_shard),
+                         B.moe_ffn_workspace_bytes(T, self.shared_shard) if sh else 0, hint, self.gathers(T))
+            if len(self._plans) >= 256:
+                self._plans.clear()
+            self._plans[key] = plan
+        return plan
+
     def forward(self, x: torch.Tensor, logits: torch.Tensor | None = None, stream=None) -> torch.Tensor:
         T = x.shape[0]
         if T > self.Tmax:
@@ -178,30 +203,37 @@ class ExpertShardLayer:
                 raise RuntimeError("run one eager forward with this token count before capturing a graph")
             self._alloc(T)
         self._last_T = T
-        k, H, E = self.k, self.H, self.E
+        k, H = self.k, self.H
+        plan = self._plan(T)
         # the FFN scratch depends on the regime (decode-sized calls need split-K partials)
-        need = B.moe_ffn_workspace_bytes(T * k, self.ffn_shard)
-        if need > self.ffn_ws.numel():
+        if plan.ffn_ws > self.ffn_ws.numel():
             self._retire(("ffn_ws",))
-            self.ffn_ws = torch.empty(need, dtype=torch.uint8, device=self.device)
-        if self.shared is not None:
-            need = B.moe_ffn_workspace_bytes(T, self.shared_shard)
-            if need > self.ffn_ws_sh.numel():
-                self._retire(("ffn_ws_sh",))
-                self.ffn_ws_sh = torch.empty(need, dtype=torch.uint8, device=self.device)
+            self.ffn_ws = torch.empty(plan.ffn_ws, dtype=torch.uint8, device=self.device)
+        if self.shared is not None and plan.ffn_ws_sh > self.ffn_ws_sh.numel():
+            self._retire(("ffn_ws_sh",))
+            self.ffn_ws_sh = torch.empty(plan.ffn_ws_sh, dtype=torch.uint8, device=self.device)
         flags = B.MOE_RENORM_TOPK if self.renorm else 0
         if logits is not None:
             self.logits[:T].copy_(logits)
             flags |= B.MOE_LOGITS_GIVEN
         yflag = B.MOE_Y_PERM_BF16 if self.y_perm_bf16 else 0
-        rflag = yflag
-        if self.shared is not None and self.overlap_shared:
-            rflag |= routed_hint_beside_shared(self.ffn_shard, self.shared_shard, T)
-        y_shared, joined = None, None
-        if self.shared is not None:
-            sh_offsets = self._shared_offsets(T)
-            y_shared = self.y_shared
-        if self.shared is not None and self.overlap_shared:
+        cflags = yflag | (B.MOE_OUT_F32 if self.out_f32 else 0)
+        ptr = B._ptr
+        gate_x = x if self.w_shared_gate is not None else None
+        # one call for the whole chain: a decoding batch's kernels take less time than the marshalling of four
+        # calls.  The addresses are taken anew each time, nothing is kept from one forward to the next.
+        args = B.MoeForwardArgs(
+            ptr(x), ptr(self.w_router), ptr(self.logits), ptr(self.topk_idx), ptr(self.topk_w),
+            None if plan.gather else ptr(self.x_perm), ptr(self.expert_offsets), ptr(self.row_src), ptr(self.slot_row),
+            ptr(self.workspace), self.workspace.numel(), ptr(self.w_gate), ptr(self.w_up), ptr(self.w_down),
+            ptr(self.h_ws), ptr(self.y_perm), ptr(self.ffn_ws), self.ffn_ws.numel(),
+            None, ptr(gate_x), ptr(self.w_shared_gate), ptr(self.y_out), T, k, flags, yflag | plan.hint, cflags)
+        if self.shared is None:
+            B.moe_forward(args, self.shard, self.ffn_shard, stream)
+            return self.y_out[:T]
+        args.y_out = None                         # the combine waits for the shared expert
+        sh_offsets = self._shared_offsets(T)
+        if self.overlap_shared:
             if stream is not None:
                 raise ValueError("overlap_shared works on torch's current stream only")
             main = torch.cuda.current_stream()
@@ -211,25 +243,13 @@ class ExpertShardLayer:
             # at once instead of waiting for a resident workgroup to finish (-2 to -3.5 % at 16 to 64 tokens)
             B.moe_expert_ffn(x, sh_offsets, T, self.shared_shard, self.shared[0], self.shared[1], self.shared[2],
                              self.h_sh, self.y_shared, self.ffn_ws_sh, yflag | B.MOE_FFN_LEAVE_ROOM, self._side)
-            joined = self._side
-        B.moe_route_topk(x, self.w_router, self.logits, T, H, E, k, flags, self.topk_idx, self.topk_w, stream)
-        gather = self.gathers(T)
-        B.moe_permute(x, self.topk_idx, T, k, self.shard, None if gather else self.x_perm, self.expert_offsets,
-                      self.row_src, self.slot_row, self.workspace, stream=stream)
-        if gather:
-            B.moe_expert_ffn_gather(x, self.row_src, k, self.expert_offsets, T * k, self.ffn_shard, self.w_gate,
-                                    self.w_up, self.w_down, self.h_ws, self.y_perm, self.ffn_ws, rflag, stream)
+            B.moe_forward(args, self.shard, self.ffn_shard, main)
+            main.wait_stream(self._side)
         else:
-            B.moe_expert_ffn(self.x_perm, self.expert_offsets, T * k, self.ffn_shard, self.w_gate, self.w_up,
-                             self.w_down, self.h_ws, self.y_perm, self.ffn_ws, rflag, stream)
-        if self.shared is not None and not self.overlap_shared:
+            B.moe_forward(args, self.shard, self.ffn_shard, stream)
             B.moe_expert_ffn(x, sh_offsets, T, self.shared_shard, self.shared[0], self.shared[1], self.shared[2],
                              self.h_sh, self.y_shared, self.ffn_ws_sh, yflag, stream)
-        if joined is not None:
-            torch.cuda.current_stream().wait_stream(joined)
-        cflags = yflag | (B.MOE_OUT_F32 if self.out_f32 else 0)
-        gate_x = x if self.w_shared_gate is not None else None
-        B.moe_combine(self.y_perm, self.slot_row, self.topk_w, T, k, H, y_shared, gate_x, self.w_shared_gate,
+        B.moe_combine(self.y_perm, self.slot_row, self.topk_w, T, k, H, self.y_shared, gate_x, self.w_shared_gate,
                       self.y_out, cflags, stream)
         return self.y_out[:T]
 

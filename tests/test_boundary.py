@@ -206,3 +206,16 @@ def test_public_headers_are_plain_c(tmp_path):
         r = subprocess.run([gcc, "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror", "-I", inc, "-c", str(src),
                             "-o", str(tmp_path / (name + ".o"))], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
+
+
+def test_forward_returns_the_first_error_of_its_steps():
+    """Every check of the separate calls holds for the whole-forward call (host checks only, nothing is launched)."""
+    import ctypes
+    L, shard = B.lib(), B.make_shard(8, 8, 0, 512, 1024, 1024)
+    sp = ctypes.byref(shard)
+    assert L.moe_forward(None, sp, sp, None) == B.MOE_ERR_INVALID_ARG
+    args = B.MoeForwardArgs(T=4, k=2)
+    assert L.moe_forward(ctypes.byref(args), None, sp, None) == B.MOE_ERR_INVALID_ARG
+    assert L.moe_forward(ctypes.byref(args), sp, sp, None) == B.MOE_ERR_INVALID_ARG      # no logits
+    args = B.MoeForwardArgs(T=4, k=9)
+    assert L.moe_forward(ctypes.byref(args), sp, sp, None) == B.MOE_ERR_INVALID_ARG      # k above the expert count
