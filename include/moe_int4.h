@@ -41,7 +41,8 @@ int moe_int4_dequantize(const void* codes, const void* qparams, int64_t n_elems,
 
 /*
  * w_bf16 [n] bf16  ->  codes [n/2] uint8, qparams [n/64][2] bf16.
- * Requires n_elems >= 0 and n_elems % 64 == 0.
+ * Requires n_elems >= 0 and n_elems % 64 == 0.  A quiet NaN, outside the contract as it is, gets code 0 and leaves
+ * the scale, the minimum and the codes of its group's other weights as they are without it.
  */
 int moe_int4_quantize(const void* w_bf16, int64_t n_elems, void* codes, void* qparams, void* stream);
 

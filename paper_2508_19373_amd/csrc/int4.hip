@@ -51,7 +51,8 @@ __global__ __launch_bounds__(kThreads) void int4_dequantize_kernel(const uint32_
 }
 
 // Minimum / maximum in the form the hardware has for three operands (v_minimum3_f32): fminf / fmaxf make the
-// compiler quiet each of the loaded values first, one more instruction per weight.
+// compiler quiet each of the loaded values first, one more instruction per weight.  Unlike those they hand a NaN on,
+// which is how quantize_block finds a group that has one.
 __device__ __forceinline__ float min2(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 __device__ __forceinline__ float max2(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 template <int CTRL>
@@ -80,12 +81,13 @@ __device__ __forceinline__ float fifteenth(float range) {
 // is a half integer only if the exact one is (it cannot round to one: (q + 1/2) has so few bits that its
 // neighbours w - min are more than half an ulp of the quotient away).  A few weights in a thousand of bf16 data
 // are exact ties, so most wavefronts take that second look, and none of it divides.  A subnormal
-// scale, which may be far from range / 15 and has no finite reciprocal, takes the division itself.
-__device__ __forceinline__ uint32_t pack_codes(const float (&v)[8], float mn, float scale) {
+// scale, which may be far from range / 15 and has no finite reciprocal, takes the division itself, and so does a
+// group with a NaN (whose own code is 0).
+__device__ __forceinline__ uint32_t pack_codes(const float (&v)[8], float mn, float scale, bool has_nan) {
   constexpr float kShift = 12582912.f;  // 1.5 * 2^23
   constexpr uint32_t kShiftSum = 0x4B400000u * 0x11111111u;
   uint32_t packed = 0;
-  if (!(scale >= 1.17549435e-38f && scale < 3e38f)) {
+  if (has_nan || !(scale >= 1.17549435e-38f && scale < 3e38f)) {
 #pragma unroll 1
     for (int j = 0; j < 8; ++j) {
       float q = rintf((v[j] - mn) / scale);
@@ -153,9 +155,24 @@ __device__ __forceinline__ void quantize_block(const uint4* __restrict__ w, int6
     mx = max2(mx, dpp_move<0x4E>(mx));
     mn = min2(mn, dpp_move<0x141>(mn));
     mx = max2(mx, dpp_move<0x141>(mx));
+    // a NaN in the group: the extremes of its other weights, so that one bad weight costs no more than its own value
+    const bool has_nan = mn != mn;
+    if (has_nan) {
+      mn = mx = v[0];
+#pragma unroll
+      for (int j = 1; j < 8; ++j) {
+        mn = fminf(mn, v[j]);
+        mx = fmaxf(mx, v[j]);
+      }
+#pragma unroll
+      for (int o = 1; o < 8; o <<= 1) {  // the eight lanes of a group are here together
+        mn = fminf(mn, __shfl_xor(mn, o, kWave));
+        mx = fmaxf(mx, __shfl_xor(mx, o, kWave));
+      }
+    }
     const uint32_t scale_bits = f32_to_bf16_bits(fifteenth(mx - mn));
     const float scale = bf16_bits_to_f32(scale_bits);
-    const uint32_t packed = scale > 0.f ? pack_codes(v, mn, scale) : 0u;
+    const uint32_t packed = scale > 0.f ? pack_codes(v, mn, scale, has_nan) : 0u;
     if (FULL || i < n_items) {
       __builtin_nontemporal_store(packed, codes + i);
       if ((i & 7) == 0) qparams[i >> 3] = scale_bits | (__float_as_uint(mn) & 0xFFFF0000u);  // mn is a bf16 value

@@ -100,6 +100,24 @@ def test_quantize_rounding_edges(kind):
     assert np.array_equal(codes, ref_codes)
 
 
+def test_quantize_passes_over_nan_weights():
+    """A (quiet) NaN counts for neither extreme and gets code 0: the group is what it is with the minimum of its
+    other weights in the NaN's place."""
+    rng = np.random.default_rng(11)
+    g = 8192 // 64 + 5
+    w = _weights(g * 64, seed=4).reshape(g, 64)
+    plain = w.copy()
+    for i in range(0, g, 2):
+        where = rng.choice(64, size=int(rng.integers(1, 63)) if i % 4 else 1, replace=False)
+        w[i, where] = rng.choice(np.array([0x7FC0, 0xFFC0, 0x7FE5, 0xFFFF], dtype=np.uint16), size=where.size)
+        rest = np.delete(plain[i], where)
+        plain[i, where] = rest[np.argmin(I.bf16_bits_to_f32(rest))]
+    codes, qp = _gpu_quantize(w.reshape(-1))
+    ref_codes, ref_qp = Q.quantize(plain.reshape(-1))
+    assert np.array_equal(qp, ref_qp)
+    assert np.array_equal(codes, ref_codes)
+
+
 def test_empty_tensor_is_a_no_op():
     out = _gpu_dequantize(np.zeros(0, np.uint8), np.zeros((0, 2), np.uint16), 0)
     assert np.all(I.bf16_bits_to_f32(out) == -1.0)
