@@ -218,7 +218,8 @@ int moe_int4_quantize(const void* w_bf16, int64_t n_elems, void* codes, void* qp
   if (codes == nullptr || qparams == nullptr || w_bf16 == nullptr) return MOE_ERR_INVALID_ARG;
   if (!aligned16(codes) || !aligned16(qparams) || !aligned16(w_bf16)) return MOE_ERR_INVALID_ARG;
   const int64_t n_items = n_elems / 8;
-  if (n_elems / kBlockWeights >= 0x7FFFFFFF) return MOE_ERR_UNSUPPORTED_SHAPE;
+  // (a bound in blocks of one item per lane, which a grid of blocks of kItems would not need)
+  if ((n_items + kThreads - 1) / kThreads >= 0x7FFFFFFF) return MOE_ERR_UNSUPPORTED_SHAPE;
   if (n_elems == 0) return MOE_OK;
   const unsigned grid = (unsigned)((n_elems + kBlockWeights - 1) / kBlockWeights);
   hipLaunchKernelGGL(int4_quantize_kernel, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(stream),

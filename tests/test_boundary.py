@@ -219,3 +219,11 @@ def test_forward_returns_the_first_error_of_its_steps():
     assert L.moe_forward(ctypes.byref(args), sp, sp, None) == B.MOE_ERR_INVALID_ARG      # no logits
     args = B.MoeForwardArgs(T=4, k=9)
     assert L.moe_forward(ctypes.byref(args), sp, sp, None) == B.MOE_ERR_INVALID_ARG      # k above the expert count
+
+
+def test_int4_sizes_beyond_the_grid_are_refused_on_the_host(lib):
+    """The smallest refused sizes: 2^31 - 1 blocks, of 2048 weights when quantising, of 8192 when dequantising."""
+    p = 64  # any aligned address: the call ends before it is used
+    assert lib.moe_int4_quantize(p, 2048 * 0x7FFFFFFE + 64, p, p, None) == B.MOE_ERR_UNSUPPORTED_SHAPE
+    assert lib.moe_int4_quantize(p, 2048 * 0x7FFFFFFF, p, p, None) == B.MOE_ERR_UNSUPPORTED_SHAPE
+    assert lib.moe_int4_dequantize(p, p, 8192 * 0x7FFFFFFF, p, None) == B.MOE_ERR_UNSUPPORTED_SHAPE
