@@ -504,11 +504,14 @@ __global__ __launch_bounds__(256) void grouped_gemm_tall_kernel(
     if (!find_tile<true>(expert_offsets, n_local, n_col_blocks, blockIdx.x, cls, tc)) return;
   }
   // full blocks address their input rows with 32-bit byte offsets: from their own first row, or from x when the
-  // rows are gathered; rows of x beyond 4 GiB (assignments are in order inside an expert, so its last row is the
-  // furthest) run as 64-row tiles one after the other, which address any row
+  // rows are gathered; a block with a row of x beyond 4 GiB, wherever in the block it stands, runs as 64-row tiles one
+  // after the other, which address any row
   if (cls == 0 && rows.row_src != nullptr) {
     const int end = min(tc.row_end, tc.row0 + 256 + 16 * tc.nx);
-    if ((uint64_t)(rows(end - 1) + 1) * K * 2 > kBufBytes) {
+    const int64_t first_far = (int64_t)(kBufBytes / (2u * (uint32_t)K)) * rows.k;  // in assignments, as row_src is
+    bool far = false;
+    for (int r = tc.row0 + (int)(threadIdx.x & 63); r < end; r += 64) far |= rows.row_src[r] >= first_far;
+    if (__any(far)) {
       tc.row_end = end;
       cls = 2;
     }

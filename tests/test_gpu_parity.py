@@ -331,8 +331,10 @@ def test_expert_ffn_160_row_blocks():
     assert _rel(y, ref) < REL_L2 and np.abs(y - ref).max() < MAX_ABS
 
 
-def test_expert_ffn_tall_row_blocks_of_rows_beyond_4_gib():
-    """Gathered rows whose byte offset in x does not fit 32 bits (the tall tiles' lane offsets)."""
+@pytest.mark.parametrize("in_order", [True, False])
+def test_expert_ffn_tall_row_blocks_of_rows_beyond_4_gib(in_order):
+    """Gathered rows whose byte offset in x does not fit 32 bits (the tall tiles' lane offsets): inside an expert in
+    ascending order, as moe_permute writes them, and in any order."""
     H, I_s, n = 1024, 1024, 64
     rng = np.random.default_rng(1)
     counts = rng.integers(250, 400, n)
@@ -341,6 +343,8 @@ def test_expert_ffn_tall_row_blocks_of_rows_beyond_4_gib():
     T = (1 << 32) // (2 * H) + 3000          # x: 4 GiB and 3000 rows
     row_src = np.sort(rng.choice(T - 6000, R, replace=False)).astype(np.int32)
     row_src[-5000:] = np.arange(T - 5000, T)  # the last experts' tokens lie on both sides of the 4 GiB line
+    if not in_order:
+        row_src = rng.permutation(row_src)
     shard = B.make_shard(n, n, 0, H, I_s, I_s)
     assert B.moe_debug_tall(R, shard)
     w = [bf16_tensor(a) for a in I.make_expert_weights(5, I.MoEShape("f", H, n, 1, I_s, True))]
