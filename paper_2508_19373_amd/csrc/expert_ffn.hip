@@ -311,8 +311,11 @@ inline bool prefer_even(int est_rows, int n_local, int H, int I_s) {
 // spreads 4096 tokens 1538 + 780 / 1461 + 735; no remainders at all (1024) 1353 + 675 / 1363 + 675.  Qwen1.5-MoE (60
 // experts, the 160-row tiling before) 256: 262 + 144 / 216 + 123, 286: 262 + 150 / 234 + 134, spread about 273: 258 +
 // 154 / 223 + 144.  Both K extents have to be 1024 at least: on a short walk the larger kernel costs more than it
-// saves (8 and 16 k-tiles, 8 experts of 932 rows each: layer 81 -> 87 us).
+// saves (8 and 16 k-tiles, 8 experts of 932 rows each: layer 81 -> 87 us).  A tall block addresses its operands with
+// 32-bit byte offsets from its first row, so 304 rows of either K extent have to fit.
 bool tall_blocks_allowed(int est_rows, int n_local, int H, int I_s) {
+  constexpr uint64_t kMaxK = gg::kBufBytes / (2 * (256 + 16 * gg::kMaxExtra));
+  if ((uint64_t)H > kMaxK || (uint64_t)I_s > kMaxK) return false;
   return (double)est_rows / n_local >= 150.0 && H >= 1024 && I_s >= 1024;
 }
 

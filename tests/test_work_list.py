@@ -181,6 +181,14 @@ def test_tile_rows_rule():
     assert B.lib().moe_debug_tile_rows(-1, None) == B.MOE_ERR_INVALID_ARG
 
 
+def test_tall_row_blocks_only_where_their_offsets_fit_32_bits():
+    """A tall block reaches 304 rows of K bf16 values with 32-bit byte offsets from its first row."""
+    fits = 0xFFFFFFFF // (2 * 304) // 64 * 64
+    for K, ok in ((fits, True), (fits + 64, False), (1 << 24, False)):
+        assert B.moe_debug_tall(4 * 300, B.make_shard(4, 4, 0, 1024, K, K)) == ok
+        assert B.moe_debug_tall(4 * 300, B.make_shard(4, 4, 0, K, 1024, 1024)) == ok
+
+
 def _routings_for_tall_blocks(rng, n_local):
     kind = rng.integers(0, 4)
     if kind == 0:
