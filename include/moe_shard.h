@@ -199,8 +199,8 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
  * y_out == NULL it ends before the combine.  Same checks and results as the separate calls; it returns the
  * first error, and what was enqueued before it runs.  For callers that a call per step costs too much: a
  * small batch's kernels take less time than marshalling and checking the arguments of four calls.
- * shard describes the routing and permutation, ffn_shard the matrices (they differ where a slice of the
- * intermediate dimension was padded).
+ * shard describes the routing and permutation, ffn_shard the matrices: they differ where a slice of the
+ * intermediate dimension was padded, and in nothing but inter_full and inter_slice (MOE_ERR_INVALID_ARG).
  */
 typedef struct {
   const void* x_bf16;

@@ -152,6 +152,10 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
 
 int moe_forward(const moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard_t* ffn_shard, void* stream) {
   if (a == nullptr || shard == nullptr || ffn_shard == nullptr) return MOE_ERR_INVALID_ARG;
+  // the routing's offsets and rows are what the experts read: only the intermediate extents may differ
+  if (shard->n_experts != ffn_shard->n_experts || shard->n_local_experts != ffn_shard->n_local_experts ||
+      shard->expert_offset != ffn_shard->expert_offset || shard->hidden != ffn_shard->hidden)
+    return MOE_ERR_INVALID_ARG;
   const int32_t H = shard->hidden;
   int st = moe_route_topk(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k, a->route_flags, a->topk_idx,
                           a->topk_w, stream);

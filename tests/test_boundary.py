@@ -221,6 +221,28 @@ def test_forward_returns_the_first_error_of_its_steps():
     assert L.moe_forward(ctypes.byref(args), sp, sp, None) == B.MOE_ERR_INVALID_ARG      # k above the expert count
 
 
+def _forward_args(shard, T=4, k=2, **kw):
+    """Arguments no check objects to (fake addresses: nothing may be launched with them)."""
+    ws, fws = B.moe_workspace_bytes(T, k, shard), B.moe_ffn_workspace_bytes(T * k, shard)
+    names = [n for n, t in B.MoeForwardArgs._fields_ if t is ctypes.c_void_p and n not in
+             ("y_shared", "shared_gate_x", "w_shared_gate")]
+    d = dict({n: P for n in names}, workspace_bytes=ws, ffn_workspace_bytes=fws, T=T, k=k)
+    d.update(kw)
+    return B.MoeForwardArgs(**d)
+
+
+@pytest.mark.parametrize("other", [dict(n_local_experts=4), dict(n_local_experts=4, expert_offset=4), dict(hidden=1024),
+                                   dict(n_experts=16, n_local_experts=16)])
+def test_forward_refuses_shards_that_disagree(lib, other):
+    """expert_offsets has n_local_experts + 1 entries and the combine reads rows of `hidden` values: with two
+    descriptions that differ the experts would read past the one or walk the other with another length."""
+    a, b = _shard(n_experts=16) if "n_experts" in other else _shard(), _shard(**other)
+    for one, two in ((a, b), (b, a)):
+        args = _forward_args(a, combine_flags=1 << 30)      # (the last step's check would end the call in any case)
+        args.workspace_bytes = args.ffn_workspace_bytes = 1 << 40
+        assert lib.moe_forward(ctypes.byref(args), ctypes.byref(one), ctypes.byref(two), None) == B.MOE_ERR_INVALID_ARG
+
+
 def test_int4_sizes_beyond_the_grid_are_refused_on_the_host(lib):
     """The smallest refused sizes: 2^31 - 1 blocks, of 2048 weights when quantising, of 8192 when dequantising."""
     p = 64  # any aligned address: the call ends before it is used
