@@ -196,8 +196,8 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
 /*
  * A whole forward of one shard in one call: moe_route_topk, moe_permute, moe_expert_ffn (or, with x_perm == NULL,
  * moe_expert_ffn_gather) and moe_combine with the arguments below, on one stream and in this order; with
- * y_out == NULL it ends before the combine.  Same checks and results as the separate calls; it returns the
- * first error, and what was enqueued before it runs.  For callers that a call per step costs too much: a
+ * y_out == NULL it ends before the combine.  Same checks and results as the separate calls; the checks of all
+ * steps come first, so with an invalid argument nothing is enqueued.  For callers that a call per step costs too much: a
  * small batch's kernels take less time than marshalling and checking the arguments of four calls.
  * shard describes the routing and permutation, ffn_shard the matrices: they differ where a slice of the
  * intermediate dimension was padded, and in nothing but inter_full and inter_slice (MOE_ERR_INVALID_ARG).

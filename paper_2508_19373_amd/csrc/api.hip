@@ -32,8 +32,8 @@ inline int hip_status(hipError_t e) { return e == hipSuccess ? MOE_OK : MOE_ERR_
 
 extern "C" {
 
-int moe_route_topk(const void* x_bf16, const float* w_router, float* logits, int32_t T, int32_t H, int32_t E,
-                   int32_t k, uint32_t flags, int32_t* topk_idx, float* topk_w, void* stream) {
+static int route_status(const void* x_bf16, const float* w_router, const float* logits, int32_t T, int32_t H, int32_t E,
+                        int32_t k, uint32_t flags, const int32_t* topk_idx, const float* topk_w) {
   if (T < 0 || E < 1 || E > MOE_MAX_EXPERTS || k < 1 || k > E || k > MOE_MAX_TOPK) return MOE_ERR_INVALID_ARG;
   if (flags & ~(uint32_t)(MOE_RENORM_TOPK | MOE_LOGITS_GIVEN)) return MOE_ERR_INVALID_ARG;
   if (logits == nullptr || topk_idx == nullptr || topk_w == nullptr) return MOE_ERR_INVALID_ARG;
@@ -42,6 +42,13 @@ int moe_route_topk(const void* x_bf16, const float* w_router, float* logits, int
     if (H % 8 != 0) return MOE_ERR_UNSUPPORTED_SHAPE;
     if (!aligned16(x_bf16)) return MOE_ERR_INVALID_ARG;
   }
+  return MOE_OK;
+}
+
+int moe_route_topk(const void* x_bf16, const float* w_router, float* logits, int32_t T, int32_t H, int32_t E,
+                   int32_t k, uint32_t flags, int32_t* topk_idx, float* topk_w, void* stream) {
+  const int st = route_status(x_bf16, w_router, logits, T, H, E, k, flags, topk_idx, topk_w);
+  if (st != MOE_OK) return st;
   return hip_status(moe::launch_route_topk(x_bf16, w_router, logits, T, H, E, k, flags, topk_idx, topk_w,
                                            static_cast<hipStream_t>(stream)));
 }
@@ -57,9 +64,9 @@ size_t moe_ffn_workspace_bytes(int32_t cap_rows, const moe_shard_t* shard) {
                                   shard->inter_slice);
 }
 
-int moe_permute(const void* x_bf16, const int32_t* topk_idx, int32_t T, int32_t k, const moe_shard_t* shard,
-                void* x_perm, int32_t* expert_offsets, int32_t* row_src, int32_t* slot_row, void* workspace,
-                size_t workspace_bytes, void* stream) {
+static int permute_status(const void* x_bf16, const int32_t* topk_idx, int32_t T, int32_t k, const moe_shard_t* shard,
+                          const void* x_perm, const int32_t* expert_offsets, const int32_t* row_src,
+                          const int32_t* slot_row, const void* workspace, size_t workspace_bytes) {
   const int st = shard_status(shard);
   if (st != MOE_OK) return st;
   if (T < 0 || k < 1 || k > MOE_MAX_TOPK || k > shard->n_experts) return MOE_ERR_INVALID_ARG;
@@ -70,6 +77,15 @@ int moe_permute(const void* x_bf16, const int32_t* topk_idx, int32_t T, int32_t 
   if (shard->hidden % 8 != 0) return MOE_ERR_UNSUPPORTED_SHAPE;
   if (!aligned16(x_bf16) || !aligned16(x_perm)) return MOE_ERR_INVALID_ARG;
   if (workspace == nullptr || workspace_bytes < moe_workspace_bytes(T, k, shard)) return MOE_ERR_WORKSPACE;
+  return MOE_OK;
+}
+
+int moe_permute(const void* x_bf16, const int32_t* topk_idx, int32_t T, int32_t k, const moe_shard_t* shard,
+                void* x_perm, int32_t* expert_offsets, int32_t* row_src, int32_t* slot_row, void* workspace,
+                size_t workspace_bytes, void* stream) {
+  const int st = permute_status(x_bf16, topk_idx, T, k, shard, x_perm, expert_offsets, row_src, slot_row, workspace,
+                                workspace_bytes);
+  if (st != MOE_OK) return st;
   return hip_status(moe::launch_permute(x_bf16, topk_idx, T, k, shard->hidden, shard->n_local_experts,
                                         shard->expert_offset, x_perm, expert_offsets, row_src, slot_row, workspace,
                                         static_cast<hipStream_t>(stream)));
@@ -93,10 +109,9 @@ int moe_permute_static(const void* x_bf16, const int32_t* topk_idx, int32_t T, i
                                                static_cast<hipStream_t>(stream)));
 }
 
-static int expert_ffn_common(const void* x, moe::RowMap rows, const int32_t* expert_offsets, int32_t cap_rows,
-                             const moe_shard_t* shard, const void* w_gate, const void* w_up, const void* w_down,
-                             void* h_workspace, void* y_perm, void* workspace, size_t workspace_bytes, uint32_t flags,
-                             void* stream) {
+static int expert_ffn_status(const void* x, const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard,
+                             const void* w_gate, const void* w_up, const void* w_down, const void* h_workspace,
+                             const void* y_perm, const void* workspace, size_t workspace_bytes, uint32_t flags) {
   const int st = shard_status(shard);
   if (st != MOE_OK) return st;
   if (cap_rows < 0 || (flags & ~(uint32_t)(MOE_Y_PERM_BF16 | MOE_FFN_SKIP_GATEUP | MOE_FFN_SKIP_DOWN | MOE_FFN_TILED |
@@ -111,6 +126,16 @@ static int expert_ffn_common(const void* x, moe::RowMap rows, const int32_t* exp
     return MOE_ERR_INVALID_ARG;
   const size_t need = moe_ffn_workspace_bytes(cap_rows, shard);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned16(workspace))) return MOE_ERR_WORKSPACE;
+  return MOE_OK;
+}
+
+static int expert_ffn_common(const void* x, moe::RowMap rows, const int32_t* expert_offsets, int32_t cap_rows,
+                             const moe_shard_t* shard, const void* w_gate, const void* w_up, const void* w_down,
+                             void* h_workspace, void* y_perm, void* workspace, size_t workspace_bytes, uint32_t flags,
+                             void* stream) {
+  const int st = expert_ffn_status(x, expert_offsets, cap_rows, shard, w_gate, w_up, w_down, h_workspace, y_perm,
+                                   workspace, workspace_bytes, flags);
+  if (st != MOE_OK) return st;
   return hip_status(moe::launch_expert_ffn(x, rows, expert_offsets, cap_rows, moe::expected_rows(cap_rows, shard),
                                            shard->n_local_experts, shard->hidden,
                                            shard->inter_slice, w_gate, w_up, w_down, h_workspace, y_perm, workspace,
@@ -133,9 +158,9 @@ int moe_expert_ffn_gather(const void* x_bf16, const int32_t* row_src, int32_t k,
                            h_workspace, y_perm, workspace, workspace_bytes, flags, stream);
 }
 
-int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w, int32_t T, int32_t k, int32_t H,
-                const void* y_shared, const void* x_bf16, const float* w_shared_gate, void* y_out, uint32_t flags,
-                void* stream) {
+static int combine_status(const void* y_perm, const int32_t* slot_row, const float* topk_w, int32_t T, int32_t k,
+                          int32_t H, const void* y_shared, const void* x_bf16, const float* w_shared_gate,
+                          const void* y_out, uint32_t flags) {
   if (T < 0 || k < 1 || k > MOE_MAX_TOPK || H < 8) return MOE_ERR_INVALID_ARG;
   if (flags & ~(uint32_t)(MOE_Y_PERM_BF16 | MOE_OUT_F32)) return MOE_ERR_INVALID_ARG;
   if (y_perm == nullptr || slot_row == nullptr || topk_w == nullptr || y_out == nullptr) return MOE_ERR_INVALID_ARG;
@@ -145,6 +170,14 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
   if (!aligned16(y_perm) || !aligned16(y_out) || (y_shared && !aligned16(y_shared)) ||
       (x_bf16 && (!aligned16(x_bf16) || !aligned16(w_shared_gate))))
     return MOE_ERR_INVALID_ARG;
+  return MOE_OK;
+}
+
+int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w, int32_t T, int32_t k, int32_t H,
+                const void* y_shared, const void* x_bf16, const float* w_shared_gate, void* y_out, uint32_t flags,
+                void* stream) {
+  const int st = combine_status(y_perm, slot_row, topk_w, T, k, H, y_shared, x_bf16, w_shared_gate, y_out, flags);
+  if (st != MOE_OK) return st;
   return hip_status(moe::launch_combine(y_perm, slot_row, topk_w, T, k, H, y_shared, x_bf16, w_shared_gate, y_out,
                                         (flags & MOE_Y_PERM_BF16) != 0, (flags & MOE_OUT_F32) != 0,
                                         static_cast<hipStream_t>(stream)));
@@ -157,23 +190,40 @@ int moe_forward(const moe_forward_args_t* a, const moe_shard_t* shard, const moe
       shard->expert_offset != ffn_shard->expert_offset || shard->hidden != ffn_shard->hidden)
     return MOE_ERR_INVALID_ARG;
   const int32_t H = shard->hidden;
-  int st = moe_route_topk(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k, a->route_flags, a->topk_idx,
-                          a->topk_w, stream);
+  // every check of every step first, so that an invalid argument of the last one does not leave the others enqueued
+  int st = route_status(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k, a->route_flags, a->topk_idx,
+                        a->topk_w);
   if (st != MOE_OK) return st;
-  st = moe_permute(a->x_bf16, a->topk_idx, a->T, a->k, shard, a->x_perm, a->expert_offsets, a->row_src, a->slot_row,
-                   a->workspace, a->workspace_bytes, stream);
+  st = permute_status(a->x_bf16, a->topk_idx, a->T, a->k, shard, a->x_perm, a->expert_offsets, a->row_src, a->slot_row,
+                      a->workspace, a->workspace_bytes);
   if (st != MOE_OK) return st;
-  const int32_t cap_rows = a->T * a->k;  // moe_permute has checked the range
-  if (a->x_perm == nullptr)
-    st = moe_expert_ffn_gather(a->x_bf16, a->row_src, a->k, a->expert_offsets, cap_rows, ffn_shard, a->w_gate, a->w_up,
-                               a->w_down, a->h_workspace, a->y_perm, a->ffn_workspace, a->ffn_workspace_bytes,
-                               a->ffn_flags, stream);
-  else
-    st = moe_expert_ffn(a->x_perm, a->expert_offsets, cap_rows, ffn_shard, a->w_gate, a->w_up, a->w_down, a->h_workspace,
-                        a->y_perm, a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags, stream);
-  if (st != MOE_OK || a->y_out == nullptr) return st;
-  return moe_combine(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x, a->w_shared_gate,
-                     a->y_out, a->combine_flags, stream);
+  const int32_t cap_rows = a->T * a->k;  // permute_status has checked the range
+  const bool gather = a->x_perm == nullptr;
+  const void* rows = gather ? a->x_bf16 : a->x_perm;
+  st = expert_ffn_status(rows, a->expert_offsets, cap_rows, ffn_shard, a->w_gate, a->w_up, a->w_down, a->h_workspace,
+                         a->y_perm, a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags);
+  if (st != MOE_OK) return st;
+  if (a->y_out != nullptr) {
+    st = combine_status(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x,
+                        a->w_shared_gate, a->y_out, a->combine_flags);
+    if (st != MOE_OK) return st;
+  }
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  hipError_t err = moe::launch_route_topk(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k,
+                                          a->route_flags, a->topk_idx, a->topk_w, s);
+  if (err != hipSuccess) return MOE_ERR_HIP;
+  err = moe::launch_permute(a->x_bf16, a->topk_idx, a->T, a->k, H, shard->n_local_experts, shard->expert_offset, a->x_perm,
+                            a->expert_offsets, a->row_src, a->slot_row, a->workspace, s);
+  if (err != hipSuccess) return MOE_ERR_HIP;
+  err = moe::launch_expert_ffn(rows, gather ? moe::RowMap{a->row_src, a->k} : moe::RowMap{nullptr, 1}, a->expert_offsets,
+                               cap_rows, moe::expected_rows(cap_rows, ffn_shard), ffn_shard->n_local_experts, H,
+                               ffn_shard->inter_slice, a->w_gate, a->w_up, a->w_down, a->h_workspace, a->y_perm,
+                               a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags, s);
+  if (err != hipSuccess) return MOE_ERR_HIP;
+  if (a->y_out == nullptr) return MOE_OK;
+  return hip_status(moe::launch_combine(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x,
+                                        a->w_shared_gate, a->y_out, (a->combine_flags & MOE_Y_PERM_BF16) != 0,
+                                        (a->combine_flags & MOE_OUT_F32) != 0, s));
 }
 
 const char* moe_status_string(int status) {

@@ -243,6 +243,24 @@ def test_forward_refuses_shards_that_disagree(lib, other):
         assert lib.moe_forward(ctypes.byref(args), ctypes.byref(one), ctypes.byref(two), None) == B.MOE_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("bad,status", [
+    (dict(route_flags=1 << 7), B.MOE_ERR_INVALID_ARG), (dict(w_router=None), B.MOE_ERR_INVALID_ARG),
+    (dict(slot_row=None), B.MOE_ERR_INVALID_ARG), (dict(x_perm=P + 8), B.MOE_ERR_INVALID_ARG),
+    (dict(workspace_bytes=0), B.MOE_ERR_WORKSPACE),
+    (dict(w_up=P + 8), B.MOE_ERR_INVALID_ARG), (dict(x_perm=None, w_down=None), B.MOE_ERR_INVALID_ARG),
+    (dict(ffn_workspace=None), B.MOE_ERR_WORKSPACE), (dict(ffn_workspace_bytes=16), B.MOE_ERR_WORKSPACE),
+    (dict(ffn_flags=B.MOE_OUT_F32), B.MOE_ERR_INVALID_ARG),
+    (dict(combine_flags=B.MOE_RENORM_TOPK), B.MOE_ERR_INVALID_ARG), (dict(y_out=P + 8), B.MOE_ERR_INVALID_ARG),
+    (dict(w_shared_gate=P), B.MOE_ERR_INVALID_ARG), (dict(w_shared_gate=P, shared_gate_x=P), B.MOE_ERR_INVALID_ARG),
+])
+def test_forward_checks_every_step_before_it_enqueues_any(lib, bad, status):
+    """One bad argument of any step, all others good: the error of that step's own call, and no step has been launched
+    (here, without a GPU, a launch would come back as a HIP error instead)."""
+    shard = _shard(hidden=4096, inter_full=14336, inter_slice=14336)
+    args = _forward_args(shard, **bad)
+    assert lib.moe_forward(ctypes.byref(args), ctypes.byref(shard), ctypes.byref(shard), None) == status
+
+
 def test_int4_sizes_beyond_the_grid_are_refused_on_the_host(lib):
     """The smallest refused sizes: 2^31 - 1 blocks, of 2048 weights when quantising, of 8192 when dequantising."""
     p = 64  # any aligned address: the call ends before it is used
