@@ -227,8 +227,10 @@ typedef struct {
   void* y_out;
   int32_t T, k;
   uint32_t route_flags, ffn_flags, combine_flags;
+  int32_t step; /* written by the call: the step an error belongs to, MOE_STEP_*; 0 with MOE_OK or bad descriptions */
 } moe_forward_args_t;
-int moe_forward(const moe_forward_args_t* args, const moe_shard_t* shard, const moe_shard_t* ffn_shard, void* stream);
+enum { MOE_STEP_ROUTE = 1, MOE_STEP_PERMUTE = 2, MOE_STEP_FFN = 3, MOE_STEP_COMBINE = 4 };
+int moe_forward(moe_forward_args_t* args, const moe_shard_t* shard, const moe_shard_t* ffn_shard, void* stream);
 
 /* Bytes of scratch moe_permute needs for (T, k, shard); 0 on invalid arguments. */
 size_t moe_workspace_bytes(int32_t T, int32_t k, const moe_shard_t* shard);

@@ -54,7 +54,7 @@ class MoeForwardArgs(ctypes.Structure):
                 + [("ffn_workspace_bytes", ctypes.c_size_t)]
                 + [(n, ctypes.c_void_p) for n in ("y_shared", "shared_gate_x", "w_shared_gate", "y_out")]
                 + [("T", ctypes.c_int32), ("k", ctypes.c_int32), ("route_flags", ctypes.c_uint32),
-                   ("ffn_flags", ctypes.c_uint32), ("combine_flags", ctypes.c_uint32)])
+                   ("ffn_flags", ctypes.c_uint32), ("combine_flags", ctypes.c_uint32), ("step", ctypes.c_int32)])
 
 
 class MoeError(RuntimeError):
@@ -199,8 +199,10 @@ def moe_combine(y_perm, slot_row, topk_w, T, k, H, y_shared, x, w_shared_gate, y
 
 
 def moe_forward(args: MoeForwardArgs, shard: MoeShard, ffn_shard: MoeShard, stream=None):
-    _check("moe_forward", lib().moe_forward(ctypes.byref(args), ctypes.byref(shard), ctypes.byref(ffn_shard),
-                                            _stream(stream)))
+    status = lib().moe_forward(ctypes.byref(args), ctypes.byref(shard), ctypes.byref(ffn_shard), _stream(stream))
+    if status != MOE_OK:   # under the name of the call the failing step has on its own
+        ffn = "moe_expert_ffn" if args.x_perm else "moe_expert_ffn_gather"
+        raise MoeError(("moe_forward", "moe_route_topk", "moe_permute", ffn, "moe_combine")[args.step], status)
 
 
 def moe_int4_dequantize(codes, qparams, n_elems, w_bf16, stream=None):

@@ -183,47 +183,53 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
                                         static_cast<hipStream_t>(stream)));
 }
 
-int moe_forward(const moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard_t* ffn_shard, void* stream) {
+int moe_forward(moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard_t* ffn_shard, void* stream) {
   if (a == nullptr || shard == nullptr || ffn_shard == nullptr) return MOE_ERR_INVALID_ARG;
+  a->step = 0;
   // the routing's offsets and rows are what the experts read: only the intermediate extents may differ
   if (shard->n_experts != ffn_shard->n_experts || shard->n_local_experts != ffn_shard->n_local_experts ||
       shard->expert_offset != ffn_shard->expert_offset || shard->hidden != ffn_shard->hidden)
     return MOE_ERR_INVALID_ARG;
   const int32_t H = shard->hidden;
   // every check of every step first, so that an invalid argument of the last one does not leave the others enqueued
+  const auto error = [a](int32_t step, int st) {
+    a->step = step;
+    return st;
+  };
   int st = route_status(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k, a->route_flags, a->topk_idx,
                         a->topk_w);
-  if (st != MOE_OK) return st;
+  if (st != MOE_OK) return error(MOE_STEP_ROUTE, st);
   st = permute_status(a->x_bf16, a->topk_idx, a->T, a->k, shard, a->x_perm, a->expert_offsets, a->row_src, a->slot_row,
                       a->workspace, a->workspace_bytes);
-  if (st != MOE_OK) return st;
+  if (st != MOE_OK) return error(MOE_STEP_PERMUTE, st);
   const int32_t cap_rows = a->T * a->k;  // permute_status has checked the range
   const bool gather = a->x_perm == nullptr;
   const void* rows = gather ? a->x_bf16 : a->x_perm;
   st = expert_ffn_status(rows, a->expert_offsets, cap_rows, ffn_shard, a->w_gate, a->w_up, a->w_down, a->h_workspace,
                          a->y_perm, a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags);
-  if (st != MOE_OK) return st;
+  if (st != MOE_OK) return error(MOE_STEP_FFN, st);
   if (a->y_out != nullptr) {
     st = combine_status(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x,
                         a->w_shared_gate, a->y_out, a->combine_flags);
-    if (st != MOE_OK) return st;
+    if (st != MOE_OK) return error(MOE_STEP_COMBINE, st);
   }
   const hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t err = moe::launch_route_topk(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k,
                                           a->route_flags, a->topk_idx, a->topk_w, s);
-  if (err != hipSuccess) return MOE_ERR_HIP;
+  if (err != hipSuccess) return error(MOE_STEP_ROUTE, MOE_ERR_HIP);
   err = moe::launch_permute(a->x_bf16, a->topk_idx, a->T, a->k, H, shard->n_local_experts, shard->expert_offset, a->x_perm,
                             a->expert_offsets, a->row_src, a->slot_row, a->workspace, s);
-  if (err != hipSuccess) return MOE_ERR_HIP;
+  if (err != hipSuccess) return error(MOE_STEP_PERMUTE, MOE_ERR_HIP);
   err = moe::launch_expert_ffn(rows, gather ? moe::RowMap{a->row_src, a->k} : moe::RowMap{nullptr, 1}, a->expert_offsets,
                                cap_rows, moe::expected_rows(cap_rows, ffn_shard), ffn_shard->n_local_experts, H,
                                ffn_shard->inter_slice, a->w_gate, a->w_up, a->w_down, a->h_workspace, a->y_perm,
                                a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags, s);
-  if (err != hipSuccess) return MOE_ERR_HIP;
+  if (err != hipSuccess) return error(MOE_STEP_FFN, MOE_ERR_HIP);
   if (a->y_out == nullptr) return MOE_OK;
-  return hip_status(moe::launch_combine(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x,
-                                        a->w_shared_gate, a->y_out, (a->combine_flags & MOE_Y_PERM_BF16) != 0,
-                                        (a->combine_flags & MOE_OUT_F32) != 0, s));
+  err = moe::launch_combine(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x,
+                            a->w_shared_gate, a->y_out, (a->combine_flags & MOE_Y_PERM_BF16) != 0,
+                            (a->combine_flags & MOE_OUT_F32) != 0, s);
+  return err == hipSuccess ? MOE_OK : error(MOE_STEP_COMBINE, MOE_ERR_HIP);
 }
 
 const char* moe_status_string(int status) {

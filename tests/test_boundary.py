@@ -261,6 +261,19 @@ def test_forward_checks_every_step_before_it_enqueues_any(lib, bad, status):
     assert lib.moe_forward(ctypes.byref(args), ctypes.byref(shard), ctypes.byref(shard), None) == status
 
 
+@pytest.mark.parametrize("bad,name", [
+    (dict(route_flags=1 << 7), "moe_route_topk"), (dict(slot_row=None), "moe_permute"),
+    (dict(w_up=None), "moe_expert_ffn"), (dict(x_perm=None, w_up=None), "moe_expert_ffn_gather"),
+    (dict(combine_flags=1 << 30), "moe_combine"),
+])
+def test_forward_error_names_the_step(lib, bad, name):
+    shard = _shard()
+    with pytest.raises(B.MoeError, match="^%s failed" % name):
+        B.moe_forward(_forward_args(shard, **bad), shard, shard, stream=0)
+    with pytest.raises(B.MoeError, match="^moe_forward failed"):
+        B.moe_forward(_forward_args(shard), shard, _shard(hidden=1024), stream=0)
+
+
 def test_int4_sizes_beyond_the_grid_are_refused_on_the_host(lib):
     """The smallest refused sizes: 2^31 - 1 blocks, of 2048 weights when quantising, of 8192 when dequantising."""
     p = 64  # any aligned address: the call ends before it is used
