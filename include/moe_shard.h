@@ -51,7 +51,8 @@ enum {
   MOE_FFN_SKIP_GATEUP = 1u << 4, /* moe_expert_ffn: do not run GEMM1; h_workspace is an input  */
   MOE_FFN_SKIP_DOWN = 1u << 5,   /* moe_expert_ffn: stop after GEMM1; y_perm is not written    */
   MOE_FFN_TILED = 1u << 6,       /* moe_expert_ffn: tiled kernels whatever the cost estimate says */
-  MOE_FFN_LEAVE_ROOM = 1u << 7   /* moe_expert_ffn: streaming kernels leave 1/16 of the compute units free */
+  MOE_FFN_LEAVE_ROOM = 1u << 7,  /* moe_expert_ffn: streaming kernels leave 1/16 of the compute units free */
+  MOE_NO_COMBINE = 1u << 8       /* moe_forward, in combine_flags: end before the combine; y_out unused */
 };
 
 /* limits of this implementation */
@@ -196,7 +197,7 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
 /*
  * A whole forward of one shard in one call: moe_route_topk, moe_permute, moe_expert_ffn (or, with x_perm == NULL,
  * moe_expert_ffn_gather) and moe_combine with the arguments below, on one stream and in this order; with
- * y_out == NULL it ends before the combine.  Same checks and results as the separate calls; the checks of all
+ * MOE_NO_COMBINE it ends before the combine (whose arguments are then unused).  Same checks and results as the separate calls; the checks of all
  * steps come first, so with an invalid argument nothing is enqueued.  For callers that a call per step costs too much: a
  * small batch's kernels take less time than marshalling and checking the arguments of four calls.
  * shard describes the routing and permutation, ffn_shard the matrices: they differ where a slice of the

@@ -24,6 +24,7 @@ MOE_FFN_SKIP_GATEUP = 1 << 4
 MOE_FFN_SKIP_DOWN = 1 << 5
 MOE_FFN_TILED = 1 << 6
 MOE_FFN_LEAVE_ROOM = 1 << 7
+MOE_NO_COMBINE = 1 << 8
 MOE_MAX_EXPERTS = 256
 MOE_MAX_TOPK = 16
 MOE_PERMUTE_STATIC_MAX_COUNTS = 262144

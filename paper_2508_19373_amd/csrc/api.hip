@@ -208,7 +208,8 @@ int moe_forward(moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard
   st = expert_ffn_status(rows, a->expert_offsets, cap_rows, ffn_shard, a->w_gate, a->w_up, a->w_down, a->h_workspace,
                          a->y_perm, a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags);
   if (st != MOE_OK) return error(MOE_STEP_FFN, st);
-  if (a->y_out != nullptr) {
+  const bool combine = (a->combine_flags & MOE_NO_COMBINE) == 0;
+  if (combine) {
     st = combine_status(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x,
                         a->w_shared_gate, a->y_out, a->combine_flags);
     if (st != MOE_OK) return error(MOE_STEP_COMBINE, st);
@@ -225,7 +226,7 @@ int moe_forward(moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard
                                ffn_shard->inter_slice, a->w_gate, a->w_up, a->w_down, a->h_workspace, a->y_perm,
                                a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags, s);
   if (err != hipSuccess) return error(MOE_STEP_FFN, MOE_ERR_HIP);
-  if (a->y_out == nullptr) return MOE_OK;
+  if (!combine) return MOE_OK;
   err = moe::launch_combine(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x,
                             a->w_shared_gate, a->y_out, (a->combine_flags & MOE_Y_PERM_BF16) != 0,
                             (a->combine_flags & MOE_OUT_F32) != 0, s);

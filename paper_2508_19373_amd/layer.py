@@ -231,7 +231,7 @@ class ExpertShardLayer:
         if self.shared is None:
             B.moe_forward(args, self.shard, self.ffn_shard, stream)
             return self.y_out[:T]
-        args.y_out = None                         # the combine waits for the shared expert
+        args.combine_flags = B.MOE_NO_COMBINE     # the combine waits for the shared expert
         sh_offsets = self._shared_offsets(T)
         if self.overlap_shared:
             if stream is not None:

@@ -64,7 +64,7 @@ def test_header_constants_match_binding():
         m = re.search(name + r"\s*=\s*(-?\d+)", src)
         assert int(m.group(1)) == getattr(B, name)
     for name in ("MOE_RENORM_TOPK", "MOE_LOGITS_GIVEN", "MOE_Y_PERM_BF16", "MOE_OUT_F32", "MOE_FFN_SKIP_GATEUP",
-                 "MOE_FFN_SKIP_DOWN", "MOE_FFN_TILED", "MOE_FFN_LEAVE_ROOM"):
+                 "MOE_FFN_SKIP_DOWN", "MOE_FFN_TILED", "MOE_FFN_LEAVE_ROOM", "MOE_NO_COMBINE"):
         m = re.search(name + r"\s*=\s*1u\s*<<\s*(\d+)", src)
         assert 1 << int(m.group(1)) == getattr(B, name)
     assert ctypes.sizeof(B.MoeShard) == 24
@@ -272,6 +272,19 @@ def test_forward_error_names_the_step(lib, bad, name):
         B.moe_forward(_forward_args(shard, **bad), shard, shard, stream=0)
     with pytest.raises(B.MoeError, match="^moe_forward failed"):
         B.moe_forward(_forward_args(shard), shard, _shard(hidden=1024), stream=0)
+
+
+def test_forward_without_an_output_is_an_error_unless_asked_for(lib):
+    """A missing y_out is the error it is for moe_combine; ending before the combine is a flag."""
+    shard = _shard()
+    args = _forward_args(shard, y_out=None)
+    assert lib.moe_forward(ctypes.byref(args), ctypes.byref(shard), ctypes.byref(shard), None) == B.MOE_ERR_INVALID_ARG
+    assert args.step == 4
+    # with the flag the combine's arguments do not matter, the other steps' do (nothing is launched here either)
+    args = _forward_args(shard, y_out=None, combine_flags=B.MOE_NO_COMBINE | 1, w_up=None)
+    assert lib.moe_forward(ctypes.byref(args), ctypes.byref(shard), ctypes.byref(shard), None) == B.MOE_ERR_INVALID_ARG
+    assert args.step == 3
+    assert lib.moe_combine(P, P, P, 4, 2, 512, None, None, None, P, B.MOE_NO_COMBINE, None) == B.MOE_ERR_INVALID_ARG
 
 
 def test_int4_sizes_beyond_the_grid_are_refused_on_the_host(lib):
