@@ -102,7 +102,7 @@ extern "C" int32_t moe_debug_tall_units(const int32_t* expert_offsets, int32_t n
   const int grid = sliced ? sliced_grid(cap_rows, n_local, n_col_blocks) : max_grid(cap_rows, n_local, n_col_blocks);
   if (grid > max_units) return MOE_ERR_WORKSPACE;
   const ClassCounts cc =
-      count_tiles(expert_offsets, n_local, n_col_blocks, sliced ? sliced_pad_from(nk) : kPadLowTiles, true);
+      count_tiles(expert_offsets, n_local, n_col_blocks, sliced ? sliced_pad_from(nk) : kPadLowTiles, true, nk, max_slices);
   const SliceChoice sc = sliced ? choose_slices(cc, n_col_blocks, nk, max_slices) : SliceChoice{0, 1};
   for (int b = 0; b < grid; ++b) {
     int32_t* rec = units + (size_t)b * MOE_DEBUG_DEVICE_INTS;

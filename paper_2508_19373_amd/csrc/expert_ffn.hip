@@ -22,6 +22,43 @@
 namespace moe {
 namespace {
 
+// Rows the fullest local expert is planned for.  A shard that holds every expert gets exactly the
+// capacity, and only its spread over the experts is open: the average plus two sigma.  An
+// expert-parallel shard's share of the batch follows the routing ("Expert Parallelism": load
+// imbalance), and the shard that sets the latency of the step is the one that got more than its
+// share, so it is planned for twice the balanced share (under Zipf(1.2) popularity the first of four
+// shards receives 55 % of the rows, 2.2 times a quarter), never more than the whole capacity.
+inline double planned_rows_hi(int cap_rows, int est_rows, int n_local) {
+  double avg = (double)est_rows / n_local;
+  if (n_local == 1 && est_rows == cap_rows) return avg;  // one expert that takes every row
+  if (est_rows < cap_rows) avg = fmin(2.0 * avg, (double)cap_rows / n_local);
+  return avg + 2.0 * sqrt(avg);
+}
+
+// Whether a GEMM's list is expected to have tall blocks: the list itself, for a routing that spreads as a balanced router does
+// (1.7 sigma to either side of the average) or, on an expert-parallel shard, for one that got what it is planned for.
+// A launch without any takes the plain kernel: the one with tall blocks costs it a few per cent (shared expert of 333
+// rows, 88 tiles: gate/up 53.1 -> 56.6 us; 8 experts of 160 rows, down projection 228 -> 233; 4 of 600 rows 317 -> 328).
+bool expects_tall_blocks(int cap_rows, int est_rows, int n_local, int ncb, int nk, bool sliced) {
+  const bool exact = n_local == 1 && est_rows == cap_rows;  // one expert that takes every row
+  const double avg = (double)est_rows / n_local;
+  int32_t offsets[MOE_MAX_EXPERTS + 1];
+  auto tall = [&](double rows, double spread) {
+    double at = 0.0;
+    offsets[0] = 0;
+    for (int e = 0; e < n_local; ++e) {
+      at += rows + spread * sqrt(rows) * ((2 * e + 1.0) / n_local - 1.0);
+      offsets[e + 1] = (int32_t)fmin(at + 0.5, 1 << 30);
+    }
+    return gg::count_tiles(offsets, n_local, ncb, sliced ? gg::sliced_pad_from(nk) : gg::kPadLowTiles, true, nk,
+                           sliced ? gg::max_k_slices(nk * gg::BK) : 0)
+        .tall;
+  };
+  if (exact) return tall(avg, 0.0);
+  return tall(avg, 1.7) ||
+         (est_rows < cap_rows && tall(fmin(2.0 * avg, (double)cap_rows / n_local), 1.7));
+}
+
 // Prefill-sized groups: LDS-DMA kernel, 256-column tiles of 256 / 128 / 64 rows.  `tall`: full row blocks may take
 // their expert's remainder.
 template <int BN>
@@ -30,17 +67,15 @@ hipError_t launch_pair_dlds(bool allow_tall, const void* x_perm, RowMap rows, co
                             void* y_perm, void* workspace, uint32_t flags, hipStream_t stream) {
   const bool y_bf16 = (flags & MOE_Y_PERM_BF16) != 0;
   const dim3 block(256);
-  // the kernel with tall blocks only where the launch is expected to fill the chip: one that does not has none of
-  // them and would pay for the larger kernel (shared expert of 333 rows, 88 tiles: gate/up 53.1 -> 56.6 us)
-  auto tall_for = [&](int ncb, int from) {
-    return allow_tall && gg::expected_tiles(est_rows, n_local, ncb, n_local == 1 && est_rows == cap_rows) >= from;
+  auto tall_for = [&](int ncb, int nk, bool sliced) {
+    return allow_tall && expects_tall_blocks(cap_rows, est_rows, n_local, ncb, nk, sliced);
   };
   const uint16_t* xp = static_cast<const uint16_t*>(x_perm);
   uint16_t* hw = static_cast<uint16_t*>(h_ws);
   auto grid_for = [&](int ncb) { return dim3((unsigned)gg::max_grid(cap_rows, n_local, ncb)); };
   if (!(flags & MOE_FFN_SKIP_GATEUP)) {
     const int ncb = (I_s + BN / 2 - 1) / (BN / 2);
-    const auto kernel = tall_for(ncb, gg::kPadLowTiles) ? gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>
+    const auto kernel = tall_for(ncb, H / gg::BK, false) ? gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>
                              : gg::grouped_gemm_dlds_kernel<BN, true, uint16_t, false>;
     hipLaunchKernelGGL(kernel, grid_for(ncb), block, 0, stream, xp,
                        expert_offsets, n_local, cap_rows, static_cast<const uint16_t*>(w_gate),
@@ -50,7 +85,9 @@ hipError_t launch_pair_dlds(bool allow_tall, const void* x_perm, RowMap rows, co
   }
   if (flags & MOE_FFN_SKIP_DOWN) return hipSuccess;
   const int ncb = (H + BN - 1) / BN;
-  const bool tall = tall_for(ncb, y_bf16 ? gg::kPadLowTiles : gg::sliced_pad_from(I_s / gg::BK));
+  const gg::SlicePlan sp =
+      y_bf16 || workspace == nullptr ? gg::SlicePlan{1, 0} : gg::slice_plan(cap_rows, ncb, I_s);
+  const bool tall = tall_for(ncb, I_s / gg::BK, sp.max_slices > 1);
   if (y_bf16) {
     const auto kernel = tall ? gg::grouped_gemm_tall_kernel<BN, false, uint16_t, false>
                              : gg::grouped_gemm_dlds_kernel<BN, false, uint16_t, false>;
@@ -60,7 +97,6 @@ hipError_t launch_pair_dlds(bool allow_tall, const void* x_perm, RowMap rows, co
                        static_cast<uint16_t*>(nullptr), 0, RowMap{nullptr, 1});
     return hipGetLastError();
   }
-  const gg::SlicePlan sp = workspace == nullptr ? gg::SlicePlan{1, 0} : gg::slice_plan(cap_rows, ncb, I_s);
   float* yp = static_cast<float*>(y_perm);
   float* ws = static_cast<float*>(workspace);
   const uint16_t* wd = static_cast<const uint16_t*>(w_down);
@@ -208,19 +244,6 @@ hipError_t launch_pair_decode(const void* x_perm, RowMap rows, const int32_t* ex
                        expert_offsets, static_cast<const uint16_t*>(w_down), static_cast<const uint16_t*>(nullptr),
                        H, I_s, static_cast<float*>(y_perm), RowMap{nullptr, 1});
   return hipGetLastError();
-}
-
-// Rows the fullest local expert is planned for.  A shard that holds every expert gets exactly the
-// capacity, and only its spread over the experts is open: the average plus two sigma.  An
-// expert-parallel shard's share of the batch follows the routing ("Expert Parallelism": load
-// imbalance), and the shard that sets the latency of the step is the one that got more than its
-// share, so it is planned for twice the balanced share (under Zipf(1.2) popularity the first of four
-// shards receives 55 % of the rows, 2.2 times a quarter), never more than the whole capacity.
-inline double planned_rows_hi(int cap_rows, int est_rows, int n_local) {
-  double avg = (double)est_rows / n_local;
-  if (n_local == 1 && est_rows == cap_rows) return avg;  // one expert that takes every row
-  if (est_rows < cap_rows) avg = fmin(2.0 * avg, (double)cap_rows / n_local);
-  return avg + 2.0 * sqrt(avg);
 }
 
 // MT = 1 (16 activation rows per pass) when the fullest expert is expected to stay within 16 rows

@@ -31,8 +31,8 @@ constexpr int kNumXcd = 8;
 // on average, spread as a router does: gate/up 802 us with every remainder dealt out, 691 with this limit, 716-742
 // without tall blocks).  An expert with several blocks takes 16 rows more per block at most: an XCD runs a contiguous
 // eighth of the tiles, often one expert's, and waits for nobody else's (blocks of 288 rows there would make the launch an
-// eighth longer).  Only in launches that fill the chip (ClassCounts::tall): with compute units
-// to spare a remainder tile of its own costs nothing.
+// eighth longer).  Only in launches that end sooner for it (dealing_pays): with compute units to spare a remainder tile
+// of its own costs nothing.
 constexpr int kMaxExtra = 3;
 constexpr int kMaxTallRemainder = 144;
 struct RowBlocks {
@@ -67,10 +67,11 @@ struct TileCoord {
 // Tiles per height class (0: 256 rows, 1: 128, 2: 64), over all local experts and column blocks.
 // pad_low: the launch has at least 256 tiles before any padding of experts below 256 rows, that is,
 // it fills every compute unit (every function below takes the flag from here).
-// tall: full blocks take the remainders where they can (the call allows it and the launch fills the chip).
+// tall: full blocks take the remainders where they can (the call allows it and dealing_pays says so).
 struct ClassCounts {
   int n[3];
   bool pad_low, tall;
+  __host__ __device__ inline int total() const { return n[0] + n[1] + n[2]; }
 };
 constexpr int kPadLowTiles = 256;
 // The sliced down projection pads from 128 tiles on (sliced_pad_from): its tiles are cut along K until they fill the
@@ -83,18 +84,56 @@ constexpr int kPadLowTiles = 256;
 // that 128 padded tiles allow are short (Mixtral TP=8, 28 k-tiles: layer 151 -> 162 us at 512 tokens,
 // 179 -> 172 us at 768).
 __host__ __device__ inline int sliced_pad_from(int nk) { return nk >= 48 ? 128 : kPadLowTiles; }
+
+// Whether a launch is shorter with its remainders dealt out (`dealt`) than with remainder tiles (`plain`).  A tall tile
+// takes up to a fifth longer than a 256-row one, so there has to be something for it:
+//   - the tiles take a round of 256 fewer, or there are so many rounds (three and more) that the streamed weights are
+//     what counts.  The full blocks have to occupy three quarters of the chip themselves: in a launch of fewer
+//     the remainder tiles run beside them on units that would idle;
+//   - or a K-sliced launch of up to 128 tiles, all of which run as slices, is cut finer than the plain list (which
+//     has 128 tiles at least, pad_low).
+// Measured on 1050 random launches of one to 64 experts with tall blocks (two GEMMs, 21 shard shapes, each list's time): geometric mean over
+// the faster of the two lists, gate/up 1.040 with remainder tiles always, 1.013 dealt wherever there are 256 tiles,
+// 1.007 with this rule; down projection 1.025, 1.035, 1.010.  Single launches, us, remainder tiles / dealt: down projection of 8
+// Mixtral experts of 300 rows 381 / 486 (128 tiles of 304 rows and half the chip idle, against 256), of 4 196 / 271; one
+// expert of 2066 rows 272 / 194 (128 tiles in two slices against 144 whole); gate/up of 8 experts of 287 rows (TP=2) 406 / 296.
+constexpr int kDealtTiles = 192, kDealtManyTiles = 768;
+// Bound on the rows of a launch of dealt tiles, times its column blocks (rows of partial sums: sliced_rows).
+__host__ __device__ inline int dealt_volume(const ClassCounts& c) {
+  return c.n[0] * (256 + kMaxExtra * 16) + c.n[1] * 128 + c.n[2] * 64;
+}
+__host__ __device__ inline bool dealing_pays(const ClassCounts& plain, const ClassCounts& dealt, int nk, int max_slices) {
+  const int tiles = dealt.total();
+  if (max_slices > 1 && tiles <= 128) {  // (the estimate of fit_slices, for the most slices only: it runs in every workgroup)
+    const int volume = dealt_volume(dealt), uncut = plain.total() <= 128 ? 2 : 1;
+    const int s = min(min(256 / tiles, max_slices), 1 + 65536 / volume);
+    return s > uncut && nk * 16 / s + 64 + volume * (s + 1) / 275 < nk * 16 / uncut;
+  }
+  return dealt.n[0] >= kDealtTiles && (tiles >= kDealtManyTiles || (tiles + 255) / 256 < (plain.total() + 255) / 256);
+}
+
+// nk, max_slices: k-tiles and most K slices of a sliced launch (0 slices: a launch that is not cut), for allow_tall only.
 __host__ __device__ inline ClassCounts count_tiles(const int32_t* __restrict__ expert_offsets, int n_local,
-                                                   int n_col_blocks, int pad_from = kPadLowTiles, bool allow_tall = false) {
+                                                   int n_col_blocks, int pad_from = kPadLowTiles, bool allow_tall = false,
+                                                   int nk = 0, int max_slices = 0) {
   ClassCounts c = {{0, 0, 0}, false, false};
   int blocks = 0;
   for (int e = 0; e < n_local; ++e) blocks += row_blocks(expert_offsets[e + 1] - expert_offsets[e], false).total();
   c.pad_low = blocks * n_col_blocks >= pad_from;
-  c.tall = allow_tall && c.pad_low;
-  for (int e = 0; e < n_local; ++e) {
-    const RowBlocks rb = row_blocks(expert_offsets[e + 1] - expert_offsets[e], c.pad_low, c.tall);
-    c.n[0] += rb.n256 * n_col_blocks;
-    c.n[1] += rb.n128 * n_col_blocks;
-    c.n[2] += rb.n64 * n_col_blocks;
+  auto count = [&](bool tall) {
+    ClassCounts n = {{0, 0, 0}, c.pad_low, tall};
+    for (int e = 0; e < n_local; ++e) {
+      const RowBlocks rb = row_blocks(expert_offsets[e + 1] - expert_offsets[e], c.pad_low, tall);
+      n.n[0] += rb.n256 * n_col_blocks;
+      n.n[1] += rb.n128 * n_col_blocks;
+      n.n[2] += rb.n64 * n_col_blocks;
+    }
+    return n;
+  };
+  c = count(false);
+  if (allow_tall && c.pad_low) {
+    const ClassCounts dealt = count(true);
+    if (dealing_pays(c, dealt, nk, max_slices)) return dealt;
   }
   return c;
 }

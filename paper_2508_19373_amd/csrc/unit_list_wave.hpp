@@ -83,8 +83,8 @@ struct WaveRouting {
   ClassCounts cc;  // as count_tiles
 };
 __device__ inline WaveRouting wave_routing(const int32_t* __restrict__ expert_offsets, int n_local,
-                                           int n_col_blocks, int pad_from = kPadLowTiles,
-                                           bool allow_tall = false) {
+                                           int n_col_blocks, int pad_from = kPadLowTiles, bool allow_tall = false,
+                                           int nk = 0, int max_slices = 0) {
   WaveRouting w;
   const int lane = threadIdx.x & 63;
   w.chunks = (n_local + 63) >> 6;
@@ -95,10 +95,37 @@ __device__ inline WaveRouting wave_routing(const int32_t* __restrict__ expert_of
     const bool ok = j < w.chunks && e < n_local;
     w.lo[j] = ok ? expert_offsets[e] : 0;
     w.rows[j] = ok ? expert_offsets[e + 1] - w.lo[j] : 0;
-    blocks += row_blocks(w.rows[j], false).total();
+    const RowBlocks rb = row_blocks(w.rows[j], false);
+    blocks += allow_tall ? rb.n256 : rb.total();
   }
-  w.cc.pad_low = __builtin_amdgcn_readlane(wave_incl_scan(blocks), 63) * n_col_blocks >= pad_from;
-  w.cc.tall = allow_tall && w.cc.pad_low;
+  blocks = __builtin_amdgcn_readlane(wave_incl_scan(blocks), 63);
+  w.cc.tall = false;
+  if (!allow_tall) {
+    w.cc.pad_low = blocks * n_col_blocks >= pad_from;
+  } else {
+    // both lists' counts from that one scan (of the 256-row blocks) and a few ballots
+    int t128 = 0, t64 = 0, both = 0, d256 = 0, d128 = 0, d64 = 0;  // both: experts of a 128- and a 64-row tile, padded or not
+#pragma unroll
+    for (int j = 0; j < kLaneChunks; ++j) {
+      if (j < w.chunks) {
+        const RowBlocks rb = row_blocks(w.rows[j], false);
+        const unsigned long long b128 = __ballot(rb.n128 != 0), b64 = __ballot(rb.n64 != 0),
+                                 dealt = __ballot(row_blocks(w.rows[j], true, true).nt > 0);
+        t128 += __popcll(b128 & ~b64);
+        t64 += __popcll(b64 & ~b128);
+        both += __popcll(b128 & b64);
+        d128 += __popcll(dealt & b128);  // (an expert with full blocks has one tile behind them at most)
+        d64 += __popcll(dealt & b64);
+        d256 += __popcll(dealt & ~b128 & ~b64);
+      }
+    }
+    w.cc.pad_low = (blocks + t128 + t64 + 2 * both) * n_col_blocks >= pad_from;
+    const int t256 = blocks + both;
+    const ClassCounts plain = {{t256 * n_col_blocks, t128 * n_col_blocks, t64 * n_col_blocks}, true, false};
+    const ClassCounts dealt = {
+        {(t256 - d256) * n_col_blocks, (t128 - d128) * n_col_blocks, (t64 - d64) * n_col_blocks}, true, true};
+    w.cc.tall = w.cc.pad_low && dealing_pays(plain, dealt, nk, max_slices);
+  }
   int t128 = 0, t64 = 0;
 #pragma unroll
   for (int j = 0; j < kLaneChunks; ++j) {
@@ -205,7 +232,7 @@ __device__ inline WaveSlicedUnit wave_find_sliced_unit(const int32_t* __restrict
                                                        int n_col_blocks, int nk_all, int max_slices, int bid) {
   WaveSlicedUnit r;
   r.valid = false;
-  const WaveRouting w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL);
+  const WaveRouting w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL, nk_all, max_slices);
   const SliceChoice sc = choose_slices(w.cc, n_col_blocks, nk_all, max_slices);
   const SlicedUnit u = find_sliced_unit(w.cc, sc, n_col_blocks, bid);
   if (u.cls < 0) return r;
@@ -266,7 +293,8 @@ __device__ inline WaveSlicedUnit find_sliced_unit_of(const int32_t* __restrict__
     return wave_find_sliced_unit<TALL>(expert_offsets, n_local, n_col_blocks, nk_all, max_slices, bid);
   WaveSlicedUnit r;
   r.valid = false;
-  const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL);
+  const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL, nk_all,
+                                       max_slices);
   const SliceChoice sc = choose_slices(cc, n_col_blocks, nk_all, max_slices);
   const SlicedUnit u = find_sliced_unit(cc, sc, n_col_blocks, bid);
   if (u.cls < 0) return r;
@@ -307,7 +335,8 @@ __device__ inline SumPlan sum_plan(const int32_t* __restrict__ expert_offsets, i
   p.total = 0;
   p.pad_low = p.tall = false;
   if (p.plain) {
-    const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL);
+    const ClassCounts cc = count_tiles(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL, nk_all,
+                                       max_slices);
     const SliceChoice sc = choose_slices(cc, n_col_blocks, nk_all, max_slices);
     p.slices = sc.slices;
     p.keep_rb = sc.keep_rb;
@@ -315,7 +344,7 @@ __device__ inline SumPlan sum_plan(const int32_t* __restrict__ expert_offsets, i
     p.tall = cc.tall;
     if (sc.slices > 1) p.total = sliced_rows(expert_offsets, n_local, 0, sc.keep_rb, cc.pad_low, cc.tall).total;
   } else {
-    p.w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL);
+    p.w = wave_routing(expert_offsets, n_local, n_col_blocks, sliced_pad_from(nk_all), TALL, nk_all, max_slices);
     const SliceChoice sc = choose_slices(p.w.cc, n_col_blocks, nk_all, max_slices);
     p.slices = sc.slices;
     p.keep_rb = sc.keep_rb;

@@ -247,3 +247,26 @@ def test_tall_row_blocks_are_the_fewest_that_hold_the_remainder():
     # a launch that leaves compute units idle has none: a remainder tile of its own costs nothing there
     units = B.moe_debug_tall_units(_offsets([1040, 1050]), 2090, 20, 64, 0)
     assert set(units[:, 0].tolist()) == {0, 256, 64}
+
+
+@pytest.mark.parametrize("rows,ncb,nk,max_slices,tall", [
+    # as many rounds of 256 tiles either way: the remainder tiles run on units that would idle beside tall ones
+    ([302, 333, 332, 368, 303, 320, 325, 333], 16, 56, 7, False),
+    ([349, 329, 312, 171, 173, 301, 729, 236], 16, 224, 16, False),
+    ([315, 292, 295, 321], 16, 224, 16, False),
+    ([126, 1394, 588, 267, 148, 421, 126, 303], 14, 64, 0, False),
+    ([2304, 2305, 2320, 2337], 8, 32, 0, False),
+    # a round fewer, or many rounds
+    ([306, 281, 282, 295, 273, 300, 269, 317], 56, 64, 0, True),
+    ([255, 281, 265, 253, 238, 241, 279, 231], 28, 64, 0, True),
+    ([1053] * 8, 112, 64, 0, True),
+    ([1053] * 8, 16, 224, 16, True),
+    # a down projection that is cut into more slices
+    ([2066], 16, 224, 16, True),
+    ([283, 290, 271, 281, 265, 289, 294, 279], 16, 112, 14, True),
+])
+def test_remainders_are_dealt_out_only_where_the_launch_ends_sooner(rows, ncb, nk, max_slices, tall):
+    """Routings measured both ways: dealing the remainders to the full blocks where that saves no round of tiles made the
+    launch up to a third longer (half the chip idle beside tiles of 304 rows)."""
+    units = B.moe_debug_tall_units(_offsets(rows), sum(rows), ncb, nk, max_slices)
+    assert bool((units[:, 0] > 256).any()) == tall
