@@ -152,55 +152,72 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
 
-  // DMA instruction j of a wave loads 8 rows of 128 bytes; the swizzled chunk a lane fetches is the same for all j
+  // DMA instruction j of a wave loads 8 rows of 128 bytes: row (j * NW + wave) * 8 + lane / 8 of the tile, chunk
+  // lane % 8 as the swizzle places it (the same chunk for all j)
   static_assert(NW % 2 == 0, "a wave's DMA instructions start at rows with the same swizzle");
-  const int dma_row = lane >> 3, dma_chunk = (lane & 7) ^ swz(wave * 8 + dma_row);
-  // BUF: both operands are addressed as buffers (32-bit lane offsets + scalar offsets).  That saves the registers
-  // a tall tile's extra rows need, and only between buffer instructions does the compiler count how many loads may be
-  // outstanding behind a register load (behind global_load_lds it waits for all of them)
+  // Operand addresses.  Without BUF: a pointer per lane and instruction.  With BUF both operands are buffers (32-bit lane
+  // offsets + scalar offsets): that saves the registers a tall tile's extra rows need, and only between buffer
+  // instructions does the compiler count how many loads may be outstanding behind a register load (behind
+  // global_load_lds it waits for all of them).  The two are computed apart: sharing the lane arithmetic cost the
+  // tiles without BUF a spilled register and up to 4 % (gate/up of one expert of 333 rows 45.4 -> 47.4 us).
+  // Rows past the tile's expert are computed and dropped: they read any valid row (with a row map, the expert's last
+  // one: entries past the routed rows are not defined).
   static_assert(NX == 0 || BUF, "extra rows need buffer addressing");
-  const uint16_t* a_base = A + (rows.row_src ? 0 : (size_t)row0 * K) + (size_t)kt0 * BK;
+  const uint16_t* a_src[BUF ? 1 : A_INST];
+  const uint16_t* b_src[BUF ? 1 : B_INST];
+  uint32_t a_lane[BUF ? A_INST : 1], b_off[BUF ? B_INST : 1], b_lane = 0;  // byte offsets from a_buf, b_buf
   const int a_row0 = rows.row_src ? 0 : row0;
-  uint32_t a_lane[A_INST];  // BUF: byte offsets from a_base
-  const uint16_t* a_src[A_INST];
-#pragma unroll
-  for (int j = 0; j < A_INST; ++j) {
-    const int r = row0 + (j * NW + wave) * 8 + dma_row;
-    // rows past the tile's expert are computed and dropped: they read any valid row (with a row
-    // map, the expert's last one: entries past the routed rows are not defined)
-    const int gr = rows.row_src ? rows(min(r, hi - 1)) : min(r, cap_rows - 1);
-    a_src[j] = A + (size_t)gr * K + (size_t)kt0 * BK + dma_chunk * 8;
-    a_lane[j] = (uint32_t)(gr - a_row0) * (uint32_t)K * 2u + (uint32_t)dma_chunk * 16u;
-  }
-  // weights: the 8 rows of an instruction are consecutive rows of one matrix, so as buffers their address is a scalar
-  // offset per instruction plus one 32-bit lane offset for all of them (14 vector registers fewer than lane pointers);
-  // n_out is a multiple of 64, so the last column block is clamped by whole instructions
-  const uint32_t b_lane = (uint32_t)dma_row * (uint32_t)K * 2u + (uint32_t)dma_chunk * 16u;
-  const uint16_t* b_src[B_INST];
-  uint32_t b_off[B_INST];  // BUF: byte offset from the tile's first weight row
+  buf_t a_buf, b_buf;
   const size_t expert_stride = (size_t)n_out * K;
+  if constexpr (BUF) {
+    const int dma_row = lane >> 3, dma_chunk = (lane & 7) ^ swz(wave * 8 + dma_row);
 #pragma unroll
-  for (int j = 0; j < B_INST; ++j) {
-    const int r = (j * NW + wave) * 8;
-    const uint16_t* base = B0;
-    int wrow;
-    if (GATEUP) {  // 16-row blocks alternate gate, up, gate, up ... of the same output columns
-      const int jb = r >> 4;
-      wrow = col0 + (jb >> 1) * 16 + (r & 15);
-      if (jb & 1) base = B1;
-    } else {
-      wrow = col0 + r;
+    for (int j = 0; j < A_INST; ++j) {
+      const int r = row0 + (j * NW + wave) * 8 + dma_row;
+      const int gr = rows.row_src ? rows(min(r, hi - 1)) : min(r, cap_rows - 1);
+      a_lane[j] = (uint32_t)(gr - a_row0) * (uint32_t)K * 2u + (uint32_t)dma_chunk * 16u;
     }
-    b_src[j] = base + (size_t)tc.expert * expert_stride + (size_t)min(wrow + dma_row, n_out - 1) * K +
-               (size_t)kt0 * BK + dma_chunk * 8;
-    b_off[j] = (uint32_t)(min(wrow, n_out - 8) - col0) * (uint32_t)K * 2u;
+    // weights: the 8 rows of an instruction are consecutive rows of one matrix, so their address is a scalar
+    // offset per instruction plus one 32-bit lane offset for all of them (14 vector registers fewer than lane
+    // pointers); n_out is a multiple of 64, so the last column block is clamped by whole instructions
+    b_lane = (uint32_t)dma_row * (uint32_t)K * 2u + (uint32_t)dma_chunk * 16u;
+#pragma unroll
+    for (int j = 0; j < B_INST; ++j) {
+      const int r = (j * NW + wave) * 8, jb = r >> 4;
+      const int wrow = GATEUP ? col0 + (jb >> 1) * 16 + (r & 15) : col0 + r;
+      b_off[j] = (uint32_t)(min(wrow, n_out - 8) - col0) * (uint32_t)K * 2u;
+    }
+    // (in GATEUP mode all instructions of a wave load from the same matrix: 16-row blocks alternate, a wave's
+    // instructions are NW * 8 = 32 rows apart)
+    static_assert(!GATEUP || NW * 8 % 32 == 0, "one matrix per wave");
+    a_buf = make_buf(A + (size_t)a_row0 * K + (size_t)kt0 * BK);
+    b_buf = make_buf((GATEUP && ((wave >> 1) & 1) ? B1 : B0) + (size_t)tc.expert * expert_stride + (size_t)col0 * K +
+                     (size_t)kt0 * BK);
+  } else {
+#pragma unroll
+    for (int j = 0; j < A_INST; ++j) {
+      const int r = (j * NW + wave) * 8 + (lane >> 3);
+      const int c = (lane & 7) ^ swz(r);
+      const int gr = rows.row_src ? rows(min(row0 + r, hi - 1)) : min(row0 + r, cap_rows - 1);
+      a_src[j] = A + (size_t)gr * K + (size_t)kt0 * BK + c * 8;
+    }
+#pragma unroll
+    for (int j = 0; j < B_INST; ++j) {
+      const int r = (j * NW + wave) * 8 + (lane >> 3);
+      const int c = (lane & 7) ^ swz(r);
+      const uint16_t* base = B0;
+      int wrow;
+      if (GATEUP) {  // 16-row blocks alternate gate, up, gate, up ... of the same output columns
+        const int jb = r >> 4;
+        wrow = col0 + (jb >> 1) * 16 + (r & 15);
+        if (jb & 1) base = B1;
+      } else {
+        wrow = col0 + r;
+      }
+      wrow = min(wrow, n_out - 1);
+      b_src[j] = base + (size_t)tc.expert * expert_stride + (size_t)wrow * K + (size_t)kt0 * BK + c * 8;
+    }
   }
-  // (in GATEUP mode all instructions of a wave load from the same matrix: 16-row blocks alternate, a wave's
-  // instructions are NW * 8 = 32 rows apart)
-  static_assert(!GATEUP || NW * 8 % 32 == 0, "one matrix per wave");
-  const uint16_t* b_base = (GATEUP && ((wave >> 1) & 1) ? B1 : B0) + (size_t)tc.expert * expert_stride +
-                           (size_t)col0 * K + (size_t)kt0 * BK;
-  const buf_t a_buf = make_buf(a_base), b_buf = make_buf(b_base);
 
   const int lrow = lane & 15;
   const int kq = lane >> 4;
@@ -226,18 +243,21 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
   auto issue_dma = [&](int kt_a, int stage_a, int kt_b, int stage_b, auto idx_tag) {
     constexpr int idx = decltype(idx_tag)::value;
     if constexpr (idx < A_INST) {
-      lds_void_t* dst = (lds_void_t*)(smem + stage_a * A_STAGE + (idx * NW + wave) * 8 * BK);
       if constexpr (BUF)
-        buf_to_lds(a_buf, dst, a_lane[idx], kt_a * (BK * 2));
+        buf_to_lds(a_buf, (lds_void_t*)(smem + stage_a * A_STAGE + (idx * NW + wave) * 8 * BK), a_lane[idx],
+                   kt_a * (BK * 2));
       else
-        __builtin_amdgcn_global_load_lds((global_void_t*)(a_src[idx] + (size_t)kt_a * BK), dst, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((global_void_t*)(a_src[idx] + (size_t)kt_a * BK),
+                                         (lds_void_t*)(smem + stage_a * A_STAGE + (idx * NW + wave) * 8 * BK), 16, 0, 0);
     } else {
       constexpr int j = idx - A_INST;
-      lds_void_t* dst = (lds_void_t*)(smem + NSA * A_STAGE + stage_b * B_STAGE + (j * NW + wave) * 8 * BK);
       if constexpr (BUF)
-        buf_to_lds(b_buf, dst, b_lane, b_off[j] + kt_b * (BK * 2));
+        buf_to_lds(b_buf, (lds_void_t*)(smem + NSA * A_STAGE + stage_b * B_STAGE + (j * NW + wave) * 8 * BK), b_lane,
+                   b_off[j] + kt_b * (BK * 2));
       else
-        __builtin_amdgcn_global_load_lds((global_void_t*)(b_src[j] + (size_t)kt_b * BK), dst, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(
+            (global_void_t*)(b_src[j] + (size_t)kt_b * BK),
+            (lds_void_t*)(smem + NSA * A_STAGE + stage_b * B_STAGE + (j * NW + wave) * 8 * BK), 16, 0, 0);
     }
   };
 
@@ -396,40 +416,45 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
   const int lcol = kq * 4;
   const bool full = (row0 + BM + 16 * NX <= hi) && (col0 + NCOLS <= n_out);  // n_out is a multiple of 4
   auto store_tile = [&](auto guard) {
-    auto store_row = [&](int row, const f32x4* r, int n_blocks) {
+    // one lane's four values of weight row block j (in GATEUP mode with its up block v1)
+    auto store = [&](int row, int col, const f32x4& v, const f32x4& v1) {
       if constexpr (GATEUP) {
-#pragma unroll
-        for (int j = 0; j < n_blocks; j += 2) {
-          const int jb = wn * TN + j_phys(j);  // even: gate block; jb + 1: up block of the same columns
-          const int col = col0 + (jb >> 1) * 16 + lcol;
-          if (guard(row, col)) {
-            uint2 o;
-            o.x = pack_bf16x2(silu_mul(r[j][0], r[j + 1][0]), silu_mul(r[j][1], r[j + 1][1]));
-            o.y = pack_bf16x2(silu_mul(r[j][2], r[j + 1][2]), silu_mul(r[j][3], r[j + 1][3]));
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(C) + (size_t)row * n_out + col) = o;
-          }
-        }
+        uint2 o;
+        o.x = pack_bf16x2(silu_mul(v[0], v1[0]), silu_mul(v[1], v1[1]));
+        o.y = pack_bf16x2(silu_mul(v[2], v1[2]), silu_mul(v[3], v1[3]));
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(C) + (size_t)row * n_out + col) = o;
+      } else if constexpr (sizeof(OutT) == 4) {
+        *reinterpret_cast<float4*>(C + (size_t)row * n_out + col) = make_float4(v[0], v[1], v[2], v[3]);
       } else {
-#pragma unroll
-        for (int j = 0; j < n_blocks; ++j) {
-          const int col = col0 + wn * (BN / WN) + j_phys(j) * 16 + lcol;
-          if (guard(row, col)) {
-            if constexpr (sizeof(OutT) == 4) {
-              *reinterpret_cast<float4*>(C + (size_t)row * n_out + col) = make_float4(r[j][0], r[j][1], r[j][2], r[j][3]);
-            } else {
-              uint2 o;
-              o.x = pack_bf16x2(r[j][0], r[j][1]);
-              o.y = pack_bf16x2(r[j][2], r[j][3]);
-              *reinterpret_cast<uint2*>(C + (size_t)row * n_out + col) = o;
-            }
-          }
-        }
+        uint2 o;
+        o.x = pack_bf16x2(v[0], v[1]);
+        o.y = pack_bf16x2(v[2], v[3]);
+        *reinterpret_cast<uint2*>(C + (size_t)row * n_out + col) = o;
       }
     };
+    constexpr int JS = GATEUP ? 2 : 1;  // even blocks: gate; the next one: up of the same columns
+    auto col_of = [&](int j) {
+      if constexpr (GATEUP) return col0 + ((wn * TN + j_phys(j)) >> 1) * 16 + lcol;
+      return col0 + wn * (BN / WN) + j_phys(j) * 16 + lcol;
+    };
 #pragma unroll
-    for (int i = 0; i < TM; ++i) store_row(row0 + wm * (BM / WM) + i * 16 + lrow, acc[i], TN);
+    for (int i = 0; i < TM; ++i) {
+      const int row = row0 + wm * (BM / WM) + i * 16 + lrow;
 #pragma unroll
-    for (int x = 0; x < NX; ++x) store_row(row0 + BM + x * 16 + lrow, xacc[x], XN);
+      for (int j = 0; j < TN; j += JS) {
+        const int col = col_of(j);
+        if (guard(row, col)) store(row, col, acc[i][j], acc[i][j + JS - 1]);
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+      const int row = row0 + BM + x * 16 + lrow;
+#pragma unroll
+      for (int j = 0; j < XN; j += JS) {
+        const int col = col_of(j);
+        if (guard(row, col)) store(row, col, xacc[x][j], xacc[x][j + JS - 1]);
+      }
+    }
   };
   if (full)
     store_tile([](int, int) { return true; });
