@@ -103,7 +103,7 @@ __device__ inline bf16x8 buf_load(buf_t, uint32_t, uint32_t) { return bf16x8{}; 
 // a kernel's own MFMAs in the 256 accumulation registers, and a tall tile has up to 304).  The compiler does not see
 // that this is an MFMA and adds no wait states for it: 2 after a VALU write of an operand (gemm_tile keeps two
 // MFMAs in between), none before a dependent MFMA of the same kind, and the accumulator is next read by
-// another instruction hundreds of MFMAs later.
+// another instruction hundreds of MFMAs later.  tests/test_device_code.py looks for all of this in the built code.
 __device__ __forceinline__ void mfma_vgpr(f32x4& acc, const bf16x8& a, const bf16x8& b) {
 #ifdef __HIP_DEVICE_COMPILE__
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));

@@ -1,5 +1,5 @@
 """What the built library's own device code (gfx950) has to look like where the sources rely on it: register spills of the
-tiled kernels."""
+tiled kernels, and the waits around matrix instructions that the compiler does not know to be any."""
 import os
 import re
 import struct
@@ -56,3 +56,77 @@ def test_tiled_kernels_do_not_spill(code_object):
         assert n <= (1 if "grouped_gemm_dlds_kernelILi256ELb1E" in name else 0), (name, n)
     tall = {n: s for n, s in spills.items() if "grouped_gemm_tall_kernel" in n}
     assert len(tall) == 4 and all(s <= 2 for s in tall.values()), tall
+
+
+def _regs(operand):
+    """Vector registers an operand names."""
+    m = re.fullmatch(r"-?\|?v(?:\[(\d+):(\d+)\]|(\d+))\|?", operand)
+    if not m:
+        return set()
+    return {int(m.group(3))} if m.group(3) else set(range(int(m.group(1)), int(m.group(2)) + 1))
+
+
+class _Instr:
+    def __init__(self, line, start):
+        text, _, comment = line.strip().partition("//")
+        self.addr = int(comment.split(":")[0], 16) - start
+        self.op, _, rest = text.strip().partition(" ")
+        self.operands = [o.strip() for o in rest.split(",")] if rest else []
+        target = re.search(r"<[^>+]+(?:\+0x([0-9a-fA-F]+))?>", comment)
+        self.target = int(target.group(1) or "0", 16) if target and self.op.startswith(("s_branch", "s_cbranch")) else None
+        self.mfma = self.op.startswith("v_mfma")
+        self.states = int(self.operands[0]) + 1 if self.op == "s_nop" else 1
+
+
+def _tall_kernels(code_object):
+    kernels, cur = {}, None
+    for line in _tool("llvm-objdump", "-d", code_object).splitlines():
+        head = re.match(r"([0-9a-f]+) <(\S+)>:", line)
+        if head:
+            cur = None
+            if "grouped_gemm_tall_kernel" in head.group(2):
+                start = int(head.group(1), 16)
+                cur = kernels.setdefault(head.group(2), [])
+        elif cur is not None and line.startswith("\t") and "//" in line:
+            cur.append(_Instr(line, start))
+    return kernels
+
+
+def test_matrix_instructions_in_inline_assembly_keep_their_distance(code_object):
+    """The extra rows of a tall tile accumulate in vector registers through inline assembly, and the compiler inserts no
+    waits for it.  Nobody may touch such a result within the instruction's latency (8 passes of 4 cycles, 11 wait states
+    before an access by anything but the next MFMA on the same accumulator; asked for here: 16 instructions), and no
+    vector instruction may write an operand within the 2 wait states before it."""
+    kernels = _tall_kernels(code_object)
+    assert len(kernels) == 4
+    for name, code in kernels.items():
+        index = {ins.addr: i for i, ins in enumerate(code)}
+        own = [i for i, ins in enumerate(code) if ins.mfma and ins.operands[0].startswith("v")]
+        assert len(own) > 100, name
+        for i in own:
+            dst = _regs(code[i].operands[0])
+            assert code[i].operands[3] == code[i].operands[0]
+            todo, seen = [(i + 1, 16)], set()
+            while todo:
+                at, left = todo.pop()
+                if left <= 0 or at >= len(code) or (at, left) in seen:
+                    continue
+                seen.add((at, left))
+                ins = code[at]
+                touched = [o for o in ins.operands if _regs(o) & dst]
+                if ins.mfma and ins.operands[0] == code[i].operands[0]:
+                    assert not any(_regs(o) & dst for o in ins.operands[1:3]), (name, hex(ins.addr))
+                else:
+                    assert not touched, (name, hex(code[i].addr), ins.op, ins.operands)
+                if ins.op == "s_endpgm":
+                    continue
+                if ins.target is not None:
+                    todo.append((index[ins.target], left - 1))
+                if ins.op != "s_branch":
+                    todo.append((at + 1, left - ins.states))
+            sources, at, left = _regs(code[i].operands[1]) | _regs(code[i].operands[2]) | dst, i - 1, 2
+            while left > 0:
+                ins = code[at]
+                if ins.op.startswith("v_") and not ins.mfma and not ins.op.startswith("v_cmp"):
+                    assert not _regs(ins.operands[0]) & sources, (name, hex(code[i].addr), ins.op, ins.operands)
+                left, at = left - ins.states, at - 1
