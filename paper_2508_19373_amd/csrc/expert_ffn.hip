@@ -304,8 +304,8 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
   return walk < tiled;
 }
 
-// Row-block height of the tiled kernels for a call without tall row blocks (tall_blocks_allowed comes first: of the
-// two bands below it leaves the lower one): 160 (the one-height list) or 256.
+// Row-block height of the tiled kernels for a call without tall row blocks (tall_blocks_allowed comes first: it takes
+// the band around 273 rows up to 305, given K extents of 1024): 160 (the one-height list) or 256.
 // The 160-row tiling pays where it saves the second stream of an expert's weights (or a padded
 // 256-row tile) without adding a block: with the rows per expert just below a multiple of 160.
 // Measured, gate/up + down projection in us, 256-row tiling against 160-row tiling, by average rows
@@ -333,13 +333,18 @@ inline bool prefer_even(int est_rows, int n_local, int H, int I_s) {
 // 1667 + 836 / 1463 + 744, 1152: 1714 + 862 / 1569 + 845; its TP=4 slice 2068: 738 + 430 / 693 + 381; counts as a router
 // spreads 4096 tokens 1538 + 780 / 1461 + 735; no remainders at all (1024) 1353 + 675 / 1363 + 675.  Qwen1.5-MoE (60
 // experts, the 160-row tiling before) 256: 262 + 144 / 216 + 123, 286: 262 + 150 / 234 + 134, spread about 273: 258 +
-// 154 / 223 + 144.  Both K extents have to be 1024 at least: on a short walk the larger kernel costs more than it
+// 154 / 223 + 144.  Not in the 160-row tiling's band above 305 rows per expert: from there on most experts have more than
+// the 304 rows of one tall block, so the remainder tiles are back.  160-row / tall: Qwen1.5-MoE 300 255 + 151 / 252 + 154,
+// 320 285 + 169 / 295 + 173, 330 298 + 169 / 311 + 193; Qwen2-57B 300 794 + 467 / 790 + 461, 310 840 + 505 / 874 + 516, 320
+// 899 + 510 / 943 + 564, 340 (256-row before) 1015 + 617 / 1000 + 595; its EP=2 shard 310 423 + 249 / 456 + 263.  Both K extents have to be 1024 at least: on a short walk the larger kernel costs more than it
 // saves (8 and 16 k-tiles, 8 experts of 932 rows each: layer 81 -> 87 us).  A tall block addresses its operands with
 // 32-bit byte offsets from its first row, so 304 rows of either K extent have to fit.
 bool tall_blocks_allowed(int est_rows, int n_local, int H, int I_s) {
   constexpr uint64_t kMaxK = gg::kBufBytes / (2 * (256 + 16 * gg::kMaxExtra));
   if ((uint64_t)H > kMaxK || (uint64_t)I_s > kMaxK) return false;
-  return (double)est_rows / n_local >= 150.0 && H >= 1024 && I_s >= 1024;
+  const double avg = (double)est_rows / n_local;
+  if (avg > 305.0 && prefer_even(est_rows, n_local, H, I_s)) return false;
+  return avg >= 150.0 && H >= 1024 && I_s >= 1024;
 }
 
 int tiled_block_rows(int cap_rows, int est_rows, int n_local, int H, int I_s) {

@@ -181,6 +181,17 @@ def test_tile_rows_rule():
     assert B.lib().moe_debug_tile_rows(-1, None) == B.MOE_ERR_INVALID_ARG
 
 
+def test_calls_just_below_320_rows_per_expert_keep_the_160_row_tiling():
+    """One tall block holds 304 rows: with 306 to 330 rows on average most experts would have a remainder tile behind it,
+    two blocks of 160 rows hold them all."""
+    for shard in (B.make_shard(60, 60, 0, 2048, 1408, 1408), B.make_shard(64, 64, 0, 3584, 2560, 1280),
+                  B.make_shard(64, 32, 32, 3584, 2560, 2560)):
+        for avg, tall in ((256, True), (304, True), (306, False), (315, False), (330, False), (331, True)):
+            cap = avg * shard.n_experts
+            assert B.moe_debug_tall(cap, shard) == tall, avg
+            assert (B.moe_debug_tile_rows(cap, shard) == 160) == (avg <= 330)
+
+
 def test_tall_row_blocks_only_where_their_offsets_fit_32_bits():
     """A tall block reaches 304 rows of K bf16 values with 32-bit byte offsets from its first row."""
     fits = 0xFFFFFFFF // (2 * 304) // 64 * 64
