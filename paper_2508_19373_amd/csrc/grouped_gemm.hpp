@@ -533,9 +533,14 @@ __global__ __launch_bounds__(256) void grouped_gemm_tall_kernel(
   // after the other, which address any row
   if (cls == 0 && rows.row_src != nullptr) {
     const int end = min(tc.row_end, tc.row0 + 256 + 16 * tc.nx);
-    const int64_t first_far = (int64_t)(kBufBytes / (2u * (uint32_t)K)) * rows.k;  // in assignments, as row_src is
-    bool far = false;
-    for (int r = tc.row0 + (int)(threadIdx.x & 63); r < end; r += 64) far |= rows.row_src[r] >= first_far;
+    int32_t a[5], last = 0;  // assignments a of 304 rows, all loads in flight together
+    static_assert(256 + 16 * kMaxExtra <= 5 * 64, "a block's rows");
+#pragma unroll
+    for (int i = 0; i < 5; ++i) a[i] = rows.row_src[min(tc.row0 + i * 64 + (int)(threadIdx.x & 63), end - 1)];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) last = max(last, a[i]);
+    // (a / k + 1) * 2 K > kBufBytes, without the divisions (from the last row that fits on it may say so already)
+    const bool far = (uint64_t)((uint32_t)last + (uint32_t)rows.k) * ((uint32_t)K * 2u) > (uint64_t)kBufBytes * rows.k;
     if (__any(far)) {
       tc.row_end = end;
       cls = 2;

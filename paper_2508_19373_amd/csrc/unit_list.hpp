@@ -48,8 +48,9 @@ __host__ __device__ inline RowBlocks row_blocks(int rows, bool pad_low, bool tal
   const int q = rows >> 8, r = rows & 255;
   if (tall && r > 0 && r <= kMaxTallRemainder && r <= q * 16 * (q == 1 ? kMaxExtra : 1)) {
     rb.n256 = q;
-    rb.nx = r <= q * 16 ? 1 : (r <= q * 32 ? 2 : 3);
-    rb.nt = (r + rb.nx * 16 - 1) / (rb.nx * 16);
+    const int sixteens = (r + 15) >> 4;  // (no division: every workgroup of the kernels comes through here)
+    rb.nx = q == 1 ? sixteens : 1;
+    rb.nt = q == 1 ? 1 : sixteens;
     return rb;
   }
   const int pad = (q > 0 || pad_low) ? 128 : 192;  // remainders above this become a 256-row block

@@ -110,7 +110,7 @@ __device__ inline WaveRouting wave_routing(const int32_t* __restrict__ expert_of
       if (j < w.chunks) {
         const RowBlocks rb = row_blocks(w.rows[j], false);
         const unsigned long long b128 = __ballot(rb.n128 != 0), b64 = __ballot(rb.n64 != 0),
-                                 dealt = __ballot(row_blocks(w.rows[j], true, true).nt > 0);
+                                 dealt = __ballot(row_blocks(w.rows[j], true, true).nx > 0);
         t128 += __popcll(b128 & ~b64);
         t64 += __popcll(b64 & ~b128);
         both += __popcll(b128 & b64);
