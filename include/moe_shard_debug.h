@@ -83,18 +83,23 @@ int32_t moe_debug_down_slices(const int32_t* expert_offsets, int32_t cap_rows, c
 #define MOE_DEBUG_DEVICE_INTS 9
 
 /*
- * Whether the tiled kernels of moe_expert_ffn may give an expert's last rows to its 256-row blocks for
- * (cap_rows, shard), 16, 32 or 48 rows to a block (a remainder tile of their own would stream the
+ * Which GEMMs of moe_expert_ffn, where they run tiled, launch the kernel that may give an expert's last rows to its
+ * 256-row blocks, 16, 32 or 48 rows to a block (a remainder tile of their own would stream the
  * expert's weights once more; "Generative Inference": prefill is bound by compute as long as weights are read
- * once): 1 or 0, or a negative MOE_ERR_* code.  Calls for which this is 1 run the work lists of
- * moe_debug_tall_units, the others those of moe_debug_gemm_units, moe_debug_even_units and moe_debug_down_slices.
+ * once): MOE_DEBUG_TALL_* bits, or a negative MOE_ERR_* code.  Those run the work lists of moe_debug_tall_units (which
+ * decide from the routing whether there are tall blocks), the others those of moe_debug_gemm_units, moe_debug_even_units
+ * and moe_debug_down_slices.  Decided per GEMM from what the call expects: the K extents, the
+ * rows per expert, and whether their list would have tall blocks for a routing with the expected spread.
  */
+#define MOE_DEBUG_TALL_GATEUP 1    /* gate/up projection */
+#define MOE_DEBUG_TALL_DOWN 2      /* down projection with fp32 y_perm (and its workspace) */
+#define MOE_DEBUG_TALL_DOWN_BF16 4 /* down projection with bf16 y_perm */
 int32_t moe_debug_tall(int32_t cap_rows, const moe_shard_t* shard);
 
 /*
  * The work lists of such calls: for max_slices == 0 the plain list (gate/up projection, bf16 down
  * projection), for max_slices >= 1 the list of a down projection of nk k-tiles that may be cut along K into up to
- * that many slices.  Launches that do not fill the chip have no tall blocks in them.
+ * that many slices.  Launches that would not end sooner for it have no tall blocks in them.
  * units  [max_units][MOE_DEBUG_DEVICE_INTS] int32 HOST, records as moe_debug_device_units writes them (heights
  *        256 to 304, 128, 64)
  * Returns the grid size, or a negative MOE_ERR_* code.

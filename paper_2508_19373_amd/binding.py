@@ -39,6 +39,7 @@ DEBUG_UNIT_INTS = 5
 DEBUG_SLICE_INTS = 8
 DEBUG_DEVICE_INTS = 9
 DEBUG_TALL = 64
+DEBUG_TALL_GATEUP, DEBUG_TALL_DOWN, DEBUG_TALL_DOWN_BF16 = 1, 2, 4
 
 
 class MoeShard(ctypes.Structure):
@@ -252,12 +253,17 @@ def moe_debug_tile_rows(cap_rows, shard: MoeShard) -> int:
     return int(n)
 
 
-def moe_debug_tall(cap_rows, shard: MoeShard) -> bool:
-    """Host-only: whether the tiled kernels may give an expert's last rows to its 256-row blocks."""
+def moe_debug_tall_gemms(cap_rows, shard: MoeShard) -> int:
+    """Host-only: the GEMMs whose tiled kernel may give an expert's last rows to its 256-row blocks, DEBUG_TALL_* bits."""
     n = lib().moe_debug_tall(cap_rows, ctypes.byref(shard))
     if n < 0:
         raise MoeError("moe_debug_tall", n)
-    return bool(n)
+    return int(n)
+
+
+def moe_debug_tall(cap_rows, shard: MoeShard) -> bool:
+    """Whether any GEMM's does."""
+    return moe_debug_tall_gemms(cap_rows, shard) != 0
 
 
 def _max_device_units(cap_rows, n_local, n_col_blocks):

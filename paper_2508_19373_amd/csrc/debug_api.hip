@@ -82,10 +82,11 @@ extern "C" int32_t moe_debug_tall(int32_t cap_rows, const moe_shard_t* shard) {
   if (cap_rows < 0 || shard == nullptr) return MOE_ERR_INVALID_ARG;
   if (shard->n_experts < 1 || shard->n_local_experts < 1 || shard->n_local_experts > shard->n_experts)
     return MOE_ERR_INVALID_ARG;
-  return moe::tall_blocks_allowed(moe::expected_rows(cap_rows, shard), shard->n_local_experts, shard->hidden,
-                                  shard->inter_slice)
-             ? 1
-             : 0;
+  static_assert(moe::kTallGateUp == MOE_DEBUG_TALL_GATEUP && moe::kTallDown == MOE_DEBUG_TALL_DOWN &&
+                    moe::kTallDownBf16 == MOE_DEBUG_TALL_DOWN_BF16,
+                "the header's names");
+  return moe::tall_gemms(cap_rows, moe::expected_rows(cap_rows, shard), shard->n_local_experts, shard->hidden,
+                         shard->inter_slice, moe::kTallGateUp | moe::kTallDown | moe::kTallDownBf16);
 }
 
 extern "C" int32_t moe_debug_tall_units(const int32_t* expert_offsets, int32_t n_local, int32_t cap_rows,

@@ -35,48 +35,91 @@ inline double planned_rows_hi(int cap_rows, int est_rows, int n_local) {
   return avg + 2.0 * sqrt(avg);
 }
 
+// Row-block height of the tiled kernels for a call without tall row blocks (tall_blocks_allowed comes first: it takes
+// the band around 273 rows up to 305, given K extents of 1024): 160 (the one-height list) or 256.
+// The 160-row tiling pays where it saves the second stream of an expert's weights (or a padded
+// 256-row tile) without adding a block: with the rows per expert just below a multiple of 160.
+// Measured, gate/up + down projection in us, 256-row tiling against 160-row tiling, by average rows
+// per expert: Qwen1.5-MoE (60 experts) 102: 243 / 243; 136: 275 / 254; 170: 296 / 359; 204: 301 / 392;
+// 238: 323 / 397; 273: 441 / 402; 307: 488 / 435; 341: 497 / 522; 409: 512 / 534; Qwen2-57B (64
+// experts) 128: 830 / 753; 192: 895 / 1141; 256: 1206 / 1172; 320: 1593 / 1408; 384: 1518 / 1645.
+// With 30 local experts (273 rows each) the two are equal, with 8 large experts the 160-row tiling
+// loses a fifth, hence the expert count in the rule.
+#ifndef MOE_EVEN_MODE
+#define MOE_EVEN_MODE 0  // 1: always 160, 2: never (tuning builds)
+#endif
+inline bool prefer_even(int est_rows, int n_local, int H, int I_s) {
+  (void)H;
+  (void)I_s;
+  if (MOE_EVEN_MODE != 0) return MOE_EVEN_MODE == 1;
+  const double avg = (double)est_rows / n_local;
+  return n_local >= 32 && ((avg >= 115.0 && avg <= 148.0) || (avg >= 255.0 && avg <= 330.0));
+}
+
+// Whether a tiled call's full row blocks may take their expert's remainder (the kernel then does so in launches
+// that fill the chip).  From 150 rows per expert on: below, hardly an expert has a full block.  Measured, gate/up +
+// down projection in us on one box, without / with: Mixtral (8 experts) 1053 rows each 1653 + 833 / 1419 + 722, 1088:
+// 1667 + 836 / 1463 + 744, 1152: 1714 + 862 / 1569 + 845; its TP=4 slice 2068: 738 + 430 / 693 + 381; counts as a router
+// spreads 4096 tokens 1538 + 780 / 1461 + 735; no remainders at all (1024) 1353 + 675 / 1363 + 675.  Qwen1.5-MoE (60
+// experts, the 160-row tiling before) 256: 262 + 144 / 216 + 123, 286: 262 + 150 / 234 + 134, spread about 273: 258 +
+// 154 / 223 + 144.  Not in the 160-row tiling's band above 305 rows per expert: from there on most experts have more than
+// the 304 rows of one tall block, so the remainder tiles are back.  160-row / tall: Qwen1.5-MoE 300 255 + 151 / 252 + 154,
+// 320 285 + 169 / 295 + 173, 330 298 + 169 / 311 + 193; Qwen2-57B 300 794 + 467 / 790 + 461, 310 840 + 505 / 874 + 516, 320
+// 899 + 510 / 943 + 564, 340 (256-row before) 1015 + 617 / 1000 + 595; its EP=2 shard 310 423 + 249 / 456 + 263.  Both K extents have to be 1024 at least: on a short walk the larger kernel costs more than it
+// saves (8 and 16 k-tiles, 8 experts of 932 rows each: layer 81 -> 87 us).  A tall block addresses its operands with
+// 32-bit byte offsets from its first row, so 304 rows of either K extent have to fit.
+bool tall_blocks_allowed(int est_rows, int n_local, int H, int I_s) {
+  constexpr uint64_t kMaxK = gg::kBufBytes / (2 * (256 + 16 * gg::kMaxExtra));
+  if ((uint64_t)H > kMaxK || (uint64_t)I_s > kMaxK) return false;
+  const double avg = (double)est_rows / n_local;
+  if (avg > 305.0 && prefer_even(est_rows, n_local, H, I_s)) return false;
+  return avg >= 150.0 && H >= 1024 && I_s >= 1024;
+}
+
 // Whether a GEMM's list is expected to have tall blocks: the list itself, for a routing that spreads as a balanced router does
-// (1.7 sigma to either side of the average) or, on an expert-parallel shard, for one that got what it is planned for.
+// (the experts at the quantiles of a normal distribution) or, on an expert-parallel shard, for one that got what it is
+// planned for.
 // A launch without any takes the plain kernel: the one with tall blocks costs it a few per cent (shared expert of 333
 // rows, 88 tiles: gate/up 53.1 -> 56.6 us; 8 experts of 160 rows, down projection 228 -> 233; 4 of 600 rows 317 -> 328).
 bool expects_tall_blocks(int cap_rows, int est_rows, int n_local, int ncb, int nk, bool sliced) {
   const bool exact = n_local == 1 && est_rows == cap_rows;  // one expert that takes every row
   const double avg = (double)est_rows / n_local;
   int32_t offsets[MOE_MAX_EXPERTS + 1];
-  auto tall = [&](double rows, double spread) {
+  auto tall = [&](double rows, bool cut) {
     double at = 0.0;
     offsets[0] = 0;
     for (int e = 0; e < n_local; ++e) {
-      at += rows + spread * sqrt(rows) * ((2 * e + 1.0) / n_local - 1.0);
+      const double u = (2 * e + 1.0) / n_local - 1.0, u2 = u * u, u8 = u2 * u2 * u2 * u2;
+      at += rows + sqrt(rows) * u * (1.25 + 0.2 * u2 + 0.95 * u8);  // normal quantile, within 0.2 for up to 64 experts
       offsets[e + 1] = (int32_t)fmin(at + 0.5, 1 << 30);
     }
-    return gg::count_tiles(offsets, n_local, ncb, sliced ? gg::sliced_pad_from(nk) : gg::kPadLowTiles, true, nk,
-                           sliced ? gg::max_k_slices(nk * gg::BK) : 0)
+    return gg::count_tiles(offsets, n_local, ncb, cut ? gg::sliced_pad_from(nk) : gg::kPadLowTiles, true, nk,
+                           cut ? gg::max_k_slices(nk * gg::BK) : 0)
         .tall;
   };
-  if (exact) return tall(avg, 0.0);
-  return tall(avg, 1.7) ||
-         (est_rows < cap_rows && tall(fmin(2.0 * avg, (double)cap_rows / n_local), 1.7));
+  // (not for a finer cut either: the lookup costs it more, shared expert of 4100 rows, down projection 109 us plain, 116)
+  if (exact) return !sliced && tall(avg, false);
+  // (a shard's planned share not for a finer cut, which hangs on a tile more or less: 4 of 8 experts of 256 rows, 187 us plain, 199)
+  return tall(avg, sliced) || (est_rows < cap_rows && tall(fmin(2.0 * avg, (double)cap_rows / n_local), false));
 }
 
-// Prefill-sized groups: LDS-DMA kernel, 256-column tiles of 256 / 128 / 64 rows.  `tall`: full row blocks may take
-// their expert's remainder.
+// Prefill-sized groups: LDS-DMA kernel, 256-column tiles of 256 / 128 / 64 rows, or the kernel whose full row blocks may take
+// their expert's remainder (tall_gemms).
 template <int BN>
-hipError_t launch_pair_dlds(bool allow_tall, const void* x_perm, RowMap rows, const int32_t* expert_offsets, int cap_rows, int est_rows, int n_local, int H,
+hipError_t launch_pair_dlds(const void* x_perm, RowMap rows, const int32_t* expert_offsets, int cap_rows, int est_rows, int n_local, int H,
                             int I_s, const void* w_gate, const void* w_up, const void* w_down, void* h_ws,
                             void* y_perm, void* workspace, uint32_t flags, hipStream_t stream) {
   const bool y_bf16 = (flags & MOE_Y_PERM_BF16) != 0;
   const dim3 block(256);
-  auto tall_for = [&](int ncb, int nk, bool sliced) {
-    return allow_tall && expects_tall_blocks(cap_rows, est_rows, n_local, ncb, nk, sliced);
-  };
+  static_assert(BN == 256, "tall_gemms counts column blocks of 256 weight rows");
   const uint16_t* xp = static_cast<const uint16_t*>(x_perm);
   uint16_t* hw = static_cast<uint16_t*>(h_ws);
   auto grid_for = [&](int ncb) { return dim3((unsigned)gg::max_grid(cap_rows, n_local, ncb)); };
   if (!(flags & MOE_FFN_SKIP_GATEUP)) {
     const int ncb = (I_s + BN / 2 - 1) / (BN / 2);
-    const auto kernel = tall_for(ncb, H / gg::BK, false) ? gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>
-                             : gg::grouped_gemm_dlds_kernel<BN, true, uint16_t, false>;
+    const auto kernel = tall_gemms(cap_rows, est_rows, n_local, H, I_s, kTallGateUp)
+                            ? gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>
+                            : gg::grouped_gemm_dlds_kernel<BN, true, uint16_t, false>;
     hipLaunchKernelGGL(kernel, grid_for(ncb), block, 0, stream, xp,
                        expert_offsets, n_local, cap_rows, static_cast<const uint16_t*>(w_gate),
                        static_cast<const uint16_t*>(w_up), I_s, H, hw, ncb, static_cast<uint16_t*>(nullptr), 0, rows);
@@ -87,7 +130,8 @@ hipError_t launch_pair_dlds(bool allow_tall, const void* x_perm, RowMap rows, co
   const int ncb = (H + BN - 1) / BN;
   const gg::SlicePlan sp =
       y_bf16 || workspace == nullptr ? gg::SlicePlan{1, 0} : gg::slice_plan(cap_rows, ncb, I_s);
-  const bool tall = tall_for(ncb, I_s / gg::BK, sp.max_slices > 1);
+  const bool tall =
+      tall_gemms(cap_rows, est_rows, n_local, H, I_s, y_bf16 || workspace == nullptr ? kTallDownBf16 : kTallDown) != 0;
   if (y_bf16) {
     const auto kernel = tall ? gg::grouped_gemm_tall_kernel<BN, false, uint16_t, false>
                              : gg::grouped_gemm_dlds_kernel<BN, false, uint16_t, false>;
@@ -304,47 +348,20 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
   return walk < tiled;
 }
 
-// Row-block height of the tiled kernels for a call without tall row blocks (tall_blocks_allowed comes first: it takes
-// the band around 273 rows up to 305, given K extents of 1024): 160 (the one-height list) or 256.
-// The 160-row tiling pays where it saves the second stream of an expert's weights (or a padded
-// 256-row tile) without adding a block: with the rows per expert just below a multiple of 160.
-// Measured, gate/up + down projection in us, 256-row tiling against 160-row tiling, by average rows
-// per expert: Qwen1.5-MoE (60 experts) 102: 243 / 243; 136: 275 / 254; 170: 296 / 359; 204: 301 / 392;
-// 238: 323 / 397; 273: 441 / 402; 307: 488 / 435; 341: 497 / 522; 409: 512 / 534; Qwen2-57B (64
-// experts) 128: 830 / 753; 192: 895 / 1141; 256: 1206 / 1172; 320: 1593 / 1408; 384: 1518 / 1645.
-// With 30 local experts (273 rows each) the two are equal, with 8 large experts the 160-row tiling
-// loses a fifth, hence the expert count in the rule.
-#ifndef MOE_EVEN_MODE
-#define MOE_EVEN_MODE 0  // 1: always 160, 2: never (tuning builds)
-#endif
-inline bool prefer_even(int est_rows, int n_local, int H, int I_s) {
-  (void)H;
-  (void)I_s;
-  if (MOE_EVEN_MODE != 0) return MOE_EVEN_MODE == 1;
-  const double avg = (double)est_rows / n_local;
-  return n_local >= 32 && ((avg >= 115.0 && avg <= 148.0) || (avg >= 255.0 && avg <= 330.0));
-}
-
 }  // namespace
 
-// Whether a tiled call's full row blocks may take their expert's remainder (the kernel then does so in launches
-// that fill the chip).  From 150 rows per expert on: below, hardly an expert has a full block.  Measured, gate/up +
-// down projection in us on one box, without / with: Mixtral (8 experts) 1053 rows each 1653 + 833 / 1419 + 722, 1088:
-// 1667 + 836 / 1463 + 744, 1152: 1714 + 862 / 1569 + 845; its TP=4 slice 2068: 738 + 430 / 693 + 381; counts as a router
-// spreads 4096 tokens 1538 + 780 / 1461 + 735; no remainders at all (1024) 1353 + 675 / 1363 + 675.  Qwen1.5-MoE (60
-// experts, the 160-row tiling before) 256: 262 + 144 / 216 + 123, 286: 262 + 150 / 234 + 134, spread about 273: 258 +
-// 154 / 223 + 144.  Not in the 160-row tiling's band above 305 rows per expert: from there on most experts have more than
-// the 304 rows of one tall block, so the remainder tiles are back.  160-row / tall: Qwen1.5-MoE 300 255 + 151 / 252 + 154,
-// 320 285 + 169 / 295 + 173, 330 298 + 169 / 311 + 193; Qwen2-57B 300 794 + 467 / 790 + 461, 310 840 + 505 / 874 + 516, 320
-// 899 + 510 / 943 + 564, 340 (256-row before) 1015 + 617 / 1000 + 595; its EP=2 shard 310 423 + 249 / 456 + 263.  Both K extents have to be 1024 at least: on a short walk the larger kernel costs more than it
-// saves (8 and 16 k-tiles, 8 experts of 932 rows each: layer 81 -> 87 us).  A tall block addresses its operands with
-// 32-bit byte offsets from its first row, so 304 rows of either K extent have to fit.
-bool tall_blocks_allowed(int est_rows, int n_local, int H, int I_s) {
-  constexpr uint64_t kMaxK = gg::kBufBytes / (2 * (256 + 16 * gg::kMaxExtra));
-  if ((uint64_t)H > kMaxK || (uint64_t)I_s > kMaxK) return false;
-  const double avg = (double)est_rows / n_local;
-  if (avg > 305.0 && prefer_even(est_rows, n_local, H, I_s)) return false;
-  return avg >= 150.0 && H >= 1024 && I_s >= 1024;
+// The GEMMs of `which` (kTall*) that run the kernel with tall row blocks.
+int tall_gemms(int cap_rows, int est_rows, int n_local, int H, int I_s, int which) {
+  if (!tall_blocks_allowed(est_rows, n_local, H, I_s)) return 0;
+  int out = 0;
+  if ((which & kTallGateUp) && expects_tall_blocks(cap_rows, est_rows, n_local, (I_s + 127) / 128, H / gg::BK, false))
+    out |= kTallGateUp;
+  const int ncb = (H + 255) / 256, nk = I_s / gg::BK;
+  if ((which & kTallDown) &&
+      expects_tall_blocks(cap_rows, est_rows, n_local, ncb, nk, gg::slice_plan(cap_rows, ncb, I_s).max_slices > 1))
+    out |= kTallDown;
+  if ((which & kTallDownBf16) && expects_tall_blocks(cap_rows, est_rows, n_local, ncb, nk, false)) out |= kTallDownBf16;
+  return out;
 }
 
 int tiled_block_rows(int cap_rows, int est_rows, int n_local, int H, int I_s) {
@@ -386,14 +403,13 @@ hipError_t launch_expert_ffn(const void* x_perm, RowMap rows, const int32_t* exp
   if (cap_rows == 0) return hipSuccess;
   // each GEMM picks its kernel family on its own: h is row-major bf16 for both
   const int mt = decode_mt(cap_rows, est_rows, n_local);
-  const bool tall = tall_blocks_allowed(est_rows, n_local, H, I_s);
-  const bool even = !tall && prefer_even(est_rows, n_local, H, I_s);
+  const bool even = !tall_blocks_allowed(est_rows, n_local, H, I_s) && prefer_even(est_rows, n_local, H, I_s);
   auto run = [&](bool walk, uint32_t f) {
     if (!walk && even)
       return launch_pair_even(x_perm, rows, expert_offsets, cap_rows, n_local, H, I_s, w_gate, w_up, w_down, h_ws,
                               y_perm, f, stream);
     if (!walk)
-      return launch_pair_dlds<256>(tall, x_perm, rows, expert_offsets, cap_rows, est_rows, n_local, H, I_s, w_gate, w_up, w_down,
+      return launch_pair_dlds<256>(x_perm, rows, expert_offsets, cap_rows, est_rows, n_local, H, I_s, w_gate, w_up, w_down,
                                    h_ws, y_perm, workspace, f, stream);
     if (mt == 1)
       return launch_pair_decode<1>(x_perm, rows, expert_offsets, cap_rows, n_local, H, I_s, w_gate, w_up, w_down, h_ws,

@@ -66,8 +66,10 @@ size_t ffn_workspace_bytes(int cap_rows, int est_rows, int n_local, int H, int I
 void ffn_plan(int cap_rows, int est_rows, int n_local, int H, int I_s, int32_t out[4]);
 // Row-block height of the tiled kernels for such a call (256, or 160 for the one-height work list).
 int tiled_block_rows(int cap_rows, int est_rows, int n_local, int H, int I_s);
-// Whether full row blocks of the tiled kernels may take their expert's remainder in such a call.
-bool tall_blocks_allowed(int est_rows, int n_local, int H, int I_s);
+// Which GEMMs of such a call, when tiled, run the kernel whose full row blocks may take their expert's remainder: those
+// of `which`, MOE_DEBUG_TALL_*.
+constexpr int kTallGateUp = 1, kTallDown = 2, kTallDownBf16 = 4;
+int tall_gemms(int cap_rows, int est_rows, int n_local, int H, int I_s, int which);
 int expected_rows(int cap_rows, const moe_shard_t* shard);
 hipError_t launch_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w, int T, int k, int H,
                           const void* y_shared, const void* x, const float* w_shared_gate, void* y_out,

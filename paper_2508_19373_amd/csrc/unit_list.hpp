@@ -91,8 +91,7 @@ __host__ __device__ inline int sliced_pad_from(int nk) { return nk >= 48 ? 128 :
 //   - the tiles take a round of 256 fewer, or there are so many rounds (three and more) that the streamed weights are
 //     what counts.  The full blocks have to occupy three quarters of the chip themselves: in a launch of fewer
 //     the remainder tiles run beside them on units that would idle;
-//   - or a K-sliced launch of up to 128 tiles, all of which run as slices, is cut finer than the plain list (which
-//     has 128 tiles at least, pad_low).
+//   - or a K-sliced launch of up to 128 tiles, all of which run as slices, is cut finer than the plain list.
 // Measured on 1050 random launches of one to 64 experts with tall blocks (two GEMMs, 21 shard shapes, each list's time): geometric mean over
 // the faster of the two lists, gate/up 1.040 with remainder tiles always, 1.013 dealt wherever there are 256 tiles,
 // 1.007 with this rule; down projection 1.025, 1.035, 1.010.  Single launches, us, remainder tiles / dealt: down projection of 8
@@ -104,13 +103,14 @@ __host__ __device__ inline int dealt_volume(const ClassCounts& c) {
   return c.n[0] * (256 + kMaxExtra * 16) + c.n[1] * 128 + c.n[2] * 64;
 }
 __host__ __device__ inline bool dealing_pays(const ClassCounts& plain, const ClassCounts& dealt, int nk, int max_slices) {
-  const int tiles = dealt.total();
+  const int tiles = dealt.total(), plain_tiles = plain.total();
+  if (tiles == plain_tiles) return false;  // nothing to deal out
   if (max_slices > 1 && tiles <= 128) {  // (the estimate of fit_slices, for the most slices only: it runs in every workgroup)
-    const int volume = dealt_volume(dealt), uncut = plain.total() <= 128 ? 2 : 1;
+    const int volume = dealt_volume(dealt), before = plain_tiles <= 128 ? min(256 / plain_tiles, max_slices) : 1;
     const int s = min(min(256 / tiles, max_slices), 1 + 65536 / volume);
-    return s > uncut && nk * 16 / s + 64 + volume * (s + 1) / 275 < nk * 16 / uncut;
+    return s > before && nk * 16 / s + 64 + volume * (s + 1) / 275 < nk * 16 / before;
   }
-  return dealt.n[0] >= kDealtTiles && (tiles >= kDealtManyTiles || (tiles + 255) / 256 < (plain.total() + 255) / 256);
+  return dealt.n[0] >= kDealtTiles && (tiles >= kDealtManyTiles || (tiles + 255) / 256 < (plain_tiles + 255) / 256);
 }
 
 // nk, max_slices: k-tiles and most K slices of a sliced launch (0 slices: a launch that is not cut), for allow_tall only.

@@ -284,11 +284,11 @@ def test_expert_ffn_even_row_blocks(H, I_s, lo, hi, gather):
 @pytest.mark.parametrize("H,I_s,n,lo,hi,gather", [
     (1024, 1024, 64, 240, 340, False),   # one block per expert, 0 to 3 x 16 rows more, or a remainder tile
     (1024, 1024, 40, 300, 1300, True),   # up to five blocks, the first ones tall; rows read through row_src
-    (1024, 1088, 40, 257, 560, False),   # ragged last column block; down projection may be cut along K (17 k-tiles)
+    (1024, 1088, 40, 257, 280, False),   # ragged last column block, 17 k-tiles in the down projection
     (2048, 1792, 4, 2049, 2500, True),   # few experts: the plain loops find the tiles
 ])
 def test_expert_ffn_tall_row_blocks(H, I_s, n, lo, hi, gather):
-    """Launches that fill the chip give an expert's last rows to its 256-row blocks."""
+    """Launches that end sooner for it give an expert's last rows to its 256-row blocks (here: the gate/up projection)."""
     rng = np.random.default_rng(H + n)
     counts = rng.integers(lo, hi + 1, n)
     counts[:4] = (lo // 256 * 256 + 256) + np.array([0, 1, 16, 33])

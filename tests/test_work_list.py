@@ -281,3 +281,19 @@ def test_remainders_are_dealt_out_only_where_the_launch_ends_sooner(rows, ncb, n
     launch up to a third longer (half the chip idle beside tiles of 304 rows)."""
     units = B.moe_debug_tall_units(_offsets(rows), sum(rows), ncb, nk, max_slices)
     assert bool((units[:, 0] > 256).any()) == tall
+
+
+def test_debug_tall_names_the_gemms_that_run_the_kernel_with_tall_blocks():
+    """Decided per GEMM, by the function the launcher asks."""
+    up, down, down16 = B.DEBUG_TALL_GATEUP, B.DEBUG_TALL_DOWN, B.DEBUG_TALL_DOWN_BF16
+    full, tp4 = B.make_shard(8, 8, 0, 4096, 14336, 14336), B.make_shard(8, 8, 0, 4096, 14336, 3584)
+    shared = B.make_shard(1, 1, 0, 2048, 5632, 5632)
+    assert B.moe_debug_tall_gemms(2 * 4096, full) == up | down | down16
+    assert B.moe_debug_tall_gemms(8 * 300, full) == up          # down: 128 tall tiles on 256 compute units
+    assert B.moe_debug_tall_gemms(8 * 300, tp4) == 0            # nor does a round of the gate/up projection go away
+    assert B.moe_debug_tall_gemms(8 * 160, full) == 0           # no expert with a full block
+    assert B.moe_debug_tall_gemms(8 * 160, B.make_shard(8, 4, 0, 4096, 14336, 14336)) & down == 0
+    assert B.moe_debug_tall_gemms(333, shared) == 0             # 88 tiles
+    assert B.moe_debug_tall_gemms(4096, shared) == 0            # no remainder (one expert that takes every row)
+    assert B.moe_debug_tall_gemms(4100, shared) == 0            # 128 tiles in two slices each would be no faster than 136
+    assert B.moe_debug_tall_gemms(300, B.make_shard(1, 1, 0, 1024, 1024, 1024)) == 0
