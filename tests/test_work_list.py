@@ -297,3 +297,29 @@ def test_debug_tall_names_the_gemms_that_run_the_kernel_with_tall_blocks():
     assert B.moe_debug_tall_gemms(4096, shared) == 0            # no remainder (one expert that takes every row)
     assert B.moe_debug_tall_gemms(4100, shared) == 0            # 128 tiles in two slices each would be no faster than 136
     assert B.moe_debug_tall_gemms(300, B.make_shard(1, 1, 0, 1024, 1024, 1024)) == 0
+
+
+def test_a_sample_of_edge_rows_comes_from_the_lists_that_run():
+    """Rows in tiles cut along K: of the list with tall blocks where the call runs that, whatever the other lists say."""
+    import sampling
+    rng = np.random.default_rng(0)
+    qwen, n_cut = B.make_shard(60, 60, 0, 2048, 1408, 1408), 0
+    for _ in range(8):
+        offs = _offsets(rng.multinomial(4096 * 4, np.ones(60) / 60))
+        units = B.moe_debug_tall_units(offs, 4096 * 4, 8, 22, B.moe_debug_ffn_plan(4096 * 4, qwen)[3])
+        cut = units[(units[:, 0] > 0) & (units[:, 5] >= 1)]
+        rows, n = sampling.edge_rows(offs, 4096 * 4, qwen)
+        assert n == len(cut)
+        for h, e, row0, row_end in cut[:, :4]:
+            assert ((rows >= row0) & (rows < min(row0 + h, row_end))).any()
+        tall = units[(units[:, 0] > 256) & (units[:, 4] == 0)]
+        for h, e, row0, row_end in tall[:, :4]:                 # the first of a tall tile's extra rows, and its last row
+            assert {min(int(row0) + 256, int(row_end) - 1), int(min(row0 + h, row_end)) - 1} <= set(rows.tolist())
+        n_cut += len(cut)
+    assert n_cut > 0
+    # one 160-row and one plain call
+    assert sampling.edge_rows(_offsets([320] * 60), 320 * 60, qwen)[1] == 0
+    mix = B.make_shard(8, 8, 0, 4096, 14336, 14336)
+    offs = _offsets([180, 190, 150, 160, 130, 170, 141, 200])
+    assert sampling.edge_rows(offs, int(offs[-1]), mix)[1] == sum(
+        1 for u in B.moe_debug_down_slices(offs, int(offs[-1]), mix, with_units=True)[1] if u[0] > 0 and u[4] >= 1)
