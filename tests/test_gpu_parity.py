@@ -315,6 +315,32 @@ def test_expert_ffn_tall_row_blocks(H, I_s, n, lo, hi, gather):
     assert np.all(np.isnan(yb[R:])) and _rel(yb[:R], ref) < REL_L2
 
 
+@pytest.mark.parametrize("n,H,I_s,lo,hi,cut", [
+    (10, 2048, 3072, 262, 300, True),    # 80 tall tiles, every one cut along K into up to three slices
+    (64, 1024, 1024, 257, 275, False),   # one round of tall tiles, none cut
+])
+def test_expert_ffn_tall_row_blocks_of_the_down_projection(n, H, I_s, lo, hi, cut):
+    """Tall tiles of the fp32 down projection: whole ones, and slices of them along K whose partial sums a second kernel
+    adds; the bf16 form of the same calls beside it."""
+    counts = np.random.default_rng(n).integers(lo, hi + 1, n)
+    offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    R = int(offs[-1])
+    cap = R + 3
+    shard = B.make_shard(n, n, 0, H, I_s, I_s)
+    assert B.moe_debug_tall_gemms(cap, shard) & B.DEBUG_TALL_DOWN
+    units = B.moe_debug_tall_units(offs, cap, H // 256, I_s // 64, B.moe_debug_ffn_plan(cap, shard)[3])
+    tall = units[units[:, 0] > 256]
+    assert len(tall) > 0 and (tall[:, 5].max() >= 2) == cut and (tall[:, 5] == 0).any()
+    wg, wu, wd = I.make_expert_weights(5, I.MoEShape("f", H, n, 1, I_s, True))
+    xp = I.make_x(3, cap, H)
+    ref = O.expert_ffn(xp[:R], offs, wg, wu, wd)
+    y = _ffn_gpu(xp, offs, shard, wg, wu, wd)
+    assert np.all(np.isnan(y[R:])), "rows past R must not be written"
+    assert _rel(y[:R], ref) < REL_L2 and np.abs(y[:R] - ref).max() < MAX_ABS
+    yb = _ffn_gpu(xp, offs, shard, wg, wu, wd, y_bf16=True)
+    assert np.all(np.isnan(yb[R:])) and _rel(yb[:R], ref) < REL_L2
+
+
 def test_expert_ffn_160_row_blocks():
     """About 130 rows per expert: one or two blocks of 160 rows."""
     n, H, I_s = 64, 512, 320
