@@ -31,9 +31,9 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E
 # (FETCH_SIZE, WRITE_SIZE in KiB per dispatch; see profiles/<workload>_rocprofv3.txt), each scaled by
 # what the same counter reads for a plain 1 GiB device copy: FETCH_SIZE x 2.0, WRITE_SIZE x 1.0.
 MEASURED_TRAFFIC_BYTES = {
-    "mixtral_prefill": (1958763.1 * 2.0 + 232963.1) * 1024,
+    "mixtral_prefill": (1384050.8 * 2.0 + 230272.0) * 1024,
     "mixtral_decode": (936763.1 * 2.0 + 898.7) * 1024,
-    "qwen_prefill": (405805.6 * 2.0 + 45056.0) * 1024,
+    "qwen_prefill": (397214.6 * 2.0 + 45375.3) * 1024,
 }
 
 # measured after the main workload in the same run (`also` in the JSON line): the other target shapes

@@ -56,17 +56,20 @@ inline bool prefer_even(int est_rows, int n_local, int H, int I_s) {
   return n_local >= 32 && ((avg >= 115.0 && avg <= 148.0) || (avg >= 255.0 && avg <= 330.0));
 }
 
-// Whether a tiled call's full row blocks may take their expert's remainder (the kernel then does so in launches
-// that fill the chip).  From 150 rows per expert on: below, hardly an expert has a full block.  Measured, gate/up +
+// Whether a tiled call's full row blocks may take their expert's remainder (where the list then has tall blocks:
+// dealing_pays, expects_tall_blocks).  From 150 rows per expert on: below, hardly an expert has a full block.  Measured, gate/up +
 // down projection in us on one box, without / with: Mixtral (8 experts) 1053 rows each 1653 + 833 / 1419 + 722, 1088:
 // 1667 + 836 / 1463 + 744, 1152: 1714 + 862 / 1569 + 845; its TP=4 slice 2068: 738 + 430 / 693 + 381; counts as a router
-// spreads 4096 tokens 1538 + 780 / 1461 + 735; no remainders at all (1024) 1353 + 675 / 1363 + 675.  Qwen1.5-MoE (60
+// spreads 4096 tokens 1538 + 780 / 1461 + 735.  No remainders at all, when such launches still ran the kernel with tall
+// blocks: 1024 rows 1353 + 675 / 1363 + 675, TP=4 slice 2048 down projection 370 / 383, 2304 gate/up 752 / 760.  Qwen1.5-MoE (60
 // experts, the 160-row tiling before) 256: 262 + 144 / 216 + 123, 286: 262 + 150 / 234 + 134, spread about 273: 258 +
 // 154 / 223 + 144.  Not in the 160-row tiling's band above 305 rows per expert: from there on most experts have more than
 // the 304 rows of one tall block, so the remainder tiles are back.  160-row / tall: Qwen1.5-MoE 300 255 + 151 / 252 + 154,
 // 320 285 + 169 / 295 + 173, 330 298 + 169 / 311 + 193; Qwen2-57B 300 794 + 467 / 790 + 461, 310 840 + 505 / 874 + 516, 320
-// 899 + 510 / 943 + 564, 340 (256-row before) 1015 + 617 / 1000 + 595; its EP=2 shard 310 423 + 249 / 456 + 263.  Both K extents have to be 1024 at least: on a short walk the larger kernel costs more than it
-// saves (8 and 16 k-tiles, 8 experts of 932 rows each: layer 81 -> 87 us).  A tall block addresses its operands with
+// 899 + 510 / 943 + 564, 340 (256-row before) 1015 + 617 / 1000 + 595; its EP=2 shard 310 423 + 249 / 456 + 263.  Both K extents
+// from 1024 on: on a shorter walk the larger kernel costs more than it saves.  H = I_s = 768: 8 experts of 1040 rows 29.5 +
+// 29.2 / 31.2 + 30.6, 16 of 1050 54.1 + 30.3 / 55.4 + 31.5, 64 of 280 68.8 + 41.0 / 63.8 + 38.4 (76.0 + 41.9 in blocks of 160); 1024: 16 of 1050
+// 78.8 + 53.6 / 71.7 + 44.1, 64 of 280 116 + 65 / 106 + 59 (122 + 72).  A tall block addresses its operands with
 // 32-bit byte offsets from its first row, so 304 rows of either K extent have to fit.
 bool tall_blocks_allowed(int est_rows, int n_local, int H, int I_s) {
   constexpr uint64_t kMaxK = gg::kBufBytes / (2 * (256 + 16 * gg::kMaxExtra));

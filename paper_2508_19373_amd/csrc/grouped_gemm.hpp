@@ -501,8 +501,8 @@ __global__ __launch_bounds__(256) void grouped_gemm_dlds_kernel(
 
 // The same GEMM with tall row blocks (RowBlocks in unit_list.hpp), bound: bf16 MFMA at the power limit, like the
 // 256-row tile (1088 rows per expert, four tiles of 272: gate/up 1397 TFLOP/s, four of 256 1411; with remainder tiles
-// 1226).  A kernel of its own: the additional variants would cost the one above registers.  Its 256-row tiles use
-// buffer addressing too (gate/up at 1024 rows per expert 1426 -> 1363 us).
+// 1226).  A kernel of its own: the additional variants would cost the one above registers.  Its 256-row tiles are no
+// faster than that one's (gate/up at 1024 rows per expert 1363 us, there 1353), so a launch without tall blocks runs there.
 template <int BN, bool GATEUP, typename OutT, bool SLICED>
 __global__ __launch_bounds__(256) void grouped_gemm_tall_kernel(
     const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,

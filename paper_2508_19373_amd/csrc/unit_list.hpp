@@ -92,9 +92,10 @@ __host__ __device__ inline int sliced_pad_from(int nk) { return nk >= 48 ? 128 :
 //     what counts.  The full blocks have to occupy three quarters of the chip themselves: in a launch of fewer
 //     the remainder tiles run beside them on units that would idle;
 //   - or a K-sliced launch of up to 128 tiles, all of which run as slices, is cut finer than the plain list.
-// Measured on 1050 random launches of one to 64 experts with tall blocks (two GEMMs, 21 shard shapes, each list's time): geometric mean over
-// the faster of the two lists, gate/up 1.040 with remainder tiles always, 1.013 dealt wherever there are 256 tiles,
-// 1.007 with this rule; down projection 1.025, 1.035, 1.010.  Single launches, us, remainder tiles / dealt: down projection of 8
+// Measured on 1050 random routings of one to 64 experts and 21 shard shapes, each list's time, where the two differ; geometric
+// mean over the faster one: gate/up 1.040 with remainder tiles always, 1.013 dealt wherever there are 256 tiles, 1.007 with
+// this rule; down projection 1.025, 1.035, 1.010.  (768 tiles against 512 and 1024: 1.0069, 1.0079, 1.0082 and 1.0066, 1.0093, 1.0068 on
+// the second half of them; 192 against 256: 1.0080, 1.0158.)  Single launches, us, remainder tiles / dealt: down projection of 8
 // Mixtral experts of 300 rows 381 / 486 (128 tiles of 304 rows and half the chip idle, against 256), of 4 196 / 271; one
 // expert of 2066 rows 272 / 194 (128 tiles in two slices against 144 whole); gate/up of 8 experts of 287 rows (TP=2) 406 / 296.
 constexpr int kDealtTiles = 192, kDealtManyTiles = 768;
