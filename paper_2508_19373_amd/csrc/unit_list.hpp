@@ -119,23 +119,38 @@ __host__ __device__ inline ClassCounts count_tiles(const int32_t* __restrict__ e
                                                    int n_col_blocks, int pad_from = kPadLowTiles, bool allow_tall = false,
                                                    int nk = 0, int max_slices = 0) {
   ClassCounts c = {{0, 0, 0}, false, false};
+  if (allow_tall) {  // both lists in one pass (each reads the offsets with dependent scalar loads)
+    int t256 = 0, t128 = 0, t64 = 0, both = 0, d256 = 0, d128 = 0, d64 = 0;  // both: 128 + 64 rows, or padded to 256
+    for (int e = 0; e < n_local; ++e) {
+      const int rows = expert_offsets[e + 1] - expert_offsets[e];
+      const RowBlocks rb = row_blocks(rows, false);
+      const bool dealt = row_blocks(rows, true, true).nx > 0;
+      t256 += rb.n256;
+      both += rb.n128 & rb.n64;
+      t128 += rb.n128 & ~rb.n64;
+      t64 += rb.n64 & ~rb.n128;
+      d128 += dealt ? rb.n128 : 0;  // (an expert with full blocks has one tile behind them at most)
+      d64 += dealt ? rb.n64 : 0;
+      d256 += dealt && (rb.n128 | rb.n64) == 0 ? 1 : 0;
+    }
+    c.pad_low = (t256 + t128 + t64 + 2 * both) * n_col_blocks >= pad_from;
+    const int p256 = t256 + (c.pad_low ? both : 0), rest = c.pad_low ? 0 : both;
+    c.n[0] = p256 * n_col_blocks;
+    c.n[1] = (t128 + rest) * n_col_blocks;
+    c.n[2] = (t64 + rest) * n_col_blocks;
+    const ClassCounts d = {{(p256 - d256) * n_col_blocks, (t128 - d128) * n_col_blocks, (t64 - d64) * n_col_blocks},
+                           true, true};
+    if (c.pad_low && dealing_pays(c, d, nk, max_slices)) return d;
+    return c;
+  }
   int blocks = 0;
   for (int e = 0; e < n_local; ++e) blocks += row_blocks(expert_offsets[e + 1] - expert_offsets[e], false).total();
   c.pad_low = blocks * n_col_blocks >= pad_from;
-  auto count = [&](bool tall) {
-    ClassCounts n = {{0, 0, 0}, c.pad_low, tall};
-    for (int e = 0; e < n_local; ++e) {
-      const RowBlocks rb = row_blocks(expert_offsets[e + 1] - expert_offsets[e], c.pad_low, tall);
-      n.n[0] += rb.n256 * n_col_blocks;
-      n.n[1] += rb.n128 * n_col_blocks;
-      n.n[2] += rb.n64 * n_col_blocks;
-    }
-    return n;
-  };
-  c = count(false);
-  if (allow_tall && c.pad_low) {
-    const ClassCounts dealt = count(true);
-    if (dealing_pays(c, dealt, nk, max_slices)) return dealt;
+  for (int e = 0; e < n_local; ++e) {
+    const RowBlocks rb = row_blocks(expert_offsets[e + 1] - expert_offsets[e], c.pad_low);
+    c.n[0] += rb.n256 * n_col_blocks;
+    c.n[1] += rb.n128 * n_col_blocks;
+    c.n[2] += rb.n64 * n_col_blocks;
   }
   return c;
 }
