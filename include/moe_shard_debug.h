@@ -97,6 +97,15 @@ int32_t moe_debug_down_slices(const int32_t* expert_offsets, int32_t cap_rows, c
 int32_t moe_debug_tall(int32_t cap_rows, const moe_shard_t* shard);
 
 /*
+ * Which GEMMs of such a call run the kernel for experts of up to about a hundred rows, whatever moe_debug_ffn_plan says of
+ * them (that is the choice between the two others, made where this kernel is not used and with MOE_FFN_TILED): 0,
+ * MOE_DEBUG_FLOW_GATEUP, MOE_DEBUG_FLOW_DOWN or both.  Negative on invalid arguments.
+ */
+#define MOE_DEBUG_FLOW_GATEUP 1
+#define MOE_DEBUG_FLOW_DOWN 2
+int32_t moe_debug_flow(int32_t cap_rows, const moe_shard_t* shard);
+
+/*
  * The work lists of such calls: for max_slices == 0 the plain list (gate/up projection, bf16 down
  * projection), for max_slices >= 1 the list of a down projection of nk k-tiles that may be cut along K into up to
  * that many slices.  Launches that would not end sooner for it have no tall blocks in them.

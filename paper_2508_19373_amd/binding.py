@@ -32,7 +32,8 @@ MOE_PERMUTE_STATIC_MAX_COUNTS = 262144
 EXPORTS = ("moe_route_topk", "moe_permute", "moe_permute_static", "moe_expert_ffn", "moe_expert_ffn_gather", "moe_combine", "moe_forward", "moe_workspace_bytes",
            "moe_ffn_workspace_bytes", "moe_status_string")
 DEBUG_EXPORTS = ("moe_debug_gemm_units", "moe_debug_ffn_plan", "moe_debug_down_slices", "moe_debug_device_units",
-                 "moe_debug_tile_rows", "moe_debug_even_units", "moe_debug_tall", "moe_debug_tall_units")
+                 "moe_debug_tile_rows", "moe_debug_even_units", "moe_debug_tall", "moe_debug_tall_units",
+                 "moe_debug_flow")
 INT4_EXPORTS = ("moe_int4_dequantize", "moe_int4_quantize")
 INT4_GROUP = 64
 DEBUG_UNIT_INTS = 5
@@ -112,6 +113,8 @@ def lib() -> ctypes.CDLL:
         L.moe_debug_tile_rows.restype = i32
         L.moe_debug_tall.argtypes = [i32, shp]
         L.moe_debug_tall.restype = i32
+        L.moe_debug_flow.argtypes = [i32, shp]
+        L.moe_debug_flow.restype = i32
         L.moe_debug_tall_units.argtypes = [vp, i32, i32, i32, i32, i32, vp, i32]
         L.moe_debug_tall_units.restype = i32
         _lib = L
@@ -264,6 +267,17 @@ def moe_debug_tall_gemms(cap_rows, shard: MoeShard) -> int:
 def moe_debug_tall(cap_rows, shard: MoeShard) -> bool:
     """Whether any GEMM's does."""
     return moe_debug_tall_gemms(cap_rows, shard) != 0
+
+
+DEBUG_FLOW_GATEUP, DEBUG_FLOW_DOWN = 1, 2
+
+
+def moe_debug_flow(cap_rows, shard: MoeShard) -> int:
+    """Host-only: the GEMMs that run the kernel for experts of up to about a hundred rows, DEBUG_FLOW_* bits."""
+    n = lib().moe_debug_flow(cap_rows, ctypes.byref(shard))
+    if n < 0:
+        raise MoeError("moe_debug_flow", n)
+    return int(n)
 
 
 def _max_device_units(cap_rows, n_local, n_col_blocks):

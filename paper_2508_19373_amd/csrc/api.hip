@@ -139,7 +139,7 @@ static int expert_ffn_common(const void* x, moe::RowMap rows, const int32_t* exp
   return hip_status(moe::launch_expert_ffn(x, rows, expert_offsets, cap_rows, moe::expected_rows(cap_rows, shard),
                                            shard->n_local_experts, shard->hidden,
                                            shard->inter_slice, w_gate, w_up, w_down, h_workspace, y_perm, workspace,
-                                           workspace_bytes, flags, static_cast<hipStream_t>(stream)));
+                                           workspace_bytes, flags, nullptr, static_cast<hipStream_t>(stream)));
 }
 
 int moe_expert_ffn(const void* x_perm, const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard,
@@ -218,13 +218,14 @@ int moe_forward(moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard
   hipError_t err = moe::launch_route_topk(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k,
                                           a->route_flags, a->topk_idx, a->topk_w, s);
   if (err != hipSuccess) return error(MOE_STEP_ROUTE, MOE_ERR_HIP);
+  int32_t* const tickets = moe::permute_tickets(a->workspace, a->T, a->k, shard->n_local_experts);
   err = moe::launch_permute(a->x_bf16, a->topk_idx, a->T, a->k, H, shard->n_local_experts, shard->expert_offset, a->x_perm,
-                            a->expert_offsets, a->row_src, a->slot_row, a->workspace, s);
+                            a->expert_offsets, a->row_src, a->slot_row, a->workspace, s, tickets);
   if (err != hipSuccess) return error(MOE_STEP_PERMUTE, MOE_ERR_HIP);
   err = moe::launch_expert_ffn(rows, gather ? moe::RowMap{a->row_src, a->k} : moe::RowMap{nullptr, 1}, a->expert_offsets,
                                cap_rows, moe::expected_rows(cap_rows, ffn_shard), ffn_shard->n_local_experts, H,
                                ffn_shard->inter_slice, a->w_gate, a->w_up, a->w_down, a->h_workspace, a->y_perm,
-                               a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags, s);
+                               a->ffn_workspace, a->ffn_workspace_bytes, a->ffn_flags, tickets, s);
   if (err != hipSuccess) return error(MOE_STEP_FFN, MOE_ERR_HIP);
   if (!combine) return MOE_OK;
   err = moe::launch_combine(a->y_perm, a->slot_row, a->topk_w, a->T, a->k, H, a->y_shared, a->shared_gate_x,

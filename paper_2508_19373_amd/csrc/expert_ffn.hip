@@ -353,6 +353,31 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
 
 }  // namespace
 
+// Experts of up to 128 planned rows, in tiles of 64 or 128 rows: there the GEMM is bound by HBM, and this kernel streams
+// at 5.2-6.0 TB/s where the tiled ones reach 3.3-5.4 and the streaming one 4.0-5.4 (in one pass of 16 rows up to 6.0).
+// Measured alone on weights that are not in any cache, us, before / this kernel, gate/up and down projection, by average
+// rows per expert: Qwen1.5-MoE (60 experts) 3 rows 119 / 113, 65 / 58; 14: 139 / 127, 86 / 67; 36: 144 / 130, 82 / 74;
+// 100: 161 / 144, 96 / 95; Mixtral (8 experts) 3: 278 / 281, 160 / 146; 14: 343 / 317, 185 / 163; 100: 389 / 333, 199 /
+// 201; its TP=4 slice 14: 96 / 83, 52 / 45; 100: 104 / 90, 63 / 57; Qwen2-57B (64 experts) 14: 417 / 395, 254 / 208; its
+// TP=8 slice (K = 320) 14: 64 / 54, 147 / 32.
+// Where it does not pay: too few output strips of 16 columns to keep 256 workgroups in tiles (a single expert's down
+// projection: Mixtral EP=8 (256 strips) 33 / 67, EP=4 (512) 52 / 73; 1024 strips 94 / 89) or, with 16 rows and fewer, to beat
+// the streaming kernel (Qwen2-57B's shared expert under TP=8, 160 strips, 8 rows 14.7 / 19.5; the tiny layer, K = 512, 3 rows
+// 6.4 / 7.8).  Tiles of 256 weight rows from 4 gate/up strips per workgroup on (TP=4 slice of Mixtral, 7: 83 / 89 with 128; 8
+// experts of TP=8, 2.8: 24 / 22); the down projection's are the same within 2 %.
+FlowPlan flow_plan(int cap_rows, int est_rows, int n_local, int n_out, int K, bool gateup) {
+  const FlowPlan none = {0, 0};
+  if (cap_rows == 0 || K % 64 != 0 || K < 192 || K > (1 << 21) || n_out % 16 != 0) return none;  // (K: 32-bit offsets in a tile)
+  const double hi = planned_rows_hi(cap_rows, est_rows, n_local);
+  if (hi > 128.0) return none;
+  const long strips = (long)(est_rows < n_local ? est_rows : n_local) * (n_out / 16);
+  const double bytes = (double)strips * 16 * (gateup ? 2 : 1) * K * 2;
+  if (gateup ? strips < 320 : strips < 1024) return none;
+  if (bytes < 32e6 || (hi <= 16.0 && (strips < 448 || (gateup && K >= 4096 && bytes > 1e9)))) return none;
+  if (hi > 64.0) return FlowPlan{128, 256};
+  return FlowPlan{64, gateup && strips >= 1024 ? 256 : 128};
+}
+
 // The GEMMs of `which` (kTall*) that run the kernel with tall row blocks.
 int tall_gemms(int cap_rows, int est_rows, int n_local, int H, int I_s, int which) {
   if (!tall_blocks_allowed(est_rows, n_local, H, I_s)) return 0;
@@ -401,7 +426,7 @@ void ffn_plan(int cap_rows, int est_rows, int n_local, int H, int I_s, int32_t o
 hipError_t launch_expert_ffn(const void* x_perm, RowMap rows, const int32_t* expert_offsets, int cap_rows, int est_rows,
                              int n_local, int H, int I_s, const void* w_gate, const void* w_up, const void* w_down,
                              void* h_ws, void* y_perm, void* workspace, size_t workspace_bytes, uint32_t flags,
-                             hipStream_t stream) {
+                             int32_t* tickets, hipStream_t stream) {
   (void)workspace_bytes;
   if (cap_rows == 0) return hipSuccess;
   // each GEMM picks its kernel family on its own: h is row-major bf16 for both
@@ -423,10 +448,26 @@ hipError_t launch_expert_ffn(const void* x_perm, RowMap rows, const int32_t* exp
   const bool tiled_only = (flags & MOE_FFN_TILED) != 0;
   const bool walk1 = !tiled_only && prefer_walk(cap_rows, est_rows, n_local, I_s, H, true),
              walk2 = !tiled_only && prefer_walk(cap_rows, est_rows, n_local, H, I_s, false);
-  if (walk1 == walk2 || (flags & (MOE_FFN_SKIP_GATEUP | MOE_FFN_SKIP_DOWN)))
-    return run((flags & MOE_FFN_SKIP_GATEUP) ? walk2 : walk1, flags);
-  const hipError_t err = run(walk1, flags | MOE_FFN_SKIP_DOWN);
-  if (err != hipSuccess) return err;
+  const FlowPlan none = {0, 0};
+  const FlowPlan flow1 = tiled_only ? none : flow_plan(cap_rows, est_rows, n_local, I_s, H, true),
+                 flow2 = tiled_only ? none : flow_plan(cap_rows, est_rows, n_local, H, I_s, false);
+  const bool leave_room = (flags & MOE_FFN_LEAVE_ROOM) != 0;
+  // the counters pay where another stream holds compute units when the launch starts; alone they cost the longer look-up
+  // (TP=4 slice of Qwen1.5, 22 rows per expert, down projection 26 us dealt, 31 from a counter; launches of 100 us the same)
+  if (!leave_room) tickets = nullptr;
+  if (!(flags & MOE_FFN_SKIP_GATEUP)) {
+    const bool both = flow1.rows == 0 && flow2.rows == 0 && walk1 == walk2;
+    const hipError_t err =
+        flow1.rows != 0 ? launch_flow(flow1, true, true, x_perm, rows, expert_offsets, cap_rows, n_local, w_gate, w_up, I_s,
+                                      H, h_ws, tickets, leave_room, stream)
+                        : run(walk1, both ? flags : flags | MOE_FFN_SKIP_DOWN);
+    if (err != hipSuccess || both) return err;
+  }
+  if (flags & MOE_FFN_SKIP_DOWN) return hipSuccess;
+  if (flow2.rows != 0)
+    return launch_flow(flow2, false, (flags & MOE_Y_PERM_BF16) != 0, h_ws, RowMap{nullptr, 1}, expert_offsets, cap_rows,
+                       n_local, w_down, nullptr, H, I_s, y_perm, tickets == nullptr ? nullptr : tickets + 1, leave_room,
+                       stream);
   return run(walk2, flags | MOE_FFN_SKIP_GATEUP);
 }
 

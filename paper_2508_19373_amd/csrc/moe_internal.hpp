@@ -47,8 +47,12 @@ hipError_t launch_route_topk(const void* x, const float* w_router, float* logits
                              uint32_t flags, int32_t* topk_idx, float* topk_w, hipStream_t stream);
 hipError_t launch_permute(const void* x, const int32_t* topk_idx, int T, int k, int H, int n_local, int offset,
                           void* x_perm, int32_t* expert_offsets, int32_t* row_src, int32_t* slot_row,
-                          void* workspace, hipStream_t stream);
+                          void* workspace, hipStream_t stream, int32_t* tickets = nullptr);
 size_t permute_workspace_bytes(int T, int k, int n_local);
+// Words at the end of that workspace for launch_permute to clear as `tickets` (kTickets of them): the counters the GEMM
+// kernels of the same forward take their tiles from.
+constexpr int kTickets = 2;
+int32_t* permute_tickets(void* workspace, int T, int k, int n_local);
 // The same with the library's own static scratch; permute_static_counts: int32 counts it would use.
 hipError_t launch_permute_static(const void* x, const int32_t* topk_idx, int T, int k, int H, int n_local, int offset,
                                  void* x_perm, int32_t* expert_offsets, int32_t* row_src, int32_t* slot_row,
@@ -59,7 +63,7 @@ size_t permute_static_counts(int T, int k, int n_local);
 hipError_t launch_expert_ffn(const void* x_perm, RowMap rows, const int32_t* expert_offsets, int cap_rows, int est_rows,
                              int n_local, int H, int I_s, const void* w_gate, const void* w_up, const void* w_down,
                              void* h_ws, void* y_perm, void* workspace, size_t workspace_bytes, uint32_t flags,
-                             hipStream_t stream);
+                             int32_t* tickets, hipStream_t stream);
 size_t ffn_workspace_bytes(int cap_rows, int est_rows, int n_local, int H, int I_s);
 // What launch_expert_ffn would do: {GEMM1 by the walk kernel, GEMM2 by the walk kernel, rows per
 // walk pass / 16, K slices of GEMM2}.
@@ -71,6 +75,16 @@ int tiled_block_rows(int cap_rows, int est_rows, int n_local, int H, int I_s);
 constexpr int kTallGateUp = 1, kTallDown = 2, kTallDownBf16 = 4;
 int tall_gemms(int cap_rows, int est_rows, int n_local, int H, int I_s, int which);
 int expected_rows(int cap_rows, const moe_shard_t* shard);
+// The kernel for experts of up to about a hundred rows (grouped_flow.hpp): rows and weight rows of its tiles for one of
+// the two GEMMs of such a call, rows = 0 where another kernel runs it.
+struct FlowPlan {
+  int rows, cols;
+};
+FlowPlan flow_plan(int cap_rows, int est_rows, int n_local, int n_out, int K, bool gateup);
+// ticket: a zero in device memory (nullptr: tiles are dealt in turn)
+hipError_t launch_flow(const FlowPlan& plan, bool gateup, bool out_bf16, const void* A, RowMap rows,
+                       const int32_t* expert_offsets, int cap_rows, int n_local, const void* B0, const void* B1,
+                       int n_out, int K, void* C, int32_t* ticket, bool leave_room, hipStream_t stream);
 hipError_t launch_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w, int T, int k, int H,
                           const void* y_shared, const void* x, const float* w_shared_gate, void* y_out,
                           bool y_perm_bf16, bool out_f32, hipStream_t stream);

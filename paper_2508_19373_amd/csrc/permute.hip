@@ -53,11 +53,13 @@ __global__ __launch_bounds__(kIdxThreads) void permute_index_kernel(const int32_
                                                                    int32_t* __restrict__ row_src,
                                                                    int32_t* __restrict__ slot_row,
                                                                    const uint4* __restrict__ x, int k,
-                                                                   int chunks_per_row, uint4* __restrict__ x_perm) {
+                                                                   int chunks_per_row, uint4* __restrict__ x_perm,
+                                                                   int32_t* __restrict__ tickets) {
   __shared__ int32_t base[MOE_MAX_EXPERTS];                   // next free row of each expert
   __shared__ int32_t wave_cnt[kIdxWaves][MOE_MAX_EXPERTS];    // per-wave counts, then per-wave bases
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
 
+  if (tickets != nullptr && tid < kTickets) tickets[tid] = 0;
   for (int e = tid; e < n_local; e += kIdxThreads) base[e] = 0;
   __syncthreads();
   for (int a = tid; a < A; a += kIdxThreads) {
@@ -186,9 +188,11 @@ __global__ __launch_bounds__(kIdxThreads) void permute_rank_kernel(const int32_t
 }
 
 __global__ __launch_bounds__(256) void permute_scan_kernel(int32_t* __restrict__ block_counts, int n_blocks,
-                                                          int n_local, int32_t* __restrict__ expert_offsets) {
+                                                          int n_local, int32_t* __restrict__ expert_offsets,
+                                                          int32_t* __restrict__ tickets) {
   __shared__ int32_t total[MOE_MAX_EXPERTS];
   const int tid = threadIdx.x;
+  if (tickets != nullptr && tid < kTickets) tickets[tid] = 0;
   for (int e = tid; e < n_local; e += 256) {
     int run = 0;
     for (int b = 0; b < n_blocks; ++b) {
@@ -250,6 +254,10 @@ size_t permute_workspace_bytes(int T, int k, int n_local) {
   return 256 + blocks * n_local * sizeof(int32_t);
 }
 
+int32_t* permute_tickets(void* workspace, int T, int k, int n_local) {  // the last 256 bytes are nobody else's
+  return reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + permute_workspace_bytes(T, k, n_local) - 256);
+}
+
 size_t permute_static_counts(int T, int k, int n_local) {
   const size_t A = (size_t)T * k;
   if (A <= 2 * kIdxThreads) return 0;  // the one-workgroup path keeps its counts in LDS
@@ -269,14 +277,14 @@ hipError_t launch_permute_static(const void* x, const int32_t* topk_idx, int T, 
 
 hipError_t launch_permute(const void* x, const int32_t* topk_idx, int T, int k, int H, int n_local, int offset,
                           void* x_perm, int32_t* expert_offsets, int32_t* row_src, int32_t* slot_row,
-                          void* workspace, hipStream_t stream) {
+                          void* workspace, hipStream_t stream, int32_t* tickets) {
   const int A = T * k;
   hipError_t err;
   if (A <= 2 * kIdxThreads) {  // small batch: one workgroup does it all in one launch
     const bool fuse = x_perm != nullptr && (size_t)A * H * 2 <= (256u << 10);
     hipLaunchKernelGGL(permute_index_kernel, dim3(1), dim3(kIdxThreads), 0, stream, topk_idx, A, n_local, offset,
                        expert_offsets, row_src, slot_row, fuse ? static_cast<const uint4*>(x) : nullptr, k, H / 8,
-                       static_cast<uint4*>(x_perm));
+                       static_cast<uint4*>(x_perm), tickets);
     err = hipGetLastError();
     if (fuse) return err;
   } else {
@@ -284,7 +292,8 @@ hipError_t launch_permute(const void* x, const int32_t* topk_idx, int T, int k, 
     int32_t* counts = static_cast<int32_t*>(workspace);
     hipLaunchKernelGGL(permute_rank_kernel, dim3(blocks), dim3(kIdxThreads), 0, stream, topk_idx, A, n_local, offset,
                        counts, slot_row);
-    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(256), 0, stream, counts, blocks, n_local, expert_offsets);
+    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(256), 0, stream, counts, blocks, n_local, expert_offsets,
+                       tickets);
     hipLaunchKernelGGL(permute_place_kernel, dim3(blocks), dim3(kIdxThreads), 0, stream, A, n_local, counts, row_src,
                        slot_row);
     err = hipGetLastError();

@@ -179,7 +179,9 @@ class ExpertShardLayer:
         """Whether a forward of T tokens reads the routed experts' rows of x in place (no permuted copy)."""
         if self.gather_in_ffn or not self._gather_auto:
             return self.gather_in_ffn
-        return bool(B.moe_debug_ffn_plan(T * self.k, self.ffn_shard)[0])   # GEMM1 on the streaming kernel
+        # GEMM1 on a kernel that streams the weights: the rows are few
+        return bool(B.moe_debug_ffn_plan(T * self.k, self.ffn_shard)[0] or
+                    B.moe_debug_flow(T * self.k, self.ffn_shard) & B.DEBUG_FLOW_GATEUP)
 
     def _plan(self, T) -> "_Plan":
         """What a forward of T tokens needs to know about itself: a function of T, the shards and the switches,
@@ -188,7 +190,13 @@ class ExpertShardLayer:
         plan = self._plans.get(key)
         if plan is None:
             sh = self.shared is not None
-            hint = routed_hint_beside_shared(self.ffn_shard, self.shared_shard, T) if sh and self.overlap_shared else 0
+            hint = 0
+            if sh and self.overlap_shared:
+                hint = routed_hint_beside_shared(self.ffn_shard, self.shared_shard, T)
+                if hint == B.MOE_FFN_TILED and B.moe_debug_flow(T * self.k, self.ffn_shard):
+                    # its streaming workgroups stay, too: room for the shared expert's tiles instead (333 tokens of
+                    # Qwen1.5-MoE: 268 us tiled, 252 with room)
+                    hint = B.MOE_FFN_LEAVE_ROOM
             plan = _Plan(B.moe_ffn_workspace_bytes(T * self.k, self.ffn_shard),
                          B.moe_ffn_workspace_bytes(T, self.shared_shard) if sh else 0, hint, self.gathers(T))
             if len(self._plans) >= 256:

@@ -1,0 +1,115 @@
+"""The grouped GEMM for experts of up to about a hundred rows (csrc/grouped_flow.hpp): when it runs (host) and what it
+computes at the edges of its tiles (device, against the CPU oracle)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle as O
+from paper_2508_19373_amd import binding as B
+from paper_2508_19373_amd import inputs as I
+from paper_2508_19373_amd.layer import ExpertShardLayer, bf16_tensor
+
+BOTH = B.DEBUG_FLOW_GATEUP | B.DEBUG_FLOW_DOWN
+
+
+def test_when_it_runs():
+    mixtral = B.make_shard(8, 8, 0, 4096, 14336, 14336)
+    assert B.moe_debug_flow(16, mixtral) == B.DEBUG_FLOW_DOWN        # one 16-row pass over long rows streams as fast
+    assert B.moe_debug_flow(64, mixtral) == B.DEBUG_FLOW_DOWN        # 8 rows per expert, 14 planned
+    assert B.moe_debug_flow(128, mixtral) == BOTH
+    assert B.moe_debug_flow(848, mixtral) == BOTH                    # 106 rows per expert, 127 planned
+    assert B.moe_debug_flow(860, mixtral) == 0                       # 128 planned and a few more
+    one = B.make_shard(8, 1, 0, 4096, 14336, 14336)
+    assert B.moe_debug_flow(256, one) == B.DEBUG_FLOW_GATEUP         # 256 output strips of the down projection: one each
+    assert B.moe_debug_flow(0, one) == 0
+    tiny = B.make_shard(8, 8, 0, 512, 1024, 1024)
+    assert B.moe_debug_flow(128, tiny) == 0                          # 17 MB of weights
+    qwen_tp8 = B.make_shard(60, 60, 0, 2048, 1536, 192)
+    assert B.moe_debug_flow(1024, qwen_tp8) == BOTH                  # K = 192, three k-tiles: the shortest it takes
+    assert B.moe_debug_flow(1024, B.make_shard(60, 60, 0, 2048, 1024, 128)) == B.DEBUG_FLOW_GATEUP
+    assert B.moe_debug_flow(4, qwen_tp8) == 0                        # four experts at most: 48 gate/up strips
+
+
+def _counts(n, avg, special, rng):
+    c = rng.integers(0, 2 * avg, n)
+    c[:len(special)] = special
+    c[len(special):] = c[len(special):] * max(avg * n - sum(special), 0) // max(int(c[len(special):].sum()), 1)
+    return c
+
+
+CASES = [
+    # n, H, I_s, average rows, first experts' rows: tiles of 64 x 256 and 64 x 128, two and three row passes
+    (24, 1024, 704, 40, [64, 65, 0, 1, 130, 63]),
+    # 64 x 128 for both, strips that do not divide by the tile
+    (15, 2048, 704, 20, [16, 17, 0, 64, 65]),
+    # 128-row tiles
+    (24, 1024, 704, 90, [128, 129, 0, 1, 257, 127]),
+    # three k-tiles: the loaders are more than a tile ahead
+    (64, 1536, 192, 10, [0, 0, 33, 64, 65, 1]),
+    (64, 1536, 192, 80, [0, 128, 129, 1]),
+    # five, and one row per expert or none
+    (64, 1024, 320, 2, [0, 1, 9]),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,H,I_s,avg,special", CASES)
+@pytest.mark.parametrize("gather", [False, True])
+def test_against_oracle(n, H, I_s, avg, special, gather):
+    """fp32 and bf16 y_perm, rows permuted or read in place.  Tolerance: h and (bf16) y are rounded to bf16 once, 1.6e-3
+    and 2.3e-3 rel-L2; sums in another order differ by 1e-6."""
+    rng = np.random.default_rng(n + avg)
+    counts = _counts(n, avg, special, rng)
+    offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    R = int(offs[-1])
+    cap = R + 5
+    shard = B.make_shard(n, n, 0, H, I_s, I_s)
+    assert B.moe_debug_flow(cap, shard) == BOTH
+    wg, wu, wd = I.make_expert_weights(4, I.MoEShape("f", H, n, 1, I_s, True))
+    k = 2
+    T = (cap + k - 1) // k
+    x = I.make_x(5, T, H)
+    row_src = rng.permutation(T * k)[:cap].astype(np.int32)
+    xp = x[row_src // k]
+    ref = O.expert_ffn(xp[:R], offs, wg, wu, wd)
+    W = [bf16_tensor(w) for w in (wg, wu, wd)]
+    h = torch.empty((cap, I_s), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(max(B.moe_ffn_workspace_bytes(cap, shard), 256), dtype=torch.uint8, device="cuda")
+    d_offs, d_src = torch.from_numpy(offs).cuda(), torch.from_numpy(row_src).cuda()
+    rows = bf16_tensor(x if gather else xp)
+    outs = []
+    for flags in (0, B.MOE_FFN_LEAVE_ROOM, B.MOE_Y_PERM_BF16):
+        y = torch.full((cap, H), float("nan"), dtype=torch.bfloat16 if flags & B.MOE_Y_PERM_BF16 else torch.float32,
+                       device="cuda")
+        if gather:
+            B.moe_expert_ffn_gather(rows, d_src, k, d_offs, cap, shard, *W, h, y, ws, flags)
+        else:
+            B.moe_expert_ffn(rows, d_offs, cap, shard, *W, h, y, ws, flags)
+        y = y.float().cpu().numpy().astype(np.float64)
+        assert np.all(np.isnan(y[R:])), "rows past R must not be written"
+        rel = np.linalg.norm(y[:R] - ref) / np.linalg.norm(ref)
+        assert rel < 5e-3, (flags, rel)
+        outs.append(y[:R])
+    assert np.array_equal(outs[0], outs[1])          # fewer workgroups, the same tiles
+
+
+@pytest.mark.gpu
+def test_tiles_from_the_counter_give_the_same_bits():
+    """Beside another stream the tiles come from a counter that the permutation clears; every forward starts it anew."""
+    n, H, I_s, k = 24, 1024, 704, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda")
+    W = dict(w_gate=(r(n, I_s, H) * 0.02).bfloat16(), w_up=(r(n, I_s, H) * 0.02).bfloat16(),
+             w_down=(r(n, H, I_s) * 0.02).bfloat16(), w_router=r(H, n) * 0.02)
+    layer = ExpertShardLayer(n_experts=n, top_k=k, hidden=H, inter_full=I_s, inter_slice=I_s, max_tokens=600, **W)
+    for tokens in (300, 600, 37):   # permuted by one workgroup and (more than 2048 assignments) by several
+        x = r(tokens, H).bfloat16()
+        assert B.moe_debug_flow(tokens * k, layer.ffn_shard)
+        want = layer.forward(x).clone()
+        plan = layer._plan(tokens)
+        layer._plan = lambda _, p=plan: p._replace(hint=B.MOE_FFN_LEAVE_ROOM)
+        for _ in range(3):
+            layer.y_perm.fill_(float("nan"))
+            assert torch.equal(layer.forward(x), want)
+        del layer._plan
