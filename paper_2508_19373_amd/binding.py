@@ -272,12 +272,22 @@ def moe_debug_tall(cap_rows, shard: MoeShard) -> bool:
 DEBUG_FLOW_GATEUP, DEBUG_FLOW_DOWN = 1, 2
 
 
-def moe_debug_flow(cap_rows, shard: MoeShard) -> int:
-    """Host-only: the GEMMs that run the kernel for experts of up to about a hundred rows, DEBUG_FLOW_* bits."""
+def _flow(cap_rows, shard):
     n = lib().moe_debug_flow(cap_rows, ctypes.byref(shard))
     if n < 0:
         raise MoeError("moe_debug_flow", n)
     return int(n)
+
+
+def moe_debug_flow(cap_rows, shard: MoeShard) -> int:
+    """Host-only: the GEMMs that run the kernel for experts of up to about a hundred rows, DEBUG_FLOW_* bits."""
+    return _flow(cap_rows, shard) & 3
+
+
+def moe_debug_flow_rows(cap_rows, shard: MoeShard) -> int:
+    """Rows per tile of that kernel's gate/up projection, else of its down projection; 0: neither runs on it."""
+    n = _flow(cap_rows, shard)
+    return (n >> 8 & 255) or n >> 16
 
 
 def _max_device_units(cap_rows, n_local, n_col_blocks):

@@ -94,8 +94,9 @@ extern "C" int32_t moe_debug_flow(int32_t cap_rows, const moe_shard_t* shard) {
   if (shard->n_experts < 1 || shard->n_local_experts < 1 || shard->n_local_experts > shard->n_experts)
     return MOE_ERR_INVALID_ARG;
   const int est = moe::expected_rows(cap_rows, shard), n = shard->n_local_experts;
-  return (moe::flow_plan(cap_rows, est, n, shard->inter_slice, shard->hidden, true).rows != 0 ? MOE_DEBUG_FLOW_GATEUP : 0) |
-         (moe::flow_plan(cap_rows, est, n, shard->hidden, shard->inter_slice, false).rows != 0 ? MOE_DEBUG_FLOW_DOWN : 0);
+  const int gu = moe::flow_plan(cap_rows, est, n, shard->inter_slice, shard->hidden, true).rows,
+            dn = moe::flow_plan(cap_rows, est, n, shard->hidden, shard->inter_slice, false).rows;
+  return (gu != 0 ? MOE_DEBUG_FLOW_GATEUP : 0) | (dn != 0 ? MOE_DEBUG_FLOW_DOWN : 0) | gu << 8 | dn << 16;
 }
 
 extern "C" int32_t moe_debug_tall_units(const int32_t* expert_offsets, int32_t n_local, int32_t cap_rows,

@@ -12,6 +12,7 @@
 // K extents it is not instantiated for) for decode-sized groups.  Each of the two GEMMs picks its
 // family from a cost estimate (prefer_walk below).  In both, the work list is derived on the
 // device from expert_offsets without a host round trip.
+#include "flow_tiles.hpp"
 #include "grouped_gemm.hpp"
 #include "grouped_stream.hpp"
 #include "grouped_walk.hpp"
@@ -106,6 +107,14 @@ bool expects_tall_blocks(int cap_rows, int est_rows, int n_local, int ncb, int n
   return tall(avg, sliced) || (est_rows < cap_rows && tall(fmin(2.0 * avg, (double)cap_rows / n_local), false));
 }
 
+// Whether the tiles of a gate/up projection begin their walk over K apart (gemm_tile): where rows are a multiple of 4 KB and
+// the weights, not the matrix cores, set the pace.  Measured from one place / spread, us: TP=4 slice of Mixtral, 160 rows
+// per expert 128 / 113, 300: 207 / 180; Qwen1.5-MoE 256: 200 / 194, 272: 211 / 205; 64 experts of 280 rows, K = 2048, 257 /
+// 242; at the power limit it costs a little (Mixtral 1024 rows 1383 / 1391, 1040: 1432 / 1458), and so does the arithmetic (the
+// choice made in the kernel: TP=4 slice 2048 rows 676 -> 692 from one place), hence kernels of their own; on other K nothing
+// changes (Qwen2-57B, K = 3584, 553 / 549).  The 160-row tiling gains 1 %, the down projections lose (Mixtral 1024 rows 678 / 689).
+inline bool spread_k(int est_rows, int n_local, int K) { return K % 2048 == 0 && est_rows <= 512 * n_local; }
+
 // Prefill-sized groups: LDS-DMA kernel, 256-column tiles of 256 / 128 / 64 rows, or the kernel whose full row blocks may take
 // their expert's remainder (tall_gemms).
 template <int BN>
@@ -120,9 +129,10 @@ hipError_t launch_pair_dlds(const void* x_perm, RowMap rows, const int32_t* expe
   auto grid_for = [&](int ncb) { return dim3((unsigned)gg::max_grid(cap_rows, n_local, ncb)); };
   if (!(flags & MOE_FFN_SKIP_GATEUP)) {
     const int ncb = (I_s + BN / 2 - 1) / (BN / 2);
+    const bool spread = spread_k(est_rows, n_local, H);
     const auto kernel = tall_gemms(cap_rows, est_rows, n_local, H, I_s, kTallGateUp)
-                            ? gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>
-                            : gg::grouped_gemm_dlds_kernel<BN, true, uint16_t, false>;
+                            ? (spread ? gg::grouped_gemm_spread_tall_kernel<BN> : gg::grouped_gemm_tall_kernel<BN, true, uint16_t, false>)
+                            : (spread ? gg::grouped_gemm_spread_kernel<BN> : gg::grouped_gemm_dlds_kernel<BN, true, uint16_t, false>);
     hipLaunchKernelGGL(kernel, grid_for(ncb), block, 0, stream, xp,
                        expert_offsets, n_local, cap_rows, static_cast<const uint16_t*>(w_gate),
                        static_cast<const uint16_t*>(w_up), I_s, H, hw, ncb, static_cast<uint16_t*>(nullptr), 0, rows);
@@ -353,13 +363,21 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
 
 }  // namespace
 
-// Experts of up to 128 planned rows, in tiles of 64 or 128 rows: there the GEMM is bound by HBM, and this kernel streams
+// Experts of up to 160 planned rows, in tiles of 64, 128 or 160 rows: there the GEMM is bound by HBM, and this kernel streams
 // at 5.2-6.0 TB/s where the tiled ones reach 3.3-5.4 and the streaming one 4.0-5.4 (in one pass of 16 rows up to 6.0).
 // Measured alone on weights that are not in any cache, us, before / this kernel, gate/up and down projection, by average
 // rows per expert: Qwen1.5-MoE (60 experts) 3 rows 119 / 113, 65 / 58; 14: 139 / 127, 86 / 67; 36: 144 / 130, 82 / 74;
 // 100: 161 / 144, 96 / 95; Mixtral (8 experts) 3: 278 / 281, 160 / 146; 14: 343 / 317, 185 / 163; 100: 389 / 333, 199 /
 // 201; its TP=4 slice 14: 96 / 83, 52 / 45; 100: 104 / 90, 63 / 57; Qwen2-57B (64 experts) 14: 417 / 395, 254 / 208; its
 // TP=8 slice (K = 320) 14: 64 / 54, 147 / 32.
+// With 160 rows: TP=4 slice of Mixtral, 130 rows 112 / 93, 71 / 64, 145: 115 / 93, 76 / 67; Qwen1.5-MoE 130: 164 / 147, 97 / 98;
+// Qwen2-57B TP=2 EP=2 130: 151 / 134, 88 / 87; 8 experts of TP=2, 145: 222 / 180, 130 / 126.  An expert-parallel shard takes
+// them by its balanced share: the passes of the experts that got more share their weights in L2.
+// Two passes of 160 rows share them, too, at 1.2 us per k-tile of 160 x 256: the down projection just above one 256-row
+// block, where the tiled kernels have tall blocks or remainders, (Qwen1.5-MoE 250 rows 143 / 131, 270: 144 / 137, 290: 167 / 140;
+// Mixtral TP=2 270: 173 / 136, TP=4 104 / 74, TP=8 59 / 43; Qwen2-57B 270: 406 / 396; 30 experts of Qwen1.5 250: 59 / 65, 270: 73 /
+// 66), and gate/up projections whose tall tiles leave most of a round idle (estimated; 30 experts of Qwen1.5 270: 124 / 117, its
+// TP=2 slice 136 / 118, Mixtral TP=8 99 / 78, Qwen2-57B TP=2 EP=2 201 / 188; not Qwen1.5 214 / 229, Mixtral TP=4 142 / 149).
 // Where it does not pay: too few output strips of 16 columns to keep 256 workgroups in tiles (a single expert's down
 // projection: Mixtral EP=8 (256 strips) 33 / 67, EP=4 (512) 52 / 73; 1024 strips 94 / 89) or, with 16 rows and fewer, to beat
 // the streaming kernel (Qwen2-57B's shared expert under TP=8, 160 strips, 8 rows 14.7 / 19.5; the tiny layer, K = 512, 3 rows
@@ -368,14 +386,21 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
 FlowPlan flow_plan(int cap_rows, int est_rows, int n_local, int n_out, int K, bool gateup) {
   const FlowPlan none = {0, 0};
   if (cap_rows == 0 || K % 64 != 0 || K < 192 || K > (1 << 21) || n_out % 16 != 0) return none;  // (K: 32-bit offsets in a tile)
-  const double hi = planned_rows_hi(cap_rows, est_rows, n_local);
-  if (hi > 128.0) return none;
   const long strips = (long)(est_rows < n_local ? est_rows : n_local) * (n_out / 16);
   const double bytes = (double)strips * 16 * (gateup ? 2 : 1) * K * 2;
-  if (gateup ? strips < 320 : strips < 1024) return none;
-  if (bytes < 32e6 || (hi <= 16.0 && (strips < 448 || (gateup && K >= 4096 && bytes > 1e9)))) return none;
-  if (hi > 64.0) return FlowPlan{128, 256};
-  return FlowPlan{64, gateup && strips >= 1024 ? 256 : 128};
+  if ((gateup ? strips < 320 : strips < 1024) || bytes < 32e6) return none;
+  const double hi = planned_rows_hi(cap_rows, est_rows, n_local), avg = (double)est_rows / n_local;
+  if (hi <= 16.0 && (strips < 448 || (gateup && K >= 4096 && bytes > 1e9))) return none;
+  if (hi <= 64.0) return FlowPlan{64, gateup && strips >= 1024 ? 256 : 128};
+  if (hi <= 128.0) return FlowPlan{128, 256};
+  const bool exact = n_local == 1 && est_rows == cap_rows;
+  if (avg + (exact ? 0.0 : 2.0 * sqrt(avg)) <= 165.0) return FlowPlan{160, 256};
+  if (hi < 283.0 || hi > 326.0 || est_rows < cap_rows) return none;
+  if (!gateup) return FlowPlan{160, 256};
+  const int nk = K / 64, tall = n_local * ((n_out + 127) / 128);
+  const double flow_us = gf::tile_cost(2 * n_local, n_out / 16, 160, 256, true, nullptr) * nk * 0.15 + 6.0;
+  const double tall_us = (tall + 255) / 256 * (nk * 1.6 + 12.0);
+  return flow_us < 0.95 * tall_us ? FlowPlan{160, 256} : none;
 }
 
 // The GEMMs of `which` (kTall*) that run the kernel with tall row blocks.

@@ -24,14 +24,17 @@ hipError_t launch_flow(const FlowPlan& plan, bool gateup, bool out_bf16, const v
 #define MOE_FLOW(BM, BN, GATEUP, OutT) \
   return launch<BM, BN, GATEUP, OutT>(a, rows, expert_offsets, cap_rows, n_local, b0, b1, n_out, K, C, ticket, leave_room, stream)
   if (gateup) {
+    if (plan.rows == 160) MOE_FLOW(160, 256, true, uint16_t);
     if (plan.rows == 128) MOE_FLOW(128, 256, true, uint16_t);
     if (plan.cols == 256) MOE_FLOW(64, 256, true, uint16_t);
     MOE_FLOW(64, 128, true, uint16_t);
   }
   if (out_bf16) {
+    if (plan.rows == 160) MOE_FLOW(160, 256, false, uint16_t);
     if (plan.rows == 128) MOE_FLOW(128, 256, false, uint16_t);
     MOE_FLOW(64, 128, false, uint16_t);
   }
+  if (plan.rows == 160) MOE_FLOW(160, 256, false, float);
   if (plan.rows == 128) MOE_FLOW(128, 256, false, float);
   MOE_FLOW(64, 128, false, float);
 #undef MOE_FLOW

@@ -18,6 +18,7 @@
 #pragma once
 #include <type_traits>
 
+#include "flow_tiles.hpp"
 #include "moe_internal.hpp"
 #include "unit_list_wave.hpp"
 
@@ -27,8 +28,7 @@ namespace gf {
 constexpr int BK = 64;           // K elements per LDS row (128 bytes, 8 chunks of 16 bytes)
 constexpr int kMul = 4, kLoad = 4;  // wavefronts that multiply / that load
 constexpr int kThreads = (kMul + kLoad) * 64;
-constexpr int kSlots = 8;        // ring of looked-up tiles
-constexpr int kRound = 256;      // workgroups of a full launch
+constexpr int kSlots = 4;        // ring of looked-up tiles
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void global_void_t;
@@ -55,7 +55,7 @@ struct Shape {
   static constexpr int NSA = BN >= 256 ? 3 : 6;
   static constexpr int NSB = BN >= 256 ? (BM >= 128 ? 3 : 4) : NSA;
   static_assert(NSA <= NSB, "the weights run ahead at least as far as the activations");
-  static_assert((NSA * kStageA + NSB * kStageB) * 2 <= (160 - 7) * 1024, "LDS budget, beside the tile slots");
+  static_assert((NSA * kStageA + NSB * kStageB) * 2 <= (160 - 4) * 1024, "LDS budget, beside the tile slots");
   static constexpr int kRowsA = BM / 8, kRowsB = BN / 8;      // 1 KB DMA instructions per k-tile
   static constexpr int A_INST = (kRowsA + kLoad - 1) / kLoad, B_INST = kRowsB / kLoad;
   static_assert(kRowsB % kLoad == 0 && (kRowsA % kLoad == 0), "whole instructions per loader");
@@ -100,11 +100,9 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
     const RowMap rows, int32_t* __restrict__ ticket) {
   using S = Shape<BM, BN>;
   constexpr int NSA = S::NSA, NSB = S::NSB;
-  constexpr int NCOLS = GATEUP ? BN / 2 : BN;
   constexpr int TM = BM / 16, TN = BN / kMul / 16;
   static_assert(!GATEUP || TN % 2 == 0, "gate and up blocks pair up inside a wavefront");
   __shared__ __attribute__((aligned(1024))) uint16_t stages[NSA * S::kStageA + NSB * S::kStageB];
-  __shared__ int s_off[MOE_MAX_EXPERTS + 1];    // expert_offsets
   __shared__ int s_pre[MOE_MAX_EXPERTS];        // row passes before each expert
   __shared__ Slot s_slot[kSlots];
   __shared__ int s_row[kSlots][BM];             // source row of each of a tile's rows
@@ -112,7 +110,6 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nk = K / BK;
-  constexpr int kMaxStrips = NCOLS / 16;
   const int strips = n_out / 16;
   int ncb = 1;  // tiles a (expert, row pass) is cut into
   // A look-up waits twice for memory (counter, source rows), `pace` k-tiles each: three under load (3 us).  Tiles are looked
@@ -135,7 +132,11 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
   auto find = [&](int id, Slot& s) {
     s.expert = -1;
     s.row0 = s.row_end = s.strip0 = s.strips = s.kt0 = 0;
-    if (id >= total) return;
+    // Each XCD takes a contiguous eighth of the list (workgroup b runs on XCD b % 8), in which the row passes of a column tile
+    // are neighbours: they walk K together and the later readers of its weights find them in that XCD's L2.
+    const int xcd = id % gg::kNumXcd, chunk = (total + gg::kNumXcd - 1) / gg::kNumXcd;
+    id = xcd * chunk + id / gg::kNumXcd;
+    if (id >= min(total, (xcd + 1) * chunk)) return;
     int before = 0;
 #pragma unroll
     for (int j = 0; j < gg::kLaneChunks; ++j) {
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
       }
     }
     const int e = before - 1;  // the last expert that starts at or before it
-    const int lo = __builtin_amdgcn_readfirstlane(s_off[e]), hi = __builtin_amdgcn_readfirstlane(s_off[e + 1]);
+    const int lo = expert_offsets[e], hi = expert_offsets[e + 1];
     const int local = id - __builtin_amdgcn_readfirstlane(s_pre[e]) * ncb;
     const int passes = (hi - lo + BM - 1) / BM;
     const int nb = local / passes;
@@ -153,12 +154,13 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
     s.strip0 = nb * strips / ncb;
     s.strips = (nb + 1) * strips / ncb - s.strip0;
     s.row0 = lo + (local - nb * passes) * BM;
-    // The walk over K begins at one of 16 places: workgroups that all stand at the same k read the same 128 bytes of rows
-    // 4 or 8 KB apart, which fall on a few of the memory channels (gate/up of Qwen1.5-MoE, K = 2048, 22 rows per expert 138 us
-    // from k = 0, 125 from 16 places; TP=4 slice of Mixtral, K = 4096, 94 and 83; K = 1408 and 3584 no difference).  A
-    // function of the tile alone, so that the sums' order does not hang on who computes it; tiles 8 apart, on one
-    // XCD where they are dealt in turn, stand close together and share their activations in its L2.
-    s.kt0 = ((id & 7) * 2 + ((id >> 3) & 1)) * nk / 16;
+    // The walk over K begins at one of 8 or 16 places: workgroups that all stand at the same k read the same 128 bytes of
+    // rows 4 or 8 KB apart, which fall on a few of the memory channels (gate/up of Qwen1.5-MoE, K = 2048, 22 rows per expert
+    // 138 us from k = 0, 125 from 16 places; TP=4 slice of Mixtral, K = 4096, 94 and 83; K = 1408 and 3584 no
+    // difference).  A function of the tile alone, so that the sums' order does not hang on who computes it; the same
+    // for an XCD's tiles where they share so many rows' activations in its L2 that these should be walked together
+    // (Qwen1.5-MoE, 90 rows: 139 us from 8 places, 152 from 16).
+    s.kt0 = BM >= 128 ? xcd * nk / gg::kNumXcd : (xcd * 2 + (nb & 1)) * nk / (2 * gg::kNumXcd);
     s.row_end = hi;
   };
   // source rows of a tile's rows, the last valid one behind its end
@@ -178,21 +180,12 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
       const bool ok = j < chunks && e < n_local;
       const int lo = ok ? expert_offsets[e] : 0, hi = ok ? expert_offsets[e + 1] : 0;
       len[j] = (hi - lo + BM - 1) / BM;
-      if (ok) {
-        s_off[e] = lo;
-        if (e == n_local - 1) s_off[n_local] = hi;
-      }
     }
     const int units = gg::wave_prefix(len, chunks, pre);
-    // Tiles of equal width, as many as leave no workgroup idle in the last round: lane l prices n = fewest + l tiles per
-    // unit at rounds times width, and a quarter of a strip for each tile.  A k-tile has a shortest time (barrier, operand
-    // reads, MFMAs of the whole tile shape), that of kMinWidth strips at the HBM rate.
+    // tiles of equal width, as many as leave no workgroup idle in the last round: lane l prices fewest + l
     {
-      const int fewest = (strips + kMaxStrips - 1) / kMaxStrips, n = fewest + lane;
-      constexpr float kMinWidth = kMaxStrips * (BM >= 128 ? 0.55f : (BN >= 256 ? 0.35f : 0.5f));
-      const int rounds = (units * n + kRound - 1) / kRound;
-      const float cost =
-          n <= strips ? (float)rounds * (fmaxf((float)strips / (float)n, kMinWidth) + 0.25f) : 3e38f;
+      const int fewest = fewest_tiles(strips, BN, GATEUP), n = fewest + lane;
+      const float cost = n <= strips ? tile_cost_of(units, strips, n, BM, BN, GATEUP) : 3e38f;
       float best = cost;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o, 64));

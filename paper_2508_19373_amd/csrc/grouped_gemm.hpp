@@ -127,7 +127,8 @@ __device__ __forceinline__ void mfma_vgpr(f32x4& acc, const bf16x8& a, const bf1
 // taken, so their operands go from memory (L2: every column block reads the same rows) straight to registers,
 // one k-tile ahead; the two wave-rows share their MFMA work, each taking half of the wave-column's weight rows.
 // Those have to be the same registers in both: wave-row 1 numbers its weight row blocks from the middle.
-template <int BM, int BN, int WM, int WN, int NSA, int NSB, bool GATEUP, typename OutT, int NX = 0, bool BUF = false>
+template <int BM, int BN, int WM, int WN, int NSA, int NSB, bool GATEUP, typename OutT, int NX = 0, bool BUF = false,
+          bool SPREAD = false>
 __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, const uint16_t* __restrict__ A,
                                             int cap_rows, const uint16_t* __restrict__ B0,
                                             const uint16_t* __restrict__ B1, int n_out, int K, int kt0, int nk,
@@ -219,6 +220,15 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
     }
   }
 
+  // Where the walk over K begins (SPREAD): an eighth of K further on each XCD, whose tiles share
+  // their panels in its own L2 and so keep walking together.  Tiles that all stand at the same k read the same 128 bytes of
+  // rows 4 or 8 KB apart, which fall on a few of the memory channels.  Only where HBM counts (spread_k).
+  const int k_first = SPREAD ? (int)(blockIdx.x % kNumXcd) * nk / kNumXcd : 0;
+  auto k_at = [&](int kt) {
+    if constexpr (SPREAD) return kt + k_first >= nk ? kt + k_first - nk : kt + k_first;
+    return kt;
+  };
+
   const int lrow = lane & 15;
   const int kq = lane >> 4;
   uint32_t x_lane[NX > 0 ? NX : 1];
@@ -234,7 +244,7 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
     for (int x = 0; x < NX; ++x)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
-        xf[x][ks] = buf_load(a_buf, x_lane[x] + ks * 64, kt * (BK * 2));
+        xf[x][ks] = buf_load(a_buf, x_lane[x] + ks * 64, k_at(kt) * (BK * 2));
   };
 
   constexpr int N_DMA = A_INST + B_INST;
@@ -245,18 +255,18 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
     if constexpr (idx < A_INST) {
       if constexpr (BUF)
         buf_to_lds(a_buf, (lds_void_t*)(smem + stage_a * A_STAGE + (idx * NW + wave) * 8 * BK), a_lane[idx],
-                   kt_a * (BK * 2));
+                   k_at(kt_a) * (BK * 2));
       else
-        __builtin_amdgcn_global_load_lds((global_void_t*)(a_src[idx] + (size_t)kt_a * BK),
+        __builtin_amdgcn_global_load_lds((global_void_t*)(a_src[idx] + (size_t)k_at(kt_a) * BK),
                                          (lds_void_t*)(smem + stage_a * A_STAGE + (idx * NW + wave) * 8 * BK), 16, 0, 0);
     } else {
       constexpr int j = idx - A_INST;
       if constexpr (BUF)
         buf_to_lds(b_buf, (lds_void_t*)(smem + NSA * A_STAGE + stage_b * B_STAGE + (j * NW + wave) * 8 * BK), b_lane,
-                   b_off[j] + kt_b * (BK * 2));
+                   b_off[j] + k_at(kt_b) * (BK * 2));
       else
         __builtin_amdgcn_global_load_lds(
-            (global_void_t*)(b_src[j] + (size_t)kt_b * BK),
+            (global_void_t*)(b_src[j] + (size_t)k_at(kt_b) * BK),
             (lds_void_t*)(smem + NSA * A_STAGE + stage_b * B_STAGE + (j * NW + wave) * 8 * BK), 16, 0, 0);
     }
   };
@@ -467,12 +477,11 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
 // be cut along K as choose_slices decides from the routing; slice 0 of a tile writes `y`, slice
 // z >= 1 its partial sums into `C` (see sliced_rows), which sum_sliced_kernel adds to y.  A separate
 // instantiation, so that the unsliced kernels keep their register allocation.
-template <int BN, bool GATEUP, typename OutT, bool SLICED>
-__global__ __launch_bounds__(256) void grouped_gemm_dlds_kernel(
-    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
+template <int BN, bool GATEUP, typename OutT, bool SLICED, bool SPREAD>
+__device__ __forceinline__ void dlds_tile(
+    uint16_t* smem, const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
     const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, OutT* __restrict__ C,
     int n_col_blocks, OutT* __restrict__ y, int max_slices, const RowMap rows) {
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[kLdsBytes / 2];
   int nk = K / BK, kt0 = 0, cls;
   OutT* out = C;
   TileCoord tc;
@@ -492,23 +501,40 @@ __global__ __launch_bounds__(256) void grouped_gemm_dlds_kernel(
     if (!find_tile(expert_offsets, n_local, n_col_blocks, blockIdx.x, cls, tc)) return;
   }
   if (cls == 0)
-    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
   else if (cls == 1)
-    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
   else
-    gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+}
+
+template <int BN, bool GATEUP, typename OutT, bool SLICED>
+__global__ __launch_bounds__(256) void grouped_gemm_dlds_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
+    const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, OutT* __restrict__ C,
+    int n_col_blocks, OutT* __restrict__ y, int max_slices, const RowMap rows) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kLdsBytes / 2];
+  dlds_tile<BN, GATEUP, OutT, SLICED, false>(smem, A, expert_offsets, n_local, cap_rows, B0, B1, n_out, K, C, n_col_blocks, y, max_slices, rows);
+}
+// ... gate/up projection with its tiles' walks over K spread out (see gemm_tile and spread_k)
+template <int BN>
+__global__ __launch_bounds__(256) void grouped_gemm_spread_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
+    const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, uint16_t* __restrict__ C,
+    int n_col_blocks, uint16_t* __restrict__ y, int max_slices, const RowMap rows) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kLdsBytes / 2];
+  dlds_tile<BN, true, uint16_t, false, true>(smem, A, expert_offsets, n_local, cap_rows, B0, B1, n_out, K, C, n_col_blocks, y, max_slices, rows);
 }
 
 // The same GEMM with tall row blocks (RowBlocks in unit_list.hpp), bound: bf16 MFMA at the power limit, like the
 // 256-row tile (1088 rows per expert, four tiles of 272: gate/up 1397 TFLOP/s, four of 256 1411; with remainder tiles
 // 1226).  A kernel of its own: the additional variants would cost the one above registers.  Its 256-row tiles are no
 // faster than that one's (gate/up at 1024 rows per expert 1363 us, there 1353), so a launch without tall blocks runs there.
-template <int BN, bool GATEUP, typename OutT, bool SLICED>
-__global__ __launch_bounds__(256) void grouped_gemm_tall_kernel(
-    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
+template <int BN, bool GATEUP, typename OutT, bool SLICED, bool SPREAD>
+__device__ __forceinline__ void tall_tile(
+    uint16_t* smem, const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
     const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, OutT* __restrict__ C,
     int n_col_blocks, OutT* __restrict__ y, int max_slices, const RowMap rows) {
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[kLdsBytes / 2];
   int nk = K / BK, kt0 = 0, cls;
   OutT* out = C;
   TileCoord tc;
@@ -560,22 +586,43 @@ __global__ __launch_bounds__(256) void grouped_gemm_tall_kernel(
     }
   }
   if (cls == 0 && tc.nx == 0)
-    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 0, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 0, true, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out,
+                                                                         rows);
   else if (cls == 0 && tc.nx == 1)
-    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 1, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 1, true, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out,
+                                                                         rows);
   else if (cls == 0 && tc.nx == 2)
-    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 2, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 2, true, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out,
+                                                                         rows);
   else if (cls == 0)
-    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 3, true>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 3, true, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out,
+                                                                         rows);
   else if (cls == 1)
-    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
   else
     for (;;) {
-      gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+      gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
       tc.row0 += 64;
       if (tc.row0 >= tc.row_end) break;  // a 64-row tile proper is its expert's last
       __syncthreads();                   // before the next one refills the LDS stages
     }
+}
+
+template <int BN, bool GATEUP, typename OutT, bool SLICED>
+__global__ __launch_bounds__(256) void grouped_gemm_tall_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
+    const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, OutT* __restrict__ C,
+    int n_col_blocks, OutT* __restrict__ y, int max_slices, const RowMap rows) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kLdsBytes / 2];
+  tall_tile<BN, GATEUP, OutT, SLICED, false>(smem, A, expert_offsets, n_local, cap_rows, B0, B1, n_out, K, C, n_col_blocks, y, max_slices, rows);
+}
+template <int BN>
+__global__ __launch_bounds__(256) void grouped_gemm_spread_tall_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
+    const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, uint16_t* __restrict__ C,
+    int n_col_blocks, uint16_t* __restrict__ y, int max_slices, const RowMap rows) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kLdsBytes / 2];
+  tall_tile<BN, true, uint16_t, false, true>(smem, A, expert_offsets, n_local, cap_rows, B0, B1, n_out, K, C, n_col_blocks, y, max_slices, rows);
 }
 
 // The same GEMM on the work list of unit_list_even.hpp: every tile is 160 rows x 256 weight rows, four

@@ -193,10 +193,17 @@ class ExpertShardLayer:
             hint = 0
             if sh and self.overlap_shared:
                 hint = routed_hint_beside_shared(self.ffn_shard, self.shared_shard, T)
-                if hint == B.MOE_FFN_TILED and B.moe_debug_flow(T * self.k, self.ffn_shard):
-                    # its streaming workgroups stay, too: room for the shared expert's tiles instead (333 tokens of
-                    # Qwen1.5-MoE: 268 us tiled, 252 with room)
+                # Up to about 64 rows per expert (128 on long rows) the kernel whose weight stream never stops is the
+                # faster one also beside the shared expert's tiles, with room left for them; from there on its workgroups,
+                # which stay for the whole launch, keep the tiles from filling in.  Tiled / with room, us: Qwen1.5-MoE 333
+                # tokens 270 / 260, 600: 302 / 292, 800: 313 / 321, 1200: 347 / 357, 2000: 412 / 424; Qwen2-57B 450: 932 /
+                # 888, 1000: 1164 / 1131.
+                rows = B.moe_debug_flow_rows(T * self.k, self.ffn_shard)
+                if hint == B.MOE_FFN_TILED and 0 < rows <= (128 if self.H >= 3072 else 64):
                     hint = B.MOE_FFN_LEAVE_ROOM
+                # nor in two row passes (Qwen2-57B TP=4 2107 tokens 630 / 671; in one, Qwen1.5 EP=2 2000: 326 / 304)
+                elif hint == B.MOE_FFN_LEAVE_ROOM and rows == 160 and T * self.k > 165 * self.E:
+                    hint = B.MOE_FFN_TILED
             plan = _Plan(B.moe_ffn_workspace_bytes(T * self.k, self.ffn_shard),
                          B.moe_ffn_workspace_bytes(T, self.shared_shard) if sh else 0, hint, self.gathers(T))
             if len(self._plans) >= 256:

@@ -18,7 +18,13 @@ def test_when_it_runs():
     assert B.moe_debug_flow(64, mixtral) == B.DEBUG_FLOW_DOWN        # 8 rows per expert, 14 planned
     assert B.moe_debug_flow(128, mixtral) == BOTH
     assert B.moe_debug_flow(848, mixtral) == BOTH                    # 106 rows per expert, 127 planned
-    assert B.moe_debug_flow(860, mixtral) == 0                       # 128 planned and a few more
+    assert B.moe_debug_flow_rows(848, mixtral) == 128 and B.moe_debug_flow_rows(860, mixtral) == 160
+    assert B.moe_debug_flow(1120, mixtral) == BOTH                   # 140, 164 planned
+    assert B.moe_debug_flow(1140, mixtral) == 0
+    assert B.moe_debug_flow(2160, mixtral) == B.DEBUG_FLOW_DOWN      # 270: two passes of 160, for the down projection
+    tp8 = B.make_shard(8, 8, 0, 4096, 14336, 1792)
+    assert B.moe_debug_flow(2160, tp8) == BOTH                       # and where 112 tall tiles would fill less than half a round
+    assert B.moe_debug_flow(2800, tp8) == 0
     one = B.make_shard(8, 1, 0, 4096, 14336, 14336)
     assert B.moe_debug_flow(256, one) == B.DEBUG_FLOW_GATEUP         # 256 output strips of the down projection: one each
     assert B.moe_debug_flow(0, one) == 0
@@ -44,6 +50,9 @@ CASES = [
     (15, 2048, 704, 20, [16, 17, 0, 64, 65]),
     # 128-row tiles
     (24, 1024, 704, 90, [128, 129, 0, 1, 257, 127]),
+    # 160-row tiles: one pass and a few rows more, and two passes
+    (24, 1024, 704, 130, [160, 161, 0, 1, 320, 159]),
+    (24, 1024, 704, 265, [320, 321, 0, 480, 1, 290]),
     # three k-tiles: the loaders are more than a tile ahead
     (64, 1536, 192, 10, [0, 0, 33, 64, 65, 1]),
     (64, 1536, 192, 80, [0, 128, 129, 1]),
@@ -64,7 +73,7 @@ def test_against_oracle(n, H, I_s, avg, special, gather):
     R = int(offs[-1])
     cap = R + 5
     shard = B.make_shard(n, n, 0, H, I_s, I_s)
-    assert B.moe_debug_flow(cap, shard) == BOTH
+    assert B.moe_debug_flow(cap, shard) & B.DEBUG_FLOW_DOWN
     wg, wu, wd = I.make_expert_weights(4, I.MoEShape("f", H, n, 1, I_s, True))
     k = 2
     T = (cap + k - 1) // k
@@ -113,3 +122,27 @@ def test_tiles_from_the_counter_give_the_same_bits():
             layer.y_perm.fill_(float("nan"))
             assert torch.equal(layer.forward(x), want)
         del layer._plan
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,I_s,counts", [
+    (2048, 192, [300, 129, 64, 1, 0, 255]),            # tiles of all heights
+    (4096, 128, [257, 40, 511]),
+    (2048, 1024, [260] * 40 + [300, 1, 256, 0, 401]),  # with tall row blocks
+])
+def test_walks_over_k_that_begin_apart(H, I_s, counts):
+    """Tiled gate/up projections on rows of a multiple of 4 KB start K at an eighth that depends on the XCD; tolerance as above."""
+    n = len(counts)
+    offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    R = int(offs[-1])
+    shard = B.make_shard(n, n, 0, H, I_s, I_s)
+    wg, wu, wd = I.make_expert_weights(6, I.MoEShape("f", H, n, 1, I_s, True))
+    x = I.make_x(7, R, H)
+    ref = O.expert_ffn(x, offs, wg, wu, wd)
+    h = torch.empty((R, I_s), dtype=torch.bfloat16, device="cuda")
+    y = torch.empty((R, H), device="cuda")
+    ws = torch.empty(max(B.moe_ffn_workspace_bytes(R, shard), 256), dtype=torch.uint8, device="cuda")
+    B.moe_expert_ffn(bf16_tensor(x), torch.from_numpy(offs).cuda(), R, shard, bf16_tensor(wg), bf16_tensor(wu),
+                     bf16_tensor(wd), h, y, ws, B.MOE_FFN_TILED)
+    got = y.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(got - ref) / np.linalg.norm(ref) < 5e-3
