@@ -263,11 +263,12 @@ inline WalkPlan plan_for(int K, int mt, bool down = false) {
         if (steps32 == 16 * st) return WalkPlan{16, st, 1};
     }
     const int nws[2] = {8, 4};
-    const int cand[7] = {16, 14, 11, 10, 8, 7, 5};
+    const int cand[8] = {16, 14, 11, 10, 8, 7, 5, 2};
     for (int nw : nws)
       for (int st : cand) {
-        // instantiated: (8,16) (8,14) (8,11) (8,10) (8,8) (8,7) (8,5) (4,11) (4,10) (4,8) (4,5)
+        // instantiated: (8,16) (8,14) (8,11) (8,10) (8,8) (8,7) (8,5) (8,2) (4,11) (4,10) (4,8) (4,5)
         if (nw == 4 && !(st == 11 || st == 10 || st == 8 || st == 5)) continue;
+        if (st == 2 && steps32 != 16) continue;
         if (steps32 % (nw * st) == 0) return WalkPlan{nw, st, steps32 / (nw * st)};
       }
   }
