@@ -215,12 +215,23 @@ int moe_forward(moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard
     if (st != MOE_OK) return error(MOE_STEP_COMBINE, st);
   }
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t err = moe::launch_route_topk(a->x_bf16, a->w_router, a->logits, a->T, H, shard->n_experts, a->k,
-                                          a->route_flags, a->topk_idx, a->topk_w, s);
-  if (err != hipSuccess) return error(MOE_STEP_ROUTE, MOE_ERR_HIP);
   int32_t* const tickets = moe::permute_tickets(a->workspace, a->T, a->k, shard->n_local_experts);
-  err = moe::launch_permute(a->x_bf16, a->topk_idx, a->T, a->k, H, shard->n_local_experts, shard->expert_offset, a->x_perm,
-                            a->expert_offsets, a->row_src, a->slot_row, a->workspace, s, tickets);
+  const int32_t E = shard->n_experts;
+  const bool own_logits = moe::route_has_logits_kernel(a->T, H, E, a->route_flags);
+  hipError_t err = hipSuccess;
+  if ((own_logits || (a->route_flags & MOE_LOGITS_GIVEN)) && moe::route_permute_fits(a->T, a->k, E)) {
+    if (own_logits) err = moe::launch_route_logits(a->x_bf16, a->w_router, a->logits, a->T, H, E, s);
+    if (err != hipSuccess) return error(MOE_STEP_ROUTE, MOE_ERR_HIP);
+    err = moe::launch_route_permute(a->logits, a->T, E, a->k, a->route_flags, a->topk_idx, a->topk_w, a->x_bf16, H,
+                                    shard->n_local_experts, shard->expert_offset, a->x_perm, a->expert_offsets, a->row_src,
+                                    a->slot_row, s, tickets);
+  } else {
+    err = moe::launch_route_topk(a->x_bf16, a->w_router, a->logits, a->T, H, E, a->k, a->route_flags, a->topk_idx, a->topk_w,
+                                 s);
+    if (err != hipSuccess) return error(MOE_STEP_ROUTE, MOE_ERR_HIP);
+    err = moe::launch_permute(a->x_bf16, a->topk_idx, a->T, a->k, H, shard->n_local_experts, shard->expert_offset, a->x_perm,
+                              a->expert_offsets, a->row_src, a->slot_row, a->workspace, s, tickets);
+  }
   if (err != hipSuccess) return error(MOE_STEP_PERMUTE, MOE_ERR_HIP);
   err = moe::launch_expert_ffn(rows, gather ? moe::RowMap{a->row_src, a->k} : moe::RowMap{nullptr, 1}, a->expert_offsets,
                                cap_rows, moe::expected_rows(cap_rows, ffn_shard), ffn_shard->n_local_experts, H,

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "moe_shard.h"
 
 namespace moe {
@@ -28,10 +30,31 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) { return pack_bf16x2(f, 0.f) & 0xFFFFu; }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+// Reduction over the 64 lanes, every lane gets it: lanes 32, 16, 8, 4, 2 and 1 apart in this order.  Row swaps and
+// data-parallel moves, a few cycles each where a shuffle is a trip through the LDS crossbar.  (4 apart by a rotation
+// within 16 lanes: the values repeat every 8 lanes there.)
+template <typename Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const auto half = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(half[0]), __uint_as_float(half[1]));
+  const auto row = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(row[0]), __uint_as_float(row[1]));
+  const auto move = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  v = op(v, move(v, std::integral_constant<int, 0x128>{}));  // row_ror:8
+  v = op(v, move(v, std::integral_constant<int, 0x124>{}));  // row_ror:4
+  v = op(v, move(v, std::integral_constant<int, 0x4E>{}));   // quad_perm 2,3,0,1
+  v = op(v, move(v, std::integral_constant<int, 0xB1>{}));   // quad_perm 1,0,3,2
+#endif
   return v;
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  return wave_reduce(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 // Where the rows of the first GEMM come from: row r of the input is x[row_src[r] / k] (the token of
@@ -45,10 +68,19 @@ struct RowMap {
 // launchers (each returns hipGetLastError() after enqueueing on `stream`)
 hipError_t launch_route_topk(const void* x, const float* w_router, float* logits, int T, int H, int E, int k,
                              uint32_t flags, int32_t* topk_idx, float* topk_w, hipStream_t stream);
+// Whether launch_route_topk of such a call computes the logits in a kernel of their own, and that kernel alone.
+bool route_has_logits_kernel(int T, int H, int E, uint32_t flags);
+hipError_t launch_route_logits(const void* x, const float* w_router, float* logits, int T, int H, int E, hipStream_t stream);
 hipError_t launch_permute(const void* x, const int32_t* topk_idx, int T, int k, int H, int n_local, int offset,
                           void* x_perm, int32_t* expert_offsets, int32_t* row_src, int32_t* slot_row,
                           void* workspace, hipStream_t stream, int32_t* tickets = nullptr);
 size_t permute_workspace_bytes(int T, int k, int n_local);
+// launch_route_topk and launch_permute of a small batch whose logits are given (or already computed), in one kernel:
+// whether it takes them (nothing is enqueued if not).
+bool route_permute_fits(int T, int k, int E);
+hipError_t launch_route_permute(const float* logits, int T, int E, int k, uint32_t flags, int32_t* topk_idx, float* topk_w,
+                                const void* x, int H, int n_local, int offset, void* x_perm, int32_t* expert_offsets,
+                                int32_t* row_src, int32_t* slot_row, hipStream_t stream, int32_t* tickets);
 // Words at the end of that workspace for launch_permute to clear as `tickets` (kTickets of them): the counters the GEMM
 // kernels of the same forward take their tiles from.
 constexpr int kTickets = 2;

@@ -2,8 +2,9 @@
 // softmax over all experts, k largest logits per token with ties going to the lower expert id.
 //
 // One wavefront per token.  Logits of expert e live in lane (e % 64), register slot (e / 64),
-// so the selection is k wave-wide arg-max reductions and the softmax one wave-wide sum.
+// so the selection (select_topk.hpp) is k wave-wide maxima and the softmax one wave-wide sum.
 #include "moe_internal.hpp"
+#include "select_topk.hpp"
 
 namespace moe {
 namespace {
@@ -11,60 +12,6 @@ namespace {
 constexpr int kRouteThreads = 256;
 constexpr int kTokPerBlock = kRouteThreads / kWave;
 constexpr int kExpChunk = 8;  // experts accumulated per pass over the token's row
-
-// Top-K selection and gate weights of one token by one wavefront.  myl[s] holds the logit of
-// expert lane + 64*s (-inf past E).  k rounds of wave-wide arg-max on (logit desc, expert id asc),
-// then softmax over all E logits evaluated at the selected ones.
-template <int EPL>
-__device__ __forceinline__ void select_topk(const float (&myl)[EPL], int lane, int E, int k, uint32_t flags,
-                                            int32_t* __restrict__ idx_out, float* __restrict__ w_out) {
-  uint32_t taken = 0;  // bit s set: this lane's slot s already selected
-  float sel_v = 0.f;
-  int sel_i = 0;
-  float vmax = 0.f;
-  for (int j = 0; j < k; ++j) {
-    float bv = -INFINITY;
-    int bi = 0x7FFFFFFF;
-#pragma unroll
-    for (int s = 0; s < EPL; ++s) {
-      const int e = lane + s * kWave;
-      if (e < E && !(taken & (1u << s)) && (myl[s] > bv || bi == 0x7FFFFFFF)) {
-        bv = myl[s];
-        bi = e;
-      }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, kWave);
-      const int oi = __shfl_xor(bi, o, kWave);
-      const bool take = (oi != 0x7FFFFFFF) && (bi == 0x7FFFFFFF || ov > bv || (ov == bv && oi < bi));
-      if (take) {
-        bv = ov;
-        bi = oi;
-      }
-    }
-    if ((bi & 63) == lane) taken |= 1u << (bi >> 6);
-    if (j == 0) vmax = bv;
-    if (lane == j) {
-      sel_v = bv;
-      sel_i = bi;
-    }
-  }
-  // softmax denominator over all E experts (max logit is the first selected one)
-  float part = 0.f;
-#pragma unroll
-  for (int s = 0; s < EPL; ++s) {
-    const int e = lane + s * kWave;
-    if (e < E) part += expf(myl[s] - vmax);
-  }
-  const float denom_all = wave_sum(part);
-  const float num = (lane < k) ? expf(sel_v - vmax) : 0.f;
-  const float denom_sel = wave_sum(num);
-  if (lane < k) {
-    idx_out[lane] = sel_i;
-    w_out[lane] = num / ((flags & MOE_RENORM_TOPK) ? denom_sel : denom_all);
-  }
-}
 
 template <int EPL>  // expert slots per lane: ceil(E / 64)
 __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
@@ -274,6 +221,17 @@ void launch_logits(const uint16_t* x, const float* w_router, float* logits, int 
 
 }  // namespace
 
+bool route_has_logits_kernel(int T, int H, int E, uint32_t flags) {
+  return !(flags & MOE_LOGITS_GIVEN) && H % 32 == 0 && E > 16 && T <= 1024;
+}
+hipError_t launch_route_logits(const void* x, const float* w_router, float* logits, int T, int H, int E,
+                               hipStream_t stream) {
+  hipLaunchKernelGGL((router_logits_kernel<1, 16, 4, false>), dim3((T + kLogitTok - 1) / kLogitTok, (E + 15) / 16),
+                     dim3(16 * 64), 0, stream, static_cast<const uint16_t*>(x), w_router, logits, T, H, E, 0, 0u,
+                     static_cast<int32_t*>(nullptr), static_cast<float*>(nullptr));
+  return hipGetLastError();
+}
+
 hipError_t launch_route_topk(const void* x, const float* w_router, float* logits, int T, int H, int E, int k,
                              uint32_t flags, int32_t* topk_idx, float* topk_w, hipStream_t stream) {
   if (T == 0) return hipSuccess;
@@ -288,7 +246,7 @@ hipError_t launch_route_topk(const void* x, const float* w_router, float* logits
                          topk_idx, topk_w);
       return hipGetLastError();
     }
-    if (nt < 2 || T > 1024) {  // logits by MFMA and the selection from the logits tile, in one kernel
+    if (!route_has_logits_kernel(T, H, E, flags)) {  // logits by MFMA and the selection from the logits tile, in one kernel
       if (nt <= 1) launch_logits<1, 16, 4>(xs, w_router, logits, T, H, E, k, flags, topk_idx, topk_w, stream);
       else if (nt <= 2) launch_logits<2, 16, 4>(xs, w_router, logits, T, H, E, k, flags, topk_idx, topk_w, stream);
       else if (nt <= 4) launch_logits<4, 16, 2>(xs, w_router, logits, T, H, E, k, flags, topk_idx, topk_w, stream);
@@ -298,9 +256,7 @@ hipError_t launch_route_topk(const void* x, const float* w_router, float* logits
     }
     // up to 1024 tokens and more than 16 experts: one workgroup per (16 tokens, 16 experts), then select
     // from the logits (measured at 60 experts: 11 against 21 us at 256 and 1024 tokens, 31 against 24 us at 4096)
-    hipLaunchKernelGGL((router_logits_kernel<1, 16, 4, false>), dim3((T + kLogitTok - 1) / kLogitTok, nt),
-                       dim3(16 * 64), 0, stream, xs, w_router, logits, T, H, E, k, flags, topk_idx, topk_w);
-    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    if (launch_route_logits(x, w_router, logits, T, H, E, stream) != hipSuccess) return hipErrorLaunchFailure;
     flags |= MOE_LOGITS_GIVEN;
   }
   const int epl = (E + kWave - 1) / kWave;

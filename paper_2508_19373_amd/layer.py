@@ -72,6 +72,7 @@ class _Plan(NamedTuple):
     ffn_ws_sh: int
     hint: int
     gather: bool
+    routed_first: bool
 
 
 class ExpertShardLayer:
@@ -183,6 +184,22 @@ class ExpertShardLayer:
         return bool(B.moe_debug_ffn_plan(T * self.k, self.ffn_shard)[0] or
                     B.moe_debug_flow(T * self.k, self.ffn_shard) & B.DEBUG_FLOW_GATEUP)
 
+    def _weight_bytes(self):
+        """Bytes of the routed and of the shared experts' matrices on this device."""
+        return 6 * self.w_gate.numel(), 6 * self.shared[0].numel()
+
+    def _shared_tiled(self, T):
+        return not all(B.moe_debug_ffn_plan(T, self.shared_shard)[:2])
+
+    def _routed_first(self, T) -> bool:
+        """Whether a graph holds the routed experts' branch first (see forward).  Not before a shared expert of several
+        hundred MB, which fills the time of the router and the permutation, nor before a tiled one that ends last (the
+        routed experts few, or the tokens many).  Routed / shared first, us: Qwen1.5-MoE 128 tokens 245 / 256, TP=4 16 tokens 85 / 87,
+        TP=8 100 tokens 85 / 94, Qwen2-57B TP=2 EP=2 48 tokens 246 / 257; unsharded (440 MB) 16 tokens 644 / 628; Qwen1.5
+        TP=2 EP=4 (130 MB routed) 16 tokens 60 / 62, 128: 93 / 84, TP=4 200: 121 / 111."""
+        routed, shared = self._weight_bytes()
+        return shared <= 256e6 and (not self._shared_tiled(T) or (routed >= 135e6 and T <= 160))
+
     def _plan(self, T) -> "_Plan":
         """What a forward of T tokens needs to know about itself: a function of T, the shards and the switches,
         kept per token count (at most 256 of them)."""
@@ -199,13 +216,20 @@ class ExpertShardLayer:
                 # tokens 270 / 260, 600: 302 / 292, 800: 313 / 321, 1200: 347 / 357, 2000: 412 / 424; Qwen2-57B 450: 932 /
                 # 888, 1000: 1164 / 1131.
                 rows = B.moe_debug_flow_rows(T * self.k, self.ffn_shard)
+                routed, shared = self._weight_bytes()
                 if hint == B.MOE_FFN_TILED and 0 < rows <= (128 if self.H >= 3072 else 64):
                     hint = B.MOE_FFN_LEAVE_ROOM
                 # nor in two row passes (Qwen2-57B TP=4 2107 tokens 630 / 671; in one, Qwen1.5 EP=2 2000: 326 / 304)
                 elif hint == B.MOE_FFN_LEAVE_ROOM and rows == 160 and T * self.k > 165 * self.E:
                     hint = B.MOE_FFN_TILED
+                # nor beside as much shared weight as there is routed: those tiles are half of the work, and the two calls
+                # interleave tile by tile (Qwen2-57B EP=8, 48 / 128 / 256 tokens 192 / 216 / 240 tiled, 214 / 226 / 270)
+                # (or, from 160 tokens on, beside as few: Qwen1.5 TP=2 EP=4 256 tokens 92 / 96)
+                if hint != 0 and rows > 0 and (2 * shared >= routed or (routed < 135e6 and T > 160)):
+                    hint = B.MOE_FFN_TILED
             plan = _Plan(B.moe_ffn_workspace_bytes(T * self.k, self.ffn_shard),
-                         B.moe_ffn_workspace_bytes(T, self.shared_shard) if sh else 0, hint, self.gathers(T))
+                         B.moe_ffn_workspace_bytes(T, self.shared_shard) if sh else 0, hint, self.gathers(T),
+                         sh and self._routed_first(T))
             if len(self._plans) >= 256:
                 self._plans.clear()
             self._plans[key] = plan
@@ -253,12 +277,22 @@ class ExpertShardLayer:
                 raise ValueError("overlap_shared works on torch's current stream only")
             main = torch.cuda.current_stream()
             self._side.wait_stream(main)          # x (and sh_offsets) are ready where main stands now
-            # a streaming shared expert leaves 16 compute units free, so that the router and the
-            # permutation on the main stream, each a workgroup or two on the critical path, start
-            # at once instead of waiting for a resident workgroup to finish (-2 to -3.5 % at 16 to 64 tokens)
-            B.moe_expert_ffn(x, sh_offsets, T, self.shared_shard, self.shared[0], self.shared[1], self.shared[2],
-                             self.h_sh, self.y_shared, self.ffn_ws_sh, yflag | B.MOE_FFN_LEAVE_ROOM, self._side)
-            B.moe_forward(args, self.shard, self.ffn_shard, main)
+            def shared():
+                # a streaming shared expert leaves 16 compute units free, so that the router and the
+                # permutation on the main stream, each a workgroup or two on the critical path, start
+                # at once instead of waiting for a resident workgroup to finish (-2 to -3.5 % at 16 to 64 tokens)
+                B.moe_expert_ffn(x, sh_offsets, T, self.shared_shard, self.shared[0], self.shared[1], self.shared[2],
+                                 self.h_sh, self.y_shared, self.ffn_ws_sh, yflag | B.MOE_FFN_LEAVE_ROOM, self._side)
+
+            # Eager, the shared expert first: it starts while the host enqueues the others.  A graph runs its branches in the
+            # order of their first kernels and the combine on the first one's queue, so there the routed experts, where they
+            # end last, come first: a queue waits 10 us for another one's kernel.
+            if torch.cuda.is_current_stream_capturing() and plan.routed_first:
+                B.moe_forward(args, self.shard, self.ffn_shard, main)
+                shared()
+            else:
+                shared()
+                B.moe_forward(args, self.shard, self.ffn_shard, main)
             main.wait_stream(self._side)
         else:
             B.moe_forward(args, self.shard, self.ffn_shard, stream)
