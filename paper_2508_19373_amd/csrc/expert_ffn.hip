@@ -380,7 +380,8 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
 // 66), and gate/up projections whose tall tiles leave most of a round idle (estimated; 30 experts of Qwen1.5 270: 124 / 117, its
 // TP=2 slice 136 / 118, Mixtral TP=8 99 / 78, Qwen2-57B TP=2 EP=2 201 / 188; not Qwen1.5 214 / 229, Mixtral TP=4 142 / 149).
 // Where it does not pay: too few output strips of 16 columns to keep 256 workgroups in tiles (a single expert's down
-// projection: Mixtral EP=8 (256 strips) 33 / 67, EP=4 (512) 52 / 73; 1024 strips 94 / 89) or, with 16 rows and fewer, to beat
+// projection: Mixtral EP=8 (256 strips) 33 / 67, EP=4 (512) 52 / 73; 1024 strips 94 / 89, but with more than
+// 64 rows, where a k-tile's MFMAs want wide tiles, 110 / 169; 1792 strips 50 / 42) or, with 16 rows and fewer, to beat
 // the streaming kernel (Qwen2-57B's shared expert under TP=8, 160 strips, 8 rows 14.7 / 19.5; the tiny layer, K = 512, 3 rows
 // 6.4 / 7.8).  Tiles of 256 weight rows from 4 gate/up strips per workgroup on (TP=4 slice of Mixtral, 7: 83 / 89 with 128; 8
 // experts of TP=8, 2.8: 24 / 22); the down projection's are the same within 2 %.
@@ -393,6 +394,11 @@ FlowPlan flow_plan(int cap_rows, int est_rows, int n_local, int n_out, int K, bo
   const double hi = planned_rows_hi(cap_rows, est_rows, n_local), avg = (double)est_rows / n_local;
   if (hi <= 16.0 && (strips < 448 || (gateup && K >= 4096 && bytes > 1e9))) return none;
   if (hi <= 64.0) return FlowPlan{64, gateup && strips >= 1024 ? 256 : 128};
+  if (!gateup && strips < 1700) return none;
+  // a few large experts of a batch that may be skewed: the popular one's last pass is mostly empty between these averages
+  // (Mixtral EP=4 under Zipf(1.2), layer, 200 / 308 tokens 202 / 206 tiled, 208 / 225; 400 and 450: 287 / 300, 254 / 280; smaller
+  // weights gain throughout, TP=4 EP=2 308 tokens 156 / 137)
+  if (est_rows < cap_rows && n_local < 8 && avg < 100.0 && bytes > (gateup ? 300e6 : 150e6)) return none;
   if (hi <= 128.0) return FlowPlan{128, 256};
   const bool exact = n_local == 1 && est_rows == cap_rows;
   if (avg + (exact ? 0.0 : 2.0 * sqrt(avg)) <= 165.0) return FlowPlan{160, 256};

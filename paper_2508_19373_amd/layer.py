@@ -220,7 +220,9 @@ class ExpertShardLayer:
                 if hint == B.MOE_FFN_TILED and 0 < rows <= (128 if self.H >= 3072 else 64):
                     hint = B.MOE_FFN_LEAVE_ROOM
                 # nor in two row passes (Qwen2-57B TP=4 2107 tokens 630 / 671; in one, Qwen1.5 EP=2 2000: 326 / 304)
-                elif hint == B.MOE_FFN_LEAVE_ROOM and rows == 160 and T * self.k > 165 * self.E:
+                # or with more rows than 64 on short slices (TP=8 482 tokens 202 / 209)
+                elif hint == B.MOE_FFN_LEAVE_ROOM and ((rows == 160 and T * self.k > 165 * self.E) or
+                                                       (rows > 64 and self.ffn_shard.inter_slice < 512)):
                     hint = B.MOE_FFN_TILED
                 # nor beside as much shared weight as there is routed: those tiles are half of the work, and the two calls
                 # interleave tile by tile (Qwen2-57B EP=8, 48 / 128 / 256 tokens 192 / 216 / 240 tiled, 214 / 226 / 270)
