@@ -155,8 +155,30 @@ __host__ __device__ inline ClassCounts count_tiles(const int32_t* __restrict__ e
   return c;
 }
 
+// Tile `local` of `m` row blocks by `ncb` column blocks of one expert: column blocks in order, inside a column block the
+// row blocks.  The 32 tiles an XCD runs at once read (row blocks + 32 / row blocks) panels, 12 with 4 to 8 of them, 24 with 22, so
+// 12 row blocks and more are cut into groups of up to 8, each with all column blocks.  Gate/up, us, in one group / so: K = 4096, one
+// expert of 32 row blocks 1398 / 1262, 23: 993 / 952, two of 16 1305 / 1277; Qwen2-57B's shared expert, 16 840 / 825; 8 experts
+// of 9 and 10 796 / 818 (groups of 5 and 4), hence not those.
+constexpr int kRowGroupFrom = 12, kRowGroup = 8;
+__host__ __device__ inline void tile_of(int local, int m, int ncb, int& nb, int& rb) {
+  int first = 0;
+  if (m >= kRowGroupFrom) {
+    const int groups = (m + kRowGroup - 1) / kRowGroup, small = m / groups, large = m - small * groups;  // `large` groups of small + 1
+    const int split = large * (small + 1) * ncb;
+    const bool back = local >= split;
+    if (back) local -= split;
+    const int size = small + (back ? 0 : 1), g = local / (size * ncb);
+    local -= g * size * ncb;
+    first = (back ? large * (small + 1) : 0) + g * size;
+    m = size;
+  }
+  nb = local / m;
+  rb = first + local - nb * m;
+}
+
 // Tile `idx` of height class `cls`: experts in order, inside an expert column blocks in order,
-// inside a column block the row blocks of that class (row block fastest, so neighbours share the
+// inside a column block the row blocks of that class (row block fastest, in groups where there are many, see tile_of, so neighbours share the
 // weight panel and a run of tiles covers all full row blocks of a few column blocks).
 __host__ __device__ inline TileCoord locate_tile(const int32_t* __restrict__ expert_offsets, int n_local,
                                                  int n_col_blocks, int cls, int idx, bool pad_low,
@@ -168,11 +190,12 @@ __host__ __device__ inline TileCoord locate_tile(const int32_t* __restrict__ exp
     const int mbs = cls == 0 ? rb.n256 : (cls == 1 ? rb.n128 : rb.n64);
     const int tiles = mbs * n_col_blocks;
     if (idx < tiles) {
+      int b;
+      tile_of(idx, mbs, n_col_blocks, t.nb, b);
       t.expert = e;
-      t.nb = idx / mbs;
       t.row_end = hi;
-      t.row0 = lo + (cls == 0 ? rb.start(idx % mbs) : (cls == 1 ? rb.n256 * 256 : rb.n256 * 256 + rb.n128 * 128));
-      t.nx = cls == 0 ? rb.extra(idx % mbs) : 0;
+      t.row0 = lo + (cls == 0 ? rb.start(b) : (cls == 1 ? rb.n256 * 256 : rb.n256 * 256 + rb.n128 * 128));
+      t.nx = cls == 0 ? rb.extra(b) : 0;
       return t;
     }
     idx -= tiles;
@@ -329,11 +352,13 @@ __host__ __device__ inline TileCoord locate_full_tile(const int32_t* __restrict_
     const int mbs = tail ? n256 - kept : kept;
     const int tiles = mbs * n_col_blocks;
     if (idx < tiles) {
+      int b;
+      tile_of(idx, mbs, n_col_blocks, t.nb, b);
+      if (tail) b += kept;
       t.expert = e;
-      t.nb = idx / mbs;
       t.row_end = hi;
-      t.row0 = lo + rb.start(idx % mbs + (tail ? kept : 0));
-      t.nx = rb.extra(idx % mbs + (tail ? kept : 0));
+      t.row0 = lo + rb.start(b);
+      t.nx = rb.extra(b);
       return t;
     }
     idx -= tiles;

@@ -43,8 +43,9 @@ __host__ __device__ inline TileCoord even_locate(const int32_t* __restrict__ exp
     const int mbs = even_blocks(hi - lo), tiles = mbs * n_col_blocks;
     if (idx < tiles) {
       t.expert = e;
-      t.nb = idx / mbs;
-      t.row0 = lo + (idx % mbs) * kEvenRows;
+      int b;
+      tile_of(idx, mbs, n_col_blocks, t.nb, b);
+      t.row0 = lo + b * kEvenRows;
       t.row_end = hi;
       return t;
     }

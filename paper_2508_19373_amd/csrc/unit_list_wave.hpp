@@ -163,13 +163,15 @@ __device__ inline TileCoord wave_locate(const WaveRouting& w, const int (&mbs)[k
   const int local = idx - wave_pick(pre, h) * n_col_blocks;
   // (the values are uniform by construction; reading them from the first lane tells the compiler so)
   t.expert = __builtin_amdgcn_readfirstlane(h.lane + 64 * h.j);
-  t.nb = __builtin_amdgcn_readfirstlane(local / m);
+  int rb;
+  tile_of(local, m, n_col_blocks, t.nb, rb);
+  t.nb = __builtin_amdgcn_readfirstlane(t.nb);
   if constexpr (TALL) {
-    const int b = wave_pick(base, h) + local % m, nt = wave_pick(w.nt, h), nx = wave_pick(w.nx, h);
+    const int b = wave_pick(base, h) + rb, nt = wave_pick(w.nt, h), nx = wave_pick(w.nx, h);
     t.row0 = __builtin_amdgcn_readfirstlane(lo + b * 256 + min(b, nt) * nx * 16);
     t.nx = __builtin_amdgcn_readfirstlane(b < nt ? nx : 0);
   } else {
-    t.row0 = __builtin_amdgcn_readfirstlane(lo + wave_pick(base, h) + (local % m) * block_rows);
+    t.row0 = __builtin_amdgcn_readfirstlane(lo + wave_pick(base, h) + rb * block_rows);
   }
   t.row_end = __builtin_amdgcn_readfirstlane(lo + wave_pick(w.rows, h));
   return t;

@@ -49,10 +49,10 @@ CASES = [
     # 64 x 128 for both, strips that do not divide by the tile
     (15, 2048, 704, 20, [16, 17, 0, 64, 65]),
     # 128-row tiles
-    (24, 1024, 704, 90, [128, 129, 0, 1, 257, 127]),
+    (28, 1024, 704, 90, [128, 129, 0, 1, 257, 127]),
     # 160-row tiles: one pass and a few rows more, and two passes
-    (24, 1024, 704, 130, [160, 161, 0, 1, 320, 159]),
-    (24, 1024, 704, 265, [320, 321, 0, 480, 1, 290]),
+    (28, 1024, 704, 130, [160, 161, 0, 1, 320, 159]),
+    (28, 1024, 704, 265, [320, 321, 0, 480, 1, 290]),
     # three k-tiles: the loaders are more than a tile ahead
     (64, 1536, 192, 10, [0, 0, 33, 64, 65, 1]),
     (64, 1536, 192, 80, [0, 128, 129, 1]),
@@ -146,3 +146,23 @@ def test_walks_over_k_that_begin_apart(H, I_s, counts):
                      bf16_tensor(wd), h, y, ws, B.MOE_FFN_TILED)
     got = y.cpu().numpy().astype(np.float64)
     assert np.linalg.norm(got - ref) / np.linalg.norm(ref) < 5e-3
+
+
+@pytest.mark.parametrize("blocks", [11, 12, 13, 16, 17, 23, 32, 40])
+def test_row_blocks_of_a_large_expert_in_groups(blocks):
+    """Every tile once; from 12 row blocks on, 32 neighbouring tiles on an XCD touch few row and column blocks together."""
+    ncb = 56
+    offs = np.array([0, 256 * blocks, 256 * blocks + 300], dtype=np.int32)
+    units = B.moe_debug_gemm_units(offs, int(offs[-1]), ncb)
+    full = [(b, u) for b, u in enumerate(units.tolist()) if u[0] == 256 and u[1] == 0]
+    seen = {(u[2] // 256, u[4]) for _, u in full}
+    assert len(full) == len(seen) == blocks * ncb and seen == {(r, c) for r in range(blocks) for c in range(ncb)}
+    windows = within = 0
+    for xcd in range(8):
+        mine = [(u[2] // 256, u[4]) for b, u in full if b % 8 == xcd]
+        for i in range(0, len(mine) - 32, 32):
+            rows, cols = ({t[j] for t in mine[i:i + 32]} for j in (0, 1))
+            windows += 1
+            # s row blocks and the column blocks that 32 tiles of them touch, s <= 8 in a group (11 alone: 11 + 4)
+            within += len(rows) <= (8 if blocks >= 12 else 11) and len(rows) + len(cols) <= (14 if blocks >= 12 else 15)
+    assert within >= 0.75 * windows          # the others lie across a change of groups
