@@ -1,6 +1,6 @@
-// Grouped "NT" GEMM for experts of a few dozen rows (gfx950), bound: HBM.
+// Grouped "NT" GEMM for experts of up to about 160 rows (gfx950), bound: HBM.
 //
-// Up to about a hundred rows per expert a grouped GEMM is bound by streaming every active expert's weights once.  One
+// Up to there a grouped GEMM is bound by streaming every active expert's weights once.  One
 // workgroup per tile (grouped_gemm.hpp) spends a fifth to a third of such a tile's time outside its k-loop: finding the
 // tile, filling the LDS stages, the epilogue and the gap to the next workgroup, during all of which its compute
 // unit has little or nothing in flight.  Here a workgroup stays and takes tile after tile, and the weight stream never stops:
@@ -12,6 +12,9 @@
 //    done with the one before, whose stages the loaders refill behind it;
 //  * the multipliers' first wavefront looks up tiles ahead of time and leaves them (coordinates, source rows) in a
 //    ring of slots in LDS, from the prefix of tiles per expert computed once per workgroup;
+//  * an expert's row passes are of one height and multiply the 32-row pairs of blocks that hold rows, no more (skewed
+//    batches: Mixtral EP=2 under Zipf(1.2), 450 tokens, layer 429 -> 419 us, the cold shard of Qwen2-57B TP=2 EP=2 at 1000 404 ->
+//    392; equal where all passes are full);
 //  * tiles are taken from a counter where the caller has one (cleared by an earlier kernel of the same stream), so that a
 //    workgroup that starts late, behind another stream's kernel, takes fewer; else dealt round-robin.
 // Nothing waits for another workgroup.
@@ -66,7 +69,7 @@ struct Shape {
 };
 
 struct Slot {
-  int expert, row0, row_end;  // expert < 0: no more tiles
+  int expert, row0, row_end;  // expert < 0: no more tiles; row_end - row0 <= BM
   int strip0, strips;         // its 16-column output strips
   int kt0;                    // the k-tile its walk over K begins with
 };
@@ -92,7 +95,7 @@ __device__ inline void buf_to_lds(buf_t, lds_void_t*, uint32_t, uint32_t) {}
 // 68 (5.1); TP=4 slice of Mixtral, 14 rows, 96 -> 83 (5.7) and 52 -> 45; against one workgroup per 64-row tile and the
 // streaming kernel.  About 5 us of a launch are not the stream: start, first look-up, first and last tile.
 // grid = any number of workgroups (one per compute unit); GATEUP: B0 = gate, B1 = up, C = h (bf16); else B0 = down.
-// Requires K % 64 == 0, K >= 256 and n_out % 16 == 0.
+// Requires K % 64 == 0, 192 <= K <= 2^21 and n_out % 16 == 0.
 template <int BM, int BN, bool GATEUP, typename OutT>
 __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
     const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
@@ -148,12 +151,13 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
     const int e = before - 1;  // the last expert that starts at or before it
     const int lo = expert_offsets[e], hi = expert_offsets[e + 1];
     const int local = id - __builtin_amdgcn_readfirstlane(s_pre[e]) * ncb;
-    const int passes = (hi - lo + BM - 1) / BM;
+    // the row passes of an expert are of one height, and multiply no more than that: an expert of 215 rows is two passes of 112
+    const int passes = (hi - lo + BM - 1) / BM, height = ((hi - lo + passes - 1) / passes + 15) & ~15;
     const int nb = local / passes;
     s.expert = e;
     s.strip0 = nb * strips / ncb;
     s.strips = (nb + 1) * strips / ncb - s.strip0;
-    s.row0 = lo + (local - nb * passes) * BM;
+    s.row0 = lo + (local - nb * passes) * height;
     // The walk over K begins at one of 8 or 16 places: workgroups that all stand at the same k read the same 128 bytes of
     // rows 4 or 8 KB apart, which fall on a few of the memory channels (gate/up of Qwen1.5-MoE, K = 2048, 22 rows per expert
     // 138 us from k = 0, 125 from 16 places; TP=4 slice of Mixtral, K = 4096, 94 and 83; K = 1408 and 3584 no
@@ -161,7 +165,7 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
     // for an XCD's tiles where they share so many rows' activations in its L2 that these should be walked together
     // (Qwen1.5-MoE, 90 rows: 139 us from 8 places, 152 from 16).
     s.kt0 = BM >= 128 ? xcd * nk / gg::kNumXcd : (xcd * 2 + (nb & 1)) * nk / (2 * gg::kNumXcd);
-    s.row_end = hi;
+    s.row_end = min(hi, s.row0 + height);
   };
   // source rows of a tile's rows, the last valid one behind its end
   auto source_row = [&](const Slot& s, int r) { return rows(min(s.row0 + r, s.row_end - 1)); };
@@ -224,10 +228,12 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
       const int sl = t & (kSlots - 1);
       more_a = __builtin_amdgcn_readfirstlane(s_slot[sl].expert) >= 0;
       ca = __builtin_amdgcn_readfirstlane(s_slot[sl].kt0);
+      const int live = (__builtin_amdgcn_readfirstlane(s_slot[sl].row_end - s_slot[sl].row0) + 31) & ~31;
 #pragma unroll
       for (int j = 0; j < S::A_INST; ++j) {
-        const int r = (j * kLoad + w) * 8 + dma_row;
-        a_src[j] = A + (size_t)s_row[sl][r] * K + dma_chunk * 8;
+        // rows that are not multiplied: one 16-byte piece for the whole instruction
+        const int r = (j * kLoad + w) * 8 + dma_row, chunk = (j * kLoad + w) * 8 < live ? dma_chunk : 0;
+        a_src[j] = A + (size_t)s_row[sl][r] * K + chunk * 8;
       }
     };
     auto open_b = [&](int t) {
@@ -312,6 +318,7 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
     cur.row_end = __builtin_amdgcn_readfirstlane(s_slot[t & (kSlots - 1)].row_end);
     cur.strip0 = __builtin_amdgcn_readfirstlane(s_slot[t & (kSlots - 1)].strip0);
     cur.strips = __builtin_amdgcn_readfirstlane(s_slot[t & (kSlots - 1)].strips);
+    const int pairs = (cur.row_end - cur.row0 + 31) >> 5;  // of 16-row blocks that hold rows
     f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -327,19 +334,38 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           bfr[j][ks] = *reinterpret_cast<const bf16x8*>(pb + lds_off(wave * (BN / kMul) + j * 16 + lrow, ks * 4 + kq));
+      // Pairs of 16-row blocks, as many as hold rows; a pair's operands are read in front of the MFMAs of the one before.
+      // (A version of the whole k-tile per height spills: the accumulators change registers between them.)
+      static_assert(TM % 2 == 0, "row blocks in pairs");
+      bf16x8 af[2][2][2];
+      auto read_pair = [&](auto p_tag) {
+        constexpr int p = decltype(p_tag)::value;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        bf16x8 af[2];
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-          af[ks] = *reinterpret_cast<const bf16x8*>(pa + lds_off(i * 16 + lrow, ks * 4 + kq));
-        // weights as the MFMA "A" operand: a lane ends up with 4 consecutive output columns of one row
+          for (int ks = 0; ks < 2; ++ks)
+            af[p & 1][h][ks] = *reinterpret_cast<const bf16x8*>(pa + lds_off((p * 2 + h) * 16 + lrow, ks * 4 + kq));
+      };
+      auto pair_from = [&](auto self, auto p_tag) {
+        constexpr int p = decltype(p_tag)::value;
+        if constexpr (p < TM / 2) {
+          if (p == 0 || p < pairs) {
+            if constexpr (p + 1 < TM / 2) read_pair(std::integral_constant<int, p + 1>{});
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j][0], af[0], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j][1], af[1], acc[i][j], 0, 0, 0);
+            for (int h = 0; h < 2; ++h)
+              // weights as the MFMA "A" operand: a lane ends up with 4 consecutive output columns of one row
+#pragma unroll
+              for (int j = 0; j < TN; ++j) {
+                f32x4& c = acc[p * 2 + h][j];
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j][0], af[p & 1][h][0], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j][1], af[p & 1][h][1], c, 0, 0, 0);
+              }
+            self(self, std::integral_constant<int, p + 1>{});
+          }
         }
-      }
+      };
+      read_pair(std::integral_constant<int, 0>{});
+      pair_from(pair_from, std::integral_constant<int, 0>{});
       sa = sa + 1 == NSA ? 0 : sa + 1;
       sb = sb + 1 == NSB ? 0 : sb + 1;
       if (wave == 0) {  // the look-up of tile t + ahead

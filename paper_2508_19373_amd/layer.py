@@ -198,7 +198,9 @@ class ExpertShardLayer:
         TP=8 100 tokens 85 / 94, Qwen2-57B TP=2 EP=2 48 tokens 246 / 257; unsharded (440 MB) 16 tokens 644 / 628; Qwen1.5
         TP=2 EP=4 (130 MB routed) 16 tokens 60 / 62, 128: 93 / 84, TP=4 200: 121 / 111."""
         routed, shared = self._weight_bytes()
-        return shared <= 256e6 and (not self._shared_tiled(T) or (routed >= 135e6 and T <= 160))
+        # with a token or two the routed experts that have rows are as few bytes as the shared one (Qwen1.5 EP=2, 2 tokens: 59 / 53)
+        active = routed * min(1.0, T * self.k / self.E)
+        return shared <= 256e6 and 4 * active >= 5 * shared and (not self._shared_tiled(T) or (routed >= 135e6 and T <= 160))
 
     def _plan(self, T) -> "_Plan":
         """What a forward of T tokens needs to know about itself: a function of T, the shards and the switches,
@@ -220,9 +222,11 @@ class ExpertShardLayer:
                 if hint == B.MOE_FFN_TILED and 0 < rows <= (128 if self.H >= 3072 else 64):
                     hint = B.MOE_FFN_LEAVE_ROOM
                 # nor in two row passes (Qwen2-57B TP=4 2107 tokens 630 / 671; in one, Qwen1.5 EP=2 2000: 326 / 304)
-                # or with more rows than 64 on short slices (TP=8 482 tokens 202 / 209)
+                # or with more rows than 64 on short slices (TP=8 482 tokens 202 / 209) or 160 for few experts (Qwen1.5 EP=4
+                # 1497: 208 / 212)
                 elif hint == B.MOE_FFN_LEAVE_ROOM and ((rows == 160 and T * self.k > 165 * self.E) or
-                                                       (rows > 64 and self.ffn_shard.inter_slice < 512)):
+                                                       (rows > 64 and self.ffn_shard.inter_slice < 512) or
+                                                       (rows == 160 and self.ffn_shard.n_local_experts < 24)):
                     hint = B.MOE_FFN_TILED
                 # nor beside as much shared weight as there is routed: those tiles are half of the work, and the two calls
                 # interleave tile by tile (Qwen2-57B EP=8, 48 / 128 / 256 tokens 192 / 216 / 240 tiled, 214 / 226 / 270)
