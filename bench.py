@@ -165,7 +165,9 @@ def measure(workload, steps, warmup, args, torch, np, B, I, ExpertShardLayer, bf
     g1_bytes = 2.0 * active * H * I_s * 2 + R * H * 2 + R * I_s * 2
     intensity = g1_flops / g1_bytes
     decode = B.moe_debug_ffn_plan(T * k, layer.ffn_shard)[0]   # GEMM1 takes the weight-streaming kernel
-    kname = ("moe::gw::grouped_walk_kernel<..., GATEUP> (GEMM1 + SwiGLU, weight streaming)" if decode
+    kname = ("moe::gf::grouped_flow_kernel<..., GATEUP> (GEMM1 + SwiGLU, weight streaming)"
+             if B.moe_debug_flow(T * k, layer.ffn_shard) & B.DEBUG_FLOW_GATEUP
+             else "moe::gw::grouped_walk_kernel<..., GATEUP> (GEMM1 + SwiGLU, weight streaming)" if decode
              else "moe::gg::grouped_gemm_tall_kernel<256, GATEUP> (GEMM1 + SwiGLU)" if B.moe_debug_tall_gemms(T * k, layer.ffn_shard) & B.DEBUG_TALL_GATEUP
              else ("moe::gg::grouped_gemm_even_kernel<256, GATEUP> (GEMM1 + SwiGLU, 160-row blocks)"
                    if B.moe_debug_tile_rows(T * k, layer.ffn_shard) == 160
