@@ -107,6 +107,17 @@ int32_t moe_debug_tall(int32_t cap_rows, const moe_shard_t* shard);
 int32_t moe_debug_flow(int32_t cap_rows, const moe_shard_t* shard);
 
 /*
+ * Where that kernel's id-th tile stands in a list of `total` (ids are dealt in turn or taken from a counter): [0, total), or
+ * -1 behind the end of the list.
+ */
+int32_t moe_debug_flow_place(int32_t id, int32_t total);
+/*
+ * Length of that list for a routing (expert_offsets: host memory, n_local_experts + 1), for the GEMM `which` (MOE_DEBUG_FLOW_*);
+ * 0 where another kernel runs it, negative on invalid arguments.
+ */
+int32_t moe_debug_flow_tiles(const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard, int32_t which);
+
+/*
  * The work lists of such calls: for max_slices == 0 the plain list (gate/up projection, bf16 down
  * projection), for max_slices >= 1 the list of a down projection of nk k-tiles that may be cut along K into up to
  * that many slices.  Launches that would not end sooner for it have no tall blocks in them.

@@ -33,7 +33,7 @@ EXPORTS = ("moe_route_topk", "moe_permute", "moe_permute_static", "moe_expert_ff
            "moe_ffn_workspace_bytes", "moe_status_string")
 DEBUG_EXPORTS = ("moe_debug_gemm_units", "moe_debug_ffn_plan", "moe_debug_down_slices", "moe_debug_device_units",
                  "moe_debug_tile_rows", "moe_debug_even_units", "moe_debug_tall", "moe_debug_tall_units",
-                 "moe_debug_flow")
+                 "moe_debug_flow", "moe_debug_flow_place", "moe_debug_flow_tiles")
 INT4_EXPORTS = ("moe_int4_dequantize", "moe_int4_quantize")
 INT4_GROUP = 64
 DEBUG_UNIT_INTS = 5
@@ -115,6 +115,10 @@ def lib() -> ctypes.CDLL:
         L.moe_debug_tall.restype = i32
         L.moe_debug_flow.argtypes = [i32, shp]
         L.moe_debug_flow.restype = i32
+        L.moe_debug_flow_place.argtypes = [i32, i32]
+        L.moe_debug_flow_place.restype = i32
+        L.moe_debug_flow_tiles.argtypes = [vp, i32, shp, i32]
+        L.moe_debug_flow_tiles.restype = i32
         L.moe_debug_tall_units.argtypes = [vp, i32, i32, i32, i32, i32, vp, i32]
         L.moe_debug_tall_units.restype = i32
         _lib = L
@@ -288,6 +292,21 @@ def moe_debug_flow_rows(cap_rows, shard: MoeShard) -> int:
     """Rows per tile of that kernel's gate/up projection, else of its down projection; 0: neither runs on it."""
     n = _flow(cap_rows, shard)
     return (n >> 8 & 255) or n >> 16
+
+
+def moe_debug_flow_place(tile_id, total) -> int:
+    """Host-only: where the tile of that kernel's id-th take stands in a list of `total`; -1 behind its end."""
+    return int(lib().moe_debug_flow_place(tile_id, total))
+
+
+def moe_debug_flow_tiles(expert_offsets, cap_rows, shard: MoeShard, which) -> int:
+    """Host-only: length of that list for a routing (host int32 offsets) and one of the DEBUG_FLOW_* GEMMs."""
+    import numpy as np
+    offs = np.ascontiguousarray(expert_offsets, dtype=np.int32)
+    n = lib().moe_debug_flow_tiles(offs.ctypes.data, cap_rows, ctypes.byref(shard), which)
+    if n < 0:
+        raise MoeError("moe_debug_flow_tiles", n)
+    return int(n)
 
 
 def _max_device_units(cap_rows, n_local, n_col_blocks):

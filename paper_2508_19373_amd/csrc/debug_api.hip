@@ -2,6 +2,7 @@
 // integer logic the kernel runs per workgroup, so CPU tests can check that every tile of every
 // routing is covered exactly once.
 #include "moe_shard_debug.h"
+#include "flow_tiles.hpp"
 #include "moe_internal.hpp"
 #include "unit_list_even.hpp"
 #include "unit_list_wave.hpp"
@@ -97,6 +98,27 @@ extern "C" int32_t moe_debug_flow(int32_t cap_rows, const moe_shard_t* shard) {
   const int gu = moe::flow_plan(cap_rows, est, n, shard->inter_slice, shard->hidden, true).rows,
             dn = moe::flow_plan(cap_rows, est, n, shard->hidden, shard->inter_slice, false).rows;
   return (gu != 0 ? MOE_DEBUG_FLOW_GATEUP : 0) | (dn != 0 ? MOE_DEBUG_FLOW_DOWN : 0) | gu << 8 | dn << 16;
+}
+
+extern "C" int32_t moe_debug_flow_place(int32_t id, int32_t total) {
+  return id < 0 || total < 0 ? -1 : moe::gf::tile_place(id, total);
+}
+
+extern "C" int32_t moe_debug_flow_tiles(const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard, int32_t which) {
+  if (expert_offsets == nullptr || cap_rows < 0 || shard == nullptr) return MOE_ERR_INVALID_ARG;
+  if (which != MOE_DEBUG_FLOW_GATEUP && which != MOE_DEBUG_FLOW_DOWN) return MOE_ERR_INVALID_ARG;
+  if (shard->n_experts < 1 || shard->n_local_experts < 1 || shard->n_local_experts > shard->n_experts)
+    return MOE_ERR_INVALID_ARG;
+  const bool gateup = which == MOE_DEBUG_FLOW_GATEUP;
+  const int n_out = gateup ? shard->inter_slice : shard->hidden, K = gateup ? shard->hidden : shard->inter_slice;
+  const moe::FlowPlan plan =
+      moe::flow_plan(cap_rows, moe::expected_rows(cap_rows, shard), shard->n_local_experts, n_out, K, gateup);
+  if (plan.rows == 0) return 0;
+  int units = 0, tiles = 0;
+  for (int e = 0; e < shard->n_local_experts; ++e)
+    units += (expert_offsets[e + 1] - expert_offsets[e] + plan.rows - 1) / plan.rows;
+  moe::gf::tile_cost(units, n_out / 16, plan.rows, plan.cols, gateup, &tiles);
+  return units * tiles;
 }
 
 extern "C" int32_t moe_debug_tall_units(const int32_t* expert_offsets, int32_t n_local, int32_t cap_rows,

@@ -115,10 +115,8 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
   const int nk = K / BK;
   const int strips = n_out / 16;
   int ncb = 1;  // tiles a (expert, row pass) is cut into
-  // A look-up waits twice for memory (counter, source rows), `pace` k-tiles each: three under load (3 us).  Tiles are looked
-  // up `ahead` of time, so that a loader NSB - 1 k-tiles in front finds its tile.
-  const int pace = nk >= 16 ? 3 : 1;
-  const int ahead = (NSB + 2 * pace + 1 + nk - 1) / nk;
+  const int pace = look_pace(nk), ahead = look_ahead(nk, NSB);
+  static_assert(look_ahead(3, NSB) < kSlots && look_ahead(16, NSB) < kSlots, "the tile in work keeps its slot");
 
   // ---- once: the prefix of tiles per expert
   const int chunks = (n_local + 63) >> 6;
@@ -135,11 +133,11 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
   auto find = [&](int id, Slot& s) {
     s.expert = -1;
     s.row0 = s.row_end = s.strip0 = s.strips = s.kt0 = 0;
-    // Each XCD takes a contiguous eighth of the list (workgroup b runs on XCD b % 8), in which the row passes of a column tile
-    // are neighbours: they walk K together and the later readers of its weights find them in that XCD's L2.
-    const int xcd = id % gg::kNumXcd, chunk = (total + gg::kNumXcd - 1) / gg::kNumXcd;
-    id = xcd * chunk + id / gg::kNumXcd;
-    if (id >= min(total, (xcd + 1) * chunk)) return;
+    const int xcd = id % gg::kNumXcd;
+    // The row passes of a column tile are neighbours in the list, and so on one XCD: they walk K together and the later
+    // readers of its weights find them in that XCD's L2.
+    id = tile_place(id, total);
+    if (id < 0) return;
     int before = 0;
 #pragma unroll
     for (int j = 0; j < gg::kLaneChunks; ++j) {

@@ -102,26 +102,100 @@ def test_against_oracle(n, H, I_s, avg, special, gather):
     assert np.array_equal(outs[0], outs[1])          # fewer workgroups, the same tiles
 
 
+@pytest.mark.parametrize("total", [*range(0, 70), 1019, 1020, 1026, 4095])
+def test_every_take_below_the_total_is_a_tile(total):
+    """The ids with a tile are those below the total, whatever its remainder by the XCDs, and they are all tiles once; each
+    XCD's are neighbours."""
+    places = [B.moe_debug_flow_place(i, total) for i in range(total + 80)]
+    assert sorted(places[:total]) == list(range(total)) and set(places[total:]) == {-1}
+    for xcd in range(8):
+        mine = places[xcd:total:8]
+        assert mine == list(range(mine[0], mine[0] + len(mine))) if mine else True
+
+
+def _taken(total, workgroups, ahead, counter, rng):
+    """Places computed by workgroups that take `ahead` tiles before their first and one more during each, and end at the
+    first that is none, in an order of progress drawn at random."""
+    done, n = [], [0]
+    slots, ended, dealt = [[] for _ in range(workgroups)], [False] * workgroups, [0] * workgroups
+
+    def take(w):
+        i = n[0] if counter else w + dealt[w] * workgroups
+        n[0] += 1
+        dealt[w] += 1
+        slots[w].append(B.moe_debug_flow_place(i, total))
+
+    running = list(range(workgroups))
+    late = rng.random() < 0.5       # the others start when the first are well on
+    while running:
+        some = running[:max(1, len(running) // 8)] if late and len(done) < total // 2 else running
+        w = some[rng.integers(len(some))]
+        if not slots[w] and not dealt[w]:
+            for _ in range(ahead):
+                take(w)
+            continue
+        place = slots[w].pop(0)
+        if place < 0:
+            running.remove(w)
+            continue
+        take(w)
+        done.append(place)
+    return done
+
+
+@pytest.mark.parametrize("workgroups", [1, 7, 16, 30, 240])
+@pytest.mark.parametrize("ahead", [1, 2, 3])
+@pytest.mark.parametrize("counter", [False, True])
+def test_no_tile_is_lost_between_the_look_ahead_and_the_end(workgroups, ahead, counter):
+    rng = np.random.default_rng(workgroups * 8 + ahead)
+    for total in (1, 8, 61, 95, 240, 241, 486, 1026, 1031):
+        assert sorted(_taken(total, workgroups, ahead, counter, rng)) == list(range(total))
+
+
 @pytest.mark.gpu
-def test_tiles_from_the_counter_give_the_same_bits():
-    """Beside another stream the tiles come from a counter that the permutation clears; every forward starts it anew."""
-    n, H, I_s, k = 24, 1024, 704, 4
+@pytest.mark.parametrize("n,H,I_s", [
+    (23, 1024, 704),     # a tile looked up ahead
+    (61, 2048, 192),     # three k-tiles of the down projection, three tiles ahead; and the shapes between
+    (57, 3584, 320),
+    (59, 2048, 384),
+])
+@pytest.mark.parametrize("beside", [False, True])
+def test_tiles_from_the_counter_give_the_same_bits(n, H, I_s, beside):
+    """Beside another stream the tiles come from a counter that the permutation clears; every forward starts it anew, and
+    every tile is taken, also where few workgroups run at first because another call's tiles hold the compute units."""
+    k = 4
     g = torch.Generator(device="cuda")
     g.manual_seed(7)
     r = lambda *s: torch.randn(s, generator=g, device="cuda")
     W = dict(w_gate=(r(n, I_s, H) * 0.02).bfloat16(), w_up=(r(n, I_s, H) * 0.02).bfloat16(),
              w_down=(r(n, H, I_s) * 0.02).bfloat16(), w_router=r(H, n) * 0.02)
     layer = ExpertShardLayer(n_experts=n, top_k=k, hidden=H, inter_full=I_s, inter_slice=I_s, max_tokens=600, **W)
-    for tokens in (300, 600, 37):   # permuted by one workgroup and (more than 2048 assignments) by several
+    side = torch.cuda.Stream()
+    one, rows = B.make_shard(1, 1, 0, 1024, 2048, 2048), 8192
+    sx, sh, sy = r(rows, 1024).bfloat16(), r(rows, 2048).bfloat16(), r(rows, 1024)
+    sw = [(r(*s) * 0.02).bfloat16() for s in ((1, 2048, 1024), (1, 2048, 1024), (1, 1024, 2048))]
+    so = torch.tensor([0, rows], dtype=torch.int32, device="cuda")
+    sws = torch.empty(max(B.moe_ffn_workspace_bytes(rows, one), 256), dtype=torch.uint8, device="cuda")
+    ragged = False
+    for tokens in (300, 600, 37, 100, 183):   # permuted by one workgroup and (more than 2048 assignments) by several
         x = r(tokens, H).bfloat16()
-        assert B.moe_debug_flow(tokens * k, layer.ffn_shard)
+        which = B.moe_debug_flow(tokens * k, layer.ffn_shard)
+        assert which
         want = layer.forward(x).clone()
+        offs = layer.expert_offsets.cpu().numpy()
+        ragged |= any(which & b and B.moe_debug_flow_tiles(offs, tokens * k, layer.ffn_shard, b) % 8 for b in (1, 2))
         plan = layer._plan(tokens)
         layer._plan = lambda _, p=plan: p._replace(hint=B.MOE_FFN_LEAVE_ROOM)
         for _ in range(3):
             layer.y_perm.fill_(float("nan"))
+            layer.h_ws.fill_(float("nan"))
+            torch.cuda.synchronize()
+            if beside:
+                B.moe_expert_ffn(sx, so, rows, one, *sw, sh, sy, sws, B.MOE_FFN_TILED, side)
             assert torch.equal(layer.forward(x), want)
+            torch.cuda.synchronize()
         del layer._plan
+    assert ragged, "no launch whose tiles do not divide by the XCDs"
 
 
 @pytest.mark.gpu
