@@ -117,7 +117,7 @@ extern "C" int32_t moe_debug_flow_tiles(const int32_t* expert_offsets, int32_t c
   int units = 0, tiles = 0;
   for (int e = 0; e < shard->n_local_experts; ++e)
     units += (expert_offsets[e + 1] - expert_offsets[e] + plan.rows - 1) / plan.rows;
-  moe::gf::tile_cost(units, n_out / 16, plan.rows, plan.cols, gateup, &tiles);
+  moe::gf::tile_cost(units, shard->n_local_experts, n_out / 16, plan.rows, plan.cols, gateup, &tiles);
   return units * tiles;
 }
 

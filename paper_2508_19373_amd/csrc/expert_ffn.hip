@@ -405,7 +405,7 @@ FlowPlan flow_plan(int cap_rows, int est_rows, int n_local, int n_out, int K, bo
   if (hi < 283.0 || hi > 326.0 || est_rows < cap_rows) return none;
   if (!gateup) return FlowPlan{160, 256};
   const int nk = K / 64, tall = n_local * ((n_out + 127) / 128);
-  const double flow_us = gf::tile_cost(2 * n_local, n_out / 16, 160, 256, true, nullptr) * nk * 0.15 + 6.0;
+  const double flow_us = gf::tile_cost(2 * n_local, n_local, n_out / 16, 160, 256, true, nullptr) * nk * 0.15 + 6.0;
   const double tall_us = (tall + 255) / 256 * (nk * 1.6 + 12.0);
   return flow_us < 0.95 * tall_us ? FlowPlan{160, 256} : none;
 }
@@ -490,14 +490,14 @@ hipError_t launch_expert_ffn(const void* x_perm, RowMap rows, const int32_t* exp
   if (!(flags & MOE_FFN_SKIP_GATEUP)) {
     const bool both = flow1.rows == 0 && flow2.rows == 0 && walk1 == walk2;
     const hipError_t err =
-        flow1.rows != 0 ? launch_flow(flow1, true, true, x_perm, rows, expert_offsets, cap_rows, n_local, w_gate, w_up, I_s,
+        flow1.rows != 0 ? launch_flow(flow1, true, true, x_perm, rows, expert_offsets, n_local, w_gate, w_up, I_s,
                                       H, h_ws, tickets, leave_room, stream)
                         : run(walk1, both ? flags : flags | MOE_FFN_SKIP_DOWN);
     if (err != hipSuccess || both) return err;
   }
   if (flags & MOE_FFN_SKIP_DOWN) return hipSuccess;
   if (flow2.rows != 0)
-    return launch_flow(flow2, false, (flags & MOE_Y_PERM_BF16) != 0, h_ws, RowMap{nullptr, 1}, expert_offsets, cap_rows,
+    return launch_flow(flow2, false, (flags & MOE_Y_PERM_BF16) != 0, h_ws, RowMap{nullptr, 1}, expert_offsets,
                        n_local, w_down, nullptr, H, I_s, y_perm, tickets == nullptr ? nullptr : tickets + 1, leave_room,
                        stream);
   return run(walk2, flags | MOE_FFN_SKIP_GATEUP);

@@ -32,15 +32,28 @@ __host__ __device__ inline float tile_cost_of(int units, int strips, int n, int 
   const float width = (float)strips / (float)n;
   return (float)((units * n + kRound - 1) / kRound) * ((width > least ? width : least) + 0.25f);
 }
-// The fewest tiles per unit, and the cheapest number among 64 from there on (host code; the kernel prices one per lane).
-__host__ __device__ inline int fewest_tiles(int strips, int bn, bool gateup) {
-  const int full = bn / (gateup ? 32 : 16);
-  return (strips + full - 1) / full;
+// Where a tile's walk over K begins: the matrices of all local experts, one after the other, are cut into regions of
+// output columns, and a region's walk begins at its own share of K.  A few large experts have several regions each, and
+// then a multiple of as many tiles, so that no tile lies across two.  A function of the expert and the output column
+// alone: a row's sums are added in the same order whatever the other rows are and whoever computes them.
+__host__ __device__ constexpr int k_regions(int n_local, int bm) { return ((bm >= 128 ? 8 : 16) + n_local - 1) / n_local; }
+// (a region's share of K in k-tiles and 1/65536 of one; K <= 2^21, so that K / 64 << 16 fits)
+__host__ __device__ inline uint32_t k_step(int n_local, int regions, int nk) {
+  return ((uint32_t)nk << 16) / (uint32_t)(n_local * regions);
 }
-inline double tile_cost(int units, int strips, int bm, int bn, bool gateup, int* tiles) {
+__host__ __device__ inline int k_first(int expert, int nb, int ncb, int regions, uint32_t step) {
+  const int region = regions == 1 ? 0 : nb / (ncb / regions);
+  return (int)((uint32_t)(expert * regions + region) * step >> 16);
+}
+// The fewest tiles per unit, and the cheapest number among 64 steps from there on (host code; the kernel prices one per lane).
+__host__ __device__ inline int fewest_tiles(int strips, int bn, bool gateup, int regions) {
+  const int full = bn / (gateup ? 32 : 16) * regions;
+  return (strips + full - 1) / full * regions;
+}
+inline double tile_cost(int units, int n_local, int strips, int bm, int bn, bool gateup, int* tiles) {
   float best = 3e38f;
-  const int fewest = fewest_tiles(strips, bn, gateup);
-  for (int n = fewest; n < fewest + 64 && n <= strips; ++n) {
+  const int regions = k_regions(n_local, bm), fewest = fewest_tiles(strips, bn, gateup, regions);
+  for (int n = fewest; n < fewest + 64 * regions && n <= strips; n += regions) {
     const float c = tile_cost_of(units, strips, n, bm, bn, gateup);
     if (c < best) {
       best = c;

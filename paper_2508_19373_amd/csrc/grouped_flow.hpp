@@ -95,11 +95,11 @@ __device__ inline void buf_to_lds(buf_t, lds_void_t*, uint32_t, uint32_t) {}
 // 68 (5.1); TP=4 slice of Mixtral, 14 rows, 96 -> 83 (5.7) and 52 -> 45; against one workgroup per 64-row tile and the
 // streaming kernel.  About 5 us of a launch are not the stream: start, first look-up, first and last tile.
 // grid = any number of workgroups (one per compute unit); GATEUP: B0 = gate, B1 = up, C = h (bf16); else B0 = down.
-// Requires K % 64 == 0, 192 <= K <= 2^21 and n_out % 16 == 0.
+// regions, step: k_regions and k_step, of which the tiles' walks over K take their begin.  Requires K % 64 == 0, 192 <= K <= 2^21 and n_out % 16 == 0.
 template <int BM, int BN, bool GATEUP, typename OutT>
 __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
-    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local, int cap_rows,
-    const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, OutT* __restrict__ C,
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ expert_offsets, int n_local,
+    int regions, uint32_t step, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1, int n_out, int K, OutT* __restrict__ C,
     const RowMap rows, int32_t* __restrict__ ticket) {
   using S = Shape<BM, BN>;
   constexpr int NSA = S::NSA, NSB = S::NSB;
@@ -133,7 +133,6 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
   auto find = [&](int id, Slot& s) {
     s.expert = -1;
     s.row0 = s.row_end = s.strip0 = s.strips = s.kt0 = 0;
-    const int xcd = id % gg::kNumXcd;
     // The row passes of a column tile are neighbours in the list, and so on one XCD: they walk K together and the later
     // readers of its weights find them in that XCD's L2.
     id = tile_place(id, total);
@@ -156,13 +155,12 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
     s.strip0 = nb * strips / ncb;
     s.strips = (nb + 1) * strips / ncb - s.strip0;
     s.row0 = lo + (local - nb * passes) * height;
-    // The walk over K begins at one of 8 or 16 places: workgroups that all stand at the same k read the same 128 bytes of
-    // rows 4 or 8 KB apart, which fall on a few of the memory channels (gate/up of Qwen1.5-MoE, K = 2048, 22 rows per expert
-    // 138 us from k = 0, 125 from 16 places; TP=4 slice of Mixtral, K = 4096, 94 and 83; K = 1408 and 3584 no
-    // difference).  A function of the tile alone, so that the sums' order does not hang on who computes it; the same
-    // for an XCD's tiles where they share so many rows' activations in its L2 that these should be walked together
-    // (Qwen1.5-MoE, 90 rows: 139 us from 8 places, 152 from 16).
-    s.kt0 = BM >= 128 ? xcd * nk / gg::kNumXcd : (xcd * 2 + (nb & 1)) * nk / (2 * gg::kNumXcd);
+    // The walks over K begin apart: workgroups that all stand at the same k read the same 128 bytes of rows 4 or 8 KB
+    // apart, which fall on a few of the memory channels (gate/up of Qwen1.5-MoE, K = 2048, 22 rows per expert 138 us from k = 0,
+    // 126 so; TP=4 slice of Mixtral, K = 4096, 94 and 84; K = 1408 and 3584 no difference.  Begins by the tile's place in the
+    // list, which the other rows decide, were no faster: 126 and 85).  With 128 rows and more, where an XCD's tiles share as
+    // much of the activations as of the weights, eight places and not 16 (90 rows: 139 us, 152 from 16).
+    s.kt0 = k_first(e, nb, ncb, regions, step);
     s.row_end = min(hi, s.row0 + height);
   };
   // source rows of a tile's rows, the last valid one behind its end
@@ -184,14 +182,14 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
       len[j] = (hi - lo + BM - 1) / BM;
     }
     const int units = gg::wave_prefix(len, chunks, pre);
-    // tiles of equal width, as many as leave no workgroup idle in the last round: lane l prices fewest + l
+    // tiles of equal width, as many as leave no workgroup idle in the last round: lane l prices fewest + l * regions
     {
-      const int fewest = fewest_tiles(strips, BN, GATEUP), n = fewest + lane;
+      const int fewest = fewest_tiles(strips, BN, GATEUP, regions), n = fewest + lane * regions;
       const float cost = n <= strips ? tile_cost_of(units, strips, n, BM, BN, GATEUP) : 3e38f;
       float best = cost;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o, 64));
-      ncb = __builtin_amdgcn_readfirstlane(fewest + __ffsll((long long)__ballot(cost == best)) - 1);
+      ncb = __builtin_amdgcn_readfirstlane(fewest + (__ffsll((long long)__ballot(cost == best)) - 1) * regions);
     }
     total = units * ncb;
 #pragma unroll

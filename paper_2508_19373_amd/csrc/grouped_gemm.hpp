@@ -132,7 +132,7 @@ template <int BM, int BN, int WM, int WN, int NSA, int NSB, bool GATEUP, typenam
 __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, const uint16_t* __restrict__ A,
                                             int cap_rows, const uint16_t* __restrict__ B0,
                                             const uint16_t* __restrict__ B1, int n_out, int K, int kt0, int nk,
-                                            OutT* __restrict__ C, const RowMap rows = RowMap{nullptr, 1}) {
+                                            OutT* __restrict__ C, const RowMap rows = RowMap{nullptr, 1}, int k_first = 0) {
   constexpr int NW = WM * WN;
   constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
   constexpr int A_INST = BM / 8 / NW, B_INST = BN / 8 / NW;
@@ -220,10 +220,7 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
     }
   }
 
-  // Where the walk over K begins (SPREAD): an eighth of K further on each XCD, whose tiles share
-  // their panels in its own L2 and so keep walking together.  Tiles that all stand at the same k read the same 128 bytes of
-  // rows 4 or 8 KB apart, which fall on a few of the memory channels.  Only where HBM counts (spread_k).
-  const int k_first = SPREAD ? (int)(blockIdx.x % kNumXcd) * nk / kNumXcd : 0;
+  // SPREAD: the walk over K begins at k_first (first_k)
   auto k_at = [&](int kt) {
     if constexpr (SPREAD) return kt + k_first >= nk ? kt + k_first - nk : kt + k_first;
     return kt;
@@ -472,6 +469,15 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileCoord& tc, c
     store_tile([&](int row, int col) { return row < hi && col < n_out; });
 }
 
+// Where a SPREAD tile's walk over K begins: the experts' column blocks, one after the other, are cut into eight regions, and
+// each region's begins an eighth of K further on.  Tiles that all stand at the same k read the same 128 bytes of rows 4 or 8 KB
+// apart, which fall on a few of the memory channels; an XCD's share of the list is a region or two, so that its tiles, which
+// share their panels in its L2, keep walking together.  A function of the expert and the output column alone, so that a
+// row's sums are added in the same order whatever the other rows are.  Only where HBM counts (spread_k).
+__device__ __forceinline__ int first_k(const TileCoord& tc, int n_local, int n_col_blocks, int nk) {
+  return (tc.expert * n_col_blocks + tc.nb) * kNumXcd / (n_local * n_col_blocks) * nk / kNumXcd;
+}
+
 // Kernel: 256 threads (4 wavefronts); each workgroup computes one tile, whose height class
 // selects the wave arrangement and the LDS stage counts.  SLICED (fp32 down projection): tiles may
 // be cut along K as choose_slices decides from the routing; slice 0 of a tile writes `y`, slice
@@ -500,12 +506,13 @@ __device__ __forceinline__ void dlds_tile(
   } else {
     if (!find_tile(expert_offsets, n_local, n_col_blocks, blockIdx.x, cls, tc)) return;
   }
+  const int k_first = SPREAD ? first_k(tc, n_local, n_col_blocks, nk) : 0;
   if (cls == 0)
-    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows, k_first);
   else if (cls == 1)
-    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows, k_first);
   else
-    gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows, k_first);
 }
 
 template <int BN, bool GATEUP, typename OutT, bool SLICED>
@@ -585,23 +592,24 @@ __device__ __forceinline__ void tall_tile(
       return;
     }
   }
+  const int k_first = SPREAD ? first_k(tc, n_local, n_col_blocks, nk) : 0;
   if (cls == 0 && tc.nx == 0)
     gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 0, true, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out,
-                                                                         rows);
+                                                                         rows, k_first);
   else if (cls == 0 && tc.nx == 1)
     gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 1, true, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out,
-                                                                         rows);
+                                                                         rows, k_first);
   else if (cls == 0 && tc.nx == 2)
     gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 2, true, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out,
-                                                                         rows);
+                                                                         rows, k_first);
   else if (cls == 0)
     gemm_tile<256, BN, 2, 2, 2, 3, GATEUP, OutT, 3, true, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out,
-                                                                         rows);
+                                                                         rows, k_first);
   else if (cls == 1)
-    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+    gemm_tile<128, BN, 2, 2, 3, 3, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows, k_first);
   else
     for (;;) {
-      gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows);
+      gemm_tile<64, BN, 1, 4, 4, 4, GATEUP, OutT, 0, false, SPREAD>(smem, tc, A, cap_rows, B0, B1, n_out, K, kt0, nk, out, rows, k_first);
       tc.row0 += 64;
       if (tc.row0 >= tc.row_end) break;  // a 64-row tile proper is its expert's last
       __syncthreads();                   // before the next one refills the LDS stages

@@ -115,7 +115,7 @@ struct FlowPlan {
 FlowPlan flow_plan(int cap_rows, int est_rows, int n_local, int n_out, int K, bool gateup);
 // ticket: a zero in device memory (nullptr: tiles are dealt in turn)
 hipError_t launch_flow(const FlowPlan& plan, bool gateup, bool out_bf16, const void* A, RowMap rows,
-                       const int32_t* expert_offsets, int cap_rows, int n_local, const void* B0, const void* B1,
+                       const int32_t* expert_offsets, int n_local, const void* B0, const void* B1,
                        int n_out, int K, void* C, int32_t* ticket, bool leave_room, hipStream_t stream);
 hipError_t launch_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w, int T, int k, int H,
                           const void* y_shared, const void* x, const float* w_shared_gate, void* y_out,

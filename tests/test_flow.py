@@ -222,6 +222,64 @@ def test_walks_over_k_that_begin_apart(H, I_s, counts):
     assert np.linalg.norm(got - ref) / np.linalg.norm(ref) < 5e-3
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,I_s,avg,n,mine,flow_rows", [
+    (2048, 704, 20, 30, [0, 13, 29], 64),     # tiles of 64 rows, one region of K per expert
+    (4096, 1792, 20, 4, [1], 64),             # four regions each
+    (4096, 5632, 40, 1, None, 64),            # 16
+    (2048, 704, 90, 30, [0, 13, 29], 128),
+    (4096, 1792, 130, 6, [2, 5], 160),
+    (2048, 704, 270, 30, [0, 13, 29], 0),     # tiled gate/up with its walks spread
+    (2048, 512, 400, 3, [1], 0),
+])
+def test_a_rows_bits_do_not_depend_on_the_other_rows(H, I_s, avg, n, mine, flow_rows):
+    """The experts `mine` get the same rows of x in two batches of one size in which all the others differ (with one expert:
+    their first 17 rows): the same kernels add the same products in the same order."""
+    rng = np.random.default_rng(H + avg)
+    cap = n * avg
+    if n == 1:
+        mine, counts = [0], [np.array([cap]), np.array([cap // 2])]
+        keep = {0: 17}
+    else:
+        keep = {e: int(rng.integers(1, 2 * avg)) for e in mine}
+        counts = []
+        for i in range(2):
+            w = rng.random(n) ** (1 if i else 4) + 1e-3
+            w[mine] = 0
+            c = np.floor((cap - sum(keep.values())) * w / w.sum()).astype(np.int64)
+            for e in mine:
+                c[e] = keep[e]
+            counts.append(c)
+    shard = B.make_shard(n, n, 0, H, I_s, I_s)
+    flow = B.moe_debug_flow(cap, shard)
+    assert (flow & B.DEBUG_FLOW_GATEUP != 0) == (flow_rows != 0)
+    if flow_rows:
+        assert B.moe_debug_flow_rows(cap, shard) == flow_rows
+    else:
+        assert not B.moe_debug_ffn_plan(cap, shard)[0]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda")
+    W = [(r(*s) * 0.02).bfloat16() for s in ((n, I_s, H), (n, I_s, H), (n, H, I_s))]
+    own = {e: r(keep[e], H).bfloat16() for e in mine}
+    ws = torch.empty(max(B.moe_ffn_workspace_bytes(cap, shard), 256), dtype=torch.uint8, device="cuda")
+    got = []
+    for c in counts:
+        offs = np.concatenate([[0], np.cumsum(c)]).astype(np.int32)
+        x = r(cap, H).bfloat16()
+        for e in mine:
+            x[offs[e]:offs[e] + keep[e]] = own[e]
+        for flags in (0, B.MOE_FFN_LEAVE_ROOM):
+            h = torch.zeros((cap, I_s), dtype=torch.bfloat16, device="cuda")
+            y = torch.zeros((cap, H), device="cuda")
+            B.moe_expert_ffn(x, torch.from_numpy(offs).cuda(), cap, shard, *W, h, y, ws, flags)
+            out = [torch.cat([t[offs[e]:offs[e] + keep[e]].float() for e in mine]) for t in (h, y)]
+            got.append(out if flow & B.DEBUG_FLOW_DOWN else out[:1])    # (a tiled down projection may be cut along K)
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("blocks", [11, 12, 13, 16, 17, 23, 32, 40])
 def test_row_blocks_of_a_large_expert_in_groups(blocks):
     """Every tile once; from 12 row blocks on, 32 neighbouring tiles on an XCD touch few row and column blocks together."""
