@@ -112,10 +112,12 @@ int32_t moe_debug_flow(int32_t cap_rows, const moe_shard_t* shard);
  */
 int32_t moe_debug_flow_place(int32_t id, int32_t total);
 /*
- * Length of that list for a routing (expert_offsets: host memory, n_local_experts + 1), for the GEMM `which` (MOE_DEBUG_FLOW_*);
- * 0 where another kernel runs it, negative on invalid arguments.
+ * Length of that list for a routing (expert_offsets: host memory, n_local_experts + 1), for the GEMM `which` (MOE_DEBUG_FLOW_*)
+ * of moe_expert_ffn with these flags (MOE_FFN_LEAVE_ROOM changes it; not in moe_forward, whose tiles then come from a
+ * counter); 0 where another kernel runs it, negative on invalid arguments.
  */
-int32_t moe_debug_flow_tiles(const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard, int32_t which);
+int32_t moe_debug_flow_tiles(const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard, int32_t which,
+                             uint32_t flags);
 
 /*
  * The work lists of such calls: for max_slices == 0 the plain list (gate/up projection, bf16 down

@@ -117,7 +117,7 @@ def lib() -> ctypes.CDLL:
         L.moe_debug_flow.restype = i32
         L.moe_debug_flow_place.argtypes = [i32, i32]
         L.moe_debug_flow_place.restype = i32
-        L.moe_debug_flow_tiles.argtypes = [vp, i32, shp, i32]
+        L.moe_debug_flow_tiles.argtypes = [vp, i32, shp, i32, ctypes.c_uint32]
         L.moe_debug_flow_tiles.restype = i32
         L.moe_debug_tall_units.argtypes = [vp, i32, i32, i32, i32, i32, vp, i32]
         L.moe_debug_tall_units.restype = i32
@@ -299,11 +299,11 @@ def moe_debug_flow_place(tile_id, total) -> int:
     return int(lib().moe_debug_flow_place(tile_id, total))
 
 
-def moe_debug_flow_tiles(expert_offsets, cap_rows, shard: MoeShard, which) -> int:
-    """Host-only: length of that list for a routing (host int32 offsets) and one of the DEBUG_FLOW_* GEMMs."""
+def moe_debug_flow_tiles(expert_offsets, cap_rows, shard: MoeShard, which, flags=0) -> int:
+    """Host-only: length of that list for a routing (host int32 offsets), one of the DEBUG_FLOW_* GEMMs and moe_expert_ffn flags."""
     import numpy as np
     offs = np.ascontiguousarray(expert_offsets, dtype=np.int32)
-    n = lib().moe_debug_flow_tiles(offs.ctypes.data, cap_rows, ctypes.byref(shard), which)
+    n = lib().moe_debug_flow_tiles(offs.ctypes.data, cap_rows, ctypes.byref(shard), which, flags)
     if n < 0:
         raise MoeError("moe_debug_flow_tiles", n)
     return int(n)

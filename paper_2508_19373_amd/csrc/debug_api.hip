@@ -104,7 +104,8 @@ extern "C" int32_t moe_debug_flow_place(int32_t id, int32_t total) {
   return id < 0 || total < 0 ? -1 : moe::gf::tile_place(id, total);
 }
 
-extern "C" int32_t moe_debug_flow_tiles(const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard, int32_t which) {
+extern "C" int32_t moe_debug_flow_tiles(const int32_t* expert_offsets, int32_t cap_rows, const moe_shard_t* shard, int32_t which,
+                                        uint32_t flags) {
   if (expert_offsets == nullptr || cap_rows < 0 || shard == nullptr) return MOE_ERR_INVALID_ARG;
   if (which != MOE_DEBUG_FLOW_GATEUP && which != MOE_DEBUG_FLOW_DOWN) return MOE_ERR_INVALID_ARG;
   if (shard->n_experts < 1 || shard->n_local_experts < 1 || shard->n_local_experts > shard->n_experts)
@@ -117,7 +118,7 @@ extern "C" int32_t moe_debug_flow_tiles(const int32_t* expert_offsets, int32_t c
   int units = 0, tiles = 0;
   for (int e = 0; e < shard->n_local_experts; ++e)
     units += (expert_offsets[e + 1] - expert_offsets[e] + plan.rows - 1) / plan.rows;
-  moe::gf::tile_cost(units, shard->n_local_experts, n_out / 16, plan.rows, plan.cols, gateup, &tiles);
+  moe::gf::tile_cost(units, moe::gf::workgroups((flags & MOE_FFN_LEAVE_ROOM) != 0), shard->n_local_experts, n_out / 16, plan.rows, plan.cols, gateup, &tiles);
   return units * tiles;
 }
 

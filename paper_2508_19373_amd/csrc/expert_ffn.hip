@@ -405,7 +405,7 @@ FlowPlan flow_plan(int cap_rows, int est_rows, int n_local, int n_out, int K, bo
   if (hi < 283.0 || hi > 326.0 || est_rows < cap_rows) return none;
   if (!gateup) return FlowPlan{160, 256};
   const int nk = K / 64, tall = n_local * ((n_out + 127) / 128);
-  const double flow_us = gf::tile_cost(2 * n_local, n_local, n_out / 16, 160, 256, true, nullptr) * nk * 0.15 + 6.0;
+  const double flow_us = gf::tile_cost(2 * n_local, gf::workgroups(false), n_local, n_out / 16, 160, 256, true, nullptr) * nk * 0.15 + 6.0;
   const double tall_us = (tall + 255) / 256 * (nk * 1.6 + 12.0);
   return flow_us < 0.95 * tall_us ? FlowPlan{160, 256} : none;
 }

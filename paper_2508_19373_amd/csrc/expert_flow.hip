@@ -8,9 +8,8 @@ template <int BM, int BN, bool GATEUP, typename OutT>
 hipError_t launch(const uint16_t* A, RowMap rows, const int32_t* expert_offsets, int n_local,
                   const uint16_t* B0, const uint16_t* B1, int n_out, int K, void* C, int32_t* ticket, bool leave_room,
                   hipStream_t stream) {
-  const int grid = leave_room ? gf::kRound * 15 / 16 : gf::kRound;  // 16 compute units stay free for another stream
   const int regions = gf::k_regions(n_local, BM);
-  hipLaunchKernelGGL((gf::grouped_flow_kernel<BM, BN, GATEUP, OutT>), dim3(grid), dim3(gf::kThreads), 0, stream, A,
+  hipLaunchKernelGGL((gf::grouped_flow_kernel<BM, BN, GATEUP, OutT>), dim3(gf::workgroups(leave_room)), dim3(gf::kThreads), 0, stream, A,
                      expert_offsets, n_local, regions, gf::k_step(n_local, regions, K / gf::BK), B0, B1, n_out, K, static_cast<OutT*>(C), rows, ticket);
   return hipGetLastError();
 }

@@ -8,7 +8,8 @@
 namespace moe {
 namespace gf {
 
-constexpr int kRound = 256;  // workgroups of a full launch
+// Workgroups of a launch, one per compute unit, or 16 units left free for another stream
+__host__ __device__ constexpr int workgroups(bool leave_room) { return leave_room ? 240 : 256; }
 
 // Workgroup b runs on XCD b % 8.  The list place of the tile that the id-th take stands for, -1 behind the end.  Each XCD takes a contiguous share of the
 // list, the first total % 8 of them one tile more, so that an id has a tile exactly where it is below `total`: a workgroup
@@ -23,14 +24,14 @@ __host__ __device__ inline int tile_place(int id, int total) {
 __host__ __device__ constexpr int look_pace(int nk) { return nk >= 16 ? 3 : 1; }
 __host__ __device__ constexpr int look_ahead(int nk, int nsb) { return (nsb + 2 * look_pace(nk) + 1 + nk - 1) / nk; }
 
-// Cost of `units` (expert, row pass) pairs of `strips` 16-column output strips in n tiles each: rounds times width, and a
-// quarter of a strip for each tile.  A k-tile has a shortest time (barrier, operand reads, MFMAs of the whole tile shape),
+// Cost of `units` (expert, row pass) pairs of `strips` 16-column output strips in n tiles each: rounds of `wgs` workgroups times
+// width, and a quarter of a strip for each tile.  A k-tile has a shortest time (barrier, operand reads, MFMAs of the whole tile shape),
 // that of a share of the full width at the HBM rate.
-__host__ __device__ inline float tile_cost_of(int units, int strips, int n, int bm, int bn, bool gateup) {
+__host__ __device__ inline float tile_cost_of(int units, int wgs, int strips, int n, int bm, int bn, bool gateup) {
   const float full = (float)(bn / (gateup ? 32 : 16));
   const float least = full * (bm >= 160 ? 0.8f : (bm >= 128 ? 0.55f : (bn >= 256 ? 0.35f : 0.5f)));
   const float width = (float)strips / (float)n;
-  return (float)((units * n + kRound - 1) / kRound) * ((width > least ? width : least) + 0.25f);
+  return (float)((units * n + wgs - 1) / wgs) * ((width > least ? width : least) + 0.25f);
 }
 // Where a tile's walk over K begins: the matrices of all local experts, one after the other, are cut into regions of
 // output columns, and a region's walk begins at its own share of K.  A few large experts have several regions each, and
@@ -50,11 +51,11 @@ __host__ __device__ inline int fewest_tiles(int strips, int bn, bool gateup, int
   const int full = bn / (gateup ? 32 : 16) * regions;
   return (strips + full - 1) / full * regions;
 }
-inline double tile_cost(int units, int n_local, int strips, int bm, int bn, bool gateup, int* tiles) {
+inline double tile_cost(int units, int wgs, int n_local, int strips, int bm, int bn, bool gateup, int* tiles) {
   float best = 3e38f;
   const int regions = k_regions(n_local, bm), fewest = fewest_tiles(strips, bn, gateup, regions);
   for (int n = fewest; n < fewest + 64 * regions && n <= strips; n += regions) {
-    const float c = tile_cost_of(units, strips, n, bm, bn, gateup);
+    const float c = tile_cost_of(units, wgs, strips, n, bm, bn, gateup);
     if (c < best) {
       best = c;
       if (tiles != nullptr) *tiles = n;

@@ -182,10 +182,16 @@ __global__ __launch_bounds__(kThreads, 2) void grouped_flow_kernel(
       len[j] = (hi - lo + BM - 1) / BM;
     }
     const int units = gg::wave_prefix(len, chunks, pre);
-    // tiles of equal width, as many as leave no workgroup idle in the last round: lane l prices fewest + l * regions
+    // tiles of equal width, as many as leave none of this launch's workgroups idle in the last round: lane l prices
+    // fewest + l * regions.  Dealt in turn to 240 workgroups, the price for 256 left a fifth of the launch idle (gate/up of 15
+    // experts of Qwen1.5-MoE, 30 rows each, 49 / 35 us, 60 of 22 134 / 129, TP=4 slice of Mixtral 111 / 84).  From the counter the
+    // workgroups that run beside the other stream's are neither all of the launch nor the same ones throughout, and narrow
+    // tiles even that out: priced as a full launch (layer of Qwen2-57B, 450 tokens, 898, at the price for 240 950; Qwen1.5-MoE 333:
+    // 259 and 265).
+    const int wgs = ticket == nullptr ? (int)gridDim.x : workgroups(false);
     {
       const int fewest = fewest_tiles(strips, BN, GATEUP, regions), n = fewest + lane * regions;
-      const float cost = n <= strips ? tile_cost_of(units, strips, n, BM, BN, GATEUP) : 3e38f;
+      const float cost = n <= strips ? tile_cost_of(units, wgs, strips, n, BM, BN, GATEUP) : 3e38f;
       float best = cost;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o, 64));

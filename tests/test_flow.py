@@ -36,6 +36,18 @@ def test_when_it_runs():
     assert B.moe_debug_flow(4, qwen_tp8) == 0                        # four experts at most: 48 gate/up strips
 
 
+@pytest.mark.parametrize("rows", [2, 22, 60])
+def test_the_tiles_fill_the_rounds_of_the_launch_that_runs(rows):
+    """60 experts' GEMMs in rounds of 240 workgroups where 16 compute units stay free, of 256 where none do: the last round
+    is not nearly empty."""
+    qwen = B.make_shard(60, 60, 0, 2048, 1408, 1408)
+    offs = np.arange(61) * rows
+    for which in (B.DEBUG_FLOW_GATEUP, B.DEBUG_FLOW_DOWN):
+        for flags, wgs in ((0, 256), (B.MOE_FFN_LEAVE_ROOM, 240)):
+            tiles = B.moe_debug_flow_tiles(offs, 60 * rows, qwen, which, flags)
+            assert tiles % 60 == 0 and tiles / wgs >= 0.9 * -(-tiles // wgs), (tiles, wgs)
+
+
 def _counts(n, avg, special, rng):
     c = rng.integers(0, 2 * avg, n)
     c[:len(special)] = special
