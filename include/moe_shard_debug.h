@@ -42,6 +42,13 @@ int32_t moe_debug_gemm_units(const int32_t* expert_offsets, int32_t n_local, int
 int32_t moe_debug_ffn_plan(int32_t cap_rows, const moe_shard_t* shard, int32_t* plan);
 
 /*
+ * How the streaming kernel that moe_debug_ffn_plan speaks of cuts a K extent with 16 or 32 rows per pass (mt = 1 or 2) for
+ * the gate/up (down = 0) or the down projection: split[3] = wavefronts, 32-wide steps per wavefront, slices; 0 wavefronts:
+ * the generic streaming kernel runs.  MOE_ERR_INVALID_ARG on invalid arguments.
+ */
+int32_t moe_debug_walk_split(int32_t K, int32_t mt, int32_t down, int32_t* split);
+
+/*
  * Row-block height of the tiled kernels moe_expert_ffn would use for (cap_rows, shard) where it does not use tall row
  * blocks (moe_debug_tall below): 256 (row
  * blocks of 256 rows plus 128- and 64-row remainder tiles, moe_debug_gemm_units), or 160 (every

@@ -33,7 +33,7 @@ EXPORTS = ("moe_route_topk", "moe_permute", "moe_permute_static", "moe_expert_ff
            "moe_ffn_workspace_bytes", "moe_status_string")
 DEBUG_EXPORTS = ("moe_debug_gemm_units", "moe_debug_ffn_plan", "moe_debug_down_slices", "moe_debug_device_units",
                  "moe_debug_tile_rows", "moe_debug_even_units", "moe_debug_tall", "moe_debug_tall_units",
-                 "moe_debug_flow", "moe_debug_flow_place", "moe_debug_flow_tiles")
+                 "moe_debug_flow", "moe_debug_flow_place", "moe_debug_flow_tiles", "moe_debug_walk_split")
 INT4_EXPORTS = ("moe_int4_dequantize", "moe_int4_quantize")
 INT4_GROUP = 64
 DEBUG_UNIT_INTS = 5
@@ -101,6 +101,8 @@ def lib() -> ctypes.CDLL:
         L.moe_int4_quantize.restype = ctypes.c_int
         L.moe_debug_ffn_plan.argtypes = [i32, shp, vp]
         L.moe_debug_ffn_plan.restype = i32
+        L.moe_debug_walk_split.argtypes = [i32, i32, i32, vp]
+        L.moe_debug_walk_split.restype = i32
         L.moe_debug_down_slices.argtypes = [vp, i32, shp, vp, vp, i32]
         L.moe_debug_down_slices.restype = i32
         L.moe_debug_device_units.argtypes = [vp, i32, i32, i32, i32, i32, vp, i32, vp]
@@ -363,6 +365,15 @@ def moe_debug_device_units(expert_offsets, cap_rows, n_col_blocks, nk, max_slice
     if n < 0:
         raise MoeError("moe_debug_device_units", n)
     return out[:n]
+
+
+def moe_debug_walk_split(K, mt, down=False):
+    """Host-only: (wavefronts, steps, slices) of the streaming kernel for a K extent and 16 * mt rows per pass."""
+    split = (ctypes.c_int32 * 3)()
+    st = lib().moe_debug_walk_split(K, mt, int(down), split)
+    if st != MOE_OK:
+        raise MoeError("moe_debug_walk_split", st)
+    return tuple(split)
 
 
 def moe_debug_ffn_plan(cap_rows, shard: MoeShard):

@@ -34,6 +34,12 @@ extern "C" int32_t moe_debug_gemm_units(const int32_t* expert_offsets, int32_t n
   return grid;
 }
 
+extern "C" int32_t moe_debug_walk_split(int32_t K, int32_t mt, int32_t down, int32_t* split) {
+  if (K < 1 || mt < 1 || mt > 2 || split == nullptr) return MOE_ERR_INVALID_ARG;
+  moe::walk_split(K, mt, down != 0, split);
+  return MOE_OK;
+}
+
 extern "C" int32_t moe_debug_ffn_plan(int32_t cap_rows, const moe_shard_t* shard, int32_t* plan) {
   if (cap_rows < 0 || shard == nullptr || plan == nullptr) return MOE_ERR_INVALID_ARG;
   if (shard->n_experts < 1 || shard->n_local_experts < 1 || shard->n_local_experts > shard->n_experts ||

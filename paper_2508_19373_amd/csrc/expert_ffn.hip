@@ -245,7 +245,7 @@ bool launch_walk(const gw::WalkPlan& plan, const uint16_t* A, const int32_t* exp
   MOE_WALK(8, 8)
   MOE_WALK(8, 7)
   MOE_WALK(8, 5)
-  MOE_WALK(8, 2)
+  if constexpr (MT == 2) MOE_WALK(8, 2)
   MOE_WALK(4, 11)
   MOE_WALK(4, 10)
   MOE_WALK(4, 8)
@@ -438,6 +438,13 @@ size_t ffn_workspace_bytes(int cap_rows, int est_rows, int n_local, int H, int I
   const int slices = p2.nw == 0 ? 1 : p2.slices;
   const size_t walk = slices > 1 ? (size_t)slices * cap_rows * H * sizeof(float) : 0;
   return walk > tiled ? walk : tiled;
+}
+
+void walk_split(int K, int mt, bool down, int32_t out[3]) {
+  const gw::WalkPlan p = gw::plan_for(K, mt, down);
+  out[0] = p.nw;
+  out[1] = p.steps;
+  out[2] = p.slices;
 }
 
 void ffn_plan(int cap_rows, int est_rows, int n_local, int H, int I_s, int32_t out[4]) {

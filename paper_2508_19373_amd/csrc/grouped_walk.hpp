@@ -268,7 +268,10 @@ inline WalkPlan plan_for(int K, int mt, bool down = false) {
       for (int st : cand) {
         // instantiated: (8,16) (8,14) (8,11) (8,10) (8,8) (8,7) (8,5) (8,2) (4,11) (4,10) (4,8) (4,5)
         if (nw == 4 && !(st == 11 || st == 10 || st == 8 || st == 5)) continue;
-        if (st == 2 && steps32 != 16) continue;
+        // K = 512, with 32 rows per pass only: with 16 the generic kernel, a workgroup per strip and expert, is the faster one on
+        // the few MB such a matrix has (this one / generic, us: gate/up of the tiny layer, 4 tokens 7.5 / 4.4, 16: 8.2 / 6.4,
+        // 32: 8.2 / 6.8; 64, 32 rows per pass, 7.6 / 8.6, 80: 7.8 / 9.4)
+        if (st == 2 && (steps32 != 16 || mt == 1)) continue;
         if (steps32 % (nw * st) == 0) return WalkPlan{nw, st, steps32 / (nw * st)};
       }
   }

@@ -100,6 +100,9 @@ size_t ffn_workspace_bytes(int cap_rows, int est_rows, int n_local, int H, int I
 // What launch_expert_ffn would do: {GEMM1 by the walk kernel, GEMM2 by the walk kernel, rows per
 // walk pass / 16, K slices of GEMM2}.
 void ffn_plan(int cap_rows, int est_rows, int n_local, int H, int I_s, int32_t out[4]);
+// How the walk kernel would cut K with 16 * mt rows per pass: wavefronts (0: not instantiated, the generic streaming kernel runs),
+// k32 steps per wavefront, slices.
+void walk_split(int K, int mt, bool down, int32_t out[3]);
 // Row-block height of the tiled kernels for such a call (256, or 160 for the one-height work list).
 int tiled_block_rows(int cap_rows, int est_rows, int n_local, int H, int I_s);
 // Which GEMMs of such a call, when tiled, run the kernel whose full row blocks may take their expert's remainder: those
