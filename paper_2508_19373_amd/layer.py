@@ -60,11 +60,24 @@ def routed_hint_beside_shared(ffn_shard, shared_shard, T) -> int:
     60 or 64 local experts (two or more rounds of tiles even with a few rows per expert, so the
     tiled kernels stream as fast as the streaming kernel); +5 to +16 % on shards with 15 or 30
     experts, hence the tile count.  Those leave 16 compute units to the shared expert instead (30
-    experts, 96 / 128 tokens: 177 / 179 -> 170 / 173 us).  A streaming shared expert needs neither."""
+    experts, 96 / 128 tokens: 177 / 179 -> 170 / 173 us).  A streaming shared expert needs neither.  (For a shared expert
+    both of whose GEMMs run as moe_debug_ffn_plan says; shared_on_streaming_tiles comes first.)"""
     if all(B.moe_debug_ffn_plan(T, shared_shard)[:2]):
         return 0
     gateup_tiles = ffn_shard.n_local_experts * ((ffn_shard.inter_slice + 127) // 128)
     return B.MOE_FFN_TILED if gateup_tiles >= 512 else B.MOE_FFN_LEAVE_ROOM
+
+
+def shared_on_streaming_tiles(shared_shard, T, y_perm_bf16) -> bool:
+    """Whether the shared expert of T tokens holds every compute unit by itself: its gate/up projection runs the streaming
+    tiles (moe_debug_flow; a workgroup of a whole LDS stays on each unit for the launch), whatever moe_debug_ffn_plan says
+    of it, and its down projection, cut along K or streaming, is over soon.  Then room left by the routed experts' call
+    serves nobody and tiles of theirs interleave with nothing, so the call needs no hint.  Hint as for tiled / none, us:
+    Qwen1.5-MoE 64 tokens 232 / 230, EP=2 48: 150 / 137, EP=4 150: 114 / 111, Qwen2-57B 48: 705 / 697, EP=4 100: 293 / 275,
+    EP=8 150: 229 / 210, TP=2 48: 393 / 376, TP=2 EP=2 300: 297 / 288, TP=4 EP=2 48: 158 / 141.  Not with a bf16 down projection:
+    uncut, its H / 256 tiles walk all of K and have to start early (Qwen1.5-MoE 160 tokens 239 / 264, Qwen2-57B TP=2 EP=2 48:
+    251 / 293)."""
+    return not y_perm_bf16 and bool(B.moe_debug_flow(T, shared_shard) & B.DEBUG_FLOW_GATEUP)
 
 
 class _Plan(NamedTuple):
@@ -196,11 +209,15 @@ class ExpertShardLayer:
         hundred MB, which fills the time of the router and the permutation, nor before a tiled one that ends last (the
         routed experts few, or the tokens many).  Routed / shared first, us: Qwen1.5-MoE 128 tokens 245 / 256, TP=4 16 tokens 85 / 87,
         TP=8 100 tokens 85 / 94, Qwen2-57B TP=2 EP=2 48 tokens 246 / 257; unsharded (440 MB) 16 tokens 644 / 628; Qwen1.5
-        TP=2 EP=4 (130 MB routed) 16 tokens 60 / 62, 128: 93 / 84, TP=4 200: 121 / 111."""
+        TP=2 EP=4 (130 MB routed) 16 tokens 60 / 62, 128: 93 / 84, TP=4 200: 121 / 111.  Nor, from 33 tokens on, before one on the
+        streaming tiles, which holds the units the longer the more of the weights are its own (Qwen2-57B TP=2 EP=4, half as
+        much shared as routed, 100 tokens 193 / 166, Qwen1.5 EP=4, a quarter, 48: 107 / 96; EP=2, an eighth, 100: 143 / 150)."""
         routed, shared = self._weight_bytes()
         # with a token or two the routed experts that have rows are as few bytes as the shared one (Qwen1.5 EP=2, 2 tokens: 59 / 53)
         active = routed * min(1.0, T * self.k / self.E)
-        return shared <= 256e6 and 4 * active >= 5 * shared and (not self._shared_tiled(T) or (routed >= 135e6 and T <= 160))
+        tiled = self._shared_tiled(T)
+        ratio = 7.0 if tiled and shared_on_streaming_tiles(self.shared_shard, T, self.y_perm_bf16) else 1.25
+        return shared <= 256e6 and active >= ratio * shared and (not tiled or (routed >= 135e6 and T <= 160))
 
     def _plan(self, T) -> "_Plan":
         """What a forward of T tokens needs to know about itself: a function of T, the shards and the switches,
@@ -210,7 +227,7 @@ class ExpertShardLayer:
         if plan is None:
             sh = self.shared is not None
             hint = 0
-            if sh and self.overlap_shared:
+            if sh and self.overlap_shared and not shared_on_streaming_tiles(self.shared_shard, T, self.y_perm_bf16):
                 hint = routed_hint_beside_shared(self.ffn_shard, self.shared_shard, T)
                 # Up to about 64 rows per expert (128 on long rows) the kernel whose weight stream never stops is the
                 # faster one also beside the shared expert's tiles, with room left for them; from there on its workgroups,

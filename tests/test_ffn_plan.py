@@ -229,3 +229,23 @@ def test_the_shortest_k_extent_streams_on_its_own_split_with_32_rows_per_pass_on
         assert B.moe_debug_walk_split(512, 1, down)[0] == 0
         assert B.moe_debug_walk_split(512, 2, down) == (8, 2, 1)
     assert B.moe_debug_walk_split(2048, 1) == (16, 4, 1) and B.moe_debug_walk_split(1024, 2)[2] == 1
+
+
+def test_no_hint_beside_a_shared_expert_on_the_streaming_tiles():
+    """The hint follows the kernel that runs, not the plan for calls without it: a shared expert whose gate/up projection holds
+    every compute unit (moe_debug_flow) needs none, unless its bf16 down projection has to start early."""
+    import torch
+    from paper_2508_19373_amd.layer import ExpertShardLayer, shared_on_streaming_tiles
+    layer = ExpertShardLayer.__new__(ExpertShardLayer)
+    layer.E, layer.k, layer.H, layer.overlap_shared, layer.gather_in_ffn, layer._gather_auto = 60, 4, 2048, True, True, True
+    layer.ffn_shard = _shard(60, 60, hidden=2048, inter_full=1408, inter_slice=1408)
+    layer.shared_shard = _shard(1, 1, hidden=2048, inter_full=5632, inter_slice=5632)
+    layer.w_gate = torch.empty((60, 1408, 2048), device="meta")
+    layer.shared = [torch.empty((1, 5632, 2048), device="meta")]
+    for bf16 in (False, True):
+        layer.y_perm_bf16, layer._plans = bf16, {}
+        for T, flow in ((64, True), (128, True), (300, True), (256, False), (333, False)):
+            assert bool(B.moe_debug_flow(T, layer.shared_shard) & B.DEBUG_FLOW_GATEUP) == flow
+            assert not all(B.moe_debug_ffn_plan(T, layer.shared_shard)[:2])     # "tiled", says the other plan
+            assert shared_on_streaming_tiles(layer.shared_shard, T, bf16) == (flow and not bf16)
+            assert (layer._plan(T).hint == 0) == (flow and not bf16), T
