@@ -106,7 +106,8 @@ int moe_route_topk(const void* x_bf16, const float* w_router, float* logits,
  * expert_offsets [E_loc+1] int32  exclusive prefix sum of local rows per expert; last = R
  * row_src        [T*k] int32   assignment id of each permuted row, rows [0,R) written
  * slot_row       [T*k] int32   permuted row of each assignment, -1 if its expert is not local
- * workspace      at least moe_workspace_bytes(T,k,shard) bytes, 256-byte aligned
+ * workspace      at least moe_workspace_bytes(T,k,shard) bytes, 256-byte aligned; not used by a batch of at most 2048
+ *                assignments, else by one call at a time
  * Requires H % 8 == 0, 1 <= k <= MOE_MAX_TOPK, T*k < 2^24.
  */
 int moe_permute(const void* x_bf16, const int32_t* topk_idx, int32_t T, int32_t k,
@@ -200,6 +201,9 @@ int moe_combine(const void* y_perm, const int32_t* slot_row, const float* topk_w
  * MOE_NO_COMBINE it ends before the combine (whose arguments are then unused).  Same checks and results as the separate calls; the checks of all
  * steps come first, so with an invalid argument nothing is enqueued.  For callers that a call per step costs too much: a
  * small batch's kernels take less time than marshalling and checking the arguments of four calls.
+ * workspace is moe_permute's: batches of more than 2048 assignments use it, and with MOE_FFN_LEAVE_ROOM every batch uses its
+ * last 256 bytes (counters, cleared by the call itself, from which the experts' GEMMs take their tiles).  Calls that overlap
+ * on one GPU, on different streams or in graphs replayed concurrently, each bring their own.
  * shard describes the routing and permutation, ffn_shard the matrices: they differ where a slice of the
  * intermediate dimension was padded, and in nothing but inter_full and inter_slice (MOE_ERR_INVALID_ARG).
  */

@@ -215,7 +215,10 @@ int moe_forward(moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard
     if (st != MOE_OK) return error(MOE_STEP_COMBINE, st);
   }
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  int32_t* const tickets = moe::permute_tickets(a->workspace, a->T, a->k, shard->n_local_experts);
+  // counters the GEMMs take their tiles from beside another stream; without that hint a small batch leaves the workspace alone
+  int32_t* const tickets = (a->ffn_flags & MOE_FFN_LEAVE_ROOM) != 0
+                               ? moe::permute_tickets(a->workspace, a->T, a->k, shard->n_local_experts)
+                               : nullptr;
   const int32_t E = shard->n_experts;
   const bool own_logits = moe::route_has_logits_kernel(a->T, H, E, a->route_flags);
   hipError_t err = hipSuccess;

@@ -235,6 +235,29 @@ def test_walks_over_k_that_begin_apart(H, I_s, counts):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("tokens", [16, 200])   # route and permutation in one kernel or two
+def test_a_small_batch_uses_the_workspace_for_the_counters_only(tokens):
+    """Without the hint that takes tiles from the counters a batch of up to 2048 assignments leaves the workspace as it is;
+    with it, all but the last 256 bytes."""
+    n, H, I_s, k = 24, 1024, 704, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda")
+    layer = ExpertShardLayer(n_experts=n, top_k=k, hidden=H, inter_full=I_s, inter_slice=I_s, max_tokens=tokens,
+                             w_router=r(H, n) * 0.02, w_gate=r(n, I_s, H).bfloat16(), w_up=r(n, I_s, H).bfloat16(),
+                             w_down=r(n, H, I_s).bfloat16())
+    x = r(tokens, H).bfloat16()
+    plan = layer._plan(tokens)
+    layer.workspace = torch.empty(B.moe_workspace_bytes(tokens, k, layer.shard), dtype=torch.uint8, device="cuda")
+    for hint in (0, B.MOE_FFN_TILED, B.MOE_FFN_LEAVE_ROOM):
+        layer.workspace.fill_(0xAB)
+        layer._plan = lambda _, h=hint: plan._replace(hint=h)
+        layer.forward(x)
+        used = (layer.workspace != 0xAB).cpu()
+        assert bool(used.any()) == (hint == B.MOE_FFN_LEAVE_ROOM) and not used[:-256].any()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("H,I_s,avg,n,mine,flow_rows", [
     (2048, 704, 20, 30, [0, 13, 29], 64),     # tiles of 64 rows, one region of K per expert
     (4096, 1792, 20, 4, [1], 64),             # four regions each
