@@ -12,9 +12,8 @@ from paper_2508_19373_amd import binding as B
 LLVM = "/opt/rocm/llvm/bin"
 
 
-@pytest.fixture(scope="module")
-def code_object(tmp_path_factory):
-    """The gfx950 code object of expert_ffn.hip, taken out of the library's offload bundles."""
+def _code_object(tmp_path_factory, kernel):
+    """The gfx950 code object with this kernel, taken out of the library's offload bundles."""
     for tool in ("llvm-objdump", "llvm-readelf"):
         if not os.path.exists(os.path.join(LLVM, tool)):
             pytest.skip("no " + tool)
@@ -30,32 +29,60 @@ def code_object(tmp_path_factory):
             target = data[p + 24:p + 24 + id_len]
             p += 24 + id_len
             blob = data[at + off:at + off + size]
-            if b"gfx950" in target and b"grouped_gemm_tall_kernel" in blob:
+            if b"gfx950" in target and kernel in blob:
                 path = tmp_path_factory.mktemp("co") / "expert_ffn.elf"
                 path.write_bytes(blob)
                 return str(path)
         at += len(magic)
-    pytest.fail("no device code with the tiled kernels in " + B._LIB_PATH)
+    pytest.fail("no device code with %s in %s" % (kernel.decode(), B._LIB_PATH))
+
+
+@pytest.fixture(scope="module")
+def code_object(tmp_path_factory):
+    """That of expert_ffn.hip."""
+    return _code_object(tmp_path_factory, b"grouped_gemm_tall_kernel")
+
+
+@pytest.fixture(scope="module")
+def flow_code_object(tmp_path_factory):
+    """That of expert_flow.hip."""
+    return _code_object(tmp_path_factory, b"grouped_flow_kernel")
 
 
 def _tool(name, *args):
     return subprocess.run([os.path.join(LLVM, name), *args], capture_output=True, text=True, check=True).stdout
 
 
-def test_tiled_kernels_do_not_spill(code_object):
-    """At 256 + 256 registers a little more address arithmetic spills; the plain gate/up projection has had one spilled
-    register, outside its k-loop, from the start, the others none."""
+def _spills(code_object):
     notes = _tool("llvm-readelf", "--notes", code_object)
     spills = {}
     for kernel in re.split(r"- \.agpr_count:", notes)[1:]:
         name = re.search(r"\.name:\s+(\S+)", kernel).group(1)
         spills[name] = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", kernel).group(1))
+    return spills
+
+
+def test_tiled_kernels_do_not_spill(code_object):
+    """At 256 + 256 registers a little more address arithmetic spills; the plain gate/up projection has had one spilled
+    register, outside its k-loop, from the start, the others none."""
+    spills = _spills(code_object)
     plain = {n: s for n, s in spills.items() if "grouped_gemm_dlds_kernel" in n or "grouped_gemm_even_kernel" in n}
     assert len(plain) == 7
     for name, n in plain.items():
         assert n <= (1 if "grouped_gemm_dlds_kernelILi256ELb1E" in name else 0), (name, n)
     tall = {n: s for n, s in spills.items() if "grouped_gemm_tall_kernel" in n}
     assert len(tall) == 4 and all(s <= 2 for s in tall.values()), tall
+    # the gate/up projections whose walks over K begin apart: as those that they stand in for
+    spread = {n: s for n, s in spills.items() if "grouped_gemm_spread_kernel" in n}
+    assert len(spread) == 1 and all(s <= 1 for s in spread.values()), spread
+    spread = {n: s for n, s in spills.items() if "grouped_gemm_spread_tall_kernel" in n}
+    assert len(spread) == 1 and all(s <= 2 for s in spread.values()), spread
+
+
+def test_streaming_tiles_do_not_spill(flow_code_object):
+    """A spilled register of theirs would be read and written in every k-tile."""
+    flow = {n: s for n, s in _spills(flow_code_object).items() if "grouped_flow_kernel" in n}
+    assert len(flow) == 10 and not any(flow.values()), flow
 
 
 def _regs(operand):
@@ -84,7 +111,7 @@ def _tall_kernels(code_object):
         head = re.match(r"([0-9a-f]+) <(\S+)>:", line)
         if head:
             cur = None
-            if "grouped_gemm_tall_kernel" in head.group(2):
+            if re.search("grouped_gemm_(spread_)?tall_kernel", head.group(2)):
                 start = int(head.group(1), 16)
                 cur = kernels.setdefault(head.group(2), [])
         elif cur is not None and line.startswith("\t") and "//" in line:
@@ -98,7 +125,7 @@ def test_matrix_instructions_in_inline_assembly_keep_their_distance(code_object)
     before an access by anything but the next MFMA on the same accumulator; asked for here: 16 instructions), and no
     vector instruction may write an operand within the 2 wait states before it."""
     kernels = _tall_kernels(code_object)
-    assert len(kernels) == 4
+    assert len(kernels) == 5
     for name, code in kernels.items():
         index = {ins.addr: i for i, ins in enumerate(code)}
         own = [i for i, ins in enumerate(code) if ins.mfma and ins.operands[0].startswith("v")]
