@@ -151,7 +151,7 @@ int moe_permute_static(const void* x_bf16, const int32_t* topk_idx, int32_t T, i
  * MOE_FFN_SKIP_GATEUP / MOE_FFN_SKIP_DOWN run one of the two GEMMs alone (operator-level
  * benchmarking, as the paper's latency model is fitted on measured operator latencies).
  * MOE_FFN_TILED: each GEMM normally picks, from a cost estimate, between weight-streaming kernels
- * (up to about a hundred rows per expert) and the tiled MFMA kernel; with this flag both run tiled.  It is meant
+ * (up to about 160 rows per expert, in places up to 300) and the tiled MFMA kernel; with this flag both run tiled.  It is meant
  * for a call that overlaps a tiled call on another stream (routed experts beside a shared
  * expert with a few dozen rows or more): the streaming kernel's workgroups stay resident on every compute unit
  * for the whole launch, and a tiled workgroup, which needs a compute unit's whole LDS, cannot

@@ -104,7 +104,7 @@ int32_t moe_debug_down_slices(const int32_t* expert_offsets, int32_t cap_rows, c
 int32_t moe_debug_tall(int32_t cap_rows, const moe_shard_t* shard);
 
 /*
- * Which GEMMs of such a call run the kernel for experts of up to about 160 rows, whatever moe_debug_ffn_plan says of
+ * Which GEMMs of such a call run the streaming tiles (up to about 160 rows per expert, in places up to 300), whatever moe_debug_ffn_plan says of
  * them (that is the choice between the two others, made where this kernel is not used and with MOE_FFN_TILED): 0,
  * MOE_DEBUG_FLOW_GATEUP, MOE_DEBUG_FLOW_DOWN or both, with the rows of their tiles in bits 8 to 15 and 16 to 23.  Negative
  * on invalid arguments.

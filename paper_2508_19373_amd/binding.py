@@ -286,7 +286,7 @@ def _flow(cap_rows, shard):
 
 
 def moe_debug_flow(cap_rows, shard: MoeShard) -> int:
-    """Host-only: the GEMMs that run the kernel for experts of up to about a hundred rows, DEBUG_FLOW_* bits."""
+    """Host-only: the GEMMs that run the streaming tiles, DEBUG_FLOW_* bits."""
     return _flow(cap_rows, shard) & 3
 
 

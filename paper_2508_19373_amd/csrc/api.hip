@@ -222,7 +222,7 @@ int moe_forward(moe_forward_args_t* a, const moe_shard_t* shard, const moe_shard
   const int32_t E = shard->n_experts;
   const bool own_logits = moe::route_has_logits_kernel(a->T, H, E, a->route_flags);
   hipError_t err = hipSuccess;
-  if ((own_logits || (a->route_flags & MOE_LOGITS_GIVEN)) && moe::route_permute_fits(a->T, a->k, E)) {
+  if ((own_logits || (a->route_flags & MOE_LOGITS_GIVEN)) && moe::route_permute_fits(a->T)) {
     if (own_logits) err = moe::launch_route_logits(a->x_bf16, a->w_router, a->logits, a->T, H, E, s);
     if (err != hipSuccess) return error(MOE_STEP_ROUTE, MOE_ERR_HIP);
     err = moe::launch_route_permute(a->logits, a->T, E, a->k, a->route_flags, a->topk_idx, a->topk_w, a->x_bf16, H,

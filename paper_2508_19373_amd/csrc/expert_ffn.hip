@@ -6,11 +6,11 @@
 // Two grouped GEMMs, both "NT" (activations and weights are K-contiguous):
 //   GEMM1  h[r, i]  = silu(x_r . Wg_e[i,:]) * (x_r . Wu_e[i,:])      K = H,   N = I_s (gate+up fused)
 //   GEMM2  y[r, n]  = h_r . Wd_e[n,:]                                K = I_s, N = H
-// bf16 operands, fp32 accumulators.  Two kernel families cover the two regimes the paper
+// bf16 operands, fp32 accumulators.  Three kernel families cover the two regimes the paper
 // distinguishes ("Generative Inference"): grouped_gemm.hpp (tiled, LDS-DMA, MFMA-bound) for
-// prefill-sized groups, grouped_walk.hpp (weight streaming, HBM-bound; grouped_stream.hpp for the
-// K extents it is not instantiated for) for decode-sized groups.  Each of the two GEMMs picks its
-// family from a cost estimate (prefer_walk below).  In both, the work list is derived on the
+// prefill-sized groups; for decode-sized groups grouped_flow.hpp (tiles whose weight stream never stops, HBM-bound; flow_plan
+// below says where) and grouped_walk.hpp (weight streaming in passes of 16 or 32 rows; grouped_stream.hpp for the K extents it
+// is not instantiated for).  Each of the two GEMMs picks its family on its own (flow_plan, then the estimate of prefer_walk).  In both, the work list is derived on the
 // device from expert_offsets without a host round trip.
 #include "flow_tiles.hpp"
 #include "grouped_gemm.hpp"
@@ -364,7 +364,7 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
 
 }  // namespace
 
-// Experts of up to 160 planned rows, in tiles of 64, 128 or 160 rows: there the GEMM is bound by HBM, and this kernel streams
+// Streaming tiles for experts of up to 160 planned rows, 64, 128 or 160 rows high: there the GEMM is bound by HBM, and this kernel streams
 // at 5.2-6.0 TB/s where the tiled ones reach 3.3-5.4 and the streaming one 4.0-5.4 (in one pass of 16 rows up to 6.0).
 // Measured alone on weights that are not in any cache, us, before / this kernel, gate/up and down projection, by average
 // rows per expert: Qwen1.5-MoE (60 experts) 3 rows 119 / 113, 65 / 58; 14: 139 / 127, 86 / 67; 36: 144 / 130, 82 / 74;

@@ -1,4 +1,4 @@
-// Launches of the grouped GEMM for experts of up to about a hundred rows (grouped_flow.hpp), and when it runs.
+// Launches of the streaming tiles (grouped_flow.hpp); flow_plan in expert_ffn.hip says when they run.
 #include "grouped_flow.hpp"
 
 namespace moe {

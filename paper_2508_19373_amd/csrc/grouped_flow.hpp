@@ -1,4 +1,5 @@
-// Grouped "NT" GEMM for experts of up to about 160 rows (gfx950), bound: HBM.
+// Streaming tiles: grouped "NT" GEMM for experts of up to about 160 rows, in places two passes of them (flow_plan in
+// expert_ffn.hip says where it runs) (gfx950), bound: HBM.
 //
 // Up to there a grouped GEMM is bound by streaming every active expert's weights once.  One
 // workgroup per tile (grouped_gemm.hpp) spends a fifth to a third of such a tile's time outside its k-loop: finding the

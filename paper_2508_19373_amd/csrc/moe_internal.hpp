@@ -77,11 +77,11 @@ hipError_t launch_permute(const void* x, const int32_t* topk_idx, int T, int k, 
 size_t permute_workspace_bytes(int T, int k, int n_local);
 // launch_route_topk and launch_permute of a small batch whose logits are given (or already computed), in one kernel:
 // whether it takes them (nothing is enqueued if not).
-bool route_permute_fits(int T, int k, int E);
+bool route_permute_fits(int T);
 hipError_t launch_route_permute(const float* logits, int T, int E, int k, uint32_t flags, int32_t* topk_idx, float* topk_w,
                                 const void* x, int H, int n_local, int offset, void* x_perm, int32_t* expert_offsets,
                                 int32_t* row_src, int32_t* slot_row, hipStream_t stream, int32_t* tickets);
-// Words at the end of that workspace for launch_permute to clear as `tickets` (kTickets of them): the counters the GEMM
+// Words at the end of that workspace for launch_permute to clear as `tickets` (kTickets of them, nullptr: none): the counters the GEMM
 // kernels of the same forward take their tiles from.
 constexpr int kTickets = 2;
 int32_t* permute_tickets(void* workspace, int T, int k, int n_local);
@@ -110,7 +110,7 @@ int tiled_block_rows(int cap_rows, int est_rows, int n_local, int H, int I_s);
 constexpr int kTallGateUp = 1, kTallDown = 2, kTallDownBf16 = 4;
 int tall_gemms(int cap_rows, int est_rows, int n_local, int H, int I_s, int which);
 int expected_rows(int cap_rows, const moe_shard_t* shard);
-// The kernel for experts of up to about a hundred rows (grouped_flow.hpp): rows and weight rows of its tiles for one of
+// The streaming tiles (grouped_flow.hpp): rows and weight rows of its tiles for one of
 // the two GEMMs of such a call, rows = 0 where another kernel runs it.
 struct FlowPlan {
   int rows, cols;

@@ -188,11 +188,11 @@ __global__ __launch_bounds__(kIdxThreads) void route_permute_kernel(const float*
                 chunks_per_row, x_perm);
 }
 
-// ---- large batches: the same stable order from three short kernels over many workgroups.
+// ---- large batches: the same stable order from two short kernels over many workgroups, three from 65 workgroups on.
 // (1) every workgroup ranks its own 1024 assignments (ballot inside a wavefront, serial prefix
 // over its 16 wavefronts) and publishes its per-expert counts; (2) one workgroup turns the counts
 // into per-(workgroup, expert) base rows (scan over workgroups, then over experts); (3) every
-// workgroup adds its bases.  No atomics on the value path: the order is the unique stable one.
+// workgroup adds its bases.  Up to 64 workgroups, each does (2) for itself ahead of (3) (permute_scan_place_kernel).  No atomics on the value path: the order is the unique stable one.
 __global__ __launch_bounds__(kIdxThreads) void permute_rank_kernel(const int32_t* __restrict__ topk_idx, int A,
                                                                   int n_local, int offset,
                                                                   int32_t* __restrict__ block_counts,
@@ -374,9 +374,9 @@ static hipError_t launch_gather(const void* x, const int32_t* row_src, const int
   return hipGetLastError();
 }
 
-bool route_permute_fits(int T, int k, int E) {
-  (void)E;
-  return T > 0 && T <= kFusedTokens && T * k <= 2 * kIdxThreads;
+bool route_permute_fits(int T) {
+  static_assert(kFusedTokens * MOE_MAX_TOPK <= 2 * kIdxThreads, "permute_small takes two assignments a thread");
+  return T > 0 && T <= kFusedTokens;
 }
 
 hipError_t launch_route_permute(const float* logits, int T, int E, int k, uint32_t flags, int32_t* topk_idx, float* topk_w,

@@ -1,4 +1,4 @@
-"""The grouped GEMM for experts of up to about a hundred rows (csrc/grouped_flow.hpp): when it runs (host) and what it
+"""The streaming tiles, the grouped GEMM for experts of up to about 160 rows (csrc/grouped_flow.hpp): when it runs (host) and what it
 computes at the edges of its tiles (device, against the CPU oracle)."""
 import numpy as np
 import pytest
