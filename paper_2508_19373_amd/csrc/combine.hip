@@ -5,6 +5,12 @@
 // Token-major gather: one workgroup per token walks the token's k slots in order and sums in
 // fp32, so every output row is written exactly once, coalesced, with no atomics -- the result
 // is deterministic.  HBM-bound: reads k rows of y_perm, writes one row of y.
+//
+// A lane takes 8 columns (16 or 32 bytes of a row) and adds a token's rows one after the other; the chip's other
+// tokens hide the latency.  The rows of 2, 4 or 8 slots loaded ahead of the first sum, 4 columns a lane, measured slower nearly
+// everywhere: the registers cost residency, bf16 rows came in half as wide loads (us, so / rows ahead: H = 3584, k = 8, 1200
+// tokens, fp32 23 / 28, bf16 13 / 26; H = 2048, k = 4, 4096 tokens 24 / 25, 15 / 19; H = 4096, k = 2, 8192 tokens 63 / 67, 31 / 32; the tiny
+// layer's 64 tokens 2.7 / 2.4).
 #include "moe_internal.hpp"
 
 namespace moe {
@@ -23,30 +29,20 @@ __device__ __forceinline__ void load8(const uint16_t* p, float (&v)[8]) {
   v[0] = bf16_lo(a.x); v[1] = bf16_hi(a.x); v[2] = bf16_lo(a.y); v[3] = bf16_hi(a.y);
   v[4] = bf16_lo(a.z); v[5] = bf16_hi(a.z); v[6] = bf16_lo(a.w); v[7] = bf16_hi(a.w);
 }
-__device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ float4 load4(const uint16_t* p) {
-  const uint2 a = *reinterpret_cast<const uint2*>(p);
-  return make_float4(bf16_lo(a.x), bf16_hi(a.x), bf16_lo(a.y), bf16_hi(a.y));
+__device__ __forceinline__ void store8(float* p, const float (&v)[8]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
 }
-__device__ __forceinline__ void store4(float* p, const float4& v) { *reinterpret_cast<float4*>(p) = v; }
-__device__ __forceinline__ void store4(uint16_t* p, const float4& v) {
-  uint2 o;
-  o.x = pack_bf16x2(v.x, v.y);
-  o.y = pack_bf16x2(v.z, v.w);
-  *reinterpret_cast<uint2*>(p) = o;
-}
-__device__ __forceinline__ void fma4(float4& acc, float w, const float4& v) {
-  acc.x = fmaf(w, v.x, acc.x);
-  acc.y = fmaf(w, v.y, acc.y);
-  acc.z = fmaf(w, v.z, acc.z);
-  acc.w = fmaf(w, v.w, acc.w);
+__device__ __forceinline__ void store8(uint16_t* p, const float (&v)[8]) {
+  uint4 o;
+  o.x = pack_bf16x2(v[0], v[1]);
+  o.y = pack_bf16x2(v[2], v[3]);
+  o.z = pack_bf16x2(v[4], v[5]);
+  o.w = pack_bf16x2(v[6], v[7]);
+  *reinterpret_cast<uint4*>(p) = o;
 }
 
-// A lane takes 4 columns at a time (whole 1 KB per wavefront and row), kPass of them 1024 columns apart, and loads those of
-// kRows rows before it adds the first, so that a token is a memory latency or two and not one per row.  Lane j of every
-// wavefront holds slot j's row and weight.  The shared expert's gate is summed while the first rows are on their way.
-constexpr int kCols = 4, kPass = 2;
-template <typename YT, typename OT, int kRows>
+template <typename YT, typename OT>
 __global__ __launch_bounds__(kCombThreads) void combine_kernel(const YT* __restrict__ y_perm,
                                                               const int32_t* __restrict__ slot_row,
                                                               const float* __restrict__ topk_w, int T, int k, int H,
@@ -54,78 +50,56 @@ __global__ __launch_bounds__(kCombThreads) void combine_kernel(const YT* __restr
                                                               const uint16_t* __restrict__ x,
                                                               const float* __restrict__ w_shared_gate,
                                                               OT* __restrict__ y_out) {
-  __shared__ float red[2][kCombThreads / kWave];
+  __shared__ float red[kCombThreads / kWave];
+  __shared__ int s_row[MOE_MAX_TOPK];
+  __shared__ float s_w[MOE_MAX_TOPK];
   const int tid = threadIdx.x;
-  const bool gated = y_shared != nullptr && w_shared_gate != nullptr;
-  int flip = 0;
   for (int t = blockIdx.x; t < T; t += gridDim.x) {
-    const int slot = min(tid & (kWave - 1), k - 1);
-    const int my_row = slot_row[(size_t)t * k + slot];
-    const float my_weight = topk_w[(size_t)t * k + slot];
-    auto row_of = [&](int j) { return __builtin_amdgcn_readlane(my_row, j); };
+    __syncthreads();  // LDS reuse across tokens
+    if (tid < k) {
+      s_row[tid] = slot_row[(size_t)t * k + tid];
+      s_w[tid] = topk_w[(size_t)t * k + tid];
+    }
     float gate = 1.f;
-    for (int h0 = tid * kCols; h0 < H || h0 == tid * kCols; h0 += kCombThreads * kCols * kPass) {
-      float4 v[kRows][kPass], sh[kPass], acc[kPass];
-      auto load_rows = [&](int j0) {
+    if (y_shared != nullptr && w_shared_gate != nullptr) {
+      float part = 0.f;
+      for (int h0 = tid * 8; h0 < H; h0 += kCombThreads * 8) {
+        float xv[8], wv[8];
+        load8(x + (size_t)t * H + h0, xv);
+        load8(w_shared_gate + h0, wv);
 #pragma unroll
-        for (int j = 0; j < kRows; ++j) {
-          const int r = j0 + j < k ? row_of(j0 + j) : -1;
-          if (r >= 0) {
+        for (int i = 0; i < 8; ++i) part = fmaf(xv[i], wv[i], part);
+      }
+      part = wave_sum(part);
+      if ((tid & (kWave - 1)) == 0) red[tid >> 6] = part;
+      __syncthreads();
+      float z = 0.f;
 #pragma unroll
-            for (int p = 0; p < kPass; ++p) {
-              const int h = h0 + p * kCombThreads * kCols;
-              if (h < H) v[j][p] = load4(y_perm + (size_t)r * H + h);
-            }
-          }
-        }
-      };
-      load_rows(0);
+      for (int w = 0; w < kCombThreads / kWave; ++w) z += red[w];
+      gate = 1.f / (1.f + expf(-z));
+    } else {
+      __syncthreads();
+    }
+    for (int h0 = tid * 8; h0 < H; h0 += kCombThreads * 8) {
+      float acc[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+      for (int j = 0; j < k; ++j) {
+        const int r = s_row[j];
+        if (r < 0) continue;
+        const float w = s_w[j];
+        float v[8];
+        load8(y_perm + (size_t)r * H + h0, v);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = fmaf(w, v[i], acc[i]);
+      }
       if (y_shared != nullptr) {
+        float v[8];
+        load8(y_shared + (size_t)t * H + h0, v);
 #pragma unroll
-        for (int p = 0; p < kPass; ++p) {
-          const int h = h0 + p * kCombThreads * kCols;
-          if (h < H) sh[p] = load4(y_shared + (size_t)t * H + h);
-        }
+        for (int i = 0; i < 8; ++i) acc[i] = fmaf(gate, v[i], acc[i]);
       }
-      if (gated && h0 == tid * kCols) {  // (every lane comes here once per token)
-        float part = 0.f;
-        for (int c = tid * 8; c < H; c += kCombThreads * 8) {
-          float xv[8], wv[8];
-          load8(x + (size_t)t * H + c, xv);
-          load8(w_shared_gate + c, wv);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) part = fmaf(xv[i], wv[i], part);
-        }
-        part = wave_sum(part);
-        if ((tid & (kWave - 1)) == 0) red[flip][tid >> 6] = part;
-        __syncthreads();
-        float z = 0.f;
-#pragma unroll
-        for (int w = 0; w < kCombThreads / kWave; ++w) z += red[flip][w];
-        flip ^= 1;  // the next token's sums go elsewhere: one barrier per token
-        gate = 1.f / (1.f + expf(-z));
-      }
-#pragma unroll
-      for (int p = 0; p < kPass; ++p) acc[p] = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int j0 = 0; j0 < k; j0 += kRows) {
-        if (j0 > 0) load_rows(j0);
-#pragma unroll
-        for (int j = 0; j < kRows; ++j) {
-          if (j0 + j < k && row_of(j0 + j) >= 0) {
-            const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_weight), j0 + j));
-#pragma unroll
-            for (int p = 0; p < kPass; ++p) fma4(acc[p], w, v[j][p]);
-          }
-        }
-      }
-#pragma unroll
-      for (int p = 0; p < kPass; ++p) {
-        const int h = h0 + p * kCombThreads * kCols;
-        if (h < H) {
-          if (y_shared != nullptr) fma4(acc[p], gate, sh[p]);
-          store4(y_out + (size_t)t * H + h, acc[p]);
-        }
-      }
+      store8(y_out + (size_t)t * H + h0, acc);
     }
   }
 }
@@ -135,9 +109,7 @@ hipError_t launch_typed(const void* y_perm, const int32_t* slot_row, const float
                         const void* y_shared, const void* x, const float* w_shared_gate, void* y_out,
                         hipStream_t stream) {
   const int grid = T < 16384 ? T : 16384;
-  const auto kernel =
-      k <= 2 ? combine_kernel<YT, OT, 2> : (k <= 4 ? combine_kernel<YT, OT, 4> : combine_kernel<YT, OT, 8>);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kCombThreads), 0, stream,
+  hipLaunchKernelGGL((combine_kernel<YT, OT>), dim3(grid), dim3(kCombThreads), 0, stream,
                      static_cast<const YT*>(y_perm), slot_row, topk_w, T, k, H, static_cast<const YT*>(y_shared),
                      static_cast<const uint16_t*>(x), w_shared_gate, static_cast<OT*>(y_out));
   return hipGetLastError();

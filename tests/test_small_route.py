@@ -66,7 +66,7 @@ def test_permutation_at_the_edges_of_its_kernels(T, k, E, E_loc, off):
 @pytest.mark.parametrize("H", [8, 1000, 1024, 2056, 4096])
 @pytest.mark.parametrize("shared", [False, True])
 def test_combine_row_groups_and_column_passes(k, H, shared):
-    """Slots in groups of 2, 4 or 8, columns in passes of 1024: missing slots, remainders, several tokens per workgroup."""
+    """Every number of slots, columns in passes of 2048: missing slots, remainders, a shared expert or none."""
     rng = np.random.default_rng(k * H)
     T, R = 37, 37 * k
     y = rng.standard_normal((R, H)).astype(np.float32)
