@@ -32,8 +32,8 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E
 # what the same counter reads for a plain 1 GiB device copy: FETCH_SIZE x 2.0, WRITE_SIZE x 1.0.
 MEASURED_TRAFFIC_BYTES = {
     "mixtral_prefill": (1384050.8 * 2.0 + 230272.0) * 1024,
-    "mixtral_decode": (936763.1 * 2.0 + 898.7) * 1024,
-    "qwen_prefill": (397214.6 * 2.0 + 45375.3) * 1024,
+    "mixtral_decode": (936907.6 * 2.0 + 898.9) * 1024,
+    "qwen_prefill": (398729.9 * 2.0 + 45375.5) * 1024,
 }
 
 # measured after the main workload in the same run (`also` in the JSON line): the other target shapes
@@ -168,10 +168,10 @@ def measure(workload, steps, warmup, args, torch, np, B, I, ExpertShardLayer, bf
     kname = ("moe::gf::grouped_flow_kernel<..., GATEUP> (GEMM1 + SwiGLU, weight streaming)"
              if B.moe_debug_flow(T * k, layer.ffn_shard) & B.DEBUG_FLOW_GATEUP
              else "moe::gw::grouped_walk_kernel<..., GATEUP> (GEMM1 + SwiGLU, weight streaming)" if decode
-             else "moe::gg::grouped_gemm_tall_kernel<256, GATEUP> (GEMM1 + SwiGLU)" if B.moe_debug_tall_gemms(T * k, layer.ffn_shard) & B.DEBUG_TALL_GATEUP
+             else "moe::gg::grouped_gemm_[spread_]tall_kernel<256, GATEUP> (GEMM1 + SwiGLU)" if B.moe_debug_tall_gemms(T * k, layer.ffn_shard) & B.DEBUG_TALL_GATEUP
              else ("moe::gg::grouped_gemm_even_kernel<256, GATEUP> (GEMM1 + SwiGLU, 160-row blocks)"
                    if B.moe_debug_tile_rows(T * k, layer.ffn_shard) == 160
-                   else "moe::gg::grouped_gemm_dlds_kernel<256, GATEUP> (GEMM1 + SwiGLU)"))
+                   else "moe::gg::grouped_gemm_{dlds,spread}_kernel<256, GATEUP> (GEMM1 + SwiGLU)"))
     if intensity > PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
         ach = g1_flops / (g1_ms * 1e-3) / 1e12
         roofline = {"kernel": kname, "bound": "mfma", "achieved": ach,

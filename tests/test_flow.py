@@ -217,7 +217,8 @@ def test_tiles_from_the_counter_give_the_same_bits(n, H, I_s, beside):
     (2048, 1024, [260] * 40 + [300, 1, 256, 0, 401]),  # with tall row blocks
 ])
 def test_walks_over_k_that_begin_apart(H, I_s, counts):
-    """Tiled gate/up projections on rows of a multiple of 4 KB start K at an eighth that depends on the XCD; tolerance as above."""
+    """Tiled gate/up projections on rows of a multiple of 4 KB start K at an eighth that depends on the expert and the output
+    column; tolerance as above."""
     n = len(counts)
     offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     R = int(offs[-1])
