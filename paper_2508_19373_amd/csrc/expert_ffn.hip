@@ -109,7 +109,7 @@ bool expects_tall_blocks(int cap_rows, int est_rows, int n_local, int ncb, int n
 
 // Whether the tiles of a gate/up projection begin their walk over K apart (gemm_tile): where rows are a multiple of 4 KB and
 // the weights, not the matrix cores, set the pace.  Measured from one place / spread, us: TP=4 slice of Mixtral, 160 rows
-// per expert 128 / 113, 300: 207 / 180; Qwen1.5-MoE 256: 200 / 194, 272: 211 / 205; 64 experts of 280 rows, K = 2048, 257 /
+// per expert 119 / 111, 300: 194 / 182; Qwen1.5-MoE 256: 210 / 194, 272: 220 / 206; 64 experts of 280 rows, K = 2048, 257 /
 // 242; at the power limit it costs a little (Mixtral 1024 rows 1383 / 1391, 1040: 1432 / 1458), and so does the arithmetic (the
 // choice made in the kernel: TP=4 slice 2048 rows 676 -> 692 from one place), hence kernels of their own; on other K nothing
 // changes (Qwen2-57B, K = 3584, 553 / 549).  The 160-row tiling gains 1 %, the down projections lose (Mixtral 1024 rows 678 / 689).
@@ -377,7 +377,7 @@ inline bool prefer_walk(int cap_rows, int est_rows, int n_local, int n_out, int 
 // Two passes of 160 rows share them, too, at 1.2 us per k-tile of 160 x 256: the down projection just above one 256-row
 // block, where the tiled kernels have tall blocks or remainders, (Qwen1.5-MoE 250 rows 143 / 131, 270: 144 / 137, 290: 167 / 140;
 // Mixtral TP=2 270: 173 / 136, TP=4 104 / 74, TP=8 59 / 43; Qwen2-57B 270: 406 / 396; 30 experts of Qwen1.5 250: 59 / 65, 270: 73 /
-// 66), and gate/up projections whose tall tiles leave most of a round idle (estimated; 30 experts of Qwen1.5 270: 124 / 117, its
+// 66; experts of exactly 256 or 272 rows each, with nothing left over, are 5 % faster tiled, Qwen1.5-MoE 122 / 128), and gate/up projections whose tall tiles leave most of a round idle (estimated; 30 experts of Qwen1.5 270: 124 / 117, its
 // TP=2 slice 136 / 118, Mixtral TP=8 99 / 78, Qwen2-57B TP=2 EP=2 201 / 188; not Qwen1.5 214 / 229, Mixtral TP=4 142 / 149).
 // Where it does not pay: too few output strips of 16 columns to keep 256 workgroups in tiles (a single expert's down
 // projection: Mixtral EP=8 (256 strips) 33 / 67, EP=4 (512) 52 / 73; 1024 strips 94 / 89, but with more than
