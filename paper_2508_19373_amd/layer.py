@@ -229,18 +229,15 @@ class ExpertShardLayer:
             hint = 0
             if sh and self.overlap_shared and not shared_on_streaming_tiles(self.shared_shard, T, self.y_perm_bf16):
                 hint = routed_hint_beside_shared(self.ffn_shard, self.shared_shard, T)
-                # Up to about 64 rows per expert (128 on long rows) the kernel whose weight stream never stops is the
-                # faster one also beside the shared expert's tiles, with room left for them; from there on its workgroups,
-                # which stay for the whole launch, keep the tiles from filling in.  Tiled / with room, us: Qwen1.5-MoE 333
-                # tokens 270 / 260, 600: 302 / 292, 800: 313 / 321, 1200: 347 / 357, 2000: 412 / 424; Qwen2-57B 450: 932 /
-                # 888, 1000: 1164 / 1131.
+                # Planned for up to 64 rows per expert the kernel whose weight stream never stops is the faster one also beside the
+                # shared expert's tiles, with room left for them (tiled / with room, us: Qwen1.5-MoE 333 tokens 270 / 260, 600:
+                # 302 / 292).
                 rows = B.moe_debug_flow_rows(T * self.k, self.ffn_shard)
                 routed, shared = self._weight_bytes()
                 if hint == B.MOE_FFN_TILED and 0 < rows <= (128 if self.H >= 3072 else 64):
                     hint = B.MOE_FFN_LEAVE_ROOM
-                # nor in two row passes (Qwen2-57B TP=4 2107 tokens 630 / 671; in one, Qwen1.5 EP=2 2000: 326 / 304)
-                # or with more rows than 64 on short slices (TP=8 482 tokens 202 / 209) or 160 for few experts (Qwen1.5 EP=4
-                # 1497: 208 / 212)
+                # not in two row passes (Qwen2-57B TP=4 2107 tokens 630 / 671) or with more rows than 64 on short slices (TP=8 482
+                # tokens 202 / 209) or 160 for few experts (Qwen1.5 EP=4 1497: 208 / 212)
                 elif hint == B.MOE_FFN_LEAVE_ROOM and ((rows == 160 and T * self.k > 165 * self.E) or
                                                        (rows > 64 and self.ffn_shard.inter_slice < 512) or
                                                        (rows == 160 and self.ffn_shard.n_local_experts < 24)):
@@ -249,6 +246,20 @@ class ExpertShardLayer:
                 # interleave tile by tile (Qwen2-57B EP=8, 48 / 128 / 256 tokens 192 / 216 / 240 tiled, 214 / 226 / 270)
                 # (or, from 160 tokens on, beside as few: Qwen1.5 TP=2 EP=4 256 tokens 92 / 96)
                 if hint != 0 and rows > 0 and (2 * shared >= routed or (routed < 135e6 and T > 160)):
+                    hint = B.MOE_FFN_TILED
+                # With more rows than 64 room left costs more than it gives: the shared expert's tiles start on 16 units and the
+                # rest of them wait for the routed call's end all the same.  Without, its stream is over sooner (with room / no
+                # hint, and tiled, us: Qwen2-57B TP=4 EP=2 384 tokens 203 / 193, 192, 1024: 277 / 256, 255, TP=2 EP=2 under Zipf(1.2)
+                # 768: 499 / 440, 462, Qwen1.5 TP=2 EP=2 768: 143 / 127, 134, 2048: 210 / 187, 197; 92 shards and token counts, none
+                # to room 0.977 eager, 0.962 in a graph).  A bf16 shared down projection, uncut, walks all of K and has to start
+                # early: tiled there (38 of them: 0.988, 0.978; no hint 1.005, 1.014), and with up to 64 rows where that walk is long
+                # and the gate/up projection before it tiled as well (Qwen2-57B 192 / 384 tokens 825 / 946 with room, 768 / 835 tiled,
+                # TP=2 448 / 491, 416 / 456; 256 tokens, one row block, 2 % slower; Qwen1.5, 5632, 256 to 512 tokens 4 % slower).
+                if hint == B.MOE_FFN_LEAVE_ROOM and rows > 64:
+                    hint = B.MOE_FFN_TILED if self.y_perm_bf16 else 0
+                elif (hint == B.MOE_FFN_LEAVE_ROOM and rows > 0 and self.y_perm_bf16 and
+                      self.shared_shard.inter_slice >= 8192 and
+                      not B.moe_debug_flow(T, self.shared_shard) & B.DEBUG_FLOW_GATEUP):
                     hint = B.MOE_FFN_TILED
             plan = _Plan(B.moe_ffn_workspace_bytes(T * self.k, self.ffn_shard),
                          B.moe_ffn_workspace_bytes(T, self.shared_shard) if sh else 0, hint, self.gathers(T),

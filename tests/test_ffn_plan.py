@@ -249,3 +249,43 @@ def test_no_hint_beside_a_shared_expert_on_the_streaming_tiles():
             assert not all(B.moe_debug_ffn_plan(T, layer.shared_shard)[:2])     # "tiled", says the other plan
             assert shared_on_streaming_tiles(layer.shared_shard, T, bf16) == (flow and not bf16)
             assert (layer._plan(T).hint == 0) == (flow and not bf16), T
+
+
+def _planning_layer(shard, shared_shard, E, k, bf16):
+    """A layer that only plans."""
+    import torch
+    from paper_2508_19373_amd.layer import ExpertShardLayer
+    layer = ExpertShardLayer.__new__(ExpertShardLayer)
+    layer.E, layer.k, layer.H, layer.overlap_shared, layer.gather_in_ffn, layer._gather_auto = E, k, shard.hidden, True, True, True
+    layer.ffn_shard, layer.shared_shard, layer.y_perm_bf16, layer._plans = shard, shared_shard, bf16, {}
+    layer.w_gate = torch.empty((shard.n_local_experts, shard.inter_slice, shard.hidden), device="meta")
+    layer.shared = [torch.empty((1, shared_shard.inter_slice, shared_shard.hidden), device="meta")]
+    return layer
+
+
+@pytest.mark.parametrize("n,inter,inter_shared,T,rows", [
+    (32, 640, 5120, 1024, 160),     # Qwen2-57B TP=4 EP=2: 255 us with the tiles interleaved, 256 without a hint, 277 with room
+    (32, 1280, 10240, 768, 160),    # TP=2 EP=2
+    (32, 640, 5120, 384, 128),
+    (64, 2560, 20480, 512, 128),    # unsharded
+])
+def test_no_room_is_left_by_streaming_tiles_of_more_than_64_rows(n, inter, inter_shared, T, rows):
+    """Room left beside a tiled shared expert made these layers up to a tenth slower than the tiled kernels: no hint, or
+    tiled where a bf16 down projection has to start early."""
+    shard = _shard(64, n, hidden=3584, inter_full=2560, inter_slice=inter)
+    shared = _shard(1, 1, hidden=3584, inter_full=20480, inter_slice=inter_shared)
+    assert B.moe_debug_flow_rows(T * 8, shard) == rows
+    assert not B.moe_debug_flow(T, shared) & B.DEBUG_FLOW_GATEUP and not all(B.moe_debug_ffn_plan(T, shared)[:2])
+    assert _planning_layer(shard, shared, 64, 8, False)._plan(T).hint == 0
+    assert _planning_layer(shard, shared, 64, 8, True)._plan(T).hint == B.MOE_FFN_TILED
+
+
+@pytest.mark.parametrize("tp", [1, 2, 4])
+def test_a_long_bf16_down_projection_beside_streaming_tiles_starts_early(tp):
+    """Qwen2-57B with bf16 between the experts and the combine, 384 tokens: 835 us tiled, 946 with room (TP=2 456 / 491); a
+    quarter of the shared expert is short enough."""
+    shard = _shard(64, 64, hidden=3584, inter_full=2560, inter_slice=2560 // tp)
+    shared = _shard(1, 1, hidden=3584, inter_full=20480, inter_slice=20480 // tp)
+    assert B.moe_debug_flow_rows(384 * 8, shard) == 64
+    assert _planning_layer(shard, shared, 64, 8, True)._plan(384).hint == (B.MOE_FFN_TILED if tp < 4 else B.MOE_FFN_LEAVE_ROOM)
+    assert _planning_layer(shard, shared, 64, 8, False)._plan(384).hint == B.MOE_FFN_LEAVE_ROOM
